@@ -15,6 +15,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr int kMaxSplit = 64;  // shares of one sequence's keys: a lane each when they are put together
 
 // What one workgroup needs, gathered by the kernels below: a query position of one unit and GQ
 // consecutive query heads of it (GQ = 1: one head; in a decode step with grouped queries a
@@ -35,7 +36,65 @@ struct RowQuery {
   T *put_k, *put_v;  // ring rows of this unit, or null
   float *put_g;
   float gate;
+  // keys shared among n_split workgroups (decode): this one's number, and where the group of
+  // workgroups that belong to the same query heads leaves its partial results
+  int split, n_split;
+  float *part_acc;   // [n_split][GQ][D] unnormalised outputs
+  float2 *part_ml;   // [n_split][GQ] (reference point, sum)
+  unsigned *part_cnt;
 };
+
+// What crosses compute units is written and read with relaxed device-scope atomics, two floats at a
+// time: such a store goes through to memory, so once the workgroup has waited for its own
+// (s_waitcnt) they are there for every other one, and no cache has to be written back or dropped.
+// (A release and an acquire fence around plain accesses: 24.4 instead of 12.3 us for the launch of one
+// sequence, 1536 keys, 32 query heads on 8.)
+__device__ __forceinline__ void put_pair(void *p, float a, float b) {
+  const unsigned long long v = ((unsigned long long)__float_as_uint(b) << 32) | __float_as_uint(a);
+  __hip_atomic_store((unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_pair(const void *p) {
+  const unsigned long long v = __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+// The last workgroup of a group to get here puts the shares together (the counter wraps to zero by
+// itself, ready for the next step).
+template <typename T, int D, int GQ>
+__device__ __forceinline__ void combine_shares(const RowQuery<T> &rq) {
+  __shared__ int last;
+  __shared__ float weight[GQ][kMaxSplit], inv_l[GQ];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicInc(rq.part_cnt, (unsigned)rq.n_split - 1u) == (unsigned)rq.n_split - 1u;
+  __syncthreads();
+  if (!last) return;
+  if (wave < GQ) {   // a wave per head, a lane per share
+    const bool on = lane < rq.n_split;
+    const float2 ml = on ? get_pair(rq.part_ml + lane * GQ + wave) : make_float2(-INFINITY, 0.f);
+    const float w = exp2f(ml.x - wave_max(ml.x));
+    const float l = wave_sum(ml.y * w);
+    if (on) weight[wave][lane] = w;
+    if (lane == 0) inv_l[wave] = 1.f / l;
+  }
+  __syncthreads();
+  for (int e = 2 * threadIdx.x; e < GQ * D; e += 512) {   // two channels of one head
+    const int hh = e / D, ch = e % D;
+    float o0 = 0.f, o1 = 0.f;
+#pragma unroll 8
+    for (int s = 0; s < rq.n_split; ++s) {
+      const float2 x = get_pair(rq.part_acc + (int64_t)(s * GQ + hh) * D + ch);
+      o0 = fmaf(x.x, weight[hh][s], o0);
+      o1 = fmaf(x.y, weight[hh][s], o1);
+    }
+    T *out = rq.out + hh * rq.o_h + ch;
+    if constexpr (sizeof(T) == 4)
+      *reinterpret_cast<float2 *>(out) = make_float2(o0 * inv_l[hh], o1 * inv_l[hh]);
+    else
+      *reinterpret_cast<uint32_t *>(out) = pack_bf16(o0 * inv_l[hh], o1 * inv_l[hh]);
+  }
+}
 
 template <typename T, int D, int GQ>
 __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
@@ -68,7 +127,15 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
   }
 
   const int m = rq.m;
-  const int total = m + (int)(pos - wb + 1);
+  int total = m + (int)(pos - wb + 1);
+  int n_first = 0;
+  if (rq.n_split > 1) {
+    // this workgroup's share: whole rounds of the loop below (a share can be empty)
+    constexpr int kRound = 4 * RPW * KB;
+    const int per = ((total + rq.n_split - 1) / rq.n_split + kRound - 1) / kRound * kRound;
+    n_first = rq.split * per;
+    total = total < n_first + per ? total : n_first + per;
+  }
   const T *khat = rq.khat, *vhat = rq.vhat, *ring_k = rq.ring_k, *ring_v = rq.ring_v;
   const T *in_k = rq.in_k, *in_v = rq.in_v;
 
@@ -81,7 +148,7 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
     for (int i = 0; i < VEC; ++i) acc[hh][i] = 0.f;
   }
 
-  for (int n0 = 0; n0 < total; n0 += 4 * RPW * KB) {
+  for (int n0 = n_first; n0 < total; n0 += 4 * RPW * KB) {
     float kf[KB][VEC], vf[KB][VEC];
     bool is_state[KB], on[KB];
 #pragma unroll
@@ -174,10 +241,19 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
       for (int i = 0; i < VEC; ++i) o[i] = 0.f;
 #pragma unroll
       for (int wv = 0; wv < 4; ++wv) {
-        const float sc = exp2f(sh_m[hh][wv] - mm);  // a wave that saw no key has max -inf -> 0
+        // a wave that saw no key has max -inf -> 0 (none of them did: an empty share)
+        const float sc = mm == -INFINITY ? 0.f : exp2f(sh_m[hh][wv] - mm);
         l += sh_l[hh][wv] * sc;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) o[i] += sh_acc[hh][wv][cl * VEC + i] * sc;
+      }
+      if (rq.n_split > 1) {
+        // a share's maximum is -inf when it was empty (then l and o are 0 * finite = 0)
+        const int slot = rq.split * GQ + hh;
+#pragma unroll
+        for (int i = 0; i < VEC; i += 2) put_pair(rq.part_acc + (int64_t)slot * D + cl * VEC + i, o[i], o[i + 1]);
+        if (cl == 0) put_pair(rq.part_ml + slot, mm, l);
+        continue;
       }
       const float inv = 1.f / l;
 #pragma unroll
@@ -186,12 +262,23 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
       if (rq.lse && cl == 0) rq.lse[hh * rq.lse_h] = (mm + log2f(l)) * kLn2;
     }
   }
+  if (rq.n_split > 1) combine_shares<T, D, GQ>(rq);
 }
 
-// One workgroup per (query, group of GQ query heads, sequence) of one state.
+// Where the shares of query-head group number `group` of the launch go.
+template <typename T, int D, int GQ>
+__device__ __forceinline__ void set_share(RowQuery<T> &rq, const Dev &dv, int group) {
+  rq.part_acc = dv.part_acc + (int64_t)group * rq.n_split * GQ * D;
+  rq.part_ml = dv.part_ml + group * rq.n_split * GQ;
+  rq.part_cnt = dv.part_cnt + group;
+}
+
+// One workgroup per (query, group of GQ query heads, sequence) of one state; in a decode step
+// several per group, sharing its keys.
 template <typename T, int D, int GQ>
 __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
-  const int qi = blockIdx.x, hq = blockIdx.y * GQ, b = blockIdx.z;
+  // a decode step has one query per sequence, and the x dimension counts the shares of its keys
+  const int qi = a.put_token ? 0 : blockIdx.x, hq = blockIdx.y * GQ, b = blockIdx.z;
   const int hkv = hq / (dv.Hq / dv.Hkv);
   const int u = b * dv.Hkv + hkv;
   RowQuery<T> rq;
@@ -217,7 +304,10 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
   rq.put_k = rq.put_v = nullptr;
   rq.put_g = nullptr;
   rq.gate = 1.f;
-  if (a.put_token && hq == hkv * (dv.Hq / dv.Hkv)) {
+  rq.split = blockIdx.x;
+  rq.n_split = a.put_token ? gridDim.x : 1;
+  set_share<T, D, GQ>(rq, dv, b * gridDim.y + blockIdx.y);
+  if (a.put_token && rq.split == 0 && hq == hkv * (dv.Hq / dv.Hkv)) {
     rq.put_k = (T *)dv.winK + (int64_t)u * dv.L * D;
     rq.put_v = (T *)dv.winV + (int64_t)u * dv.L * D;
     rq.put_g = dv.winG + (int64_t)u * dv.L;
@@ -227,13 +317,13 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
 }
 
 // Decode over sequences that live in different states (each at its own position, with its own
-// number of state rows): one workgroup per (group of GQ query heads, sequence); sequence s reads
-// seq[s].  dv is the states' common configuration (heads, chunk, window, temperatures).
+// number of state rows): one workgroup, or several sharing the keys, per (group of GQ query heads,
+// sequence); sequence s reads seq[s].  dv is the states' common configuration (heads, chunk, window, temperatures).
 template <typename T, int D, int GQ>
 __global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, const void *q,
                                                               const void *k, const void *v, const float *gate,
                                                               void *out) {
-  const int hq = blockIdx.x * GQ, s = blockIdx.y;
+  const int hq = blockIdx.y * GQ, s = blockIdx.z;
   const int hkv = hq / (dv.Hq / dv.Hkv);
   const SeqDesc sd = seq[s];
   RowQuery<T> rq;
@@ -257,7 +347,10 @@ __global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqD
   rq.put_k = rq.put_v = nullptr;
   rq.put_g = nullptr;
   rq.gate = 1.f;
-  if (hq == hkv * (dv.Hq / dv.Hkv)) {
+  rq.split = blockIdx.x;
+  rq.n_split = gridDim.x;
+  set_share<T, D, GQ>(rq, dv, s * gridDim.y + blockIdx.y);
+  if (rq.split == 0 && hq == hkv * (dv.Hq / dv.Hkv)) {
     rq.put_k = (T *)sd.winK + (int64_t)hkv * dv.L * D;
     rq.put_v = (T *)sd.winV + (int64_t)hkv * dv.L * D;
     rq.put_g = sd.winG + (int64_t)hkv * dv.L;
@@ -273,6 +366,19 @@ int heads_together(const Dev &dv) {
   const int G = dv.Hq / dv.Hkv;
   return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
 }
+
+// Workgroups that share the keys of one sequence in a decode step.  n_groups workgroups, each
+// walking all the keys, leave the chip idle when there are few of them, and a workgroup's walk is
+// a chain of memory round trips; the shares are at least one round of the loop.
+int shares_for(int n_groups, int keys, int round) {
+  if (n_groups >= kShareGroups) return 1;
+  int s = kSplitWorkgroups / n_groups;
+  const int most = (keys + round - 1) / round;
+  s = s < most ? s : most;
+  s = s < kMaxSplit ? s : kMaxSplit;
+  return s > 1 ? s : 1;
+}
+int round_keys(const Dev &dv) { return 16 * 64 / (dv.d / (dv.io == 0 ? 4 : 8)); }
 
 }  // namespace
 
@@ -295,7 +401,12 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   // a decode step (one query per sequence) takes a KV head's query heads together; a prefill on
   // this path has queries enough to fill the GPU head by head
   const int gq = a.put_token ? heads_together(dv) : 1;
-  dim3 grid(a.nq_total, dv.Hq / gq, dv.B);
+  int nx = a.nq_total;
+  if (a.put_token) {
+    const int64_t win = a.s % dv.C + 1 + dv.L - dv.C;   // window keys, at most
+    nx = shares_for(dv.Hq / gq * dv.B, a.m[0] + (int)win, round_keys(dv));
+  }
+  dim3 grid(nx, dv.Hq / gq, dv.B);
   if (gq == 4)
     KVM_ROWS_DISPATCH(attn_rows_kernel, 4, grid, dv, a);
   else if (gq == 2)
@@ -305,11 +416,11 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, const void *q, const void *k,
-                               const void *v, const float *gate, void *out, hipStream_t st) {
+hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int most_keys, const void *q,
+                               const void *k, const void *v, const float *gate, void *out, hipStream_t st) {
   if (n_seq <= 0) return hipSuccess;
   const int gq = heads_together(dv);
-  dim3 agrid(dv.Hq / gq, n_seq);
+  dim3 agrid(shares_for(dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
   if (gq == 4)
     KVM_ROWS_DISPATCH(attn_rows_multi_kernel, 4, agrid, dv, seq, q, k, v, gate, out);
   else if (gq == 2)

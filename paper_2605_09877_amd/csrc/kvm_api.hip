@@ -37,6 +37,7 @@ struct kvm_state {
   unsigned long long *xtab = nullptr;
   size_t xtab_bytes = 0;
   bool xtab_clean = false;
+  bool part_clean = false;  // the decode counters (Dev::part_cnt) have been zeroed
   uint32_t xchg = 2;
   int32_t *xerr_host = nullptr, *xerr_dev = nullptr;
   // kvm_debug_set knobs (0 = the library's own choice)
@@ -147,7 +148,8 @@ int64_t capacity_rows(const kvm_config &c, const std::vector<int64_t> &table, in
 }
 
 struct Layout {
-  size_t sK, sV, rho, w, n, khat, vhat, winK, winV, winG, kbar, score, pi, app, xtab, xtab_bytes, creator, total;
+  size_t sK, sV, rho, w, n, khat, vhat, winK, winV, winG, kbar, score, pi, app, xtab, xtab_bytes, part_acc, part_ml, part_cnt,
+      creator, total;
 };
 
 bool use_mfma(const kvm_config &c) {
@@ -188,6 +190,9 @@ Layout layout_of(const kvm_config &c, int64_t Mcap) {
   l.xtab_bytes = use_mfma(c) && U < (size_t)kClusterBelowUnits
                      ? U * 2 * (size_t)kvm::kFoldMaxSplit * 2 * C * sizeof(unsigned long long) : 0;
   l.xtab = take(l.xtab_bytes);
+  l.part_acc = take((size_t)kvm::kSplitWorkgroups * 4 * d * 4);
+  l.part_ml = take((size_t)kvm::kSplitWorkgroups * 4 * 8);
+  l.part_cnt = take((size_t)kvm::kSplitWorkgroups * 4);
   l.creator = take(U * C * 4);
   l.total = o;
   return l;
@@ -211,6 +216,9 @@ void bind(Dev &dv, const kvm_config &c, void *buf, int64_t Mcap) {
   dv.pi = (int32_t *)(p + l.pi);
   dv.app = (int32_t *)(p + l.app);
   dv.creator = (int32_t *)(p + l.creator);
+  dv.part_acc = (float *)(p + l.part_acc);
+  dv.part_ml = (float2 *)(p + l.part_ml);
+  dv.part_cnt = (unsigned *)(p + l.part_cnt);
   dv.gamma = c.ln_gamma;
   dv.beta = c.ln_beta;
   dv.tau_state = c.tau_state;
@@ -385,6 +393,20 @@ bool use_fused(const kvm_state *st) { return fold_split(st) > 0; }
 
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ull;
+}
+
+// The counters of a decode step whose keys are shared start at zero: cleared by the first decode call
+// on the buffer.  Under stream capture the clearing belongs to the graph, and later calls outside of
+// it must not count on it having run.
+int clean_shares(kvm_state *st, hipStream_t stream) {
+  if (st->part_clean) return KVM_OK;
+  hipLaunchKernelGGL(zero_words_kernel, dim3(2), dim3(256), 0, stream, (unsigned long long *)st->dv.part_cnt,
+                     (size_t)kvm::kSplitWorkgroups / 2);
+  HIP_TRY(hipGetLastError());
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(stream, &cap));
+  st->part_clean = cap == hipStreamCaptureStatusNone;
+  return KVM_OK;
 }
 
 // Arguments of a one-launch run; with shared rows also what the exchange needs: the table zeroed
@@ -602,6 +624,18 @@ int scratch_on_device(void **out) {
   }
   *out = g_scratch.ptr[dev];
   return KVM_OK;
+}
+
+// The most keys a sequence of these states attends to in this step: its state rows and the window
+// up to the new token.
+int most_keys(kvm_state *const *states, int n_states) {
+  int64_t most = 0;
+  for (int i = 0; i < n_states; ++i) {
+    const kvm_state *st = states[i];
+    const int64_t keys = st->m + st->tokens % st->dv.C + 1 + st->dv.L - st->dv.C;
+    most = keys > most ? keys : most;
+  }
+  return (int)most;
 }
 
 // Up to kPackStates states' worth of descriptors per launch, handed over as a kernel argument
@@ -1118,6 +1152,10 @@ int kvm_decode_step(kvm_state *st, const void *q, const void *k, const void *v,
     a.slot[i] = (int32_t)slot_of(st, st->folds);
   }
   {
+    const int rc = clean_shares(st, stream);
+    if (rc != KVM_OK) return rc;
+  }
+  {
     ProfileSpan span(st, 2, stream);
     HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
   }
@@ -1188,13 +1226,17 @@ int kvm_decode_step_multi(kvm_state *const *states, int32_t n_states, const void
       sd.Mcap = dv.Mcap;
     }
   }
+  {
+    const int rc = clean_shares(states[0], stream);
+    if (rc != KVM_OK) return rc;
+  }
   // pageable source: the copy is staged before the call returns, and ordered on the stream
   HIP_TRY(hipMemcpyAsync(workspace, desc.data(), desc.size() * sizeof(kvm::SeqDesc), hipMemcpyHostToDevice,
                          stream));
   {
     ProfileSpan span(states[0], 2, stream);
-    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)workspace, (int)n_seq, q, k, v, gate, out,
-                                     stream));
+    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)workspace, (int)n_seq,
+                                     most_keys(states, n_states), q, k, v, gate, out, stream));
   }
   for (int i = 0; i < n_states; ++i) {
     kvm_state *st = states[i];
@@ -1247,7 +1289,8 @@ int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, con
   }
   void *table = nullptr;
   {
-    const int rc = scratch_on_device(&table);
+    int rc = scratch_on_device(&table);
+    if (rc == KVM_OK) rc = clean_shares(states[0], stream);
     if (rc != KVM_OK) return rc;
   }
   // the descriptor table, kPackStates states per launch
@@ -1280,7 +1323,8 @@ int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, con
   }
   {
     ProfileSpan span(states[0], 2, stream);
-    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)table, (int)n_seq, q, k, v, gate, out, stream));
+    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)table, (int)n_seq, most_keys(states, n_states), q,
+                                     k, v, gate, out, stream));
   }
   for (int i = 0; i < n_states; ++i) {
     kvm_state *st = states[i];
@@ -1465,6 +1509,7 @@ int kvm_state_grow(kvm_state *st, void *new_buf, size_t new_bytes, int64_t new_m
   HIP_TRY(hipMemcpyAsync(nd.winV, od.winV, win, hipMemcpyDeviceToDevice, stream));
   HIP_TRY(hipMemcpyAsync(nd.winG, od.winG, U * od.L * 4, hipMemcpyDeviceToDevice, stream));
   st->dv = nd;
+  st->part_clean = false;
   st->buf = new_buf;
   st->bytes = new_bytes;
   {

@@ -42,6 +42,11 @@ struct Dev {
   int32_t *pi;       // [U, C]    row the token goes to
   int32_t *app;      // [U, C]    rank among appended tokens, or -1
   int32_t *creator;  // [U, C]    token that creates new row number a
+  // decode scratch: partial results of workgroups that share one sequence's keys (attn_rows.hip),
+  // for up to kSplitWorkgroups of them, and a counter per group of them (zero between launches)
+  float *part_acc;     // [workgroup][4 heads][d]
+  float2 *part_ml;     // [workgroup][4 heads]
+  unsigned *part_cnt;  // [workgroup]
   // parameters
   const float *gamma, *beta;          // [H_kv, d] or null
   const float *tau_state, *tau_bswa;  // [H_q] or null
@@ -121,6 +126,8 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
 // score_mfma.hip (bf16, d = 128)
 hipError_t launch_score_mfma(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st);
 // attn_rows.hip
+constexpr int kSplitWorkgroups = 1024;  // workgroups of a decode launch whose keys are shared
+constexpr int kShareGroups = 512;      // from this many (sequence, head group) pairs on they are not
 hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st);
 // One decode step over sequences of several states (kvm_decode_step_multi): per sequence, where
 // its arrays start (its first KV head) and where it stands.
@@ -131,8 +138,9 @@ struct SeqDesc {
   int64_t pos;              // position of the token being decoded
   int32_t m, Mcap;          // state rows now, rows per unit in the buffer
 };
-hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, const void *q, const void *k,
-                               const void *v, const float *gate, void *out, hipStream_t st);
+// most_keys: the largest number of keys (state rows and window) any of the sequences attends to
+hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int most_keys, const void *q,
+                               const void *k, const void *v, const float *gate, void *out, hipStream_t st);
 // attn_mfma.hip (bf16, d = 128)
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st);
 
