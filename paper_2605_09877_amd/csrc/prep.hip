@@ -9,6 +9,10 @@
 // and the rotation partner come through lane exchanges.
 // Arithmetic is fp32; the rotation angles are evaluated in fp64 once per position (a table),
 // because position * frequency loses its low bits in fp32 at 32k tokens.
+// The rows of q, k and v are the sections of one launch.  What that launch needs beforehand -- the
+// table, and the gate's weights as two bf16 halves -- is made by one launch ahead of it; a call of
+// a few tokens (generation) makes its own table in LDS, has its gate on the vector units and is a
+// single launch.
 #include "../../include/kvm.h"
 #include "kvm_device.h"
 #include "kvm_mfma.h"
@@ -16,14 +20,32 @@
 namespace kvm {
 namespace {
 
-__global__ __launch_bounds__(256) void rope_table_kernel(float2 *tab, int64_t n_pos, int64_t pos0, int half,
-                                                         double base) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_pos * half) return;
-  const int64_t t = i / half;
-  const int c = (int)(i % half);
-  const double ang = (double)(pos0 + t) * pow(base, -(double)c / (double)half);  // base^(-2c/r)
-  tab[i] = make_float2((float)cos(ang), (float)sin(ang));
+constexpr int64_t kGateFewMost = 64, kGateFewMostVector = 512, kGateShortMost = 16384;  // tokens
+constexpr int kGateHeads = 32;  // matrix-core gate: heads of the operand (zero rows beyond H_kv)
+
+// (cos, sin) of channel c < half at position pos
+__device__ __forceinline__ float2 rotation(int64_t pos, int c, int half, double base) {
+  const double ang = (double)pos * pow(base, -(double)c / (double)half);  // base^(-2c/r)
+  return make_float2((float)cos(ang), (float)sin(ang));
+}
+
+// Ahead of the rows: workgroups [0, table_wgs) make the rotation table, the others split W_g (fp32)
+// into hi = bf16(w) and lo = bf16(w - hi), transposed to [kGateHeads][d_model].
+__global__ __launch_bounds__(256) void prep_setup_kernel(float2 *tab, int64_t n_pos, int64_t pos0, int half, double base,
+                                                         unsigned table_wgs, const float *w, uint16_t *hi, uint16_t *lo,
+                                                         int dm, int Hkv) {
+  if (blockIdx.x < table_wgs) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n_pos * half) tab[i] = rotation(pos0 + i / half, (int)(i % half), half, base);
+    return;
+  }
+  const int i = (blockIdx.x - table_wgs) * 256 + threadIdx.x;  // over kGateHeads * dm
+  if (i >= kGateHeads * dm) return;
+  const int h = i / dm, c = i - h * dm;
+  const float x = h < Hkv ? w[(int64_t)c * Hkv + h] : 0.f;
+  const uint16_t a = float_to_bf16_bits(x);
+  hi[i] = a;
+  lo[i] = float_to_bf16_bits(x - bf16_bits_to_float(a));
 }
 
 struct RowArgs {
@@ -34,10 +56,10 @@ struct RowArgs {
   const float *alpha;   // [H, d] or null
   const float *lambda;  // [H, d] or null
   const float *gamma, *beta;  // [H, d] or null
-  const float2 *tab;    // [T, r/2] (cos, sin)
   int64_t T;
-  int H, r, normalise;
+  int H, r;
   float eps;
+  uint32_t n_hg, n_runs, n_waves;  // head groups, token runs, waves = batch * runs * head groups
 };
 
 // kN fp32 parameters starting at p (16-byte aligned), or the neutral value when p is null.
@@ -57,20 +79,23 @@ __device__ __forceinline__ void load_params(const float *p, float neutral, float
 
 // kNorm: LayerNorm + rotation (q, k); kResidual: value residual (v).
 // A wave takes 64 / (D / kN) adjacent heads (one per lane group: together a contiguous piece of a
-// token) and walks kRun consecutive tokens of them, so that the token shift's "previous token" is
+// token) and walks run_len consecutive tokens of them, so that the token shift's "previous token" is
 // the row the lane group has just had in registers instead of a second read of it (one extra row
 // per run), and the per-head parameters are fetched once per run.  Tokens go in blocks of kAhead
-// whose loads are all requested before the first of them is worked on.
-constexpr int kRun = 16, kAhead = 4;
+// whose loads are all requested before the first of them is worked on.  The run's length is 16
+// where that leaves waves enough to fill the chip, and 8 or 4 in shorter calls.
+// wg4: number of the workgroup within the tensor's section; tab: row 0 is the call's first token.
+constexpr int kRunMost = 16, kAhead = 4;
 template <typename T, int D, bool kNorm, bool kResidual>
-__global__ __launch_bounds__(256) void prep_rows_kernel(RowArgs a, uint32_t n_hg, uint32_t n_runs, uint32_t n_waves) {
+__device__ __forceinline__ void prep_rows(const RowArgs &a, uint32_t wg4, uint32_t run_len, const float2 *tab) {
   constexpr int VEC = Vec16<T>::kN;
   constexpr int LPT = D / VEC;   // lanes per row
   constexpr int RPW = 64 / LPT;  // heads per wave
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPT, cl = lane % LPT;
-  const uint32_t wg = blockIdx.x * 4u + wave;  // adjacent waves: adjacent head groups of one token run
-  if (wg >= n_waves) return;
+  const uint32_t n_hg = a.n_hg, n_runs = a.n_runs;
+  const uint32_t wg = wg4 * 4u + wave;  // adjacent waves: adjacent head groups of one token run
+  if (wg >= a.n_waves) return;
   const uint32_t hg = wg % n_hg, br = wg / n_hg, run = br % n_runs, b = br / n_runs;
   const uint32_t H = (uint32_t)a.H, T_ = (uint32_t)a.T;
   const uint32_t h_raw = hg * RPW + sub;
@@ -78,7 +103,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowArgs a, uint32_t n_hg
   const uint32_t h = live ? h_raw : H - 1;  // idle lane groups repeat the last head, store nothing
   const int c0 = cl * VEC;
   const int pc = (int)h * D + c0;  // offset into the per-head parameter arrays
-  const uint32_t t_begin = run * kRun, t_end = t_begin + kRun < T_ ? t_begin + kRun : T_;
+  const uint32_t t_begin = run * run_len, t_end = t_begin + run_len < T_ ? t_begin + run_len : T_;
   const int64_t row_stride = (int64_t)H * D;  // elements between tokens
   const int64_t off0 = (((int64_t)b * T_ + t_begin) * H + h) * D + c0;
   const bool resid = kResidual && a.first && a.lambda;
@@ -156,7 +181,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowArgs a, uint32_t n_hg
           if (c0 < a.r) {
             const bool lower = c0 < half;
             float cs[2 * VEC];  // (cos, sin) of this lane's channels
-            load_params<2 * VEC>((const float *)(a.tab + (int64_t)t * half + (lower ? c0 : c0 - half)), 0.f, cs);
+            load_params<2 * VEC>((const float *)(tab + (int64_t)t * half + (lower ? c0 : c0 - half)), 0.f, cs);
 #pragma unroll
             for (int i = 0; i < VEC; ++i)
               z[i] = lower ? z[i] * cs[2 * i] - o[i] * cs[2 * i + 1] : z[i] * cs[2 * i] + o[i] * cs[2 * i + 1];
@@ -167,6 +192,8 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(RowArgs a, uint32_t n_hg
     }
   }
 }
+
+__device__ __forceinline__ float gate_of(float z) { return 1.f + (z > 0.f ? z : expm1f(z)); }
 
 // Merge gate: a wave takes kGateTok tokens; lanes stride over the model width, 16 bytes of x each,
 // heads in blocks of eight; the per-lane partial dot products are summed across the wave at the
@@ -215,95 +242,235 @@ __global__ __launch_bounds__(256) void gate_kernel(const T *x, const float *w, f
       for (int j = 0; j < 8; ++j) {
         const float z = wave_sum(acc[k][j]);
         if (lane == 0 && tok0 + k < n_tok && h0 + j < Hkv)
-          gate[(tok0 + k) * Hkv + h0 + j] = 1.f + (z > 0.f ? z : expm1f(z));
+          gate[(tok0 + k) * Hkv + h0 + j] = gate_of(z);
       }
   }
 }
 
 // The merge gate on the matrix cores (bf16 x, at most 32 KV heads, d_model a multiple of 128).
-// W_g is fp32; it is split once per call into two bf16 halves, hi = bf16(w) and lo = bf16(w - hi),
-// transposed to [32 heads (zero rows beyond H_kv)][d_model], so that x W_g = x hi + x lo with the
-// products exact and the sums in fp32: the same 1e-6-relative arithmetic as the vector version.
-constexpr int kGateHeads = 32;
-__global__ __launch_bounds__(256) void gate_split_kernel(const float *w, uint16_t *hi, uint16_t *lo, int dm, int Hkv) {
-  const int i = blockIdx.x * 256 + threadIdx.x;  // over kGateHeads * dm
-  if (i >= kGateHeads * dm) return;
-  const int h = i / dm, c = i - h * dm;
-  const float x = h < Hkv ? w[(int64_t)c * Hkv + h] : 0.f;
-  const uint16_t a = float_to_bf16_bits(x);
-  hi[i] = a;
-  lo[i] = float_to_bf16_bits(x - bf16_bits_to_float(a));
-}
-
-// A wave takes 64 tokens (two blocks of 32 rows of the matrix instruction) and all heads; x goes
-// from global memory straight into the A operand (lane = token row, 16 bytes = its 8 channels of
-// the step), W's halves into the B operand (lane = head).  Per 128 channels: 16 loads of x in
-// flight per lane, 32 matrix instructions.
+// With W_g split into two bf16 halves, x W_g = x hi + x lo with the products exact and the sums in
+// fp32: the same 1e-6-relative arithmetic as the vector version.
+// A workgroup takes 128 tokens, a wave 32 of them and all heads.  x comes through LDS in tiles of 128
+// channels, two stages, filled by direct loads of 256-byte row pieces; W's halves go from the caches
+// straight into the B operand (lane = head).  Bound by the bytes of x: read from global memory into
+// the A operand directly, a load instruction touches 32 rows 32 bytes each, and 65536 tokens x 2048
+// took 102 us (2.6 TB/s) with 64 or 32 tokens per wave, one step of loads ahead or none; so staged, 82 us
+// (3.3 TB/s).
 __global__ __launch_bounds__(256) void gate_mfma_kernel(const uint16_t *x, const uint16_t *hi, const uint16_t *lo,
                                                         float *gate, int64_t n_tok, int dm, int Hkv) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(1024))) uint16_t Xs[2][2][kTileElems];   // [stage][token half]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int64_t tok0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
-  if (tok0 >= n_tok) return;
-  const uint16_t *xr[2];
-#pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
-    const int64_t t = tok0 + 32 * tb + l32;
-    xr[tb] = x + (t < n_tok ? t : n_tok - 1) * dm + 8 * g;
-  }
+  const int64_t wg0 = (int64_t)blockIdx.x * 128, tok0 = wg0 + 32 * wave;
+  const int valid = n_tok - wg0 < 128 ? (int)(n_tok - wg0) : 128;
+  const char *xb = (const char *)(x + wg0 * dm);
+  const uint32_t stride = (uint32_t)dm * 2, xs_addr = lds_addr_of(&Xs[0][0][0]);
+  const DmaLane dl = dma_lane(lane);
+  uint32_t koff[8];
+  ktile_offsets(lane, koff);
+  auto issue = [&](int c0, int stage) {
+    // (rows past the end repeat the last one: a second half without tokens repeats the first half's)
+    const uint32_t at = xs_addr + (uint32_t)stage * (2 * kTileElems * 2);
+    const char *from = xb + (size_t)c0 * 2;
+    tile_dma<false, 4>(from, stride, valid, at, wave, dl);
+    if (valid > kTileKeys)
+      tile_dma<false, 4>(from + (size_t)kTileKeys * stride, stride, valid - kTileKeys, at + kTileElems * 2, wave, dl);
+  };
   const bool head_lane = l32 < ((Hkv + 7) & ~7);  // lanes of the zero rows need not load them
   const uint16_t *hr = hi + (int64_t)l32 * dm + 8 * g, *lr = lo + (int64_t)l32 * dm + 8 * g;
-  f32x16 acc[2];
-#pragma unroll
-  for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[tb][v] = 0.f;
-  for (int c0 = 0; c0 < dm; c0 += 128) {
-    Frag8 xa[2][8], wh[8], wl[8];
+  f32x16 acc = {0.f};
+  struct Weights {
+    Frag8 h[8], l[8];
+  };
+  auto fetch = [&](Weights &w, int c0) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) xa[tb][ks].q = *reinterpret_cast<const uint4 *>(xr[tb] + c0 + 16 * ks);
-      wh[ks].q = wl[ks].q = make_uint4(0u, 0u, 0u, 0u);
+      w.h[ks].q = w.l[ks].q = make_uint4(0u, 0u, 0u, 0u);
       if (head_lane) {
-        wh[ks].q = *reinterpret_cast<const uint4 *>(hr + c0 + 16 * ks);
-        wl[ks].q = *reinterpret_cast<const uint4 *>(lr + c0 + 16 * ks);
+        w.h[ks].q = *reinterpret_cast<const uint4 *>(hr + c0 + 16 * ks);
+        w.l[ks].q = *reinterpret_cast<const uint4 *>(lr + c0 + 16 * ks);
       }
     }
+  };
+  // one step: everything asked for a step ago has landed; the next step's weights are asked for
+  // ahead of its x (loads return in order: behind them, they would be waited for as long as x is)
+  auto step = [&](int c0, int stage, const Weights &now, Weights &next) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (c0 + 128 < dm) {
+      fetch(next, c0 + 128);
+      issue(c0 + 128, stage ^ 1);
+    }
+    const uint16_t *Xt = &Xs[stage][wave >> 1][0];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        acc[tb] = mfma32(xa[tb][ks].v, wh[ks].v, acc[tb]);
-        acc[tb] = mfma32(xa[tb][ks].v, wl[ks].v, acc[tb]);
-      }
+    for (int ks = 0; ks < 8; ++ks) {
+      const bf16x8 xf = ktile_frag(Xt, koff, wave & 1, ks);
+      acc = mfma32(xf, now.h[ks].v, acc);
+      acc = mfma32(xf, now.l[ks].v, acc);
+    }
+  };
+  Weights w0, w1;
+  fetch(w0, 0);
+  issue(0, 0);
+  for (int c0 = 0; c0 < dm; c0 += 256) {
+    step(c0, 0, w0, w1);
+    if (c0 + 128 < dm) step(c0 + 128, 1, w1, w0);
   }
   if (l32 < Hkv) {
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t t = tok0 + 32 * tb + mfma_row(v, g);
-        const float z = acc[tb][v];
-        if (t < n_tok) gate[t * Hkv + l32] = 1.f + (z > 0.f ? z : expm1f(z));
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int64_t t = tok0 + mfma_row(v, g);
+      if (t < n_tok) gate[t * Hkv + l32] = gate_of(acc[v]);
+    }
   }
 }
 
-template <typename T, bool kNorm, bool kResidual>
-hipError_t launch_rows(const RowArgs &a, int d, int batch, hipStream_t st) {
-  const int heads_per_wave = 64 / (d / Vec16<T>::kN);
-  const uint32_t n_hg = (uint32_t)((a.H + heads_per_wave - 1) / heads_per_wave);
-  const uint32_t n_runs = (uint32_t)((a.T + kRun - 1) / kRun);
-  const int64_t n_waves = (int64_t)batch * n_runs * n_hg;
-  if (n_waves >= (1ll << 31)) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((n_waves + 3) / 4));
-  if (d == 64)
-    hipLaunchKernelGGL((prep_rows_kernel<T, 64, kNorm, kResidual>), grid, dim3(256), 0, st, a, n_hg, n_runs,
-                       (uint32_t)n_waves);
+// The gate of short calls, as a section of the rows' launch, 16 tokens per workgroup: the four waves
+// take a quarter of the channels each (a wave that walks all of them is a chain of d_model / 64 memory
+// round trips, and a short call has no other waves to hide it behind) and their sums meet in LDS.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+constexpr int kGateShortTok = 16;
+struct GateArgs {
+  const void *x;
+  const float *w;
+  const uint16_t *hi, *lo;
+  float *gate;
+  int64_t n_tok;
+  int dm, Hkv;
+};
+__device__ __forceinline__ void gate_short(const GateArgs &a, uint32_t wg, float *sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int64_t tok0 = (int64_t)wg * kGateShortTok;
+  const int64_t t_lane = tok0 + l16;
+  const int c_first = wave * (a.dm / 4);
+  const uint16_t *xr = (const uint16_t *)a.x + (t_lane < a.n_tok ? t_lane : a.n_tok - 1) * a.dm + c_first + 8 * g;
+  const uint16_t *hr = a.hi + (int64_t)l16 * a.dm + c_first + 8 * g, *lr = a.lo + (int64_t)l16 * a.dm + c_first + 8 * g;
+  const bool two = a.Hkv > 16;   // a second column tile of heads
+  const int64_t tile = (int64_t)16 * a.dm;
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 8
+  for (int c = 0; c < a.dm / 4; c += 32) {
+    Frag8 xf, hf, lf;
+    xf.q = *reinterpret_cast<const uint4 *>(xr + c);
+    hf.q = *reinterpret_cast<const uint4 *>(hr + c);
+    lf.q = *reinterpret_cast<const uint4 *>(lr + c);
+    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf.v, hf.v, acc[0], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf.v, lf.v, acc[0], 0, 0, 0);
+    if (two) {
+      hf.q = *reinterpret_cast<const uint4 *>(hr + tile + c);
+      lf.q = *reinterpret_cast<const uint4 *>(lr + tile + c);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf.v, hf.v, acc[1], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf.v, lf.v, acc[1], 0, 0, 0);
+    }
+  }
+  // D of the 16x16 instruction: column (head) = lane % 16, row (token) = 4 * (lane / 16) + element
+#pragma unroll
+  for (int ht = 0; ht < 2; ++ht)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sh[((wave * 2 + ht) * 16 + 4 * g + v) * 16 + l16] = acc[ht][v];
+  __syncthreads();
+  for (int i = threadIdx.x; i < kGateShortTok * kGateHeads; i += 256) {
+    const int tok = i / kGateHeads, h = i % kGateHeads, at = ((h >> 4) * 16 + tok) * 16 + (h & 15);
+    const float z = (sh[at] + sh[at + 512]) + (sh[at + 1024] + sh[at + 1536]);
+    if (h < a.Hkv && tok0 + tok < a.n_tok) a.gate[(tok0 + tok) * a.Hkv + h] = gate_of(z);
+  }
+}
+
+// The gate of a few tokens on the vector units, a workgroup per token: threads stride over the
+// channels, eight heads at a time, fp32 weights as they are.
+template <typename T>
+__device__ __forceinline__ void gate_few(const GateArgs &a, uint32_t tok, float *sh) {
+  constexpr int VEC = Vec16<T>::kN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const T *xr = (const T *)a.x + (int64_t)tok * a.dm;
+  const bool full = a.Hkv % 8 == 0;
+  for (int h0 = 0; h0 < a.Hkv; h0 += 8) {
+    float acc[8] = {};
+    for (int c0 = threadIdx.x * VEC; c0 < a.dm; c0 += 256 * VEC) {
+      float xv[VEC], wv[VEC][8];
+      Vec16<T>::load(xr + c0, xv);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        const float *wrow = a.w + (int64_t)(c0 + i) * a.Hkv + h0;
+        if (full) {
+          load_params<8>(wrow, 0.f, wv[i]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) wv[i][j] = h0 + j < a.Hkv ? wrow[j] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = fmaf(xv[i], wv[i][j], acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float z = wave_sum(acc[j]);
+      if (lane == 0) sh[wave * 8 + j] = z;
+    }
+    __syncthreads();
+    if (threadIdx.x < 8 && h0 + (int)threadIdx.x < a.Hkv)
+      a.gate[(int64_t)tok * a.Hkv + h0 + threadIdx.x] =
+          gate_of((sh[threadIdx.x] + sh[8 + threadIdx.x]) + (sh[16 + threadIdx.x] + sh[24 + threadIdx.x]));
+    __syncthreads();
+  }
+}
+
+// The rows of q, k and v, and with kGate the gate, as sections of one grid: the gate's workgroups
+// first (the longest), then q's, k's, v's.
+enum { kGateElsewhere = 0, kGateFew = 1, kGateShort = 2 };
+constexpr int kTableMost = 256;   // table entries a workgroup makes for itself, one per thread
+struct PrepArgs {
+  RowArgs q, k, v;
+  GateArgs gate;
+  const float2 *tab;      // [T, r/2] (cos, sin), or null: every workgroup makes its own
+  int64_t pos0;
+  double base;
+  uint32_t wg_gate, wg_q, wg_k;   // workgroups of the first three sections
+  uint32_t run;                   // tokens a wave walks
+};
+template <typename T, int D, int kGate>
+__global__ __launch_bounds__(256) void prep_rows_kernel(PrepArgs p) {
+  __shared__ float2 own_tab[kTableMost];
+  uint32_t wg = blockIdx.x;
+  if constexpr (kGate != kGateElsewhere) {
+    if (wg < p.wg_gate) {
+      __shared__ float sh[kGate == kGateShort ? 4 * 2 * 16 * 16 : 32];
+      if constexpr (kGate == kGateShort)
+        gate_short(p.gate, wg, sh);
+      else
+        gate_few<T>(p.gate, wg, sh);
+      return;
+    }
+    wg -= p.wg_gate;
+  }
+  const float2 *tab = p.tab;
+  if (!tab && p.q.r > 0 && wg < p.wg_q + p.wg_k) {
+    const int half = p.q.r / 2;
+    if ((int64_t)threadIdx.x < p.q.T * half)
+      own_tab[threadIdx.x] = rotation(p.pos0 + threadIdx.x / half, threadIdx.x % half, half, p.base);
+    __syncthreads();
+    tab = own_tab;
+  }
+  if (wg < p.wg_q)
+    prep_rows<T, D, true, false>(p.q, wg, p.run, tab);
+  else if (wg < p.wg_q + p.wg_k)
+    prep_rows<T, D, true, false>(p.k, wg - p.wg_q, p.run, tab);
   else
-    hipLaunchKernelGGL((prep_rows_kernel<T, 128, kNorm, kResidual>), grid, dim3(256), 0, st, a, n_hg, n_runs,
-                       (uint32_t)n_waves);
+    prep_rows<T, D, false, true>(p.v, wg - p.wg_q - p.wg_k, p.run, tab);
+}
+
+template <typename T, int D>
+hipError_t launch_prep(const PrepArgs &p, int gate, unsigned wgs, hipStream_t st) {
+  if (gate == kGateShort)
+    hipLaunchKernelGGL((prep_rows_kernel<T, D, kGateShort>), dim3(wgs), dim3(256), 0, st, p);
+  else if (gate == kGateFew)
+    hipLaunchKernelGGL((prep_rows_kernel<T, D, kGateFew>), dim3(wgs), dim3(256), 0, st, p);
+  else
+    hipLaunchKernelGGL((prep_rows_kernel<T, D, kGateElsewhere>), dim3(wgs), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -368,45 +535,66 @@ extern "C" int kvm_prepare_qkv(const kvm_prep_params *p, const void *q_raw, cons
   const int d = p->head_dim, r = p->rope_dims, half = r / 2;
   const float eps = p->ln_eps > 0.f ? p->ln_eps : 1e-5f;
   float2 *tab = (float2 *)scratch;
-  if (half > 0) {
-    const int64_t n = T * half;
-    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tab, T, pos0, half,
-                       p->rope_base > 0.0 ? p->rope_base : 10000.0);
+  const double base = p->rope_base > 0.0 ? p->rope_base : 10000.0;
+  const int64_t n_tok = (int64_t)p->batch * T;
+  if (n_tok * p->n_q_heads >= (1ll << 31) || n_tok * p->n_kv_heads >= (1ll << 31)) return KVM_ERR_ARG;  // 32-bit row numbers
+  const int dm = p->d_model, hk = p->n_kv_heads;
+
+  // How the gate is computed: a few tokens on the vector units, up to kGateShortMost on the matrix
+  // cores with the channels divided among the waves, both inside the rows' launch; beyond that by
+  // a launch of its own whose waves take all channels of their tokens.
+  const bool mfma = gate_on_mfma(p);
+  int how = kGateElsewhere;
+  if (gate && n_tok <= (mfma ? kGateFewMost : kGateFewMostVector)) how = kGateFew;
+  else if (gate && mfma && n_tok < kGateShortMost) how = kGateShort;
+  uint16_t *hi = (uint16_t *)((char *)scratch + rope_table_bytes(p, T)), *lo = hi + (size_t)kGateHeads * dm;
+  const bool own_table = half > 0 && T * half <= kTableMost;   // every workgroup makes its own
+  const unsigned table_wgs = half > 0 && !own_table ? (unsigned)((T * half + 255) / 256) : 0u;
+  const unsigned split_wgs = gate && mfma && how != kGateFew ? (unsigned)((kGateHeads * dm + 255) / 256) : 0u;
+  if (table_wgs + split_wgs > 0) {
+    hipLaunchKernelGGL(prep_setup_kernel, dim3(table_wgs + split_wgs), dim3(256), 0, st, tab, T, pos0, half, base, table_wgs,
+                       p->w_gate, hi, lo, dm, hk);
     if (hipGetLastError() != hipSuccess) return KVM_ERR_HIP;
   }
-  auto rows = [&](const void *in, const void *first, const void *prev, void *out, const float *alpha,
-                  const float *lambda, const float *gamma, const float *beta, int H, int normalise) -> int {
-    RowArgs a;
-    a.in = in; a.first = first; a.prev = prev; a.out = out;
-    a.alpha = alpha; a.lambda = lambda; a.gamma = gamma; a.beta = beta;
-    a.tab = tab; a.T = T; a.H = H; a.r = r; a.normalise = normalise; a.eps = eps;
-    const int64_t n_rows = (int64_t)p->batch * T * H;
-    if (n_rows >= (1ll << 31)) return KVM_ERR_ARG;  // rows are indexed with 32 bits
-    hipError_t e;
-    if (p->io_dtype == KVM_F32)
-      e = normalise ? launch_rows<float, true, false>(a, d, p->batch, st) : launch_rows<float, false, true>(a, d, p->batch, st);
-    else
-      e = normalise ? launch_rows<bf16_t, true, false>(a, d, p->batch, st)
-                    : launch_rows<bf16_t, false, true>(a, d, p->batch, st);
-    return e == hipSuccess ? KVM_OK : KVM_ERR_HIP;
+
+  PrepArgs a;
+  const int heads_per_wave = 64 / (d * (p->io_dtype == KVM_F32 ? 4 : 2) / 16);
+  // tokens per wave: long runs re-read the fewest rows for the shift, short ones make waves enough
+  const int64_t waves16 = n_tok / kRunMost * ((p->n_q_heads + 2 * hk + heads_per_wave - 1) / heads_per_wave);
+  a.run = waves16 >= 4096 ? kRunMost : waves16 >= 2048 ? kRunMost / 2 : kAhead;
+  auto section = [&](RowArgs &r_, const void *in, const void *first, const void *prev, void *out, const float *alpha,
+                     const float *lambda, const float *gamma, const float *beta, int H) -> uint32_t {
+    r_.in = in; r_.first = first; r_.prev = prev; r_.out = out;
+    r_.alpha = alpha; r_.lambda = lambda; r_.gamma = gamma; r_.beta = beta;
+    r_.T = T; r_.H = H; r_.r = r; r_.eps = eps;
+    r_.n_hg = (uint32_t)((H + heads_per_wave - 1) / heads_per_wave);
+    r_.n_runs = (uint32_t)((T + a.run - 1) / a.run);
+    r_.n_waves = (uint32_t)p->batch * r_.n_runs * r_.n_hg;
+    return (r_.n_waves + 3) / 4;
   };
-  int rc = rows(q_raw, nullptr, prev_q, q_out, p->alpha_q, nullptr, p->lnq_gamma, p->lnq_beta, p->n_q_heads, 1);
-  if (rc != KVM_OK) return rc;
-  rc = rows(k_raw, nullptr, prev_k, k_out, p->alpha_k, nullptr, p->lnk_gamma, p->lnk_beta, p->n_kv_heads, 1);
-  if (rc != KVM_OK) return rc;
-  rc = rows(v_raw, v_first, prev_v, v_out, p->alpha_v, p->lambda_v, nullptr, nullptr, p->n_kv_heads, 0);
-  if (rc != KVM_OK) return rc;
-  if (gate) {
-    const int64_t n_tok = (int64_t)p->batch * T;
+  a.wg_q = section(a.q, q_raw, nullptr, prev_q, q_out, p->alpha_q, nullptr, p->lnq_gamma, p->lnq_beta, p->n_q_heads);
+  a.wg_k = section(a.k, k_raw, nullptr, prev_k, k_out, p->alpha_k, nullptr, p->lnk_gamma, p->lnk_beta, hk);
+  const uint32_t wg_v = section(a.v, v_raw, v_first, prev_v, v_out, p->alpha_v, p->lambda_v, nullptr, nullptr, hk);
+  a.wg_gate = how == kGateFew ? (uint32_t)n_tok
+              : how == kGateShort ? (uint32_t)((n_tok + kGateShortTok - 1) / kGateShortTok) : 0u;
+  a.gate = GateArgs{x, p->w_gate, hi, lo, gate_out, n_tok, dm, hk};
+  a.tab = own_table ? nullptr : tab;
+  a.pos0 = pos0;
+  a.base = base;
+  const unsigned wgs = a.wg_gate + a.wg_q + a.wg_k + wg_v;
+  hipError_t e;
+  if (p->io_dtype == KVM_F32)
+    e = d == 64 ? launch_prep<float, 64>(a, how, wgs, st) : launch_prep<float, 128>(a, how, wgs, st);
+  else
+    e = d == 64 ? launch_prep<bf16_t, 64>(a, how, wgs, st) : launch_prep<bf16_t, 128>(a, how, wgs, st);
+  if (e != hipSuccess) return KVM_ERR_HIP;
+
+  if (gate && how == kGateElsewhere) {
     dim3 grid((unsigned)((n_tok + 4 * kGateTok - 1) / (4 * kGateTok)));
-    const bool full = p->n_kv_heads % 8 == 0;
+    const bool full = hk % 8 == 0;
     const float *wg = p->w_gate;
-    const int dm = p->d_model, hk = p->n_kv_heads;
-    if (gate_on_mfma(p)) {
-      uint16_t *hi = (uint16_t *)((char *)scratch + rope_table_bytes(p, T)), *lo = hi + (size_t)kGateHeads * dm;
-      hipLaunchKernelGGL(gate_split_kernel, dim3((unsigned)((kGateHeads * dm + 255) / 256)), dim3(256), 0, st, wg, hi,
-                         lo, dm, hk);
-      hipLaunchKernelGGL(gate_mfma_kernel, dim3((unsigned)((n_tok + 255) / 256)), dim3(256), 0, st,
+    if (mfma) {
+      hipLaunchKernelGGL(gate_mfma_kernel, dim3((unsigned)((n_tok + 127) / 128)), dim3(256), 0, st,
                          (const uint16_t *)x, hi, lo, gate_out, n_tok, dm, hk);
     } else if (p->io_dtype == KVM_F32) {
       if (full)

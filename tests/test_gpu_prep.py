@@ -83,3 +83,17 @@ def test_prep_rejects_bad_arguments():
         kb.prepare_qkv(q, q.clone(), q.clone(), rope_dims=48)          # half = 24 channels: 3 lanes
     with pytest.raises(kb.KVMError):
         kb.prepare_qkv(q, q.clone(), q.clone(), rope_dims=32, x=torch.zeros(1, 4, 64, dtype=torch.bfloat16, device=DEV))
+
+
+@pytest.mark.parametrize("io,B,T,Hq,Hkv,dm", [
+    ("bf16", 1, 1, 8, 2, 512),       # one token: own rotation table, vector gate, one launch
+    ("bf16", 3, 4, 4, 4, 256),       # the largest own table (4 positions x 64 channels), more heads than lane groups
+    ("bf16", 1, 5, 4, 4, 256),       # one position more: the table is made ahead
+    ("bf16", 1, 64, 2, 2, 128), ("bf16", 1, 65, 2, 2, 128),   # the last call with the vector gate, the first without
+    ("bf16", 1, 200, 20, 20, 384),   # more than 16 heads: two column tiles of the gate
+    ("bf16", 2, 8191, 1, 1, 128), ("bf16", 2, 8192, 1, 1, 128),   # the gate's own launch from 16384 tokens on
+    ("bf16", 1, 16384 + 37, 2, 2, 256),   # its last workgroup with 37 tokens
+    ("f32", 1, 1, 4, 2, 64), ("f32", 1, 512, 2, 2, 64), ("f32", 1, 513, 2, 2, 64)])
+def test_prep_call_sizes(io, B, T, Hq, Hkv, dm):
+    """Both sides of every size at which the preparation is arranged differently."""
+    run_case(io, B=B, T=T, Hq=Hq, Hkv=Hkv, d=128, r=128 if T < 6 else 32, dm=dm, pos0=300, seed=T, with_prev=T % 2 == 1)
