@@ -267,9 +267,9 @@ int kvm_state_import(kvm_state *st, const double *sK, const float *sV, const flo
 
 /* Choices the library normally makes by itself, forced for tests and comparisons (no passage of
  * the paper).  value 0 gives the choice back to the library.  Takes effect from the next call on.
- *   KVM_DEBUG_FOLD_PATH         1: a run of folds is one launch, one workgroup per unit (bf16,
- *                               head_dim 128, block lengths 64 * 2^k up to 1024), 2: one kernel
- *                               per fold step (the default)
+ *   KVM_DEBUG_FOLD_PATH         1: a run of folds is one launch (bf16, head_dim 128, block lengths
+ *                               64 * 2^k up to 1024; one workgroup per unit unless
+ *                               KVM_DEBUG_FOLD_SPLIT says otherwise), 2: one kernel per fold step
  *   KVM_DEBUG_FOLD_WAVES        8 or 16: wavefronts of a fold workgroup on the one-launch path
  *   KVM_DEBUG_PREFILL_SCHEDULE  1: chunk by chunk on the caller's stream, folds in place,
  *                               2: folds ahead on the library's stream, attention in groups
@@ -277,7 +277,7 @@ int kvm_state_import(kvm_state *st, const double *sK, const float *sV, const flo
  *   KVM_DEBUG_MERGE_COPY        1 / 2: token-centred merge with row copies on / off (same path)
  *   KVM_DEBUG_BACKWARD_PATH     1: attention adjoints on the vector ALU on every shape (it also
  *                               sizes kvm_backward_workspace_bytes: set it before asking)
- *   KVM_DEBUG_FOLD_SPLIT        1, 2, 4 or 8: workgroups that share a unit's state rows on the
+ *   KVM_DEBUG_FOLD_SPLIT        1, 2, 4, 8 or 16: workgroups that share a unit's state rows on the
  *                               one-launch path (ignored where the shape does not allow it) */
 enum { KVM_DEBUG_FOLD_PATH = 0, KVM_DEBUG_FOLD_WAVES = 1, KVM_DEBUG_PREFILL_SCHEDULE = 2, KVM_DEBUG_FOLD_CHAINS = 3,
        KVM_DEBUG_MERGE_COPY = 4, KVM_DEBUG_BACKWARD_PATH = 5, KVM_DEBUG_FOLD_SPLIT = 6, KVM_DEBUG_KNOBS = 8 };

@@ -268,8 +268,9 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
 // Where the shares of query-head group number `group` of the launch go.
 template <typename T, int D, int GQ>
 __device__ __forceinline__ void set_share(RowQuery<T> &rq, const Dev &dv, int group) {
-  rq.part_acc = dv.part_acc + (int64_t)group * rq.n_split * GQ * D;
-  rq.part_ml = dv.part_ml + group * rq.n_split * GQ;
+  const int n_groups = (int)(gridDim.y * gridDim.z);
+  rq.part_acc = (float *)dv.kbar + (int64_t)group * rq.n_split * GQ * D;
+  rq.part_ml = (float2 *)((float *)dv.kbar + (int64_t)n_groups * rq.n_split * GQ * D) + group * rq.n_split * GQ;
   rq.part_cnt = dv.part_cnt + group;
 }
 
@@ -369,10 +370,12 @@ int heads_together(const Dev &dv) {
 
 // Workgroups that share the keys of one sequence in a decode step.  n_groups workgroups, each
 // walking all the keys, leave the chip idle when there are few of them, and a workgroup's walk is
-// a chain of memory round trips; the shares are at least one round of the loop.
-int shares_for(int n_groups, int keys, int round) {
+// a chain of memory round trips; the shares are at least one round of the loop.  Their results must
+// fit the state's scratch (gq heads' d sums and two words each).
+int shares_for(const Dev &dv, int gq, int n_groups, int keys, int round) {
   if (n_groups >= kShareGroups) return 1;
-  int s = kSplitWorkgroups / n_groups;
+  const int64_t room = dv.kbar_bytes / (gq * (dv.d * 4 + 8));
+  int s = (int)(room < kSplitWorkgroups ? room : kSplitWorkgroups) / n_groups;
   const int most = (keys + round - 1) / round;
   s = s < most ? s : most;
   s = s < kMaxSplit ? s : kMaxSplit;
@@ -404,7 +407,7 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   int nx = a.nq_total;
   if (a.put_token) {
     const int64_t win = a.s % dv.C + 1 + dv.L - dv.C;   // window keys, at most
-    nx = shares_for(dv.Hq / gq * dv.B, a.m[0] + (int)win, round_keys(dv));
+    nx = shares_for(dv, gq, dv.Hq / gq * dv.B, a.m[0] + (int)win, round_keys(dv));
   }
   dim3 grid(nx, dv.Hq / gq, dv.B);
   if (gq == 4)
@@ -420,7 +423,7 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st) {
   if (n_seq <= 0) return hipSuccess;
   const int gq = heads_together(dv);
-  dim3 agrid(shares_for(dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
+  dim3 agrid(shares_for(dv, gq, dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
   if (gq == 4)
     KVM_ROWS_DISPATCH(attn_rows_multi_kernel, 4, agrid, dv, seq, q, k, v, gate, out);
   else if (gq == 2)

@@ -236,8 +236,6 @@ __global__ __launch_bounds__(256) void select_kernel(Dev dv, int m, int n_app, i
 //      in LDS), summed in fp64 over the I/O-dtype operands; a strictly larger score moves the
 //      token to the new row, the lowest row winning ties, compared in the stored fp32 precision
 //      as in score_kernel's second pass.
-constexpr int kAppendMax = 16;
-
 template <typename T, int D>
 __global__ __launch_bounds__(256) void append_kernel(Dev dv, Src src, int m, int n_app, int slot_new) {
   // C sort keys (8 bytes each), kAppendMax creators, 4 wave counts, n_app x D new keys
@@ -756,10 +754,6 @@ hipError_t launch_select(const Dev &dv, int m, int n_app, bool take_all, hipStre
   hipLaunchKernelGGL(select_kernel, dim3(dv.U), dim3(256), (size_t)dv.C * 8, st, dv, m, n_app,
                      take_all ? 1 : 0);
   return hipGetLastError();
-}
-
-bool append_fits(const Dev &dv, int n_app) {
-  return n_app > 0 && n_app <= kAppendMax && dv.C % 2 == 0 && dv.C <= 256;
 }
 
 hipError_t launch_append(const Dev &dv, const Src &src, int m, int n_app, int slot_new, hipStream_t st) {

@@ -1,48 +1,63 @@
-// A run of folds in one launch, one workgroup per (sequence, KV head) unit (bf16, head_dim 128).
+// A run of folds in one launch (bf16, head_dim 128), one workgroup or several per (sequence, KV head) unit.
 //
 // A fold (sections "Append", "Merge" and the readout equations of the paper's Method section) is a
 // chain of small dependent steps: similarity of the block to the normalised state, selection of
 // the tokens to append, creation of their rows, similarity of the remaining tokens to the new
 // rows, winner-take-all accumulation, readout refresh.  Units are independent of each other, and
-// consecutive folds of one unit depend on each other through that unit's state alone, so one
-// workgroup walks a unit through all of a run's folds with workgroup barriers between the steps:
+// consecutive folds of one unit depend on each other through that unit's state alone, so the
+// workgroups of a unit walk it through all of a run's folds with workgroup barriers between the steps:
 // no launch boundaries inside the chain and none between its folds.  Two shapes of workgroup: 16
-// waves with up to 160 KiB of LDS when the folds have the chip to themselves (decode, a prefill
-// whose folds outweigh its attention); 8 waves at 128 registers and under 96 KiB when they run
-// beside a prefill's attention launches, whose workgroups leave room for exactly that on a compute
-// unit (a larger workgroup would wait until a unit has drained, which a running attention launch
-// never lets happen).  Per fold:
+// waves with up to 160 KiB of LDS when the folds have the chip to themselves (a prefill whose folds
+// outweigh its attention); 8 waves at 128 registers and under 96 KiB when they run beside a
+// prefill's attention launches, whose workgroups leave room for exactly that on a compute unit (a
+// larger workgroup would wait until a unit has drained, which a running attention launch never
+// lets happen).  Per fold:
 //   1. the block's memory keys k-bar = LN_s(zero_r(k)), computed by a launch of their own ahead of
 //      the run (they depend on k alone, so they are not part of the chain), are read as matrix-core
-//      operands by the wave that owns the 32 tokens;
-//   2. D[row, token] = K-hat_tile . K-bar^T on the matrix cores, state rows streaming HBM/L2 ->
-//      LDS in 64-row tiles, two stages of several tiles: append score s_j = max over all rows,
-//      merge target = argmax over rows >= S (a lane owns a token and scans rows in ascending
-//      order: ties keep the lowest row);
-//   3. when the budget has room for some of the block: the n_append smallest (s_j, j) are taken
-//      (ranks by counting), their rows are created, and step 2 runs again over the new rows for
-//      the tokens that were not taken (a strictly larger score moves a token);
+//      operands by the wave that owns the 32 tokens, while the fold before merges;
+//   2. D[row, token] = K-hat_tile . K-bar^T on the matrix cores, 64 state rows at a time: append
+//      score s_j = max over all rows, merge target = argmax over rows >= S (a lane owns a token and
+//      scans rows in ascending order: ties keep the lowest row).  The K-hat tiles stay in LDS for
+//      the whole run where they fit, kept up to date by steps 3 and 5; otherwise they stream from
+//      HBM / L2 through a ring of two stages;
+//   3. when the budget has room for some of the block: the n_append smallest (s_j, j) are taken,
+//      their rows are created, and step 2 runs again over the new rows for the tokens that were
+//      not taken (a strictly larger score moves a token);
 //   4. every merging token pushes itself on its target row's list in LDS (an exchange on the
 //      row's head); the token that finds the list empty enters the row in the list of touched rows;
+//      the tokens' memory keys and values are loaded straight into LDS, all at once;
 //   5. 16 lanes per touched row (8 channels each): the sums are asked for, the row's list is
 //      walked, its tokens are added in ascending position, sums and the readout row (LN_s in
 //      fp64 on keys, stored radius on values) are written; rows nothing was added to are copied
-//      to the new state version (prefill) or left alone (in place).
+//      to the new state version (prefill; with resident tiles during the next fold's exchange,
+//      where nothing waits for it) or left alone (in place).
 // Integer decisions rest on fp64 LN_s and fp64 key sums, as everywhere in this library.
 //
 // With fewer units than compute units one workgroup per unit leaves most of the chip idle, so a
-// unit can be given `split` workgroups (a power of two) that divide its state rows among them in
+// unit is given `split` workgroups (a power of two) that divide its state rows among them in
 // 64-row tiles, tile t belonging to workgroup t mod split: a workgroup scores the whole block
-// against its own rows, merges the tokens bound for its own rows, creates the new rows that fall
-// to it and copies its own untouched rows.  Everything a workgroup reads of the state it wrote
-// itself, so the only data that crosses workgroups is each token's partial winner: one exchange
-// per scoring pass through a small table in global memory.  An entry is one 64-bit word (score,
-// row, a 16-bit tag of the exchange it belongs to) written and read with relaxed device-scope
-// atomics: no fences, no flags beside the data; a reader spins on the tag, with a clock limit that
-// ends the wait and raises an error word instead of hanging.  The workgroups of a launch must be
-// able to be resident together (the host checks the grid against the chip); kernels that run
-// beside it on other streams only delay a workgroup's start, they never wait for this kernel.
+// against its own rows, merges the tokens bound for its own rows and copies its own untouched
+// rows; the normalised keys of new rows every workgroup makes for itself.  Everything a workgroup
+// reads of the state it wrote itself, so the only data that crosses workgroups is each token's
+// partial winner: one exchange per fold through a small table in global memory.  An entry is one
+// 64-bit word (score, row, a 16-bit tag of the exchange it belongs to) written and read with relaxed
+// device-scope atomics: no fences, no flags beside the data; a reader spins on the tag, with a clock
+// limit that ends the wait and raises an error word instead of hanging.  The workgroups of a launch
+// must be able to be resident together (the host checks the grid against the chip and lets such
+// launches run one at a time); kernels that run beside it on other streams only delay a workgroup's
+// start, they never wait for this kernel.
+//
+// What bounds it: with shared rows, latency.  A fold of a 256-token block into some 300 rows (32 units x
+// 8 workgroups) takes 15 us without an append and 22 us with one, about 6 us more beside attention: an
+// exchange, two more round trips to memory (values of untouched rows, sums of touched rows), ten
+// barriers.  A kernel per step took 38 us and 62 us for the same.  Prefill of 65536 tokens with a
+// growing state (B 1 x H 32, 256-token blocks): 10.6 to 13.5 ms before (the box decides), 8.4 ms now; of a
+// layer's 16384 tokens with 256 rows: 3.3 ms before, 2.8 ms now.  With one workgroup per unit (256 units
+// and more) by the tiles' and rows' traffic: B 16 x H 16, 8192 tokens, 5.06 ms before, 4.61 ms now
+// (keys of the next run computed beside the folds, gathered tokens, no separate copy pass).
 #include <cstddef>
+
+#include <hip/hip_ext.h>
 
 #include "kvm_device.h"
 #include "kvm_internal.h"
@@ -55,6 +70,7 @@ namespace {
 constexpr int kNoRow = 0x7fffffff;
 constexpr int kTileBytes = kTileElems * 2;   // 16 KiB
 constexpr int kListMax = 16;                 // tokens of a row taken from its list in one go
+constexpr uint32_t kTokenBytes = 2 * kHeadDim * 2;   // memory key and value of a token
 // NW waves per workgroup; a stage of the K-hat stream is NW / 4 tiles, two stages are in LDS
 __host__ __device__ constexpr int stage_tiles(int NW) { return NW / 4; }
 
@@ -71,81 +87,75 @@ __device__ __forceinline__ bool beats(float sa, int ia, float sb, int ib) {
   return sa > sb || (sa == sb && ia < ib);
 }
 
-// LDS layout of one workgroup (bytes from the start of dynamic shared memory).
-struct FoldLds {
-  uint32_t tiles;    // 2 * stage_tiles tiles of K-hat; outside the score passes also scratch for sort keys
-  uint32_t app;      // float [C]  append score s_j
-  uint32_t best;     // float [C]  winning merge score
-  uint32_t pi;       // int   [C]  target row
-  uint32_t rank;     // int   [C]  rank among the appended tokens, or -1
-  uint32_t next;     // int   [C]  next token on the same row's list, or -1
-  uint32_t creator;  // int   [C]  token that creates new row number a
-  uint32_t rows;     // int   [C]  rows that receive tokens in this fold
-  uint32_t merge;    // float/int [3][NW * 32] partial winners of waves that share tokens
-  uint32_t masks;    // u64   [C / 64] taken-token masks
-  uint32_t counters; // int   [4]
-  uint32_t head;     // int   [Mcap] last token pushed on the row's list, or -1
-  uint32_t lall;     // float [C]  this workgroup's own winners of a scoring pass (split > 1)
-  uint32_t lbest;    // float [C]
-  uint32_t lidx;     // int   [C]
-  uint32_t total;
-};
-__host__ __device__ inline FoldLds fold_lds(int C, int Mcap, int NW, int split = 1) {
-  FoldLds l;
-  uint32_t o = 0;
-  auto take = [&](uint32_t bytes) {
-    const uint32_t at = o;
-    o += (bytes + 15u) & ~15u;
-    return at;
-  };
-  l.tiles = take(2 * stage_tiles(NW) * kTileBytes);
-  l.app = take(4u * C);
-  l.best = take(4u * C);
-  l.pi = take(4u * C);
-  l.rank = take(4u * C);
-  l.next = take(4u * C);
-  l.creator = take(4u * C);
-  l.rows = take(4u * C);
-  l.merge = take(3u * 4u * NW * 32);
-  l.masks = take(8u * ((C + 63) / 64));
-  l.counters = take(16);
-  l.head = take(4u * Mcap);
-  l.lall = take(split > 1 ? 4u * C : 0u);
-  l.lbest = take(split > 1 ? 4u * C : 0u);
-  l.lidx = take(split > 1 ? 4u * C : 0u);
-  l.total = o;
-  return l;
+// LDS layout of one workgroup, bytes from the start of dynamic shared memory.  Everything is a fixed
+// offset plus a multiple of C, so that no table of offsets has to be kept in registers.  "Local"
+// rows are the rows of this workgroup's own 64-row tiles, numbered through (all rows when a unit
+// has one workgroup).
+//   0                   int [8] counters
+//   kLdsMerge           float/int [3][NW * 32] partial winners of waves that share tokens
+//   tables(NW)          eight arrays of C words: append score s_j, winning merge score, target row, rank among
+//                       the appended tokens or -1, next token on the same row's list or -1, token that creates
+//                       new row number a (later: where a merging token has been gathered to), local rows
+//                       that receive tokens (before that: near ties), the gathered tokens
+//   then                int [local rows] last token pushed on the row's list or -1
+//   then (1-KiB bound)  scratch, one use after the other: the fresh tile (K-hat of the rows this fold creates); the
+//                       gathered tokens' memory keys and values
+//   then                K-hat tiles: this workgroup's own for the whole run (resident); otherwise a ring of 2 *
+//                       stage_tiles, which is the scratch as well (it is idle when that is needed)
+constexpr uint32_t kLdsCounters = 0, kLdsMerge = kLdsCounters + 32;
+__host__ __device__ constexpr uint32_t lds_tables(int NW) { return kLdsMerge + 3u * 4u * NW * 32; }
+__host__ __device__ constexpr uint32_t lds_fresh(int NW, int C, int own_tiles) {
+  return (lds_tables(NW) + 32u * C + 4u * kTileKeys * own_tiles + 1023u) & ~1023u;
 }
+__host__ __device__ inline int own_tiles_most(int Mcap, int split) { return (Mcap / kTileKeys + split - 1) / split; }
 
+template <int NW>
 struct Ctx {
   unsigned char *smem;
-  FoldLds l;
+  int C;                    // tokens of a block
+  uint32_t fresh_at;        // LDS offset of the scratch
+  int gather;               // tokens the scratch can hold (memory key and value)
   int u, tid, lane, wave;
-  int part, split;   // this workgroup's number among the unit's workgroups, and how many they are
+  int part, split, shift;   // this workgroup's number among the unit's workgroups, how many they are, log2 of that
+  bool resident;            // its K-hat tiles stay in LDS for the whole run
   // the workgroup that owns a state row: 64-row tiles dealt round robin
   __device__ bool owns(int row) const { return ((row >> 6) & (split - 1)) == part; }
-  __device__ float *s_lall() const { return (float *)(smem + l.lall); }
-  __device__ float *s_lbest() const { return (float *)(smem + l.lbest); }
-  __device__ int *s_lidx() const { return (int *)(smem + l.lidx); }
-  __device__ float *s_app() const { return (float *)(smem + l.app); }
-  __device__ float *s_best() const { return (float *)(smem + l.best); }
-  __device__ int *s_pi() const { return (int *)(smem + l.pi); }
-  __device__ int *s_rank() const { return (int *)(smem + l.rank); }
-  __device__ int *s_next() const { return (int *)(smem + l.next); }
-  __device__ int *s_creator() const { return (int *)(smem + l.creator); }
-  __device__ int *s_rows() const { return (int *)(smem + l.rows); }
-  __device__ int *s_cnt() const { return (int *)(smem + l.counters); }
-  __device__ int *s_head() const { return (int *)(smem + l.head); }
-  __device__ unsigned long long *s_masks() const { return (unsigned long long *)(smem + l.masks); }
+  __device__ int local(int row) const { return ((row >> (6 + shift)) << 6) | (row & 63); }
+  __device__ int global(int lr) const { return ((((lr >> 6) << shift) + part) << 6) | (lr & 63); }
+  // local rows that exist when the state has m rows
+  __device__ int n_local(int m) const {
+    const int t = m >> 6, own = t > part ? (t - part + split - 1) >> shift : 0;   // whole tiles of this workgroup
+    return 64 * own + ((m & 63) && (t & (split - 1)) == part ? (m & 63) : 0);
+  }
+  template <typename V>
+  __device__ V *table(int k) const { return (V *)(smem + lds_tables(NW) + 4u * k * C); }
+  __device__ uint16_t *s_fresh() const { return (uint16_t *)(smem + fresh_at); }
+  __device__ uint16_t *s_tiles() const { return (uint16_t *)(smem + fresh_at + (resident ? (uint32_t)gather * kTokenBytes : 0u)); }
+  __device__ uint16_t *s_keys(int slot) const { return (uint16_t *)(smem + fresh_at) + slot * kHeadDim; }
+  __device__ uint16_t *s_vals(int slot) const { return (uint16_t *)(smem + fresh_at) + (gather + slot) * kHeadDim; }
+  __device__ float *s_app() const { return table<float>(0); }
+  __device__ float *s_best() const { return table<float>(1); }
+  __device__ int *s_pi() const { return table<int>(2); }
+  __device__ int *s_rank() const { return table<int>(3); }
+  __device__ int *s_next() const { return table<int>(4); }
+  __device__ int *s_creator() const { return table<int>(5); }
+  __device__ int *s_rows() const { return table<int>(6); }
+  __device__ int *s_slot() const { return table<int>(5); }
+  __device__ int *s_own() const { return table<int>(7); }
+  __device__ int *s_head() const { return table<int>(8); }
+  __device__ int *s_cnt() const { return (int *)(smem + kLdsCounters); }
+  __device__ unsigned char *s_merge() const { return smem + kLdsMerge; }
 };
+// counters: touched rows, near ties of the append, own merging tokens, a wait has given up, (stamps)
+enum { kCntRows = 0, kCntTies = 1, kCntOwn = 2, kCntGaveUp = 3, kCntStamps = 4 };
 
 // Development aid (compiled in only with -DKVM_FOLD_STAMPS): the first workgroup leaves the clock
 // at its phase boundaries in the `creator` scratch, which this path does not use.
 #ifdef KVM_FOLD_STAMPS
 #define FOLD_STAMP()                                                                        \
   do {                                                                                      \
-    if (blockIdx.x == 0 && threadIdx.x == 0 && cx.s_cnt()[3] < 240)                         \
-      reinterpret_cast<long long *>(dv.creator)[cx.s_cnt()[3]++] = (long long)wall_clock64(); \
+    if (blockIdx.x == 0 && threadIdx.x == 0 && cx.s_cnt()[kCntStamps] < 240)                         \
+      reinterpret_cast<long long *>(args_now().dv.creator)[cx.s_cnt()[kCntStamps]++] = (long long)wall_clock64(); \
   } while (0)
 #else
 #define FOLD_STAMP() \
@@ -154,227 +164,11 @@ struct Ctx {
 #endif
 
 // ------------------------------------------------------------------------------------------------
-// Step 2: one pass of the block's tokens over state rows [row0, row1) of readout version `slot`.
-// first: rows are the state before the append; every token gets s_j and its best row >= S.
-// Otherwise rows are the ones created in this fold; a token that was not taken moves to one of
-// them when that score is strictly larger than its stored best.
-template <int NW>
-__device__ __forceinline__ void score_pass(const Dev &dv, const Ctx &cx, int slot, int row0, int row1, bool first,
-                                           const uint16_t *kbar_blk) {
-  constexpr int D = kHeadDim, ST = stage_tiles(NW);
-  const int lane = cx.lane, wave = cx.wave, u = cx.u;
-  const int g = lane >> 5, l32 = lane & 31;
-  const int C = dv.C, TG = C / 32;
-  // Tiles are 64-row blocks of the state counted from row 0; this workgroup takes the ones that
-  // fall to it, tile t_first, t_first + split, ...: local tile number lt <-> tile t_first + lt * split.
-  const int t_lo = row0 >> 6, t_hi = (row1 + kTileKeys - 1) >> 6;
-  const int t_first = t_lo + ((cx.part - t_lo) & (cx.split - 1));
-  const int n_tiles = t_first < t_hi ? (t_hi - t_first + cx.split - 1) / cx.split : 0;
-  const int n_stages = (n_tiles + ST - 1) / ST;
-  const int row_lo = row0 > dv.S ? row0 : dv.S;   // first row that may win a merge
-  uint16_t *Ks = (uint16_t *)(cx.smem + cx.l.tiles);
-  const uint32_t ks_addr = lds_addr_of(Ks);
-  const char *khat = (const char *)dv.khat + (slot * dv.slot_elems + (int64_t)u * dv.Mcap * D) * 2;
-  uint32_t koff[8];
-  ktile_offsets(lane, koff);
-  // a tile is sixteen 1-KiB pieces of four rows; wave w fetches pieces w, w + NW, ... of every
-  // tile.  The chunk permutation of a piece depends on (piece % 4) = (w % 4).
-  const DmaLane dl = dma_lane(lane);
-  const int wq = wave & 3;
-  const uint32_t kcol = wq == 0 ? dl.kcol[0] : wq == 1 ? dl.kcol[1] : wq == 2 ? dl.kcol[2] : dl.kcol[3];
-  auto issue_stage = [&](int sg) {
-#pragma unroll
-    for (int i = 0; i < ST; ++i) {
-      const int t = ST * sg + i;
-      if (t < n_tiles) {
-        const int base = (t_first + t * cx.split) * kTileKeys, valid = row1 - base;
-#pragma unroll
-        for (int n = 0; n < 16 / NW; ++n) {
-          const int piece = wave + NW * n;
-          int r = 4 * piece + (int)dl.rl;
-          r = r < valid ? r : valid - 1;   // rows past the end repeat the last one (masked below)
-          dma16(khat + (uint32_t)base * (D * 2), (uint32_t)r * (D * 2) + kcol,
-                ks_addr + (uint32_t)(ST * (sg & 1) + i) * kTileBytes + (uint32_t)piece * 1024u);
-        }
-      }
-    }
-  };
-  float *x_all = (float *)(cx.smem + cx.l.merge), *x_best = x_all + NW * 32;
-  int *x_idx = (int *)(x_best + NW * 32);
-
-  for (int g0 = 0; g0 < TG; g0 += NW) {
-    const int Gp = TG - g0 < NW ? TG - g0 : NW;   // token groups in this round
-    const int wpg = NW / Gp;                      // waves that share a group's tokens (they split the tiles)
-    const int gi = wave / wpg, sub = wave % wpg;
-    const bool active = gi < Gp;
-    const int j = (g0 + (active ? gi : 0)) * 32 + l32;
-    // The memory keys of this round's token groups, as B operands (lane = 32 g + i holds token i,
-    // channels 16 ks + 8 g .. + 7): the block's rows go through LDS as 64-token tiles in the K
-    // layout (coalesced 1-KiB pieces) instead of sixteen scattered bytes per lane and step.  When
-    // they fit the ring's second half they travel together with the first stage of K-hat.
-    const int kb_tiles = (Gp + 1) / 2;
-    const bool together = kb_tiles <= ST;
-    const int kb_buf0 = together ? ST : 0;
-#pragma unroll
-    for (int i = 0; i < 2 * ST; ++i)
-      if (i < kb_tiles) {
-        const char *from = (const char *)(kbar_blk + (int64_t)(g0 / 2 + i) * kTileKeys * D);
-#pragma unroll
-        for (int n = 0; n < 16 / NW; ++n) {
-          const int piece = wave + NW * n;
-          dma16(from, (uint32_t)(4 * piece + (int)dl.rl) * (D * 2) + kcol,
-                ks_addr + (uint32_t)(kb_buf0 + i) * kTileBytes + (uint32_t)piece * 1024u);
-        }
-      }
-    if (together && n_stages > 0) issue_stage(0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    bf16x8 kreg[8];
-    {
-      const int gsel = active ? gi : 0;
-      const uint16_t *Kb = Ks + (kb_buf0 + gsel / 2) * kTileElems;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) kreg[ks] = ktile_frag(Kb, koff, gsel & 1, ks);
-    }
-    if (!together) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();   // every wave has its operands: the ring is free for K-hat
-      if (n_stages > 0) issue_stage(0);
-    }
-    // The winner is kept as a wave-uniform code (32-row block number * 16 + accumulator element)
-    // and turned into a row at the end: selecting a scalar costs no register per candidate.
-    float best_all = -INFINITY, best = -INFINITY;
-    int best_code = -1;
-    for (int sg = 0; sg < n_stages; ++sg) {
-      // (together: stage 0 has landed with the memory keys; this wait is for the operand reads,
-      // after which the ring's second half may be overwritten by stage 1)
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      if (sg + 1 < n_stages) issue_stage(sg + 1);
-      if (active) {
-#pragma unroll
-        for (int i = 0; i < ST; ++i) {
-          const int t = ST * sg + i;
-          if (t < n_tiles && (t & (wpg - 1)) == sub) {   // wpg is a power of two: NW and C / 32 are
-            const uint16_t *Kt = Ks + (ST * (sg & 1) + i) * kTileElems;
-            // the tile's two 32-row blocks, one accumulation chain each (channels in ascending
-            // order), interleaved; four K fragments in flight from LDS
-            f32x16 acc[2];
-            {
-              bf16x8 kf[4];
-#pragma unroll
-              for (int q = 0; q < 4; ++q) kf[q] = ktile_frag(Kt, koff, q & 1, q >> 1);
-              const f32x16 zero = {0.f};
-#pragma unroll
-              for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-                for (int rh = 0; rh < 2; ++rh) {
-                  const int slot2 = (2 * ks + rh) & 3;
-                  acc[rh] = mfma32(kf[slot2], kreg[ks], ks == 0 ? zero : acc[rh]);
-                  if (ks + 2 < 8) kf[slot2] = ktile_frag(Kt, koff, rh, ks + 2);
-                }
-              // pin that order: four LDS reads up front, then one read behind every matrix
-              // instruction, so that no matrix instruction waits for the read issued just before it
-              __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-              for (int q = 0; q < 12; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-              }
-              __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-            }
-#pragma unroll
-            for (int rh = 0; rh < 2; ++rh) {
-              const int blk = 2 * (t_first + t * cx.split) + rh, base = 32 * blk;
-              if (base < row1 && base + 32 > row0) {
-                const bool edge = base < row_lo || base + 32 > row1;
-                if (edge) {
-#pragma unroll
-                  for (int v = 0; v < 16; ++v) {
-                    const int i2 = base + mfma_row(v, g);
-                    const float sc = acc[rh][v];
-                    if (i2 < row1 && i2 >= row0) {
-                      best_all = fmaxf(best_all, sc);
-                      if (i2 >= row_lo && sc > best) {
-                        best = sc;
-                        best_code = 16 * blk + v;
-                      }
-                    }
-                  }
-                } else {
-#pragma unroll
-                  for (int v = 0; v < 16; ++v) {
-                    const float sc = acc[rh][v];
-                    const bool up = sc > best;
-                    best = up ? sc : best;
-                    best_code = up ? 16 * blk + v : best_code;
-                  }
-                }
-              }
-            }
-          }
-        }
-      }
-    }
-    int best_i = best_code < 0 ? kNoRow : 32 * (best_code >> 4) + mfma_row(best_code & 15, g);
-    best_all = fmaxf(best_all, best);
-    {
-      // the other lane half holds the other rows of the same token
-      const float ob = __shfl_xor(best, 32, kWave);
-      const int oi = __shfl_xor(best_i, 32, kWave);
-      const float oa = __shfl_xor(best_all, 32, kWave);
-      if (beats(ob, oi, best, best_i)) {
-        best = ob;
-        best_i = oi;
-      }
-      best_all = fmaxf(best_all, oa);
-    }
-    // the waves that share the tokens, through LDS
-    if (wpg > 1) {
-      if (active && sub != 0 && g == 0) {
-        const int xi = wave * 32 + l32;
-        x_all[xi] = best_all;
-        x_best[xi] = best;
-        x_idx[xi] = best_i;
-      }
-      __syncthreads();
-      if (active && sub == 0 && g == 0) {
-        for (int o = 1; o < wpg; ++o) {
-          const int xi = (wave + o) * 32 + l32;
-          best_all = fmaxf(best_all, x_all[xi]);
-          if (beats(x_best[xi], x_idx[xi], best, best_i)) {
-            best = x_best[xi];
-            best_i = x_idx[xi];
-          }
-        }
-      }
-    }
-    if (active && sub == 0 && g == 0) {
-      if (cx.split > 1) {
-        // this workgroup's rows only: the unit's winner is settled by the exchange that follows
-        cx.s_lall()[j] = best_all;
-        cx.s_lbest()[j] = best;
-        cx.s_lidx()[j] = best_i;
-      } else if (first) {
-        cx.s_app()[j] = best_all;
-        cx.s_best()[j] = best;
-        cx.s_pi()[j] = best_i;
-        cx.s_rank()[j] = -1;
-      } else if (cx.s_rank()[j] < 0 && best_i != kNoRow && best > cx.s_best()[j]) {
-        cx.s_best()[j] = best;
-        cx.s_pi()[j] = best_i;
-      }
-    }
-    __syncthreads();   // tile buffers and the merge scratch are free again
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// The exchange after a scoring pass (split > 1): every workgroup of the unit publishes its own
-// winners and reads the others'; all of them end up with the same unit-wide result in LDS, as
-// score_pass leaves it when a unit has one workgroup.
+// The exchange after the scoring pass (split > 1): every workgroup of the unit publishes its own
+// winners and reads the others'; all of them end up with the same unit-wide result in LDS.
 // Table: [unit][exchange parity][workgroup][2][C] 64-bit words; word 0 of a token = (merge score,
-// row in 16 bits, tag), word 1 = (append score, tag).  A workgroup cannot be two exchanges ahead of
+// row in 16 bits, tag), word 1 = (append score, tag), the latter only from workgroups that own sink rows (elsewhere
+// every row may win, and the two scores are one).  A workgroup cannot be two exchanges ahead of
 // a sibling (it needs the sibling's entries of the exchange in between), so two parities suffice.
 // tag: the low 16 bits of the exchange's number, which the host never reuses within a state's life
 // before every entry has been rewritten many times; the table starts zeroed and 0 is never a tag.
@@ -382,126 +176,436 @@ __device__ __forceinline__ unsigned long long xchg_pack(float score, uint32_t lo
   return ((unsigned long long)__float_as_uint(score) << 32) | ((unsigned long long)(low16 & 0xffffu) << 16) |
          (unsigned long long)(tag & 0xffffu);
 }
-// gave_up: a word in LDS, set by the first wait of the workgroup that ran into the limit; from then
-// on its waits return at once (a workgroup loses at most one time limit, whatever went wrong),
-// with an entry that names no row, so that nothing downstream indexes with it.
-__device__ __forceinline__ unsigned long long xchg_wait(const unsigned long long *p, uint32_t tag, int32_t *err,
-                                                        volatile int *gave_up) {
-  unsigned long long v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <int kCtrl>
+__device__ __forceinline__ int dpp_int(int x) {
+  return (int)__builtin_amdgcn_mov_dpp((uint32_t)x, kCtrl, 0xF, 0xF, true);
+}
+// whether workgroup `part` owns rows below the number of sinks (tile t belongs to workgroup t mod split)
+__device__ __forceinline__ bool sink_owner(const Dev &dv, int part) { return part < (dv.S + kTileKeys - 1) / kTileKeys; }
+__device__ __forceinline__ void publish_winner(unsigned long long *mine, int C, int j, float best, int best_i, float all,
+                                               bool with_all, uint32_t tag) {
+  __hip_atomic_store(mine + j, xchg_pack(best, best_i == kNoRow ? 0xffffu : (uint32_t)best_i, tag), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+  if (with_all) __hip_atomic_store(mine + C + j, xchg_pack(all, 0, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// One entry, waited for.  gave_up: a word in LDS, set by the first wait of the workgroup that ran into
+// the limit; from then on its waits return at once (a workgroup loses at most one time limit, whatever
+// went wrong), with an entry that names no row, so that nothing downstream indexes with it.
+__device__ __forceinline__ unsigned long long xchg_wait(unsigned long long v, const unsigned long long *p, uint32_t tag,
+                                                        int32_t *err, volatile int *gave_up) {
   if ((uint32_t)(v & 0xffffu) == tag) return v;
   const unsigned long long t0 = wall_clock64();   // 100 MHz
   while (*gave_up == 0) {
-    __builtin_amdgcn_s_sleep(4);
     v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint32_t)(v & 0xffffu) == tag) return v;
-    if (wall_clock64() - t0 > 20000000ull) {   // 200 ms: a sibling that never came
+    __builtin_amdgcn_s_sleep(1);
+    if (wall_clock64() - t0 > 300000000ull) {   // 3 s: a sibling that never came
       *gave_up = 1;
       __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
   return xchg_pack(-INFINITY, 0xffffu, tag);
 }
-template <int NW>
-__device__ __forceinline__ void exchange_winners(const Dev &dv, const Ctx &cx, unsigned long long *xtab,
-                                                 uint32_t xnum, bool first, int32_t *err) {
-  constexpr int NT = 64 * NW;
-  const int C = dv.C;
-  const uint32_t tag = xnum & 0xffffu;
-  volatile int *gave_up = cx.s_cnt() + 2;
-  unsigned long long *base = xtab + (((size_t)cx.u * 2 + (xnum & 1u)) * cx.split) * 2 * C;
-  for (int j = cx.tid; j < C; j += NT) {
-    float best = cx.s_lbest()[j], best_all = cx.s_lall()[j];
-    int best_i = cx.s_lidx()[j];
-    unsigned long long *mine = base + (size_t)cx.part * 2 * C;
-    __hip_atomic_store(mine + j, xchg_pack(best, best_i == kNoRow ? 0xffffu : (uint32_t)best_i, tag), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    if (first)
-      __hip_atomic_store(mine + C + j, xchg_pack(best_all, 0, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the siblings' entries: all of them asked for at once (each read goes to memory, one or two
-    // microseconds away), then the stragglers waited for one by one
-    unsigned long long w0[kFoldMaxSplit - 1], w1[kFoldMaxSplit - 1];
+// A pair of lanes per token: each reads half of the workgroups' entries, all of them asked for at once
+// (a read goes to memory, one or two microseconds away), waits for the stragglers one by one and
+// puts them together; then the two halves meet.
+template <int NW, int kHalf>   // kHalf: workgroups per lane
+__device__ __forceinline__ void exchange_half(const Dev &dv, const Ctx<NW> &cx, const unsigned long long *unit_tab,
+                                              uint32_t tag, int32_t *err) {
+  const int C = cx.C, h = cx.tid & 1;
+  volatile int *gave_up = cx.s_cnt() + kCntGaveUp;
+  const unsigned long long *theirs = unit_tab + (size_t)(h * kHalf) * 2 * C;
+  const int n_sinks = (dv.S + kTileKeys - 1) / kTileKeys - h * kHalf;   // how many of this half own sink rows
+#pragma unroll 1
+  for (int j = cx.tid >> 1; j < C; j += 32 * NW) {
+    unsigned long long w0[kHalf], w1 = 0;
 #pragma unroll
-    for (int o = 1; o < kFoldMaxSplit; ++o)
-      if (o < cx.split) {
-        const unsigned long long *theirs = base + (size_t)((cx.part + o) & (cx.split - 1)) * 2 * C;
-        w0[o - 1] = __hip_atomic_load(theirs + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (first) w1[o - 1] = __hip_atomic_load(theirs + C + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+    for (int o = 0; o < kHalf; ++o)
+      w0[o] = __hip_atomic_load(theirs + (size_t)o * 2 * C + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n_sinks > 0) w1 = __hip_atomic_load(theirs + C + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool late = false;
 #pragma unroll
-    for (int o = 1; o < kFoldMaxSplit; ++o)
-      if (o < cx.split) {
-        const unsigned long long *theirs = base + (size_t)((cx.part + o) & (cx.split - 1)) * 2 * C;
-        if ((uint32_t)(w0[o - 1] & 0xffffu) != tag) w0[o - 1] = xchg_wait(theirs + j, tag, err, gave_up);
-        const float ob = __uint_as_float((uint32_t)(w0[o - 1] >> 32));
-        const uint32_t oi16 = (uint32_t)(w0[o - 1] >> 16) & 0xffffu;
-        const int oi = oi16 == 0xffffu ? kNoRow : (int)oi16;
-        if (oi != kNoRow && (best_i == kNoRow || beats(ob, oi, best, best_i))) {
-          best = ob;
-          best_i = oi;
-        }
-        if (first) {
-          if ((uint32_t)(w1[o - 1] & 0xffffu) != tag) w1[o - 1] = xchg_wait(theirs + C + j, tag, err, gave_up);
-          best_all = fmaxf(best_all, __uint_as_float((uint32_t)(w1[o - 1] >> 32)));
-        }
-      }
-    if (first) {
-      cx.s_app()[j] = best_all;
+    for (int o = 0; o < kHalf; ++o) late = late || (uint32_t)(w0[o] & 0xffffu) != tag;
+    if (late) {
+#pragma unroll
+      for (int o = 0; o < kHalf; ++o) w0[o] = xchg_wait(w0[o], theirs + (size_t)o * 2 * C + j, tag, err, gave_up);
+    }
+    float best = -INFINITY, all = -INFINITY;
+    int best_i = kNoRow;
+    auto take = [&](float ob, int oi) {
+      const bool up = beats(ob, oi, best, best_i);   // (no row: score -inf and the largest number)
+      best = up ? ob : best;
+      best_i = up ? oi : best_i;
+    };
+#pragma unroll
+    for (int o = 0; o < kHalf; ++o) {
+      const uint32_t i16 = (uint32_t)(w0[o] >> 16) & 0xffffu;
+      take(__uint_as_float((uint32_t)(w0[o] >> 32)), i16 == 0xffffu ? kNoRow : (int)i16);
+    }
+    take(dpp_get<0xB1>(best), dpp_int<0xB1>(best_i));   // the other lane of the pair
+    // the append score counts sink rows too: their owners say what they are worth
+    for (int o = 0; o < n_sinks && o < kHalf; ++o) {
+      w1 = xchg_wait(o == 0 ? w1 : 0ull, theirs + ((size_t)o * 2 + 1) * C + j, tag, err, gave_up);
+      all = fmaxf(all, __uint_as_float((uint32_t)(w1 >> 32)));
+    }
+    all = fmaxf(fmaxf(all, dpp_get<0xB1>(all)), best);
+    if (h == 0) {
+      cx.s_app()[j] = all;
       cx.s_best()[j] = best;
       cx.s_pi()[j] = best_i;
       cx.s_rank()[j] = -1;
-    } else if (cx.s_rank()[j] < 0 && best_i != kNoRow && best > cx.s_best()[j]) {
-      cx.s_best()[j] = best;
-      cx.s_pi()[j] = best_i;
     }
   }
-  __syncthreads();
+}
+template <int NW>
+__device__ __forceinline__ void exchange_winners(const Dev &dv, const Ctx<NW> &cx, const unsigned long long *unit_tab,
+                                                 uint32_t tag, int32_t *err) {
+  switch (cx.split) {
+    case 2: exchange_half<NW, 1>(dv, cx, unit_tab, tag, err); break;
+    case 4: exchange_half<NW, 2>(dv, cx, unit_tab, tag, err); break;
+    case 8: exchange_half<NW, 4>(dv, cx, unit_tab, tag, err); break;
+    default: exchange_half<NW, 8>(dv, cx, unit_tab, tag, err); break;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The memory keys of a wave's 32 tokens, as B operands of the matrix instruction: lane = 32 g + i holds
+// token i, channels 16 ks + 8 g .. + 7.  Round r of a pass: token groups r * NW .. (waves share a group
+// when the block has fewer groups than waves).
+struct TokenGroup {
+  int j;          // the lane's token
+  int wpg, sub;   // waves that share the group, and which of them this is (they split the tiles)
+  bool active;
+};
+template <int NW>
+__device__ __forceinline__ TokenGroup token_group(const Ctx<NW> &cx, int C, int g0) {
+  const int left = C / 32 - g0, Gp = left < NW ? left : NW;
+  TokenGroup t;
+  t.wpg = NW / Gp;
+  const int gi = cx.wave / t.wpg;
+  t.sub = cx.wave % t.wpg;
+  t.active = gi < Gp;
+  t.j = (g0 + (t.active ? gi : 0)) * 32 + (cx.lane & 31);
+  return t;
+}
+__device__ __forceinline__ void fetch_keys(bf16x8 (&kreg)[8], const uint16_t *kbar_blk, int j, int lane) {
+  const uint16_t *row = kbar_blk + (int64_t)j * kHeadDim + 8 * (lane >> 5);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    Frag8 f;
+    f.q = *reinterpret_cast<const uint4 *>(row + 16 * ks);
+    kreg[ks] = f.v;
+  }
+}
+
+// The running winner of a lane's token: a wave-uniform code (32-row block number * 16 + accumulator
+// element) turned into a row at the end, so that selecting a candidate costs a scalar.
+struct Winner {
+  float all, best;   // best of all rows, best of those that may win
+  int code;
+};
+// One 64-row tile (in LDS, K layout) against the wave's tokens: D[row, token] = K-hat . K-bar^T, one
+// accumulation chain per 32-row block with the channels in ascending order (as score_mfma_kernel:
+// both produce the same fp32 scores), rows scanned in ascending order (ties keep the lowest).
+// blk0: number of the tile's first 32-row block; rows below row1 count, rows >= row_lo may win.
+// fresh (the new rows of an append, all of which may win): w.all is the second best instead.
+__device__ __forceinline__ void score_tile(Winner &w, const uint16_t *Kt, const uint32_t (&koff)[8],
+                                           const bf16x8 (&kreg)[8], int blk0, int row1, int row_lo, int g, bool fresh) {
+  f32x16 acc[2];
+  {
+    bf16x8 kf[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) kf[q] = ktile_frag(Kt, koff, q & 1, q >> 1);
+    const f32x16 zero = {0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+      for (int rh = 0; rh < 2; ++rh) {
+        const int slot2 = (2 * ks + rh) & 3;
+        acc[rh] = mfma32(kf[slot2], kreg[ks], ks == 0 ? zero : acc[rh]);
+        if (ks + 2 < 8) kf[slot2] = ktile_frag(Kt, koff, rh, ks + 2);
+      }
+    // pin that order: four LDS reads up front, then one read behind every matrix instruction, so
+    // that no matrix instruction waits for the read issued just before it
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+    for (int q = 0; q < 12; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+  }
+#pragma unroll
+  for (int rh = 0; rh < 2; ++rh) {
+    const int blk = blk0 + rh, base = 32 * blk;
+    if (base < row1) {
+      if (fresh) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int i2 = base + mfma_row(v, g);
+          const float sc = i2 < row1 && i2 >= row_lo ? acc[rh][v] : -INFINITY;
+          w.all = fmaxf(w.all, fminf(sc, w.best));
+          const bool up = sc > w.best;
+          w.best = up ? sc : w.best;
+          w.code = up ? 16 * blk + v : w.code;
+        }
+      } else if (base < row_lo || base + 32 > row1) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int i2 = base + mfma_row(v, g);
+          const float sc = acc[rh][v];
+          if (i2 < row1) {
+            w.all = fmaxf(w.all, sc);
+            if (i2 >= row_lo && sc > w.best) {
+              w.best = sc;
+              w.code = 16 * blk + v;
+            }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float sc = acc[rh][v];
+          const bool up = sc > w.best;
+          w.best = up ? sc : w.best;
+          w.code = up ? 16 * blk + v : w.code;
+        }
+      }
+    }
+  }
+}
+// What the lanes and waves that share a token found, put together; the result is with the lanes
+// g = 0 of the group's first wave.  (Every wave calls this: it holds barriers when wpg > 1.)
+template <int NW>
+__device__ __forceinline__ void merge_winners(const Ctx<NW> &cx, const TokenGroup &tg, Winner &w, int &best_i, bool fresh) {
+  const int g = cx.lane >> 5, l32 = cx.lane & 31;
+  best_i = w.code < 0 ? kNoRow : 32 * (w.code >> 4) + mfma_row(w.code & 15, g);
+  if (!fresh) w.all = fmaxf(w.all, w.best);
+  {
+    // the other lane half holds the other rows of the same token
+    const float ob = __shfl_xor(w.best, 32, kWave);
+    const int oi = __shfl_xor(best_i, 32, kWave);
+    float oa = __shfl_xor(w.all, 32, kWave);
+    if (fresh) oa = fmaxf(oa, fminf(ob, w.best));   // second best of both halves
+    if (beats(ob, oi, w.best, best_i)) {
+      w.best = ob;
+      best_i = oi;
+    }
+    w.all = fmaxf(w.all, oa);
+  }
+  if (tg.wpg > 1 && !fresh) {   // (the fresh tile is one wave's work)
+    float *x_all = (float *)cx.s_merge(), *x_best = x_all + NW * 32;
+    int *x_idx = (int *)(x_best + NW * 32);
+    if (tg.active && tg.sub != 0 && g == 0) {
+      const int xi = cx.wave * 32 + l32;
+      x_all[xi] = w.all;
+      x_best[xi] = w.best;
+      x_idx[xi] = best_i;
+    }
+    __syncthreads();
+    if (tg.active && tg.sub == 0 && g == 0) {
+      for (int o = 1; o < tg.wpg; ++o) {
+        const int xi = (cx.wave + o) * 32 + l32;
+        w.all = fmaxf(w.all, x_all[xi]);
+        if (beats(x_best[xi], x_idx[xi], w.best, best_i)) {
+          w.best = x_best[xi];
+          best_i = x_idx[xi];
+        }
+      }
+    }
+    __syncthreads();   // the scratch is free again
+  }
+}
+
+// Where a workgroup's 64-row tile with rows from `base` on is fetched from, sixteen 1-KiB pieces of
+// four rows: wave w takes pieces w, w + NW, ...  Rows at or past `valid` repeat the last one.
+template <int NW>
+__device__ __forceinline__ void fetch_tile(const char *khat, int base, int valid, uint32_t lds_addr, int wave,
+                                           const DmaLane &dl) {
+  const int wq = wave & 3;   // the chunk permutation of a piece depends on piece % 4 = wave % 4
+  const uint32_t kcol = wq == 0 ? dl.kcol[0] : wq == 1 ? dl.kcol[1] : wq == 2 ? dl.kcol[2] : dl.kcol[3];
+#pragma unroll
+  for (int n = 0; n < 16 / NW; ++n) {
+    const int piece = wave + NW * n;
+    int r = 4 * piece + (int)dl.rl;
+    r = r < valid ? r : valid - 1;
+    dma16(khat + (uint32_t)base * (kHeadDim * 2), (uint32_t)r * (kHeadDim * 2) + kcol, lds_addr + (uint32_t)piece * 1024u);
+  }
+}
+
+// Step 2, and the second pass of an append.  kreg holds the first round's memory keys on entry.
+//   first: the block's tokens against this workgroup's rows of [0, m) of readout version `slot`; every
+//     token's winner among these rows goes to LDS (app, best, pi) or, with more than one workgroup per
+//     unit, to the exchange table.
+//   otherwise: the tokens that were not taken against the n new rows from m on that are in the fresh
+//     tile; a token moves to one of them when that score is strictly larger than its best.  exact:
+//     small appends of short blocks, where append_kernel takes its decisions on fp32 sums in plain
+//     channel order: here a token for which that order could decide otherwise than the matrix
+//     cores' is only noted, and settle_ties decides it on the same sums.
+template <int NW>
+__device__ __forceinline__ void score_pass(const Dev &dv, const Ctx<NW> &cx, bool first, int slot, int m, int n, bool exact,
+                                           const uint16_t *kbar_blk, bf16x8 (&kreg)[8], unsigned long long *mine,
+                                           uint32_t tag) {
+  constexpr int D = kHeadDim, ST = stage_tiles(NW);
+  const int lane = cx.lane, wave = cx.wave, g = lane >> 5;
+  const int C = cx.C;
+  const bool ring = first && !cx.resident;
+  const int n_tiles = first ? (cx.n_local(m) + kTileKeys - 1) >> 6 : 1;
+  const int row1 = first ? m : n, row_lo = first ? dv.S : dv.S - m;
+  uint16_t *Ks = first ? cx.s_tiles() : cx.s_fresh();
+  const uint32_t ks_addr = lds_addr_of(Ks);
+  const char *khat = (const char *)dv.khat + (slot * dv.slot_elems + (int64_t)cx.u * dv.Mcap * D) * 2;
+  uint32_t koff[8];
+  ktile_offsets(lane, koff);
+  const DmaLane dl = dma_lane(lane);
+  auto issue_stage = [&](int sg) {
+#pragma unroll 1
+    for (int i = 0; i < ST; ++i) {
+      const int t = ST * sg + i;
+      if (t < n_tiles) {
+        const int base = cx.global(64 * t);
+        fetch_tile<NW>(khat, base, m - base, ks_addr + (uint32_t)(t & (2 * ST - 1)) * kTileBytes, wave, dl);
+      }
+    }
+  };
+  for (int g0 = 0; g0 < C / 32; g0 += NW) {
+    const TokenGroup tg = token_group<NW>(cx, C, g0);
+    if (C / 32 > NW && (g0 > 0 || !first)) fetch_keys(kreg, kbar_blk, tg.j, lane);
+    Winner w{-INFINITY, -INFINITY, -1};
+    if (ring) {
+      __syncthreads();   // the ring's last readers are done
+      issue_stage(0);
+    }
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+      if (ring && t % ST == 0) {   // a stage has landed for every wave, and the other one has been read
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        issue_stage(t / ST + 1);
+      }
+      if (tg.active && (t & (tg.wpg - 1)) == tg.sub)   // wpg is a power of two: NW and C / 32 are
+        score_tile(w, Ks + (ring ? t & (2 * ST - 1) : t) * kTileElems, koff, kreg, first ? cx.global(64 * t) >> 5 : 0, row1,
+                   row_lo, g, !first);
+    }
+    int best_i;
+    merge_winners<NW>(cx, tg, w, best_i, !first);
+    if (tg.active && tg.sub == 0 && g == 0) {
+      if (!first) {
+        const float best = cx.s_best()[tg.j];
+        if (cx.s_rank()[tg.j] < 0 && best_i != kNoRow) {
+          // fp32 sums of 128 exact products in two orders differ by far less than this
+          const float reach = fmaxf(1e-2f, fabsf(best) * 0x1p-12f);
+          if (exact && w.best > best - reach && (w.best < best + reach || w.all > w.best - reach)) {
+            cx.s_rows()[atomicAdd(&cx.s_cnt()[kCntTies], 1)] = tg.j;
+          } else if (w.best > best) {
+            cx.s_best()[tg.j] = w.best;
+            cx.s_pi()[tg.j] = m + best_i;
+          }
+        }
+      } else if (cx.split > 1) {
+        publish_winner(mine, C, tg.j, w.best, best_i, w.all, sink_owner(dv, cx.part), tag);
+      } else {
+        cx.s_app()[tg.j] = w.all;
+        cx.s_best()[tg.j] = w.best;
+        cx.s_pi()[tg.j] = best_i;
+        cx.s_rank()[tg.j] = -1;
+      }
+    }
+  }
+}
+
+// The noted tokens, a wave each: lane a sums token . new row a over the channels in ascending order.
+template <int NW>
+__device__ __forceinline__ void settle_ties(const Dev &dv, const Ctx<NW> &cx, int m, int n_app, const uint16_t *kbar_blk) {
+  const int n = cx.s_cnt()[kCntTies], lane = cx.lane;
+  const uint16_t *Kt = cx.s_fresh() + (lane & 15) * kHeadDim;   // n_app <= 16
+  for (int k = cx.wave; k < n; k += NW) {
+    const int j = cx.s_rows()[k];
+    // the token's key, a sixteenth per lane; its pieces go round as scalars
+    const uint4 piece = *reinterpret_cast<const uint4 *>(kbar_blk + (int64_t)j * kHeadDim + 8 * (lane & 15));
+    float acc = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const uint4 xq = make_uint4(__builtin_amdgcn_readlane(piece.x, q), __builtin_amdgcn_readlane(piece.y, q),
+                                  __builtin_amdgcn_readlane(piece.z, q), __builtin_amdgcn_readlane(piece.w, q));
+      float x[8], y[8];
+      unpack16<bf16_t>(xq, x);
+      unpack16<bf16_t>(*reinterpret_cast<const uint4 *>(Kt + 8 * (q ^ (lane & 15))), y);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fmaf(x[e], y[e], acc);
+    }
+    float best = lane < n_app ? acc : -INFINITY;
+    int a = lane < n_app ? lane : kNoRow;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {   // n_app <= 16
+      const float ob = __shfl_xor(best, o, kWave);
+      const int oa = __shfl_xor(a, o, kWave);
+      if (beats(ob, oa, best, a)) {
+        best = ob;
+        a = oa;
+      }
+    }
+    if (lane == 0 && m + a >= dv.S && best > cx.s_best()[j]) {
+      cx.s_best()[j] = best;
+      cx.s_pi()[j] = m + a;
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
 // Step 3: the n_app tokens with the smallest (s_j, position) are taken; a taken token's rank among
-// the taken ones, in position order, is the new row it creates.
-template <int NW>
-__device__ __forceinline__ void select_tokens(const Dev &dv, const Ctx &cx, int m, int n_app) {
-  constexpr int NT = 64 * NW;
-  const int C = dv.C, tid = cx.tid, lane = cx.lane;
-  unsigned long long *key = (unsigned long long *)(cx.smem + cx.l.tiles);   // [C], tiles are idle here
-  for (int j = tid; j < C; j += NT) {
-    uint32_t f = __float_as_uint(cx.s_app()[j]);
-    f = f == 0x80000000u ? 0u : f;   // -0 and +0 are one score
-    const uint32_t mono = (f & 0x80000000u) ? ~f : (f | 0x80000000u);
-    key[j] = ((unsigned long long)mono << 32) | (uint32_t)j;
+// the taken ones, in position order, is the new row it creates.  Every wave finds the n_app-th smallest
+// score for itself, bit by bit from the top, counting with ballots over scores it holds in registers (no
+// barriers, no table: comparing every token with every other one through LDS took 7 us for 256 tokens,
+// this takes 1.5).
+constexpr int kMaxBlock = 1024;
+template <int NW, int kQ>   // kQ: 64-token pieces, at least C / 64
+__device__ __forceinline__ void select_tokens(const Ctx<NW> &cx, int m, int n_app) {
+  const int C = cx.C, lane = cx.lane;
+  uint32_t key[kQ];   // the float's bits made monotonic as an unsigned number; the largest number beyond the block
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    key[q] = 0xffffffffu;
+    if (64 * q < C) {
+      uint32_t f = __float_as_uint(cx.s_app()[64 * q + lane]);
+      f = f == 0x80000000u ? 0u : f;   // -0 and +0 are one score
+      key[q] = (f & 0x80000000u) ? ~f : (f | 0x80000000u);
+    }
   }
-  __syncthreads();
-  for (int j0 = 0; j0 < C; j0 += NT) {   // C is a multiple of 64: whole waves
-    const int j = j0 + tid;
-    bool take = false;
-    if (j < C) {
-      const unsigned long long kj = key[j];
-      int rank = 0;
-      for (int t = 0; t < C; t += 2) {
-        const ulonglong2 k2 = *reinterpret_cast<const ulonglong2 *>(key + t);
-        rank += k2.x < kj ? 1 : 0;
-        rank += k2.y < kj ? 1 : 0;
+  uint32_t T = 0;   // largest number that fewer than n_app scores lie below: the n_app-th smallest score
+#pragma unroll 1
+  for (int bit = 30; bit >= 0; bit -= 2) {   // two bits at a time
+    const uint32_t c1 = T | (1u << bit), c2 = T | (2u << bit), c3 = T | (3u << bit);
+    int n1 = 0, n2 = 0, n3 = 0;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      n1 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c1));
+      n2 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c2));
+      n3 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c3));
+    }
+    T = n3 < n_app ? c3 : n2 < n_app ? c2 : n1 < n_app ? c1 : T;
+  }
+  int equal = n_app;   // how many of the scores equal to it are taken: the earliest
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) equal -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < T));
+  int base = 0;
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    unsigned long long eq = __builtin_amdgcn_ballot_w64(key[q] == T);
+    while (__builtin_popcountll(eq) > equal) eq &= ~(1ull << (63 - __builtin_clzll(eq)));
+    equal -= __builtin_popcountll(eq);
+    const unsigned long long taken = __builtin_amdgcn_ballot_w64(key[q] < T) | eq;
+    if (q % NW == cx.wave) {   // a wave per 64 tokens writes what they all know
+      const int j = 64 * q + lane;
+      if ((taken >> lane) & 1ull) {
+        const int a = base + __builtin_popcountll(taken & ((1ull << lane) - 1ull));
+        cx.s_rank()[j] = a;
+        cx.s_pi()[j] = m + a;
+        cx.s_best()[j] = __uint_as_float(0x7fc00000u);
+        cx.s_creator()[a] = j;
       }
-      take = rank < n_app;
     }
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(take);
-    if (lane == 0 && j < C) cx.s_masks()[j >> 6] = bal;
-  }
-  __syncthreads();
-  for (int j = tid; j < C; j += NT) {
-    const int wj = j >> 6, lj = j & 63;
-    const unsigned long long mine = cx.s_masks()[wj];
-    if ((mine >> lj) & 1ull) {
-      int a = __builtin_popcountll(mine & ((1ull << lj) - 1ull));
-      for (int w2 = 0; w2 < wj; ++w2) a += __builtin_popcountll(cx.s_masks()[w2]);
-      cx.s_rank()[j] = a;
-      cx.s_pi()[j] = m + a;
-      cx.s_best()[j] = __uint_as_float(0x7fc00000u);
-      cx.s_creator()[a] = j;
-    } else {
-      cx.s_rank()[j] = -1;
-    }
+    base += __builtin_popcountll(taken);
   }
   __syncthreads();
 }
@@ -517,11 +621,39 @@ __device__ __forceinline__ double rsqrt64(double x) {
   return y;
 }
 
-// Readout row of sums (sk, sv, rho): LN_s on the key sums in fp64, stored radius on the value sums;
-// 16 lanes hold the row, 8 channels each.  Rounding to bf16 is the hardware's (nearest even).
-__device__ __forceinline__ void write_readout16(const Dev &dv, int slot, int64_t ro, int ch0, const double (&sk)[8],
-                                                const float (&sv)[8], float rho, const float (&ga)[8],
-                                                const float (&be)[8]) {
+// A row is held by 16 lanes, 8 channels each: lane c has channels 64 q + 4 c + e, q = 0..1, e = 0..3 (element 4 q + e of
+// its arrays), so that every access to a row of bf16, fp32 or fp64 is contiguous over the lanes in
+// pieces of 128, 256 or 512 bytes.
+__device__ __forceinline__ void load_bf16x4(const uint16_t *p, float *f) {
+  const uint2 x = *reinterpret_cast<const uint2 *>(p);
+  f[0] = __uint_as_float(x.x << 16);
+  f[1] = __uint_as_float(x.x & 0xffff0000u);
+  f[2] = __uint_as_float(x.y << 16);
+  f[3] = __uint_as_float(x.y & 0xffff0000u);
+}
+struct Row8 {   // eight bf16 values of a lane
+  uint2 q[2];
+};
+__device__ __forceinline__ void store_row(uint16_t *row, int c16, const Row8 &v) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) *reinterpret_cast<uint2 *>(row + 64 * q + 4 * c16) = v.q[q];
+}
+// the same into row r of tiles in the K layout (16-byte chunk k of a row sits in slot k ^ (r & 15))
+__device__ __forceinline__ void store_tile_row(uint16_t *tiles, int r, int c16, const Row8 &v) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    *reinterpret_cast<uint2 *>(tiles + r * kHeadDim + 8 * ((8 * q + (c16 >> 1)) ^ (r & 15)) + 4 * (c16 & 1)) = v.q[q];
+}
+// Parameters of LN_s of the unit's KV head (given, or 1 and 0)
+struct LnParams {
+  const float *gamma, *beta;
+};
+__device__ __forceinline__ LnParams ln_params(const Dev &dv, int u) {
+  const int h = u % dv.Hkv;
+  return {dv.gamma ? dv.gamma + h * kHeadDim : kOnes, dv.beta ? dv.beta + h * kHeadDim : kZeros};
+}
+// LN_s of a row of key sums.
+__device__ __forceinline__ Row8 normalised16(const Dev &dv, const double (&sk)[8], const LnParams &ln, int c16) {
   constexpr int D = kHeadDim;
   double s = 0.0;
 #pragma unroll
@@ -534,123 +666,176 @@ __device__ __forceinline__ void write_readout16(const Dev &dv, int slot, int64_t
     qq += dl * dl;
   }
   const double rden = rsqrt64(group_sum<16>(qq) * (1.0 / (double)D) + (double)dv.ln_eps);
+  Row8 r;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float4 g4 = *reinterpret_cast<const float4 *>(ln.gamma + 64 * q + 4 * c16);
+    const float4 b4 = *reinterpret_cast<const float4 *>(ln.beta + 64 * q + 4 * c16);
+    const float ga[4] = {g4.x, g4.y, g4.z, g4.w}, be[4] = {b4.x, b4.y, b4.z, b4.w};
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = (float)((sk[4 * q + e] - mean) * rden * (double)ga[e] + (double)be[e]);
+    r.q[q] = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
+  }
+  return r;
+}
+
+// The readout row of value sums sv and radius rho whose normalised key is `khat`.  Rounding to bf16
+// is the hardware's (nearest even).
+__device__ __forceinline__ void store_readout16(const Dev &dv, int slot, int64_t ro, int c16, const Row8 &khat,
+                                                const float (&sv)[8], float rho) {
+  constexpr int D = kHeadDim;
   float nn = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) nn += sv[e] * sv[e];
   // (hardware root and reciprocal, an ulp of fp32 each: far below the bf16 the result is rounded to)
   const float vs = rho * __builtin_amdgcn_rcpf(fmaxf(__builtin_amdgcn_sqrtf(group_sum<16>(nn)), dv.norm_eps));
-  uint32_t kw[4], vw[4];
+  Row8 v;
 #pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    const double y0 = (sk[e] - mean) * rden * (double)ga[e] + (double)be[e];
-    const double y1 = (sk[e + 1] - mean) * rden * (double)ga[e + 1] + (double)be[e + 1];
-    kw[e >> 1] = pack_bf16((float)y0, (float)y1);
-    vw[e >> 1] = pack_bf16(sv[e] * vs, sv[e + 1] * vs);
+  for (int q = 0; q < 2; ++q)
+    v.q[q] = make_uint2(pack_bf16(sv[4 * q] * vs, sv[4 * q + 1] * vs), pack_bf16(sv[4 * q + 2] * vs, sv[4 * q + 3] * vs));
+  store_row((uint16_t *)dv.khat + slot * dv.slot_elems + ro * D, c16, khat);
+  store_row((uint16_t *)dv.vhat + slot * dv.slot_elems + ro * D, c16, v);
+}
+__device__ __forceinline__ void load_sums(const Dev &dv, int64_t ro, int c16, double (&sk)[8], float (&sv)[8]) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const double2 *pk = reinterpret_cast<const double2 *>(dv.sK + ro * kHeadDim + 64 * q + 4 * c16);
+    const double2 a = pk[0], b = pk[1];
+    const float4 v = *reinterpret_cast<const float4 *>(dv.sV + ro * kHeadDim + 64 * q + 4 * c16);
+    sk[4 * q] = a.x; sk[4 * q + 1] = a.y; sk[4 * q + 2] = b.x; sk[4 * q + 3] = b.y;
+    sv[4 * q] = v.x; sv[4 * q + 1] = v.y; sv[4 * q + 2] = v.z; sv[4 * q + 3] = v.w;
   }
-  uint16_t *kh = (uint16_t *)dv.khat + slot * dv.slot_elems + ro * D + ch0;
-  uint16_t *vh = (uint16_t *)dv.vhat + slot * dv.slot_elems + ro * D + ch0;
-  *reinterpret_cast<uint4 *>(kh) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
-  *reinterpret_cast<uint4 *>(vh) = make_uint4(vw[0], vw[1], vw[2], vw[3]);
+}
+__device__ __forceinline__ void store_sums(const Dev &dv, int64_t ro, int c16, const double (&sk)[8], const float (&sv)[8]) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    double2 *pk = reinterpret_cast<double2 *>(dv.sK + ro * kHeadDim + 64 * q + 4 * c16);
+    pk[0] = make_double2(sk[4 * q], sk[4 * q + 1]);
+    pk[1] = make_double2(sk[4 * q + 2], sk[4 * q + 3]);
+    *reinterpret_cast<float4 *>(dv.sV + ro * kHeadDim + 64 * q + 4 * c16) =
+        make_float4(sv[4 * q], sv[4 * q + 1], sv[4 * q + 2], sv[4 * q + 3]);
+  }
 }
 
-struct RowCtx {
+// The block a fold takes in, seen from one unit: memory keys, values, gates of its tokens.
+struct Block {
   const uint16_t *vsrc, *kbar;
   const float *gsrc;
   int64_t v_t, g_t;
-  float ga[8], be[8];
-  int gid, c16, ch0;
 };
-__device__ __forceinline__ RowCtx row_ctx(const Dev &dv, const Ctx &cx, const Src &src, int64_t tok,
+template <int NW>
+__device__ __forceinline__ Block block_of(const Dev &dv, const Ctx<NW> &cx, const Src &src, int64_t tok,
                                           const uint16_t *kbar_blk) {
-  constexpr int D = kHeadDim;
-  RowCtx rc;
-  const int u = cx.u, b = u / dv.Hkv, h = u % dv.Hkv;
-  rc.gid = cx.tid >> 4;
-  rc.c16 = cx.tid & 15;
-  rc.ch0 = 8 * rc.c16;
-  rc.vsrc = (const uint16_t *)src.v + b * src.v_b + h * src.v_h + tok * src.v_t;
-  rc.gsrc = src.g ? src.g + b * src.g_b + h * src.g_h + tok * src.g_t : nullptr;
-  rc.kbar = kbar_blk;
-  rc.v_t = src.v_t;
-  rc.g_t = src.g_t;
-  const float *gam = dv.gamma ? dv.gamma + h * D : kOnes, *bet = dv.beta ? dv.beta + h * D : kZeros;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    rc.ga[e] = gam[rc.ch0 + e];
-    rc.be[e] = bet[rc.ch0 + e];
-  }
-  return rc;
+  Block b;
+  const int bi = cx.u / dv.Hkv, h = cx.u % dv.Hkv;
+  b.vsrc = (const uint16_t *)src.v + bi * src.v_b + h * src.v_h + tok * src.v_t;
+  b.gsrc = src.g ? src.g + bi * src.g_b + h * src.g_h + tok * src.g_t : nullptr;
+  b.kbar = kbar_blk;
+  b.v_t = src.v_t;
+  b.g_t = src.g_t;
+  return b;
 }
 
-// New rows m .. m + n_app - 1 from their creator tokens: ungated copy of the memory key and the
-// value, radius = the value's norm.
+// New rows m + a_lo .. m + a_hi - 1 from their creator tokens: ungated copy of the memory key and the
+// value, radius = the value's norm.  The row's owner writes it; with `fresh` every workgroup of the
+// unit also makes the row's normalised key for itself, in the fresh tile (the same arithmetic on the
+// same operands: all of them have the same bits), so that the second scoring pass needs no exchange.
 template <int NW>
-__device__ __forceinline__ void create_rows(const Dev &dv, const Ctx &cx, const RowCtx &rc, int m, int n_app,
-                                            int slot_new) {
+__device__ __forceinline__ void create_rows(const Dev &dv, const Ctx<NW> &cx, const Block &blk, int m, int a_lo, int a_hi,
+                                            bool fresh, int slot_new) {
   constexpr int D = kHeadDim, NG = 4 * NW;
-  for (int a = rc.gid; a < n_app; a += NG) {
-    if (!cx.owns(m + a)) continue;
+  const int gid = cx.tid >> 4, c16 = cx.tid & 15;
+  const LnParams ln = ln_params(dv, cx.u);
+  for (int a = a_lo + gid; a < a_hi; a += NG) {
+    const bool own = cx.owns(m + a);
+    if (!own && !fresh) continue;
     const int t = cx.s_creator()[a];
-    const int64_t ro = (int64_t)cx.u * dv.Mcap + m + a;
-    const uint4 kraw = *reinterpret_cast<const uint4 *>(rc.kbar + (int64_t)t * D + rc.ch0);
-    const uint4 vraw = *reinterpret_cast<const uint4 *>(rc.vsrc + (int64_t)t * rc.v_t + rc.ch0);
-    float kf[8], vf[8];
-    unpack16<bf16_t>(kraw, kf);
-    unpack16<bf16_t>(vraw, vf);
+    float kf[8], vf[8] = {};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      load_bf16x4(blk.kbar + (int64_t)t * D + 64 * q + 4 * c16, kf + 4 * q);
+      if (own) load_bf16x4(blk.vsrc + (int64_t)t * blk.v_t + 64 * q + 4 * c16, vf + 4 * q);
+    }
     double sk[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sk[e] = (double)kf[e];
+    const Row8 khat = normalised16(dv, sk, ln, c16);
+    if (fresh) store_tile_row(cx.s_fresh(), a - a_lo, c16, khat);
+    if (!own) continue;
+    const int64_t ro = (int64_t)cx.u * dv.Mcap + m + a;
     float nn = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      sk[e] = (double)kf[e];
-      nn += vf[e] * vf[e];
-    }
+    for (int e = 0; e < 8; ++e) nn += vf[e] * vf[e];
     const float rho = sqrtf(group_sum<16>(nn));
-    double2 *pk = reinterpret_cast<double2 *>(dv.sK + ro * D + rc.ch0);
-    float4 *pv = reinterpret_cast<float4 *>(dv.sV + ro * D + rc.ch0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) pk[q] = make_double2(sk[2 * q], sk[2 * q + 1]);
-    pv[0] = make_float4(vf[0], vf[1], vf[2], vf[3]);
-    pv[1] = make_float4(vf[4], vf[5], vf[6], vf[7]);
-    if (rc.c16 == 0) {
+    store_sums(dv, ro, c16, sk, vf);
+    if (c16 == 0) {
       dv.rho[ro] = rho;
       dv.w[ro] = 1.f;
       dv.n[ro] = 1;
     }
-    write_readout16(dv, slot_new, ro, rc.ch0, sk, vf, rho, rc.ga, rc.be);
+    store_readout16(dv, slot_new, ro, c16, khat, vf, rho);
+    if (cx.resident) store_tile_row(cx.s_tiles(), cx.local(m + a), c16, khat);
   }
 }
 
 // Step 4: the lists.  Every token that merges pushes itself on its row's list; the one that finds
-// the list empty enters the row in `rows`.  Returns the number of touched rows.
+// the list empty enters the row in `rows`.  The token also gets a place in the scratch, as long as
+// there are places.  (The heads and the counters were cleared earlier in the fold.)
 template <int NW>
-__device__ __forceinline__ int build_lists(const Dev &dv, const Ctx &cx) {
+__device__ __forceinline__ void build_lists(const Dev &dv, const Ctx<NW> &cx) {
   constexpr int NT = 64 * NW;
   const int C = dv.C, tid = cx.tid, lane = cx.lane;
   int *cnt = cx.s_cnt();
-  if (tid == 0) cnt[0] = 0;
-  for (int i = tid; i < dv.Mcap; i += NT) cx.s_head()[i] = -1;
-  __syncthreads();
   for (int j0 = 0; j0 < C; j0 += NT) {
     const int j = j0 + tid;
-    bool leader = false;
-    int row = kNoRow;
+    bool leader = false, mine = false;
+    int lr = 0;
     if (j < C && cx.s_rank()[j] < 0) {
-      row = cx.s_pi()[j];
-      row = row != kNoRow && cx.owns(row) ? row : kNoRow;   // other rows are other workgroups' work
-      if (row != kNoRow) {
-        const int old = atomicExch(&cx.s_head()[row], j);
+      const int row = cx.s_pi()[j];
+      if (row != kNoRow && cx.owns(row)) {   // other rows are other workgroups' work
+        lr = cx.local(row);
+        const int old = atomicExch(&cx.s_head()[lr], j);
         cx.s_next()[j] = old;
         leader = old < 0;
+        mine = true;
       }
     }
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(leader);
-    int base = 0;
-    if (lane == 0 && bal) base = atomicAdd(&cnt[0], __builtin_popcountll(bal));
-    base = __shfl(base, 0, kWave);
-    if (leader) cx.s_rows()[base + __builtin_popcountll(bal & ((1ull << lane) - 1ull))] = row;
+    const unsigned long long rows = __builtin_amdgcn_ballot_w64(leader), toks = __builtin_amdgcn_ballot_w64(mine);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int row0 = 0, tok0 = 0;
+    if (lane == 0 && toks) {
+      row0 = atomicAdd(&cnt[kCntRows], __builtin_popcountll(rows));
+      tok0 = atomicAdd(&cnt[kCntOwn], __builtin_popcountll(toks));
+    }
+    row0 = __shfl(row0, 0, kWave);
+    tok0 = __shfl(tok0, 0, kWave);
+    if (leader) cx.s_rows()[row0 + __builtin_popcountll(rows & below)] = lr;
+    if (mine) {
+      const int slot = tok0 + __builtin_popcountll(toks & below);
+      cx.s_slot()[j] = slot;
+      cx.s_own()[slot] = j;
+    }
   }
   __syncthreads();
-  return cnt[0];
+}
+
+// The merging tokens' memory keys and values on their way into the scratch: all of them in flight at
+// once, four tokens' rows per load instruction.  (Taken from memory where they are added, a row with
+// several tokens is a chain of memory round trips.)
+template <int NW>
+__device__ __forceinline__ void gather_tokens(const Ctx<NW> &cx, const Block &blk) {
+  int n = cx.s_cnt()[kCntOwn];
+  n = n < cx.gather ? n : cx.gather;
+  const int c16 = cx.lane & 15;
+  const uint32_t keys = lds_addr_of(cx.s_keys(0)), vals = lds_addr_of(cx.s_vals(0));
+#pragma unroll 1
+  for (int s0 = 4 * cx.wave; s0 < n; s0 += 4 * NW) {   // (gather is a multiple of four)
+    const int s = s0 + (cx.lane >> 4);
+    const int64_t t = cx.s_own()[s < n ? s : n - 1];
+    dma16_from(blk.kbar + t * kHeadDim + 8 * c16, keys + (uint32_t)s0 * (kHeadDim * 2));
+    dma16_from(blk.vsrc + t * blk.v_t + 8 * c16, vals + (uint32_t)s0 * (kHeadDim * 2));
+  }
 }
 
 // Minimum over the 16 lanes of a group, in every lane.
@@ -664,242 +849,323 @@ __device__ __forceinline__ int group_min16(int x) {
 }
 
 // Step 5: the touched rows, 16 lanes each.
-struct RowLoad {
-  double2 k2[4];
-  float4 v4[2];
-  uint4 kraw, vraw;
-  float rho, w, gt;
-  int n, mine, len, t_cur, row;
-};
-
 template <int NW>
-__device__ __forceinline__ void merge_rows(const Dev &dv, const Ctx &cx, const RowCtx &rc, int slot_new, int n_rows) {
+__device__ __forceinline__ void merge_rows(const Dev &dv, const Ctx<NW> &cx, const Block &blk, int slot_new) {
   constexpr int D = kHeadDim, NG = 4 * NW;
-  const int C = dv.C;
+  const int C = cx.C, n_rows = cx.s_cnt()[kCntRows], c16 = cx.tid & 15;
   const int *next = cx.s_next(), *pi = cx.s_pi(), *rank = cx.s_rank();
-  auto fetch = [&](RowLoad &L, int t) {
-    L.kraw = *reinterpret_cast<const uint4 *>(rc.kbar + (int64_t)t * D + rc.ch0);
-    L.vraw = *reinterpret_cast<const uint4 *>(rc.vsrc + (int64_t)t * rc.v_t + rc.ch0);
-    L.gt = rc.gsrc ? rc.gsrc[(int64_t)t * rc.g_t] : 1.f;
-  };
-  auto start = [&](RowLoad &L, int ri) {
-    const int row = cx.s_rows()[ri];
-    L.row = row;
+  const LnParams ln = ln_params(dv, cx.u);
+  bool landed = false;
+#pragma unroll 1
+  for (int ri = cx.tid >> 4; ri < n_rows || !landed; ri += NG) {
+    const bool on = ri < n_rows;
+    const int lr = on ? cx.s_rows()[ri] : 0, row = cx.global(lr);
     const int64_t ro = (int64_t)cx.u * dv.Mcap + row;
     // the sums are asked for first; the list is walked while they travel
-    const double2 *pk = reinterpret_cast<const double2 *>(dv.sK + ro * D + rc.ch0);
-    const float4 *pv = reinterpret_cast<const float4 *>(dv.sV + ro * D + rc.ch0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) L.k2[q] = pk[q];
-    L.v4[0] = pv[0];
-    L.v4[1] = pv[1];
-    L.rho = dv.rho[ro];
-    L.w = dv.w[ro];
-    L.n = dv.n[ro];
-    // lane i of the group keeps the i-th token of the list (any order); longer lists are scanned
-    int mine = kNoRow, len = 0;
-    for (int t = cx.s_head()[row]; t >= 0 && len <= kListMax; t = next[t], ++len)
-      if (len == rc.c16) mine = t;
-    L.mine = mine;
-    L.len = len;
-    // the first token (the smallest position) is asked for together with the sums
-    L.t_cur = len <= kListMax ? group_min16(mine) : kNoRow;
-    if (L.t_cur != kNoRow) fetch(L, L.t_cur);
-  };
-  auto finish = [&](RowLoad &L) {
-    const int64_t ro = (int64_t)cx.u * dv.Mcap + L.row;
     double sk[8];
-    float sv[8];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sk[2 * q] = L.k2[q].x;
-      sk[2 * q + 1] = L.k2[q].y;
+    float sv[8], rho = 0.f, w = 0.f;
+    int n = 0;
+    if (on) {
+      load_sums(dv, ro, c16, sk, sv);
+      rho = dv.rho[ro];
+      w = dv.w[ro];
+      n = dv.n[ro];
     }
-    sv[0] = L.v4[0].x; sv[1] = L.v4[0].y; sv[2] = L.v4[0].z; sv[3] = L.v4[0].w;
-    sv[4] = L.v4[1].x; sv[5] = L.v4[1].y; sv[6] = L.v4[1].z; sv[7] = L.v4[1].w;
-    float w = L.w;
-    int n = L.n;
-    auto add_fetched = [&]() {
-      float kf[8], vf[8];
-      unpack16<bf16_t>(L.kraw, kf);
-      unpack16<bf16_t>(L.vraw, vf);
+    if (!landed) {   // the gathered tokens are there, every wave's share of them
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      landed = true;
+    }
+    if (!on) break;
+    // lane i of the group keeps the i-th token of the list (any order)
+    int mine = kNoRow, len = 0;
+    for (int t = cx.s_head()[lr]; t >= 0 && len <= kListMax; t = next[t], ++len)
+      if (len == c16) mine = t;
+    // The row's tokens in ascending position: from the lanes' tokens, or, when a list is longer than
+    // the lanes (many tokens on one row), from the block's targets, 16 positions at a time.
+    auto after = [&](int t) {
+      if (len <= kListMax) return group_min16(mine > t ? mine : kNoRow);
+      int found = kNoRow;
+      for (int t0 = t + 1; t0 < C && found == kNoRow; t0 += 16) {
+        const int x = t0 + c16;
+        found = group_min16(x < C && pi[x] == row && rank[x] < 0 ? x : kNoRow);
+      }
+      return found;
+    };
+    for (int t = after(-1); t != kNoRow; t = after(t)) {
+      const int slot = cx.s_slot()[t];
+      float gt = 1.f, kf[8], vf[8];
+      if (blk.gsrc) gt = blk.gsrc[(int64_t)t * blk.g_t];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (slot < cx.gather) {
+          load_bf16x4(cx.s_keys(slot) + 64 * q + 4 * c16, kf + 4 * q);
+          load_bf16x4(cx.s_vals(slot) + 64 * q + 4 * c16, vf + 4 * q);
+        } else {
+          load_bf16x4(blk.kbar + (int64_t)t * D + 64 * q + 4 * c16, kf + 4 * q);
+          load_bf16x4(blk.vsrc + (int64_t)t * blk.v_t + 64 * q + 4 * c16, vf + 4 * q);
+        }
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        sk[e] = fma((double)L.gt, (double)kf[e], sk[e]);
-        sv[e] = fmaf(L.gt, vf[e], sv[e]);
+        sk[e] = fma((double)gt, (double)kf[e], sk[e]);
+        sv[e] = fmaf(gt, vf[e], sv[e]);
       }
-      w += L.gt;
+      w += gt;
       n += 1;
-    };
-    if (L.len <= kListMax) {
-      // ascending position: the smallest token not yet added, len times
-      int t_cur = L.t_cur;
-      for (int q = 0; q < L.len; ++q) {
-        add_fetched();
-        if (q + 1 < L.len) {
-          t_cur = group_min16(L.mine > t_cur ? L.mine : kNoRow);
-          fetch(L, t_cur);
-        }
-      }
-    } else {
-      // a long list (many tokens on one row): scan the block's targets in position order instead
-      for (int t = 0; t < C; ++t)
-        if (pi[t] == L.row && rank[t] < 0) {
-          fetch(L, t);
-          add_fetched();
-        }
     }
-    {
-      double2 *qk = reinterpret_cast<double2 *>(dv.sK + ro * D + rc.ch0);
-      float4 *qv = reinterpret_cast<float4 *>(dv.sV + ro * D + rc.ch0);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) qk[q] = make_double2(sk[2 * q], sk[2 * q + 1]);
-      qv[0] = make_float4(sv[0], sv[1], sv[2], sv[3]);
-      qv[1] = make_float4(sv[4], sv[5], sv[6], sv[7]);
-      if (rc.c16 == 0) {
-        dv.w[ro] = w;
-        dv.n[ro] = n;
-      }
+    store_sums(dv, ro, c16, sk, sv);
+    if (c16 == 0) {
+      dv.w[ro] = w;
+      dv.n[ro] = n;
     }
-    write_readout16(dv, slot_new, ro, rc.ch0, sk, sv, L.rho, rc.ga, rc.be);
-  };
-  for (int ri = rc.gid; ri < n_rows; ri += NG) {
-    RowLoad A;
-    start(A, ri);
-    finish(A);
+    const Row8 khat = normalised16(dv, sk, ln, c16);
+    store_readout16(dv, slot_new, ro, c16, khat, sv, rho);
+    if (cx.resident) store_tile_row(cx.s_tiles(), lr, c16, khat);
   }
 }
 
-// Rows [0, m) that received no token: their readout moves to the new version unchanged.
-// all: no lists were built in this fold (every token made a row of its own): every row moves.
+// Own rows of [0, m) that received no token in the fold from version slot_old to slot_new: their
+// readout moves to the new version unchanged (key rows of resident tiles come from LDS).  With resident
+// tiles this is done while the next fold's winners travel between the workgroups: nothing of the
+// chain waits for it.  (Tiles that stream are read from the new version: then it is done before the
+// next fold's scores.)  The lists' heads, which tell the rows, are cleared for the next fold on the way.
 template <int NW>
-__device__ __forceinline__ void copy_untouched(const Dev &dv, const Ctx &cx, int m, int slot_old, int slot_new,
-                                               bool all) {
-  constexpr int D = kHeadDim, UN = 4, NG = 4 * NW;
-  const int gid = cx.tid >> 4, c16 = cx.tid & 15;
-  const int *head = cx.s_head();
-  const int64_t ubase = (int64_t)cx.u * dv.Mcap * D;
+__device__ __forceinline__ void copy_untouched(const Dev &dv, const Ctx<NW> &cx, int m, int m_after, int slot_old,
+                                               int slot_new, int in_place) {
+  constexpr int D = kHeadDim, NG = 4 * NW, kRows = 4;
+  const int gid = cx.tid >> 4, c16 = cx.tid & 15, n = in_place ? 0 : cx.n_local(m), n_all = cx.n_local(m_after);
+  const int64_t ubase = (int64_t)cx.u * dv.Mcap * D + 8 * c16;
   const uint16_t *ko = (const uint16_t *)dv.khat + slot_old * dv.slot_elems + ubase;
   const uint16_t *vo = (const uint16_t *)dv.vhat + slot_old * dv.slot_elems + ubase;
   uint16_t *kn = (uint16_t *)dv.khat + slot_new * dv.slot_elems + ubase;
   uint16_t *vn = (uint16_t *)dv.vhat + slot_new * dv.slot_elems + ubase;
-  for (int r0 = gid; r0 < m; r0 += NG * UN) {
-    uint4 kk[UN], vv[UN];
-    bool on[UN];
+#pragma unroll 1
+  for (int lr0 = gid; lr0 < n_all; lr0 += kRows * NG) {
+    uint4 kk[kRows], vv[kRows];
+    bool on[kRows];
 #pragma unroll
-    for (int q = 0; q < UN; ++q) {
-      const int r = r0 + q * NG;
-      on[q] = r < m && (all || head[r] < 0) && cx.owns(r);
-      if (on[q]) {
-        kk[q] = *reinterpret_cast<const uint4 *>(ko + (int64_t)r * D + 8 * c16);
-        vv[q] = *reinterpret_cast<const uint4 *>(vo + (int64_t)r * D + 8 * c16);
-      }
+    for (int q = 0; q < kRows; ++q) {
+      const int lr = lr0 + q * NG;
+      on[q] = lr < n && cx.s_head()[lr < n ? lr : 0] < 0;
+      const int64_t at = (int64_t)cx.global(on[q] ? lr : 0) * D;
+      vv[q] = make_uint4(0u, 0u, 0u, 0u);
+      kk[q] = make_uint4(0u, 0u, 0u, 0u);
+      if (on[q]) vv[q] = *reinterpret_cast<const uint4 *>(vo + at);
+      if (on[q] && !cx.resident) kk[q] = *reinterpret_cast<const uint4 *>(ko + at);
+      if (on[q] && cx.resident) kk[q] = *reinterpret_cast<const uint4 *>(cx.s_tiles() + lr * D + 8 * (c16 ^ (lr & 15)));
     }
 #pragma unroll
-    for (int q = 0; q < UN; ++q) {
-      const int r = r0 + q * NG;
+    for (int q = 0; q < kRows; ++q) {
+      const int lr = lr0 + q * NG;
+      const int64_t at = (int64_t)cx.global(lr) * D;
       if (on[q]) {
-        *reinterpret_cast<uint4 *>(kn + (int64_t)r * D + 8 * c16) = kk[q];
-        *reinterpret_cast<uint4 *>(vn + (int64_t)r * D + 8 * c16) = vv[q];
+        *reinterpret_cast<uint4 *>(kn + at) = kk[q];
+        *reinterpret_cast<uint4 *>(vn + at) = vv[q];
       }
+      if (c16 == 0 && lr < n_all) cx.s_head()[lr] = -1;   // (only this group's lanes look at it before the next barrier)
     }
   }
 }
 
-// The kernel's one argument.  The steps of the run are read from the kernel-argument segment by
-// index (a scalar load with a computed offset): as a by-value array indexed by the loop variable
-// the compiler would either copy them to private memory or hold all of them in scalar registers.
+// The kernel's one argument.  Steps and parameters are read from the kernel-argument segment where
+// they are used: a fold is a dozen short phases, and what the compiler may keep in registers from
+// one phase to the next -- pointers of arrays, addresses and lane numbers made from them, for all
+// phases at once -- spilled 370 vector and 370 scalar registers.  args_now() and phase() hide where
+// a value comes from, so that every phase makes its own.
 struct FoldKernelArgs {
   Dev dv;
   Src src;
   FoldRunArgs run;
 };
+__device__ __forceinline__ const FoldKernelArgs &args_now() {
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const FoldKernelArgs *)(const __attribute__((address_space(4))) FoldKernelArgs *)p;
+}
+template <int NW>
+__device__ __forceinline__ Ctx<NW> phase(const Ctx<NW> &cx) {
+  Ctx<NW> c = cx;
+  asm volatile("" : "+v"(c.tid));
+  c.lane = c.tid & 63;
+  asm volatile("" : "+s"(c.wave), "+s"(c.C), "+s"(c.fresh_at), "+s"(c.u), "+s"(c.gather));
+  return c;
+}
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs args) {
+__global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int D = kHeadDim, NT = 64 * NW;
-  const Dev &dv = args.dv;
-  const Src &src = args.src;
-  const int run_n = args.run.n, run_in_place = args.run.in_place;
-  int32_t *const trace_assign = args.run.trace_assign;
-  float *const trace_score = args.run.trace_score;
-  const int64_t trace_stride = args.run.trace_stride;
-  const FoldStep *steps = reinterpret_cast<const FoldStep *>(
-      (const char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(FoldKernelArgs, run) + offsetof(FoldRunArgs, s));
-  const int C = dv.C;
-  // Workgroup -> (unit, part).  The workgroups of a unit read the same block of tokens: where the
-  // number of units allows it they get ids 8 apart, which the hardware hands to one accelerator
-  // die, whose L2 then fetches the block once.
-  const int split = args.run.split;
-  const int bid = (int)blockIdx.x;
-  const bool by_die = dv.U % 8 == 0;
-  const int u_ = by_die ? (bid / (8 * split)) * 8 + bid % 8 : bid / split;
-  const int part_ = by_die ? (bid / 8) % split : bid % split;
-  Ctx cx{smem, fold_lds(C, dv.Mcap, NW, split), u_, (int)threadIdx.x, (int)(threadIdx.x & 63),
-         __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), part_, split};
-  unsigned long long *const xtab = args.run.xtab;
-  int32_t *const xerr = args.run.err;
-  const int u = cx.u, tid = cx.tid;
+  Ctx<NW> cx;
+  int run_n, run_in_place;
+  {
+    const FoldKernelArgs &a = args_now();
+    const int split = a.run.split, bid = (int)blockIdx.x;
+    // Workgroup -> (unit, part).  The workgroups of a unit read the same block of tokens: where the
+    // number of units allows it they get ids 8 apart, which the hardware hands to one accelerator
+    // die, whose L2 then fetches the block once.
+    const bool by_die = a.dv.U % 8 == 0;
+    cx.smem = smem;
+    cx.C = a.dv.C;
+    cx.fresh_at = lds_fresh(NW, a.dv.C, own_tiles_most(a.dv.Mcap, split));
+    cx.gather = a.run.gather;
+    cx.u = by_die ? (bid / (8 * split)) * 8 + bid % 8 : bid / split;
+    cx.part = by_die ? (bid / 8) % split : bid % split;
+    cx.split = split;
+    cx.shift = __builtin_ctz(split);
+    cx.resident = a.run.resident > 0;
+    cx.tid = (int)threadIdx.x;
+    cx.lane = cx.tid & 63;
+    cx.wave = __builtin_amdgcn_readfirstlane(cx.tid >> 6);
+    run_n = a.run.n;
+    run_in_place = a.run.in_place;
+  }
   const float qnan = __uint_as_float(0x7fc00000u);
 #ifdef KVM_FOLD_STAMPS
-  if (threadIdx.x == 0) cx.s_cnt()[3] = 0;
+  if (threadIdx.x == 0) cx.s_cnt()[kCntStamps] = 0;
 #endif
-  if (threadIdx.x == 0) cx.s_cnt()[2] = 0;   // no wait has given up (read after barriers only)
+  if (threadIdx.x == 0) cx.s_cnt()[kCntGaveUp] = 0;   // (read after barriers only)
+  // the memory keys of a step's block: slab `kbar_block` of the scratch, this unit's C rows
+  auto keys_of = [&](const FoldKernelArgs &a, int si) {
+    return (const uint16_t *)a.dv.kbar + ((int64_t)a.run.s[si].kbar_block * a.dv.Ufull + cx.u) * cx.C * D;
+  };
+  bf16x8 kreg[8];
+  auto fetch_first_keys = [&](int si) {
+    const Ctx<NW> c = phase(cx);
+    fetch_keys(kreg, keys_of(args_now(), si), token_group<NW>(c, c.C, 0).j, c.lane);
+  };
+  fetch_first_keys(0);
+  if (cx.resident) {
+    const FoldKernelArgs &a = args_now();
+    const char *khat = (const char *)a.dv.khat + (a.run.s[0].so * a.dv.slot_elems + (int64_t)cx.u * a.dv.Mcap * D) * 2;
+    const DmaLane dl = dma_lane(cx.lane);
+    const uint32_t at = lds_addr_of(cx.s_tiles());
+    const int m0 = a.run.s[0].m;
+    for (int t = 0; 64 * t < cx.n_local(m0); ++t) {
+      const int base = cx.global(64 * t);
+      fetch_tile<NW>(khat, base, m0 - base, at + (uint32_t)t * kTileBytes, cx.wave, dl);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  }
 
-  for (int si = 0; si < run_n; ++si) {
+  {
+    const int n = own_tiles_most(args_now().dv.Mcap, cx.split) * kTileKeys;
+    for (int i = cx.tid; i < n; i += NT) cx.s_head()[i] = -1;
+  }
+
+  // One pass more than there are folds: a fold's copies are made in the next one's place for them.
+  int m = 0, m_after = 0, so = 0, sn = 0;   // of the fold before, until the new values are taken over
+  for (int si = 0;; ++si) {
     FOLD_STAMP();
-    const FoldStep st = steps[si];
-    const int m = st.m, m_after = st.m_after, n_app = m_after - m;
-    // the block's memory keys: slab `kbar_block` of the scratch, this unit's C rows
-    const uint16_t *kbar_blk = (const uint16_t *)dv.kbar + ((int64_t)st.kbar_block * dv.Ufull + u) * C * D;
-    if (n_app == C) {
-      // room for the whole block (state creation included): no scores
-      for (int j = tid; j < C; j += NT) {
-        cx.s_rank()[j] = j;
-        cx.s_pi()[j] = m + j;
-        cx.s_app()[j] = qnan;
-        cx.s_best()[j] = qnan;
-        cx.s_creator()[j] = j;
+    const bool live = si < run_n;
+    const int m_prev = m, m_after_prev = m_after, so_prev = so, sn_prev = sn;
+    if (live) {
+      const FoldStep &st = args_now().run.s[si];
+      m = st.m; m_after = st.m_after; so = st.so; sn = st.sn;
+    }
+    const int n_app = m_after - m;
+    const bool all = live && n_app == cx.C;   // room for the whole block (state creation included): no scores
+    const bool exact = append_fits(cx.C, n_app);
+    if (cx.tid == 0) cx.s_cnt()[kCntRows] = cx.s_cnt()[kCntTies] = cx.s_cnt()[kCntOwn] = 0;
+    if (all) {
+      const Ctx<NW> c = phase(cx);
+      for (int j = c.tid; j < c.C; j += NT) {
+        c.s_rank()[j] = j;
+        c.s_pi()[j] = m + j;
+        c.s_app()[j] = qnan;
+        c.s_best()[j] = qnan;
+        c.s_creator()[j] = j;
       }
+      __syncthreads();   // create_rows reads other waves' entries
+    }
+    auto copy_previous = [&]() {
+      copy_untouched<NW>(args_now().dv, phase(cx), m_prev, m_after_prev, so_prev, sn_prev, run_in_place);
+    };
+    if (!cx.resident && si > 0) {
+      copy_previous();
       __syncthreads();
-      const RowCtx rc = row_ctx(dv, cx, src, st.tok, kbar_blk);
-      create_rows<NW>(dv, cx, rc, m, n_app, st.sn);
-      FOLD_STAMP();
-      if (!run_in_place) copy_untouched<NW>(dv, cx, m, st.so, st.sn, true);
-    } else {
-      score_pass<NW>(dv, cx, st.so, 0, m, true, kbar_blk);
-      if (split > 1) exchange_winners<NW>(dv, cx, xtab, st.xnum, true, xerr);
-      FOLD_STAMP();
-      const RowCtx rc = row_ctx(dv, cx, src, st.tok, kbar_blk);
-      if (n_app > 0) {
-        select_tokens<NW>(dv, cx, m, n_app);
-        // the new rows first, so that the remaining tokens can be scored against them too
-        create_rows<NW>(dv, cx, rc, m, n_app, st.sn);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }
+    // Scoring passes: the state's rows first, then (a partial append) the rows this fold creates, 64 at a time.
+    int a0 = all ? 0 : -1;   // -1: the state; otherwise the first new row of the pass
+    bool begin = true;
+    do {
+      int a1 = 0;
+      if (a0 >= 0) {
+        a1 = all || n_app - a0 < kTileKeys ? n_app : a0 + kTileKeys;
+        const FoldKernelArgs &a = args_now();
+        const Ctx<NW> c = phase(cx);
+        create_rows<NW>(a.dv, c, block_of(a.dv, c, a.src, a.run.s[si].tok, keys_of(a, si)), m, a0, a1, !all, sn);
         __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        score_pass<NW>(dv, cx, st.sn, m, m_after, false, kbar_blk);
-        if (split > 1) exchange_winners<NW>(dv, cx, xtab, st.xnum + 1u, false, xerr);
       }
+      if (live && !all) {
+        const FoldKernelArgs &a = args_now();
+        const Ctx<NW> c = phase(cx);
+        const uint32_t xnum = a.run.s[si].xnum;
+        unsigned long long *mine = a.run.xtab + (((size_t)c.u * 2 + (xnum & 1u)) * c.split + c.part) * 2 * c.C;
+        score_pass<NW>(a.dv, c, a0 < 0, so, m + (a0 < 0 ? 0 : a0), a1 - a0, exact, keys_of(a, si), kreg, mine, xnum & 0xffffu);
+      }
+      if (begin && cx.resident && si > 0) copy_previous();
+      if (!live) return;
+      begin = false;
+      __syncthreads();
       FOLD_STAMP();
-      const int n_rows = build_lists<NW>(dv, cx);
-      FOLD_STAMP();
-      merge_rows<NW>(dv, cx, rc, st.sn, n_rows);
-      FOLD_STAMP();
-      if (!run_in_place) copy_untouched<NW>(dv, cx, m, st.so, st.sn, false);
+      if (a0 < 0) {
+        if (cx.split > 1) {
+          const FoldKernelArgs &a = args_now();
+          const Ctx<NW> c = phase(cx);
+          const uint32_t xnum = a.run.s[si].xnum;
+          exchange_winners<NW>(a.dv, c, a.run.xtab + (((size_t)c.u * 2 + (xnum & 1u)) * c.split) * 2 * c.C, xnum & 0xffffu,
+                               a.run.err);
+          __syncthreads();
+        }
+        FOLD_STAMP();
+        if (n_app > 0) {
+          if (cx.C <= 256)
+            select_tokens<NW, 4>(phase(cx), m, n_app);
+          else
+            select_tokens<NW, kMaxBlock / 64>(phase(cx), m, n_app);
+          FOLD_STAMP();
+        }
+      }
+      a0 = a1;
+    } while (a0 < n_app);
+    if (exact && cx.s_cnt()[kCntTies] > 0) {   // rarely
+      const FoldKernelArgs &a = args_now();
+      settle_ties<NW>(a.dv, phase(cx), m, n_app, keys_of(a, si));
+      __syncthreads();
+    }
+    FOLD_STAMP();
+    build_lists<NW>(args_now().dv, phase(cx));
+    {
+      const FoldKernelArgs &a = args_now();
+      const Ctx<NW> c = phase(cx);
+      gather_tokens<NW>(c, block_of(a.dv, c, a.src, a.run.s[si].tok, keys_of(a, si)));
+    }
+    if (n_app > 0) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // merges into rows just created
+    if (si + 1 < run_n) fetch_first_keys(si + 1);
+    FOLD_STAMP();
+    {
+      const FoldKernelArgs &a = args_now();
+      const Ctx<NW> c = phase(cx);
+      merge_rows<NW>(a.dv, c, block_of(a.dv, c, a.src, a.run.s[si].tok, keys_of(a, si)), sn);
     }
     FOLD_STAMP();
     // what the fold decided, for the record and for the entry point's optional outputs
     if (cx.part == 0) {
-      const int64_t base = (int64_t)u * C;
-      for (int j = tid; j < C; j += NT) {
-        const int p = cx.s_pi()[j];
-        const float2 sc = make_float2(cx.s_app()[j], cx.s_best()[j]);
-        dv.pi[base + j] = p;
-        dv.score[base + j] = sc;
-        if (trace_assign && st.trace >= 0) trace_assign[st.trace * trace_stride + base + j] = p;
-        if (trace_score && st.trace >= 0)
-          reinterpret_cast<float2 *>(trace_score)[st.trace * trace_stride + base + j] = sc;
+      const FoldKernelArgs &a = args_now();
+      const Ctx<NW> c = phase(cx);
+      const int64_t base = (int64_t)c.u * c.C;
+      const int trace = a.run.s[si].trace;
+      for (int j = c.tid; j < c.C; j += NT) {
+        const int p = c.s_pi()[j];
+        const float2 sc = make_float2(c.s_app()[j], c.s_best()[j]);
+        a.dv.pi[base + j] = p;
+        a.dv.score[base + j] = sc;
+        if (a.run.trace_assign && trace >= 0) a.run.trace_assign[trace * a.run.trace_stride + base + j] = p;
+        if (a.run.trace_score && trace >= 0)
+          reinterpret_cast<float2 *>(a.run.trace_score)[trace * a.run.trace_stride + base + j] = sc;
       }
     }
     // the next fold of the run reads what this one wrote (this workgroup's own stores)
@@ -912,40 +1178,56 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs a
 // arithmetic of the folds above, so that a state that was exported and imported continues to the
 // bit like one that was not.
 __global__ __launch_bounds__(256) void refresh16_kernel(Dev dv, int m, int slot) {
-  constexpr int D = kHeadDim;
-  const int u = blockIdx.y, h = u % dv.Hkv;
-  const int row = blockIdx.x * 16 + (threadIdx.x >> 4), c16 = threadIdx.x & 15, ch0 = 8 * c16;
+  const int u = blockIdx.y;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4), c16 = threadIdx.x & 15;
   if (row >= m) return;
   const int64_t ro = (int64_t)u * dv.Mcap + row;
-  const float *gam = dv.gamma ? dv.gamma + h * D : kOnes, *bet = dv.beta ? dv.beta + h * D : kZeros;
-  float ga[8], be[8];
   double sk[8];
   float sv[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    ga[e] = gam[ch0 + e];
-    be[e] = bet[ch0 + e];
-    sk[e] = dv.sK[ro * D + ch0 + e];
-    sv[e] = dv.sV[ro * D + ch0 + e];
-  }
-  write_readout16(dv, slot, ro, ch0, sk, sv, dv.rho[ro], ga, be);
+  load_sums(dv, ro, c16, sk, sv);
+  store_readout16(dv, slot, ro, c16, normalised16(dv, sk, ln_params(dv, u), c16), sv, dv.rho[ro]);
 }
 
 constexpr size_t kLdsWide = 160 * 1024, kLdsNarrow = 96 * 1024;
 bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
+constexpr int kGatherLeast = 32;   // tokens: the fresh tile's size
+// K-hat tiles a workgroup keeps in LDS for a whole run, 0 when they do not fit beside the rest
+int resident_tiles(const Dev &dv, int NW, int split, size_t limit) {
+  const int own = own_tiles_most(dv.Mcap, split);
+  const size_t rest = lds_fresh(NW, dv.C, own) + (size_t)kGatherLeast * kTokenBytes;
+  return own <= 2 * stage_tiles(NW) && rest + (size_t)own * kTileBytes <= limit ? own : 0;
+}
+// Tokens the scratch holds: with resident tiles twice the number expected per workgroup as far as the
+// limit goes; otherwise what the ring has room for.
+int gather_tokens_most(const Dev &dv, int NW, int split, size_t limit) {
+  const int kept = resident_tiles(dv, NW, split, limit);
+  if (!kept) return 2 * stage_tiles(NW) * kTileBytes / kTokenBytes;
+  const size_t rest = lds_fresh(NW, dv.C, own_tiles_most(dv.Mcap, split)) + (size_t)kept * kTileBytes;
+  const int room = (int)((limit - rest) / kTokenBytes) / 4 * 4, want = 2 * dv.C / split;
+  const int g = room < want ? room : want;
+  return g > kGatherLeast ? g : kGatherLeast;
+}
+size_t lds_bytes(const Dev &dv, int NW, int split, size_t limit) {
+  return lds_fresh(NW, dv.C, own_tiles_most(dv.Mcap, split)) + (size_t)resident_tiles(dv, NW, split, limit) * kTileBytes +
+         (size_t)gather_tokens_most(dv, NW, split, limit) * kTokenBytes;
+}
 
 }  // namespace
 
 // The shapes this path takes: bf16, head_dim 128; blocks of 2^k * 32 tokens up to 1024 (the waves
 // that share a token group split a stage's tiles by a power of two); tables that fit LDS.
 bool fold_fused_fits(const Dev &dv, int split) {
-  if (!(dv.io == 1 && dv.d == kHeadDim && dv.C % 64 == 0 && dv.C <= 1024 && pow2(dv.C / 32))) return false;
+  if (!(dv.io == 1 && dv.d == kHeadDim && dv.C % 64 == 0 && dv.C <= kMaxBlock && pow2(dv.C / 32))) return false;
   if (!pow2(split) || split > kFoldMaxSplit || dv.Mcap >= 0xffff) return false;   // rows travel in 16 bits
-  return fold_lds(dv.C, dv.Mcap, 16, split).total <= kLdsWide && fold_lds(dv.C, dv.Mcap, 8, split).total <= kLdsNarrow;
+  return lds_bytes(dv, 16, split, kLdsWide) <= kLdsWide && lds_bytes(dv, 8, split, kLdsNarrow) <= kLdsNarrow;
 }
 
-size_t fold_exchange_bytes(const Dev &dv, int split) {
-  return split > 1 ? (size_t)dv.Ufull * 2 * split * 2 * dv.C * sizeof(unsigned long long) : 0;
+bool fold_fused_resident(const Dev &dv, int split, bool narrow) {
+  return fold_fused_fits(dv, split) && resident_tiles(dv, narrow ? 8 : 16, split, narrow ? kLdsNarrow : kLdsWide) > 0;
+}
+
+size_t fold_exchange_bytes(int64_t units, int C, int split) {
+  return split > 1 ? (size_t)units * 2 * split * 2 * C * sizeof(unsigned long long) : 0;
 }
 
 hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st) {
@@ -954,15 +1236,17 @@ hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run, bool narrow, hipStream_t st) {
-  if (run.n <= 0) return hipSuccess;
+hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run_, bool narrow, hipEvent_t done,
+                             hipStream_t st) {
+  if (run_.n <= 0) return hipSuccess;
   static const hipError_t attr16 = hipFuncSetAttribute((const void *)fold_fused_kernel<16>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsWide);
   static const hipError_t attr8 = hipFuncSetAttribute((const void *)fold_fused_kernel<8>,
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsNarrow);
   if (attr16 != hipSuccess) return attr16;
   if (attr8 != hipSuccess) return attr8;
-  const int split = run.split;
+  FoldRunArgs run = run_;
+  const int split = run.split, NW = narrow ? 8 : 16;
   if (split < 1 || (split > 1 && (!run.xtab || !run.err))) return hipErrorInvalidValue;
   if (split > 1) {
     // the unit's workgroups wait for each other: all of the grid must fit the chip at once (one
@@ -973,12 +1257,15 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
     if (e != hipSuccess) return e;
     if ((int64_t)dv.U * split > cus) return hipErrorInvalidValue;
   }
+  const size_t limit = narrow ? kLdsNarrow : kLdsWide;
+  run.resident = resident_tiles(dv, NW, split, limit);
+  run.gather = gather_tokens_most(dv, NW, split, limit);
   FoldKernelArgs args{dv, src, run};
-  const unsigned grid = (unsigned)(dv.U * split);
-  if (narrow)
-    hipLaunchKernelGGL(fold_fused_kernel<8>, dim3(grid), dim3(512), fold_lds(dv.C, dv.Mcap, 8, split).total, st, args);
-  else
-    hipLaunchKernelGGL(fold_fused_kernel<16>, dim3(grid), dim3(1024), fold_lds(dv.C, dv.Mcap, 16, split).total, st, args);
+  void *argv[] = {&args};
+  const hipError_t e = hipExtLaunchKernel(narrow ? (const void *)fold_fused_kernel<8> : (const void *)fold_fused_kernel<16>,
+                                          dim3((unsigned)(dv.U * split)), dim3(64 * NW), argv,
+                                          lds_bytes(dv, NW, split, limit), st, nullptr, done, 0);
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 // schedule (integer replay of the paper's budget rule) and the per-chunk launch sequence.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -19,6 +20,11 @@ using kvm::Dev;
 using kvm::Src;
 
 struct kvm_state {
+  const uint64_t number = next_number();   // tells the states of a process apart, also those of different times
+  static uint64_t next_number() {
+    static std::atomic<uint64_t> n{0};
+    return ++n;
+  }
   kvm_config cfg;
   std::vector<int64_t> table;
   Dev dv;
@@ -29,7 +35,6 @@ struct kvm_state {
   float *trace_score = nullptr;
   int64_t trace_max = 0;
   bool mfma = false;  // bf16, d = 128, C % 64 == 0: matrix-core kernels
-  bool fused = false; // folds run as one launch per run of folds (fold_fused.hip)
   // a unit's rows shared among several workgroups of that launch: the exchange table (part of the
   // state buffer), whether it has been zeroed, the next exchange number (never reused: the
   // table's entries are told apart by it), and the error word the kernel raises when a wait for a
@@ -47,6 +52,7 @@ struct kvm_state {
   int64_t inplace = 0;  // folds done in place so far: version v lives in slot (v - inplace) mod NS
   static constexpr int kMaxChains = 2;
   hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};
+  hipEvent_t fold_done = nullptr;       // of the latest fold on a caller's stream whose workgroups wait for each other
   std::vector<hipEvent_t> sync_events;  // untimed events, reused call after call
   size_t sync_used = 0;
   // optional kernel timing: (start, stop, class) event pairs, events reused across reads
@@ -148,7 +154,7 @@ int64_t capacity_rows(const kvm_config &c, const std::vector<int64_t> &table, in
 }
 
 struct Layout {
-  size_t sK, sV, rho, w, n, khat, vhat, winK, winV, winG, kbar, score, pi, app, xtab, xtab_bytes, part_acc, part_ml, part_cnt,
+  size_t sK, sV, rho, w, n, khat, vhat, winK, winV, winG, kbar, score, pi, app, xtab, xtab_bytes, part_cnt,
       creator, total;
 };
 
@@ -158,7 +164,15 @@ bool use_mfma(const kvm_config &c) {
 // Chunks per prefill attention launch.  The matrix-core path launches groups of chunks so that
 // a launch has thousands of workgroups; the generic path launches chunk by chunk.
 int group_of(const kvm_config &c) { return use_mfma(c) ? 8 : 1; }
+static_assert(2 * kvm::kFoldMaxSteps <= 8, "two runs of one-launch folds have their memory keys in a group's scratch");
 constexpr int kClusterBelowUnits = 256;  // compute units of the chip this library is written for
+// Workgroups that may share a unit's rows (a power of two): at most kFoldMaxSplit, one 64-row tile each, and
+// a compute unit for every one of them, because they wait for each other.
+int most_split(int64_t U, int64_t Mcap) {
+  int n = 1;
+  while (2 * n <= kvm::kFoldMaxSplit && U * 2 * n <= kClusterBelowUnits && Mcap / 64 >= 2 * n) n *= 2;
+  return n;
+}
 
 Layout layout_of(const kvm_config &c, int64_t Mcap) {
   const size_t U = (size_t)c.batch * c.n_kv_heads, d = c.head_dim, C = c.chunk_len;
@@ -185,14 +199,10 @@ Layout layout_of(const kvm_config &c, int64_t Mcap) {
   l.score = take(U * C * 8);
   l.pi = take(U * C * 4);
   l.app = take(U * C * 4);
-  // exchange table of the one-launch fold when a unit's rows are shared among workgroups: only
-  // states with fewer units than the chip has compute units ever do that
-  l.xtab_bytes = use_mfma(c) && U < (size_t)kClusterBelowUnits
-                     ? U * 2 * (size_t)kvm::kFoldMaxSplit * 2 * C * sizeof(unsigned long long) : 0;
+  // exchange table of the one-launch fold when a unit's rows are shared among workgroups
+  l.xtab_bytes = use_mfma(c) ? kvm::fold_exchange_bytes((int64_t)U, (int)C, most_split((int64_t)U, Mcap)) : 0;
   l.xtab = take(l.xtab_bytes);
-  l.part_acc = take((size_t)kvm::kSplitWorkgroups * 4 * d * 4);
-  l.part_ml = take((size_t)kvm::kSplitWorkgroups * 4 * 8);
-  l.part_cnt = take((size_t)kvm::kSplitWorkgroups * 4);
+  l.part_cnt = take((size_t)kvm::kShareGroups * 4);
   l.creator = take(U * C * 4);
   l.total = o;
   return l;
@@ -216,8 +226,7 @@ void bind(Dev &dv, const kvm_config &c, void *buf, int64_t Mcap) {
   dv.pi = (int32_t *)(p + l.pi);
   dv.app = (int32_t *)(p + l.app);
   dv.creator = (int32_t *)(p + l.creator);
-  dv.part_acc = (float *)(p + l.part_acc);
-  dv.part_ml = (float2 *)(p + l.part_ml);
+  dv.kbar_bytes = (int64_t)group_of(c) * c.batch * c.n_kv_heads * c.chunk_len * c.head_dim * (int64_t)esize(c.io_dtype);
   dv.part_cnt = (unsigned *)(p + l.part_cnt);
   dv.gamma = c.ln_gamma;
   dv.beta = c.ln_beta;
@@ -328,7 +337,7 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
       HIP_TRY(kvm::launch_score_mfma(dv, so, 0, (int)m, true, stream));
     else
       HIP_TRY(kvm::launch_score(dv, so, 0, (int)m, true, stream));
-    if (kvm::append_fits(dv, n_app)) {
+    if (kvm::append_fits(dv.C, n_app)) {
       HIP_TRY(kvm::launch_append(dv, src, (int)m, n_app, sn, stream));
     } else if (n_app > 0) {
       // new rows first, so that the remaining tokens can be scored against them too
@@ -363,33 +372,83 @@ int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hip
   return KVM_OK;
 }
 
-// The one-launch fold path (a run of folds in one kernel, one workgroup per unit; bf16, d = 128
-// states whose tables fit LDS) is taken when there are at least as many units as compute units,
-// so that one workgroup per unit fills the chip (measured on 256 units of the paper's benchmark
-// shape: 17 % off the prefill with a growing state, 2 % with 256 rows), or when kvm_debug_set asks
-// for it.  With fewer units one compute unit per unit of the state is slower than launches over
-// the whole chip by more than the launch boundaries cost (64 units: 13-15 ms against 11 ms).
+// The one-launch fold path (a run of folds in one kernel; bf16, d = 128 states whose tables fit LDS)
+// is taken when there are at least as many units as compute units, so that one workgroup per unit
+// fills the chip (measured on 256 units of the paper's benchmark shape: 17 % off the prefill with
+// a growing state, 2 % with 256 rows), and with fewer units when a unit's rows can be shared among
+// several workgroups that keep their normalised keys in LDS from fold to fold (32 units, 300 rows,
+// 256-token blocks: 8.4 ms for 65536 tokens against 10.6 with a kernel per step).  Otherwise a fold
+// is a kernel per step: with tiles that stream the shared launch lost (64 units of 1024 rows, 4
+// workgroups each: 13 ms for 32768 tokens against 10.9); so it is when kvm_debug_set asks for it.
 constexpr int kFusedMinUnits = 256;
-// With fewer units a unit's rows can be shared among `split` workgroups of the launch (a power of
-// two, at most kFoldMaxSplit; units x split workgroups must be resident together, one per compute
-// unit): 0 = the kernel-per-step path.
+// Workgroups per unit on that path: 0 = a kernel per step.
 int fold_split(const kvm_state *st) {
-  if (!st->fused) return 0;
+  if (!st->mfma) return 0;
   const int path = st->dbg[KVM_DEBUG_FOLD_PATH];
   if (path == 2) return 0;
-  const int U = st->dv.U;
-  int want = st->dbg[KVM_DEBUG_FOLD_SPLIT];
-  if (want == 0) {
-    if (U >= kFusedMinUnits) return 1;
-    if (path != 1) return 0;
-    want = 1;
-  }
-  if (want == 1) return 1;
-  const bool ok = (want == 2 || want == 4 || want == 8) && st->xtab && (int64_t)U * want <= kClusterBelowUnits &&
-                  st->dv.Mcap / 64 >= want && kvm::fold_fused_fits(st->dv, want);
-  return ok ? want : 1;
+  const int U = st->dv.U, forced = st->dbg[KVM_DEBUG_FOLD_SPLIT];
+  const int whole = kvm::fold_fused_fits(st->dv, 1) ? 1 : 0;
+  const int most = most_split(U, st->dv.Mcap);
+  auto can_share = [&](int n) { return n > 1 && n <= most && kvm::fold_fused_fits(st->dv, n); };
+  if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
+  if (path == 1 || U >= kFusedMinUnits) return whole;
+  return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
 bool use_fused(const kvm_state *st) { return fold_split(st) > 0; }
+// The same for folds enqueued on `stream`: workgroups that wait for each other are ordered against
+// other streams by an event, which a stream that is being captured into a graph cannot take part in;
+// captured folds are a kernel per step.
+int use_fused_on(const kvm_state *st, hipStream_t stream, bool *fused) {
+  *fused = use_fused(st);
+  if (*fused && fold_split(st) > 1) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap));
+    if (cap != hipStreamCaptureStatusNone) *fused = false;
+  }
+  return KVM_OK;
+}
+
+// Launches whose workgroups wait for each other run one after the other on a device, whichever
+// state, stream or thread of the process they come from: two of them on the chip at once could
+// each hold compute units that the other one's missing workgroups need.  The event of the latest one
+// per device; a state's own launches are in order already.
+struct WaitingLaunches {
+  std::mutex lock;
+  hipEvent_t last = nullptr, left = nullptr;   // left: `last` when the state it came from is gone
+  uint64_t by = 0;                             // number of the state that launched last
+};
+constexpr int kMaxDevices = 64;
+WaitingLaunches g_waiting[kMaxDevices];
+// done: an event of the state's, which stands for the end of this launch afterwards
+int launch_run(const kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
+               hipStream_t stream) {
+  if (run.split <= 1) {
+    HIP_TRY(kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream));
+    return KVM_OK;
+  }
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) return KVM_ERR_ARG;
+  WaitingLaunches &w = g_waiting[dev];
+  std::lock_guard<std::mutex> hold(w.lock);
+  if (w.last && w.by != st->number) HIP_TRY(hipStreamWaitEvent(stream, w.last, 0));
+  HIP_TRY(kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream));
+  w.last = done;
+  w.by = st->number;
+  return KVM_OK;
+}
+// A state's events are about to be destroyed: one that others may still have to wait for is kept
+// (at most one per device).
+hipEvent_t keep_waiting_event(const kvm_state *st) {
+  hipEvent_t kept = nullptr;
+  for (WaitingLaunches &w : g_waiting) {
+    std::lock_guard<std::mutex> hold(w.lock);
+    if (w.by != st->number || w.last == w.left) continue;
+    if (w.left) (void)hipEventDestroy(w.left);
+    w.left = kept = w.last;
+  }
+  return kept;
+}
 
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ull;
@@ -400,8 +459,8 @@ __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, 
 // it must not count on it having run.
 int clean_shares(kvm_state *st, hipStream_t stream) {
   if (st->part_clean) return KVM_OK;
-  hipLaunchKernelGGL(zero_words_kernel, dim3(2), dim3(256), 0, stream, (unsigned long long *)st->dv.part_cnt,
-                     (size_t)kvm::kSplitWorkgroups / 2);
+  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, stream, (unsigned long long *)st->dv.part_cnt,
+                     (size_t)kvm::kShareGroups / 2);
   HIP_TRY(hipGetLastError());
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(stream, &cap));
@@ -438,18 +497,14 @@ int fused_run(kvm_state *st, bool in_place, hipStream_t stream, kvm::FoldRunArgs
   *out = run;
   return KVM_OK;
 }
-// The exchange numbers of one fold (first scoring pass, and the second one when some but not all
-// of the block is appended): consecutive, never 0 in their low 16 bits.
-uint32_t take_exchanges(kvm_state *st, int64_t m, int64_t m_after) {
+// The exchange number of a fold (none is used up when the whole block is appended): consecutive,
+// never 0 in its low 16 bits.
+uint32_t take_exchange(kvm_state *st, int64_t m, int64_t m_after) {
   const int64_t n_app = m_after - m;
-  const uint32_t need = n_app == st->dv.C ? 0u : n_app > 0 ? 2u : 1u;
-  if (((st->xchg & 0xffffu) == 0u) || (need == 2u && ((st->xchg + 1u) & 0xffffu) == 0u)) {
-    // skip the number whose tag would be 0, keeping the parity sequence strictly alternating
-    st->xchg += 2u;
-  }
-  const uint32_t first = st->xchg;
-  st->xchg += need;
-  return first;
+  if ((st->xchg & 0xffffu) == 0u) st->xchg += 2u;   // skip the tag 0, keeping the parities alternating
+  const uint32_t num = st->xchg;
+  st->xchg += n_app == st->dv.C ? 0u : 1u;
+  return num;
 }
 int cluster_error(const kvm_state *st) {
   if (st->xerr_host && *(volatile int32_t *)st->xerr_host != 0) {
@@ -469,17 +524,22 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
   const Dev &dv = st->dv;
   const int so = slot_of(st, st->folds), sn = in_place ? so : slot_of(st, st->folds + 1);
   const size_t ntok = (size_t)dv.U * dv.C;
-  if (use_fused(st)) {
+  bool fused;
+  int rc_run = use_fused_on(st, stream, &fused);
+  if (rc_run != KVM_OK) return rc_run;
+  if (fused) {
     kvm::FoldRunArgs run;
-    const int rc_run = fused_run(st, in_place, stream, &run);
+    rc_run = fused_run(st, in_place, stream, &run);
     if (rc_run != KVM_OK) return rc_run;
     run.n = 1;
     run.s[0] = {(int32_t)m, (int32_t)m_after, so, sn, 0, st->folds < st->trace_max ? (int32_t)st->folds : -1, 0,
-                take_exchanges(st, m, m_after), 0u};
+                take_exchange(st, m, m_after), 0u};
     HIP_TRY(kvm::launch_memkey(dv, src, 1, stream));
     // a fold of its own (decode, the fold entry point, the chunk-by-chunk schedule): the narrow
     // workgroup, two to a compute unit, unless asked otherwise (measured 3 % ahead of the wide one)
-    HIP_TRY(kvm::launch_fold_fused(dv, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, stream));
+    if (run.split > 1 && !st->fold_done) HIP_TRY(hipEventCreateWithFlags(&st->fold_done, hipEventDisableTiming));
+    rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, run.split > 1 ? st->fold_done : nullptr, stream);
+    if (rc_run != KVM_OK) return rc_run;
   } else {
     int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, stream);
     if (rc != KVM_OK) return rc;
@@ -722,7 +782,6 @@ int kvm_state_init(kvm_state **out, const kvm_config *cfg, void *dev_buf, size_t
     st->xtab_clean = false;
   }
   st->mfma = use_mfma(*cfg);
-  st->fused = st->mfma && kvm::fold_fused_fits(st->dv);
   st->group = group_of(*cfg);
   *out = st;
   return KVM_OK;
@@ -735,7 +794,10 @@ int kvm_state_destroy(kvm_state *st) {
       (void)hipEventDestroy(sp.b);
     }
     for (auto e : st->free_events) (void)hipEventDestroy(e);
-    for (auto e : st->sync_events) (void)hipEventDestroy(e);
+    const hipEvent_t kept = keep_waiting_event(st);
+    for (auto e : st->sync_events)
+      if (e != kept) (void)hipEventDestroy(e);
+    if (st->fold_done && st->fold_done != kept) (void)hipEventDestroy(st->fold_done);
     for (hipStream_t fs : st->fold_streams)
       if (fs) (void)hipStreamDestroy(fs);
     if (st->xerr_host) (void)hipHostFree(st->xerr_host);
@@ -908,6 +970,11 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // whose chains run side by side on streams of their own (units are independent).  Two, not
   // more: with four chains the step was measured 40 % to 100 % slower, with four, eight and
   // sixteen hardware queues alike.
+  bool fused_folds;
+  {
+    const int rc = use_fused_on(st, stream, &fused_folds);
+    if (rc != KVM_OK) return rc;
+  }
   int n_chains = 1;
   {
     int64_t m_max = 0;
@@ -916,7 +983,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     if (fold_mb < 96.0 && dv.B % 2 == 0) n_chains = 2;
     const int forced = st->dbg[KVM_DEBUG_FOLD_CHAINS];  // 1 or 2: for comparisons
     if ((forced == 1 || forced == 2) && dv.B % forced == 0) n_chains = forced;
-    if (use_fused(st)) n_chains = 1;  // one workgroup per unit already: nothing to split
+    if (fused_folds) n_chains = 1;  // one launch for all units: nothing to split
   }
   // The one-launch folds of this schedule take the wide workgroup (16 waves, one per compute
   // unit) unless asked otherwise: measured 7 % to 11 % ahead of the narrow one beside attention.
@@ -926,10 +993,13 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   hipStream_t fstream[kvm_state::kMaxChains];
   Dev cdv[kvm_state::kMaxChains];
   const int cb = dv.B / n_chains;  // sequences per chain
-  for (int c2 = 0; c2 < n_chains; ++c2) {
+  // Streams of the library: one per chain; the one-launch folds have a second one on which the
+  // memory keys of a run, which depend on k alone, are computed while the run before it folds.
+  const int n_streams = fused_folds ? 2 : n_chains;
+  for (int c2 = 0; c2 < n_streams; ++c2) {
     if (!st->fold_streams[c2]) HIP_TRY(hipStreamCreateWithFlags(&st->fold_streams[c2], hipStreamNonBlocking));
     fstream[c2] = st->fold_streams[c2];
-    cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
+    if (c2 < n_chains) cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
   }
   // From here on work is forked onto the fold streams.  Whatever happens, the caller's stream
   // waits for them before the call returns: they may still be reading the caller's k, v and gate.
@@ -939,12 +1009,14 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   hipEvent_t ev;
   HIP_TRY(next_sync_event(st, &ev));
   HIP_TRY(hipEventRecord(ev, stream));
-  for (int c2 = 0; c2 < n_chains; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], ev, 0));
+  for (int c2 = 0; c2 < n_streams; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], ev, 0));
   const int G = st->group;
   const int n_chunks = (int)plan.size();
   int next_fold = 0;                 // folds of chunks < next_fold are enqueued
   hipEvent_t last_fold_ev[kvm_state::kMaxChains] = {nullptr, nullptr};
   hipEvent_t last_att_ev = nullptr;
+  int runs = 0;                                      // one-launch runs enqueued
+  hipEvent_t keys_read_ev[2] = {nullptr, nullptr};   // the run that reads this half of the key scratch is done
   auto wait_for_folds = [&]() -> int {
     for (int c2 = 0; c2 < n_chains; ++c2)
       if (last_fold_ev[c2]) HIP_TRY(hipStreamWaitEvent(stream, last_fold_ev[c2], 0));
@@ -952,7 +1024,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   };
   auto enqueue_folds_through = [&](int last_chunk) -> int {
     if (st->isolate && last_att_ev)
-      for (int c2 = 0; c2 < n_chains; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], last_att_ev, 0));
+      for (int c2 = 0; c2 < n_streams; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], last_att_ev, 0));
     while (next_fold <= last_chunk && next_fold < n_chunks) {
       if (!plan[next_fold].folds) {
         ++next_fold;
@@ -962,7 +1034,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       // keys are computed by one launch (blocks taken from the ring go one at a time)
       const int64_t lo0 = plan[next_fold].s + C - L;
       int run = 1;
-      const int run_cap = use_fused(st) && G > kvm::kFoldMaxSteps ? kvm::kFoldMaxSteps : G;
+      const int run_cap = fused_folds ? kvm::kFoldMaxSteps : G;
       if (lo0 >= t0)
         while (run < run_cap && next_fold + run <= last_chunk && next_fold + run < n_chunks &&
                plan[next_fold + run].folds)
@@ -982,7 +1054,10 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           bool seen = e == nullptr;
           for (int k2 = 0; k2 < n_waited && !seen; ++k2) seen = waited[k2] == e;
           if (!seen) {
-            for (int c2 = 0; c2 < n_chains; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], e, 0));
+            if (fused_folds)   // (the folds wait for the memory keys anyway: no second wait in the chain)
+              HIP_TRY(hipStreamWaitEvent(fstream[1], e, 0));
+            else
+              for (int c2 = 0; c2 < n_chains; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], e, 0));
             waited[n_waited++] = e;
           }
         }
@@ -1005,22 +1080,35 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           m = steps[i].m_after;
         }
       }
-      if (use_fused(st)) {
-        ProfileSpan span(st, 1, fstream[0], run);
-        kvm::FoldRunArgs fr;
-        const int rc_run = fused_run(st, false, fstream[0], &fr);
-        if (rc_run != KVM_OK) return rc_run;
-        fr.n = run;
-        for (int i = 0; i < run; ++i) {
-          const int64_t lo = plan[next_fold + i].s + C - L;
-          const int64_t fold_no = st->folds + i;
-          fr.s[i] = {(int32_t)steps[i].m, (int32_t)steps[i].m_after, steps[i].so, steps[i].sn,
-                     batched ? lo - lo0 : 0, fold_no < st->trace_max ? (int32_t)fold_no : -1, i,
-                     take_exchanges(st, steps[i].m, steps[i].m_after), 0u};
-        }
+      if (fused_folds) {
         const Src fsrc = batched ? advance(in, lo0 - t0, es) : advance(ring, lo0 % L, es);
-        HIP_TRY(kvm::launch_memkey(dv, fsrc, run, fstream[0]));
-        HIP_TRY(kvm::launch_fold_fused(dv, fsrc, fr, narrow_folds, fstream[0]));
+        const int half = runs++ & 1, slab0 = half * kvm::kFoldMaxSteps;
+        Dev kdv = dv;
+        kdv.kbar = (char *)dv.kbar + (size_t)slab0 * dv.Ufull * C * d * es;
+        if (keys_read_ev[half]) HIP_TRY(hipStreamWaitEvent(fstream[1], keys_read_ev[half], 0));
+        HIP_TRY(kvm::launch_memkey(kdv, fsrc, run, fstream[1]));
+        hipEvent_t keys_ev;
+        HIP_TRY(next_sync_event(st, &keys_ev));
+        HIP_TRY(hipEventRecord(keys_ev, fstream[1]));
+        HIP_TRY(hipStreamWaitEvent(fstream[0], keys_ev, 0));
+        {
+          ProfileSpan span(st, 1, fstream[0], run);
+          kvm::FoldRunArgs fr;
+          int rc_run = fused_run(st, false, fstream[0], &fr);
+          if (rc_run != KVM_OK) return rc_run;
+          fr.n = run;
+          for (int i = 0; i < run; ++i) {
+            const int64_t lo = plan[next_fold + i].s + C - L;
+            const int64_t fold_no = st->folds + i;
+            fr.s[i] = {(int32_t)steps[i].m, (int32_t)steps[i].m_after, steps[i].so, steps[i].sn,
+                       batched ? lo - lo0 : 0, fold_no < st->trace_max ? (int32_t)fold_no : -1, slab0 + i,
+                       take_exchange(st, steps[i].m, steps[i].m_after), 0u};
+          }
+          HIP_TRY(next_sync_event(st, &last_fold_ev[0]));
+          rc_run = launch_run(st, fsrc, fr, narrow_folds, last_fold_ev[0], fstream[0]);
+          if (rc_run != KVM_OK) return rc_run;
+        }
+        keys_read_ev[half] = last_fold_ev[0];
       } else
       for (int c2 = 0; c2 < n_chains; ++c2) {
         // the timing bracket goes on the first chain only (the chains run side by side)
@@ -1040,7 +1128,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       }
       st->m = steps[run - 1].m_after;
       st->folds += run;
-      for (int c2 = 0; c2 < n_chains; ++c2) {
+      for (int c2 = 0; c2 < n_chains && !fused_folds; ++c2) {
         HIP_TRY(next_sync_event(st, &last_fold_ev[c2]));
         HIP_TRY(hipEventRecord(last_fold_ev[c2], fstream[c2]));
       }
@@ -1104,7 +1192,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   const int rc_forked = forked();
   if (rc_forked != KVM_OK) {
     // best effort (the runtime has already failed once): join the fold streams back
-    for (int c2 = 0; c2 < n_chains; ++c2) {
+    for (int c2 = 0; c2 < n_streams; ++c2) {
       hipEvent_t e = nullptr;
       if (next_sync_event(st, &e) == hipSuccess && hipEventRecord(e, fstream[c2]) == hipSuccess)
         (void)hipStreamWaitEvent(stream, e, 0);
@@ -1518,7 +1606,6 @@ int kvm_state_grow(kvm_state *st, void *new_buf, size_t new_bytes, int64_t new_m
     st->xtab_bytes = l.xtab_bytes;
     st->xtab_clean = false;
   }
-  st->fused = st->mfma && kvm::fold_fused_fits(st->dv);
   return KVM_OK;
 }
 

@@ -42,11 +42,10 @@ struct Dev {
   int32_t *pi;       // [U, C]    row the token goes to
   int32_t *app;      // [U, C]    rank among appended tokens, or -1
   int32_t *creator;  // [U, C]    token that creates new row number a
-  // decode scratch: partial results of workgroups that share one sequence's keys (attn_rows.hip),
-  // for up to kSplitWorkgroups of them, and a counter per group of them (zero between launches)
-  float *part_acc;     // [workgroup][4 heads][d]
-  float2 *part_ml;     // [workgroup][4 heads]
-  unsigned *part_cnt;  // [workgroup]
+  // decode: the memory-key scratch, idle while a step attends, also takes the partial results of
+  // workgroups that share one sequence's keys (attn_rows.hip), as many as it has room for
+  int64_t kbar_bytes;
+  unsigned *part_cnt;  // [kShareGroups] a counter per group of them, zero between launches
   // parameters
   const float *gamma, *beta;          // [H_kv, d] or null
   const float *tau_state, *tau_bswa;  // [H_q] or null
@@ -83,7 +82,10 @@ hipError_t launch_accum(const Dev &dv, const Src &src, int m_before, int m_after
                         bool do_create, bool do_merge, bool do_copy, bool check_app, int slot_old,
                         int slot_new, hipStream_t st);
 // selection + creation + second scoring pass of a small append, one launch
-bool append_fits(const Dev &dv, int n_app);
+constexpr int kAppendMax = 16;
+__host__ __device__ inline bool append_fits(int C, int n_app) {
+  return n_app > 0 && n_app <= kAppendMax && C % 2 == 0 && C <= 256;
+}
 hipError_t launch_append(const Dev &dv, const Src &src, int m, int n_app, int slot_new, hipStream_t st);
 // the merge of a small fold in a prefill: token-centred merge into slot_new + copies of untouched rows
 hipError_t launch_merge_copy(const Dev &dv, const Src &src, bool check_app, int slot_old, int slot_new,
@@ -93,20 +95,20 @@ hipError_t launch_refresh(const Dev &dv, int m, int slot, hipStream_t st);
 hipError_t launch_ring_copy(const Dev &dv, const Src &src, int64_t src_t0, int64_t p0, int64_t p1,
                             hipStream_t st);
 // fold_fused.hip (bf16, d = 128): a run of up to kFoldMaxSteps consecutive folds in one launch,
-// one workgroup per unit.  Step i folds the block whose first token is src's token s[i].tok and
+// run.split workgroups per unit.  Step i folds the block whose first token is src's token s[i].tok and
 // whose memory keys are in slab s[i].kbar_block of the scratch (launch_memkey), from s[i].m to
 // s[i].m_after rows, reading readout slot s[i].so and writing slot s[i].sn (the same slot when
 // in_place; otherwise untouched rows are copied over).  trace >= 0: the fold's assignments and
 // scores also go to trace_assign / trace_score at that fold index (trace_stride = tokens of one
 // fold over all units).  narrow: the 8-wave workgroup that fits beside an attention workgroup on
 // a compute unit; otherwise 16 waves and the unit to itself.
-constexpr int kFoldMaxSteps = 8;
-constexpr int kFoldMaxSplit = 8;   // workgroups that may share a unit's rows
+constexpr int kFoldMaxSteps = 4;   // half of a group: the other half of the key scratch is the next run's
+constexpr int kFoldMaxSplit = 16;  // workgroups that may share a unit's rows
 struct FoldStep {
   int32_t m, m_after, so, sn;
   int64_t tok;
   int32_t trace, kbar_block;
-  uint32_t xnum, pad;   // number of the fold's first exchange among the unit's workgroups (split > 1)
+  uint32_t xnum, pad;   // number of the fold's exchange among the unit's workgroups (split > 1)
 };
 struct FoldRunArgs {
   int32_t n, in_place;
@@ -116,13 +118,20 @@ struct FoldRunArgs {
   int64_t trace_stride;
   int32_t split;               // workgroups per unit (a power of two); 1: none of the next two is used
   unsigned long long *xtab;    // the exchange table, fold_exchange_bytes() of zeroed device memory
+  int32_t resident;            // (set by the launch) K-hat tiles a workgroup keeps in LDS, 0: they stream through a ring
+  int32_t gather;              // (likewise) merging tokens the LDS scratch holds
   int32_t *err;                // set to 1 when a wait for a sibling workgroup ran into its time limit
 };
 bool fold_fused_fits(const Dev &dv, int split = 1);
-size_t fold_exchange_bytes(const Dev &dv, int split);
+// whether each of a unit's `split` workgroups keeps its normalised keys in LDS for a whole run
+bool fold_fused_resident(const Dev &dv, int split, bool narrow);
+size_t fold_exchange_bytes(int64_t units, int C, int split);
 // readout rows [0, m) recomputed from the sums with the one-launch path's arithmetic
 hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st);
-hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run, bool narrow, hipStream_t st);
+// done: an event that stands for the end of the launch (the kernel's own completion signal: nothing more is put on the
+// stream), or null
+hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run, bool narrow, hipEvent_t done,
+                             hipStream_t st);
 // score_mfma.hip (bf16, d = 128)
 hipError_t launch_score_mfma(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st);
 // attn_rows.hip

@@ -1,0 +1,147 @@
+"""A unit's state rows shared among several workgroups of the one-launch folds, against the kernel-per-step
+path, at the edges of what the shared launch takes: one 64-row tile per workgroup and four, tiles that
+stay in LDS and tiles that stream through it, blocks of 64 to 1024 tokens, more merging tokens per
+workgroup than its scratch holds, appends of 1, 16, 17, 64, 65 and all rows, sinks beyond the first
+tile, folds in place, a captured step, two threads at once.
+
+Assignments, counts, weights, key and value sums and normalised keys are equal to the bit (the same
+products added in the same order); the value readout is scaled by a root and a reciprocal that differ
+by an ulp of fp32 each between the paths, so its bf16 element differs by at most one: 2^-7 relative."""
+import threading
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def kit():
+    import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import binding, synth
+    return pkg, binding, synth
+
+
+def make(sy, chunk, units, seq, budget, **kw):
+    kind = {"budget_fixed": budget} if isinstance(budget, int) else \
+        {"budget_kind": "table", "budget_table": budget} if isinstance(budget, tuple) else {"budget_kind": "sqrt"}
+    return sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=units, n_kv_heads=units, chunk_len=chunk, seq=seq,
+                     **kind, **kw)
+
+
+def run(w, knobs, decode_tail=0):
+    pkg, binding, sy = kit()
+    q, k, v = sy.make_qkv(w, DEV)
+    p = sy.make_params(w, DEV, plain=False)
+    st = pkg.state_for(w, device=DEV, **p)
+    for knob, value in knobs.items():
+        st.debug_set(knob, value)
+    assign, _ = st.trace(w.seq // w.chunk_len + 1)
+    n = w.seq - decode_tail
+    cut = lambda x, lo, hi: None if x is None else x[:, lo:hi].contiguous()
+    st.prefill(cut(q, 0, n), cut(k, 0, n), cut(v, 0, n), cut(p["gate"], 0, n))
+    for t in range(n, w.seq):
+        one = lambda x: None if x is None else x[:, t].contiguous()
+        st.decode(one(q), one(k), one(v), one(p["gate"]))
+    torch.cuda.synchronize()
+    return st, assign[:st.folds].clone(), st.export()
+
+
+def same(a, b):
+    assert a[0].rows == b[0].rows and a[0].folds == b[0].folds
+    assert torch.equal(a[1], b[1]), "assignments"
+    for key in ("sK", "sV", "n", "w", "khat"):
+        assert torch.equal(a[2][key], b[2][key]), key
+    torch.testing.assert_close(a[2]["vhat"].float(), b[2]["vhat"].float(), rtol=2 ** -7, atol=1e-6)
+
+
+STEP = (64, 64, 80, 81, 98, 162, 227, 227, 355, 355)   # appends of 16, 1, 17, 64, 65, 0, 128 rows at 128-token blocks
+CASES = {   # chunk, units, tokens, budget, other fields, forced split (0: the library's choice)
+    "one tile each": (64, 2, 64 * 24, 1024, {}, 0),
+    "four tiles each": (256, 64, 256 * 8, 1024, {}, 0),
+    "sixteen workgroups": (256, 1, 256 * 9, 1024, {}, 16),
+    "tiles that stream": (256, 2, 256 * 8, 1024, {}, 2),
+    "long block": (1024, 2, 1024 * 4, 1024, {}, 0),
+    "scratch too small": (512, 1, 512 * 5 + 5, 512, {}, 2),
+    "appends": (128, 3, 128 * 12, tuple(128 + x for x in STEP), {}, 0),
+    "appends, long block": (512, 2, 512 * 8, tuple(512 + x for x in STEP), {}, 0),
+    "growing": (256, 4, 256 * 24, None, {}, 0),
+    "sinks": (256, 2, 256 * 8, 512, {"n_sink": 130}, 0),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_shared_rows_agree_with_a_kernel_per_step(case):
+    _, b, sy = kit()
+    chunk, units, seq, budget, kw, split = CASES[case]
+    w = make(sy, chunk, units, seq, budget, **kw)
+    knobs = {b.KVM_DEBUG_FOLD_SPLIT: split} if split else {}
+    got = run(w, knobs)
+    assert got[0].fold_path == 1
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
+
+
+@pytest.mark.parametrize("tail", [1, 128 + 3])
+def test_folds_in_place(tail):
+    _, b, sy = kit()
+    w = make(sy, 128, 2, 128 * 9, 512)
+    w = sy.shrink(w, seq=w.seq // 128 * 128)
+    same(run(w, {}, tail), run(w, {b.KVM_DEBUG_FOLD_PATH: 2}, tail))
+
+
+def test_captured_step():
+    """A step that folds, captured: the graph holds no launch that waits for other workgroups."""
+    pkg, b, sy = kit()
+    w = make(sy, 128, 2, 128 * 8, 512)
+    q, k, v = sy.make_qkv(w, DEV)
+    p = sy.make_params(w, DEV, plain=True)
+    n = w.seq - 1
+    res = []
+    for captured in (False, True):
+        st = pkg.state_for(w, device=DEV, **p)
+        st.prefill(q[:, :n - 127].contiguous(), k[:, :n - 127].contiguous(), v[:, :n - 127].contiguous())
+        one = lambda t: (q[:, t].contiguous(), k[:, t].contiguous(), v[:, t].contiguous())
+        for t in range(n - 127, n):
+            st.decode(*one(t))
+        args = one(n)
+        torch.cuda.synchronize()
+        if captured:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                y = st.decode(*args)
+            g.replay()
+        else:
+            y = st.decode(*args)
+        torch.cuda.synchronize()
+        res.append((st, torch.zeros(0), st.export(), y))
+    same(*res)
+    assert torch.equal(res[0][3], res[1][3])
+
+
+def test_two_threads():
+    """Two states driven from two threads on streams of their own: their launches take turns."""
+    pkg, b, sy = kit()
+    w = make(sy, 256, 16, 256 * 16, 1024)
+    q, k, v = sy.make_qkv(w, DEV)
+    want = run(sy.shrink(w), {b.KVM_DEBUG_FOLD_PATH: 2})
+    p = sy.make_params(w, DEV, plain=False)
+    torch.cuda.synchronize()
+    out = [None, None]
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(3):
+                st = pkg.state_for(w, device=DEV, **p)
+                st.prefill(q, k, v, p["gate"])
+                torch.cuda.current_stream().synchronize()
+            out[i] = (st, want[1], st.export())
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=60)
+    for o in out:
+        assert o is not None
+        same(o, want)
