@@ -33,9 +33,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kXcds = 8;  // accelerator dies, each with its own L2
 
-template <int NW>
+template <int NW, int D>
 __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint16_t *Ks, uint16_t *Vs) {
-  constexpr int D = kHeadDim;
+  static_assert((D == 128 || D == 64) && (D == 128 || NW == 4), "");
+  constexpr int kKs = D / 16, kNb = D / 32;      // channel steps of the first product, channel blocks of the second
+  constexpr int kTileE = kTileKeys * D;
+  constexpr bool kSplitP = D == 64;              // P as the sum of three bf16 numbers (see the kernel)
   constexpr int kTileQ = 32 * NW;
   constexpr int kVBufs = 2;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -77,13 +80,13 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
   const int m = a.m[ci];
 
   // Q^T fragments: query myq, channels 16*ks + 8*g .. +7
-  bf16x8 qreg[8];
+  bf16x8 qreg[kKs];
   {
     const int qc = myq < nq ? myq : nq - 1;
     const uint16_t *qrow =
         (const uint16_t *)a.q + b * a.q_b + ((int64_t)ci * dv.C + qc) * a.q_t + hq * a.q_h;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < kKs; ++ks) {
       Frag8 f;
       f.q = *reinterpret_cast<const uint4 *>(qrow + 16 * ks + 8 * g);
       qreg[ks] = f.v;
@@ -132,10 +135,26 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
 
   // Per-lane fragment offsets (elements) from the start of the K / V buffers.  K has two buffers
   // and its offsets flip after every tile; V buffers are addressed by tile number.
-  uint32_t koff[8], voff[2];
-  ktile_offsets(lane, koff);
-  vtile_offsets(lane, voff);
-  const DmaLane dl = dma_lane(lane);
+  uint32_t koff[kKs], voff[2];
+  const auto dl = [&] {
+    if constexpr (D == 128) {
+      ktile_offsets(lane, koff);
+      vtile_offsets(lane, voff);
+      return dma_lane(lane);
+    } else {
+      ktile_offsets64(lane, koff);
+      vtile_offsets64(lane, voff);
+      return dma_lane64(lane);
+    }
+  }();
+  auto kfrag = [&](const uint16_t *t, int blk, int ks) {
+    if constexpr (D == 128) return ktile_frag(t, koff, blk, ks);
+    else return ktile_frag64(t, koff, blk, ks);
+  };
+  auto vfrag = [&](const uint16_t *t, int dblk, int ks) {
+    if constexpr (D == 128) return vtile_frag(t, voff, dblk, ks);
+    else return vtile_frag64(t, voff, dblk, ks);
+  };
   const uint32_t ks_addr = lds_addr_of(Ks), vs_addr = lds_addr_of(Vs);
 
   struct TileSrc {
@@ -172,41 +191,52 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
   };
   auto issue_tile = [&](int it) {
     const TileSrc t = tile_src(it);
-    tile_dma<false, NW>(t.k, t.kst, t.valid, ks_addr + (uint32_t)(it & 1) * (kTileElems * 2), wave, dl);
-    tile_dma<true, NW>(t.v, t.vst, t.valid, vs_addr + (uint32_t)(it % kVBufs) * (kTileElems * 2), wave, dl);
+    const uint32_t k_at = ks_addr + (uint32_t)(it & 1) * (kTileE * 2), v_at = vs_addr + (uint32_t)(it % kVBufs) * (kTileE * 2);
+    if constexpr (D == 128) {
+      tile_dma<false, NW>(t.k, t.kst, t.valid, k_at, wave, dl);
+      tile_dma<true, NW>(t.v, t.vst, t.valid, v_at, wave, dl);
+    } else {
+      tile_dma64<false>(t.k, t.kst, t.valid, k_at, wave, dl);
+      tile_dma64<true>(t.v, t.vst, t.valid, v_at, wave, dl);
+    }
   };
 
-  f32x16 oacc[4];
+  f32x16 oacc[kNb];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < kNb; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[i][v] = 0.f;
   float m_run = -INFINITY, l_part = 0.f;
   Frag8 pb[4];  // P^T of the tile just scored, packed for the second product
+  [[maybe_unused]] Frag8 pl[kSplitP ? 4 : 1], pll[kSplitP ? 4 : 1];  // what the rounding of pb left, and of that
 
   // O^T += V^T . P^T for the tile whose P^T is in pb.  The first eight V^T fragments are asked
   // for ahead of the softmax (pv_fetch), so that their LDS latency is not waited for here.
   bf16x8 vf[8];
   auto pv_fetch = [&](auto parity) {
-    const uint16_t *Vt = Vs + decltype(parity)::value * kTileElems;
+    const uint16_t *Vt = Vs + decltype(parity)::value * kTileE;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) vf[i] = vtile_frag(Vt, voff, i & 3, i >> 2);
+    for (int i = 0; i < 8; ++i) vf[i] = vfrag(Vt, i % kNb, i / kNb);
   };
   auto do_pv = [&](auto parity) {
-    const uint16_t *Vt = Vs + decltype(parity)::value * kTileElems;
+    const uint16_t *Vt = Vs + decltype(parity)::value * kTileE;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int dblk = 0; dblk < 4; ++dblk) {
-        const int i = 4 * ks + dblk, slot = i & 7;
+      for (int dblk = 0; dblk < kNb; ++dblk) {
+        const int i = kNb * ks + dblk, slot = i & 7;
         oacc[dblk] = mfma32(vf[slot], pb[ks].v, oacc[dblk]);
-        if (i + 8 < 16) vf[slot] = vtile_frag(Vt, voff, dblk, ks + 2);
+        if constexpr (kSplitP) {
+          oacc[dblk] = mfma32(vf[slot], pl[ks].v, oacc[dblk]);
+          oacc[dblk] = mfma32(vf[slot], pll[ks].v, oacc[dblk]);
+        }
+        if (i + 8 < 4 * kNb) vf[slot] = vfrag(Vt, dblk, ks + 2);
       }
   };
 
   // S^T = K . Q^T and the online softmax for the tile in the current K buffer; leaves P^T in pb.
   auto do_qk_softmax = [&](bool is_state, int row0, int64_t p0, auto parity) {
-    const uint16_t *Kt = Ks + decltype(parity)::value * kTileElems;
+    const uint16_t *Kt = Ks + decltype(parity)::value * kTileE;
     const float scale = is_state ? c_state : c_bswa;
     const bool need_mask = is_state ? (m - row0 < kTileKeys) : (p0 + kTileKeys - 1 > cs + wq0);
     f32x16 sacc[2];
@@ -215,23 +245,25 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
     {
       bf16x8 kf[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) kf[i] = ktile_frag(Kt, koff, i & 1, i >> 1);
+      for (int i = 0; i < 8; ++i) kf[i] = kfrag(Kt, i & 1, i >> 1);
       const f32x16 zero = {0.f};
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < kKs; ++ks) {
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
           const int slot = (2 * ks + blk) & 7;
           sacc[blk] = mfma32(kf[slot], qreg[ks], ks == 0 ? zero : sacc[blk]);
-          if (ks + 4 < 8) kf[slot] = ktile_frag(Kt, koff, blk, ks + 4);
+          if (ks + 4 < kKs) kf[slot] = kfrag(Kt, blk, ks + 4);
         }
       }
       // pin that order: 8 LDS reads up front, then one read behind every matrix instruction
       __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+      if constexpr (kKs > 4) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        for (int i = 0; i < 8; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
     }
@@ -265,7 +297,7 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
       m_run = m_new;
       l_part *= alpha;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < kNb; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[i][v] *= alpha;
     }
@@ -283,8 +315,22 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        pb[ks].w[e] = pack_bf16(sacc[ks >> 1][(ks & 1) * 8 + 2 * e], sacc[ks >> 1][(ks & 1) * 8 + 2 * e + 1]);
-        l_part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pb[ks].w[e]), ones, l_part, false);
+        const float p0 = sacc[ks >> 1][(ks & 1) * 8 + 2 * e], p1 = sacc[ks >> 1][(ks & 1) * 8 + 2 * e + 1];
+        pb[ks].w[e] = pack_bf16(p0, p1);
+        if constexpr (kSplitP) {
+          auto rest = [](float x, float y, uint32_t w, float &rx, float &ry) {   // exact
+            rx = x - __uint_as_float(w << 16);
+            ry = y - __uint_as_float(w & 0xffff0000u);
+          };
+          float r0, r1;
+          rest(p0, p1, pb[ks].w[e], r0, r1);
+          pl[ks].w[e] = pack_bf16(r0, r1);
+          rest(r0, r1, pl[ks].w[e], r0, r1);
+          pll[ks].w[e] = pack_bf16(r0, r1);
+          l_part += p0 + p1;
+        } else {
+          l_part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pb[ks].w[e]), ones, l_part, false);
+        }
       }
   };
 
@@ -305,7 +351,7 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
       asm volatile("" ::: "memory");  // stays a (rarely taken) branch
       q_negated = !q_negated;
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < kKs; ++ks) {
         Frag8 f;
         f.v = qreg[ks];
 #pragma unroll
@@ -332,7 +378,7 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
     const float inv = 1.f / l;
     uint16_t *orow = (uint16_t *)a.out + b * a.o_b + ((int64_t)ci * dv.C + myq) * a.o_t + hq * a.o_h;
 #pragma unroll
-    for (int dblk = 0; dblk < 4; ++dblk)
+    for (int dblk = 0; dblk < kNb; ++dblk)
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
         const uint32_t lo = pack_bf16(oacc[dblk][4 * vq] * inv, oacc[dblk][4 * vq + 1] * inv);
@@ -348,7 +394,20 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
 __global__ __launch_bounds__(256, 2) void attn_mfma_kernel_q128(Dev dv, AttnArgs a) {
   __shared__ __attribute__((aligned(32768))) uint16_t Ks[2 * kTileElems];
   __shared__ __attribute__((aligned(1024))) uint16_t Vs[2 * kTileElems];
-  attn_body<4>(dv, a, Ks, Vs);
+  attn_body<4, 128>(dv, a, Ks, Vs);
+}
+
+// head_dim 64.  Probabilities enter the second product as three bf16 numbers, 3 x 8 bits = the 24 of an fp32
+// significand, and their sum is taken in fp32: the row kernel, which these states used for prompts too,
+// keeps p in fp32, and the result is as close to 64-bit arithmetic as that kernel's.  What bounds it
+// at the sizes it is used for (a few heads, a launch per chunk) is the latency of the tile loop, so the extra matrix
+// instructions hardly show.  Two prompts of 4173 tokens, 16 heads on 4, 256-token chunks:
+// 19 us a chunk beside the folds (97 by the row kernel); the call 1.72 ms before, 0.90 now (scoring launches of the
+// folds, 47 to 8 us, included).
+__global__ __launch_bounds__(256, 2) void attn_mfma_kernel_d64(Dev dv, AttnArgs a) {
+  __shared__ __attribute__((aligned(16384))) uint16_t Ks[kTileElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs[kTileElems];
+  attn_body<4, 64>(dv, a, Ks, Vs);
 }
 
 }  // namespace
@@ -361,7 +420,10 @@ hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   const int per_group = ((dv.C + span - 1) / span) * (by_head ? Gq / 4 : Gq);
   const int n_groups = a.n_chunks * dv.Hkv * dv.B;
   dim3 grid((unsigned)((n_groups + kXcds - 1) / kXcds * kXcds * per_group));
-  hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), 0, st, dv, a);
+  if (dv.d == 64)
+    hipLaunchKernelGGL(attn_mfma_kernel_d64, grid, dim3(256), 0, st, dv, a);
+  else
+    hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), 0, st, dv, a);
   return hipGetLastError();
 }
 

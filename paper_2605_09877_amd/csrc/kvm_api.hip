@@ -942,7 +942,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         }
         {
           ProfileSpan span(st, 0, stream);
-          if (st->mfma)
+          if (kvm::attention_on_mfma(dv))
             HIP_TRY(kvm::launch_attn_mfma(dv, a, stream));
           else
             HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
@@ -1171,7 +1171,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     }
     {
       ProfileSpan span(st, 0, stream);
-      if (st->mfma)
+      if (kvm::attention_on_mfma(dv))
         HIP_TRY(kvm::launch_attn_mfma(dv, a, stream));
       else
         HIP_TRY(kvm::launch_attn_rows(dv, a, stream));

@@ -150,7 +150,9 @@ struct SeqDesc {
 // most_keys: the largest number of keys (state rows and window) any of the sequences attends to
 hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int most_keys, const void *q,
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st);
-// attn_mfma.hip (bf16, d = 128)
+// attn_mfma.hip: prompts in bf16, d = 128 or 64, blocks of a multiple of 64 tokens (tiles of 64 keys neither cross
+// from the ring into the call's keys nor wrap in the ring); everything else is the row kernel's
+inline bool attention_on_mfma(const Dev &dv) { return dv.io == 1 && (dv.d == 128 || dv.d == 64) && dv.C % 64 == 0; }
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st);
 
 // backward.hip: the backward pass of a whole-sequence prefill that started from an empty state.

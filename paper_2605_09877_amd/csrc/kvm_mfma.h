@@ -255,4 +255,64 @@ __device__ __forceinline__ bf16x8 vtile_frag(const uint16_t *lds_tile, const uin
   return f.v;
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same for head_dim 64: a tile is 64 x 64 bf16 = 8 KiB, a row 128 bytes = eight 16-byte chunks, two
+// rows to a bank cycle of 256 bytes.  Chunk q of row r sits in slot q ^ swz(r):
+//   K tiles: swz(r) = (r >> 1) & 7          (sixteen rows walked by sixteen lanes: sixteen bank groups)
+//   V tiles: swz(r) = 4 * ((r >> 1) & 1)    (four rows x 64 bytes: every bank group once)
+// Both swizzles repeat every 16 rows, so a row block of 32 or a step of 16 keys is a constant offset.
+struct DmaLane64 {
+  uint32_t rl, kcol[2], vcol;   // row of the lane within a piece of 8 rows; byte offset of its chunk
+};
+__device__ __forceinline__ DmaLane64 dma_lane64(int lane) {
+  DmaLane64 d;
+  const int rl = lane >> 3, c8 = lane & 7;
+  d.rl = (uint32_t)rl;
+#pragma unroll
+  for (int n = 0; n < 2; ++n) d.kcol[n] = (uint32_t)(16 * (c8 ^ ((4 * n + (rl >> 1)) & 7)));
+  d.vcol = (uint32_t)(16 * (c8 ^ (4 * ((rl >> 1) & 1))));
+  return d;
+}
+// Four waves fill a tile, two 1-KiB pieces (8 rows) each.
+template <bool kVSwz>
+__device__ __forceinline__ void tile_dma64(const char *base, uint32_t stride, int rows_valid, uint32_t lds_tile_addr,
+                                           int wave, const DmaLane64 &dl) {
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    const int bi = 2 * wave + n;
+    int r = 8 * bi + (int)dl.rl;
+    r = r < rows_valid ? r : rows_valid - 1;   // rows beyond the last repeat it
+    dma16(base, (uint32_t)r * stride + (kVSwz ? dl.vcol : dl.kcol[n]), lds_tile_addr + (uint32_t)bi * 1024u);
+  }
+}
+__device__ __forceinline__ void ktile_offsets64(int lane, uint32_t (&off)[4]) {
+  const int l32 = lane & 31;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) off[ks] = (uint32_t)(l32 * 64 + 8 * ((2 * ks + (lane >> 5)) ^ ((l32 >> 1) & 7)));
+}
+__device__ __forceinline__ bf16x8 ktile_frag64(const uint16_t *lds_tile, const uint32_t (&off)[4], int blk, int ks) {
+  Frag8 f;
+  f.q = *reinterpret_cast<const uint4 *>(lds_tile + off[ks] + 32 * blk * 64);
+  return f.v;
+}
+// (lane -> key and channel as in vtile_offsets)
+__device__ __forceinline__ void vtile_offsets64(int lane, uint32_t (&off)[2]) {
+  const int j = lane & 15, t = j >> 2, c = j & 3;
+  const int g = lane >> 5, half = (lane >> 4) & 1;
+#pragma unroll
+  for (int dblk = 0; dblk < 2; ++dblk) {
+    const int q = 4 * dblk + 2 * half + (c >> 1);
+    off[dblk] = (uint32_t)((4 * g + t) * 64 + 8 * (q ^ (4 * ((t >> 1) & 1))) + 4 * (c & 1));
+  }
+}
+__device__ __forceinline__ bf16x8 vtile_frag64(const uint16_t *lds_tile, const uint32_t (&off)[2], int dblk, int ks) {
+  const uint16_t *p = lds_tile + off[dblk] + 16 * ks * 64;
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(p));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(p + 8 * 64));
+  Frag8 f;
+  f.d[0] = __builtin_bit_cast(uint2, lo);
+  f.d[1] = __builtin_bit_cast(uint2, hi);
+  return f.v;
+}
+
 }  // namespace kvm
