@@ -591,6 +591,19 @@ hipError_t zero_fill(void *p, size_t bytes, hipStream_t st) {
 
 }  // namespace
 
+// Whether D is formed by a pass of its own ahead of the walk (matrix-core path).  It takes dq out of the chain, at the
+// price of reading out and dout once more and of two more events per chunk: worth it while a chunk's dq and
+// state-row workgroups (128 rows each) fit the chip side by side, two per compute unit, and a chunk is long
+// enough for the host to keep ahead.  Whole calls, D inside dq against D ahead, us: 64 + 128 workgroups
+// 3110 / 2870, 128 + 256 3880 / 3520, 256 + 128 4200 / 3780, 256 + 64 3020 / 2920; but 192 + 384 5036 / 5140, 512 + 512
+// 7290 / 7710, and with 64-token blocks 32 + 32 950 / 1040.
+static bool delta_ahead(const Dev &dv, const BwdChunk *chunks, int n_chunks) {
+  if (n_chunks < 2 || dv.C < 256) return false;
+  int m = 0;
+  for (int i = 0; i < n_chunks; ++i) m = chunks[i].m > m ? chunks[i].m : m;
+  return (int64_t)dv.U * (dv.Hq / dv.Hkv * ((dv.C + 127) / 128) + (m + 127) / 128) <= 512;
+}
+
 hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, hipStream_t st, const BwdStreams &x) {
   const Dev &dv = a_in.dv;
   const int G = dv.Hq / dv.Hkv, D = dv.d;
@@ -625,22 +638,24 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
     const int m_end = chunks[n_chunks - 1].m_after;
     BWD_DISPATCH(dv, bwd_readout_kernel, dim3((m_end + 3) / 4, dv.U), dim3(256), st, a, m_end);
   }
-  // D = dout . out per query (the matrix-core dq kernel computes it for its own queries)
-  if (!on_mfma)
-    BWD_DISPATCH(dv, bwd_delta_kernel, dim3((unsigned)((q_rows + 3) / 4)), dim3(256), st, a.out, a.dout, a.delta, q_rows);
-  // Matrix-core path, three streams.  The caller's carries the chain that the state imposes:
-  // undo the fold, dq (which also forms D), dk of the state rows.  dv of the state rows needs the
-  // undone fold only and runs on `side`.  dk and dv of the chunk's own tokens (window keys) need D
-  // and nothing of the state: they run on `side2` and may still be running while the next chunk
-  // of the walk is on the other two, which is what fills the chip while a fold is undone.  The
-  // ring holds one block more than a window so that the fold undone then writes another slot than
-  // they read; they must be done before the fold after that.
+  // Matrix-core path, three streams.  The caller's carries the chain that the state imposes: undo the
+  // fold, (dq,) dk and dv of the state rows.  dk and dv of the chunk's own tokens (window keys) need D and
+  // nothing of the state: they run on `side2` and may still be running while the next chunk of the
+  // walk is on the other two, which is what fills the chip while a fold is undone.  The ring holds one
+  // block more than a window so that the fold undone then writes another slot than they read; they
+  // must be done before the fold after that.
   const bool use_side = on_mfma && x.side && x.side2 && x.fork && x.dq_done && x.join_state && x.join_window[0] &&
                         x.join_window[1];
+  // D = dout . out per query.  The matrix-core dq kernel forms it for its own queries, which saves a pass over
+  // out and dout but puts dq ahead of the state rows in the chain.
+  const bool delta_first = !on_mfma || (use_side && delta_ahead(dv, chunks, n_chunks));
+  if (delta_first)
+    BWD_DISPATCH(dv, bwd_delta_kernel, dim3((unsigned)((q_rows + 3) / 4)), dim3(256), st, a.out, a.dout, a.delta, q_rows);
+  a.delta_ready = delta_first ? 1 : 0;
   bool state_busy = false, window_busy[2] = {false, false};
   for (int ci = n_chunks - 1; ci >= 0; --ci) {
     const BwdChunk &ch = chunks[ci];
-    if (state_busy) {  // the fold about to be undone reads the value adjoints the dv role adds to
+    if (state_busy) {  // the fold about to be undone rewrites the readout that dq reads
       BWD_TRY(hipStreamWaitEvent(st, x.join_state, 0));
       state_busy = false;
     }
@@ -669,24 +684,27 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
       // the chunk's own block was folded after the last chunk that had it in its window
       const int cj = ci + dv.L / dv.C - 1;
       const bool folded = cj < n_chunks && chunks[cj].fold >= 0;
-      if (use_side) {
+      if (use_side && delta_first) {
         BWD_TRY(hipEventRecord(x.fork, st));
         BWD_TRY(hipStreamWaitEvent(x.side, x.fork, 0));
-        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDV, kSecState, x.side));
+        BWD_TRY(hipStreamWaitEvent(x.side2, x.fork, 0));
+        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleKV, kSecState, st));
+        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDQ, kSecBoth, x.side));
         BWD_TRY(hipEventRecord(x.join_state, x.side));
         state_busy = true;
-        // (behind it on the same stream, so that the wait for the next chunk's join_state, one
-        // fold before the ring slot is rewritten, also covers it)
-        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDV, kSecWindow, x.side));
+        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleKV, kSecWindow, x.side2));
+        BWD_TRY(hipEventRecord(x.join_window[ci & 1], x.side2));
+        window_busy[ci & 1] = true;
+      } else if (use_side) {
         BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDQ, kSecBoth, st));
         BWD_TRY(hipEventRecord(x.dq_done, st));
         BWD_TRY(hipStreamWaitEvent(x.side2, x.dq_done, 0));
-        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDK, kSecWindow, x.side2));
+        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleKV, kSecWindow, x.side2));
         BWD_TRY(hipEventRecord(x.join_window[ci & 1], x.side2));
         window_busy[ci & 1] = true;
-        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleDK, kSecState, st));
+        BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, kRoleKV, kSecState, st));
       } else {
-        for (int role : {kRoleDQ, kRoleDK, kRoleDV})
+        for (int role : {kRoleDQ, kRoleKV})
           BWD_TRY(launch_backward_mfma(a, ch.s, ch.nq, ch.m, folded, role, kSecBoth, st));
       }
     } else {
@@ -698,10 +716,7 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
       BWD_DISPATCH(dv, bwd_readout_adjoint_kernel, dim3((ch.m + 4 * kRowsPerWave - 1) / (4 * kRowsPerWave), dv.U),
                    dim3(256), st, a, ch.m);
   }
-  if (state_busy) {  // the last launch on that stream is a dv role of window keys
-    BWD_TRY(hipEventRecord(x.join_state, x.side));
-    BWD_TRY(hipStreamWaitEvent(st, x.join_state, 0));
-  }
+  if (state_busy) BWD_TRY(hipStreamWaitEvent(st, x.join_state, 0));
   for (int i = 0; i < 2; ++i)
     if (window_busy[i]) BWD_TRY(hipStreamWaitEvent(st, x.join_window[i], 0));
   {

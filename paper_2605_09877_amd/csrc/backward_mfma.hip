@@ -1,26 +1,32 @@
 // Attention part of the backward pass for bf16, head_dim 128 on the gfx950 matrix cores.
 //
-// One kernel body in three roles.  Each wave keeps 32 "stationary" vectors in registers, as B
-// operands, and walks 64-row "streamed" tiles that come through LDS:
-//   role dQ : stationary = 32 queries (q and dout rows), streamed = keys (state rows of the
-//             visited version, then window tokens; K and V rows)           -> dq
-//   roles dK, dV: stationary = 32 keys (K and V rows), streamed = the chunk's queries, head
-//             after head of the group (q and dout rows)                    -> dk resp. dv (or
-//             the adjoint of the state readout).  One kernel for both would hold two sets of
-//             result registers and run one wave per SIMD (measured: 550 us per chunk of the bench
-//             workload); apart they run two per SIMD, at the price of the logits computed once
-//             more.
-// Per streamed tile and wave, with X the streamed "key-like" tile (K or q) and Y the streamed
+// One kernel body in two roles.  Each wave owns 32 "stationary" vectors and walks "streamed" tiles that
+// come through LDS:
+//   role dQ: stationary = 32 queries (q and dout rows, in registers as B operands), streamed = keys (64 state
+//            rows of the visited version, then window tokens, at a time; K and V rows)   -> dq
+//   role KV: stationary = 32 keys (K rows in registers, V rows in LDS), streamed = the chunk's queries, 32 at a
+//            time, head after head of the group (q and dout rows)                        -> dk and dv
+//            (or the adjoint of the state readout)
+// Per 32 streamed rows and wave, with X the streamed "key-like" tile (K or q) and Y the streamed
 // "value-like" tile (V or dout):
-//   S^T  = X . staK^T           16 matrix instructions (32x32x16)    logits, transposed
-//   dP^T = Y . staV^T           16
+//   S^T  = X . staK^T           8 matrix instructions (32x32x16)    logits, transposed
+//   dP^T = Y . staV^T           8
 //   P^T  = exp(tau * scale * S^T - lse),  dS^T = P^T * (dP^T - D)   lse and D belong to the query:
-//          to the lane's own column in role dQ, to the row in roles dK, dV (then they come from LDS)
-//   O1^T += X^T . (tau dS^T)    16      dq^T resp. dk^T          (roles dQ, dK)
-//   O2^T += Y^T . P^T           16      dv^T                     (role dV, which skips dP^T and dS^T)
+//          to the lane's own column in role dQ, to the row in role KV (then they come from LDS)
+//   O1^T += X^T . (tau dS^T)    8       dq^T resp. dk^T
+//   O2^T += Y^T . P^T           8       dv^T (role KV)
 // Both products that need a streamed tile transposed read it through the transposing LDS load
 // from the one swizzled image that the first two products read row by row.  Tiles are filled by
 // direct global -> LDS loads one tile ahead, one barrier per tile, like the forward kernel.
+//
+// What bounds it: matrix and LDS issue, two waves per SIMD.  Role KV carries two results (128 registers) at
+// 256 registers a wave; the values moved to LDS, 32-row tiles and offsets made by exclusive or are what
+// makes that fit without a spill in the loop.  Two kernels, dk and dv, each with the logits of its own,
+// took 233 + 166 us a chunk of the bench workload (one after the other); so did three things inside the loops:
+// a load of the temperature per tile, whose wait was a wait for the tile loads too; LDS fragments
+// read just ahead of their use; and bank conflicts in every transposing read (half of all LDS cycles).
+// Whole backward pass of the bench workload 44.5 ms before, 33.5 now (7 contractions at 790 TFLOP/s, undoing
+// the folds included).
 #include <type_traits>
 
 #include "kvm_device.h"
@@ -34,13 +40,31 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kXcds = 8;
 constexpr int kStaPerWg = 128;                                      // stationary vectors per workgroup (4 waves)
+constexpr int kRowScalars = 68;   // role KV, per stage: lse [32], D [32], temperature
 constexpr int kBwdTileBytes = 4 * kTileElems * 2 + 2 * 2 * 64 * 4;  // 2 stages x 2 images + row scalars
-constexpr int kBwdLdsBytes = kBwdTileBytes + 2 * 4 * kHeadDim * 4;  // + the LN_s parameter sums of the dK role
+constexpr int kBwdLdsBytes = kBwdTileBytes + 2 * 4 * kHeadDim * 4;  // + the LN_s parameter sums of role KV
 
-// Transposed (A-operand) fragment of a K-swizzled row-major tile: lane gets channel
-// 32*dblk + lane%32 and rows 16*ks + 4*g + {0..3}, 16*ks + 8 + 4*g + {0..3}.  Lane j of a group
-// of 16 addresses row 4*g + j/4 (+ 8 for the second read) and the 8 bytes at channel
-// 32*dblk + 16*half + 4*(j%4); chunk q of row r sits in slot q ^ (r & 15).
+// The tiles are read row by row and transposed: chunk q of row r sits in slot q ^ swz(r),
+// swz(r) = 4 * (r & 3) + (r >> 2 & 3), which keeps both reads free of bank conflicts (r & 15, which
+// serves the first alone, makes every transposing read take 8 cycles instead of 2).
+__device__ __forceinline__ DmaLane dma_lane_both(int lane) {
+  DmaLane d;
+  const int rl = lane >> 4, c16 = lane & 15;
+  d.rl = (uint32_t)rl;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) d.kcol[n] = (uint32_t)(16 * (c16 ^ (4 * rl + n)));   // row 4 * n + rl (mod 16)
+  d.vcol = 0;
+  return d;
+}
+// Row fragments: lane = row lane%32, chunk 2*ks + lane/32 (as ktile_offsets).
+__device__ __forceinline__ void rtile_offsets(int lane, uint32_t (&off)[8]) {
+  const int l32 = lane & 31, swz = 4 * (l32 & 3) + ((l32 >> 2) & 3);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) off[ks] = (uint32_t)(l32 * kHeadDim + 8 * ((2 * ks + (lane >> 5)) ^ swz));
+}
+// Transposed (A-operand) fragment: lane gets channel 32*dblk + lane%32 and rows 16*ks + 4*g + {0..3},
+// 16*ks + 8 + 4*g + {0..3}.  Lane j of a group of 16 addresses row 4*g + j/4 (+ 8 for the second read)
+// and the 8 bytes at channel 32*dblk + 16*half + 4*(j%4).
 __device__ __forceinline__ void ttile_offsets(int lane, uint32_t (&off)[4][2]) {
   const int j = lane & 15, t = j >> 2, c = j & 3;
   const int g = lane >> 5, half = (lane >> 4) & 1;
@@ -50,7 +74,7 @@ __device__ __forceinline__ void ttile_offsets(int lane, uint32_t (&off)[4][2]) {
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) {
       const int r = 8 * hi + 4 * g + t;
-      const int slot = ((dblk ^ (2 * hi + g)) << 2) | (x ^ t);
+      const int slot = ((dblk ^ t) << 2) | (x ^ (2 * hi + g));
       off[dblk][hi] = (uint32_t)(r * kHeadDim + 8 * slot + 4 * (c & 1));
     }
 }
@@ -63,33 +87,58 @@ __device__ __forceinline__ bf16x8 ttile_frag(const uint16_t *tile, const uint32_
   return f.v;
 }
 
+// Role KV has two results in registers and no room for offsets: both sets follow from one offset each by
+// an exclusive or: chunk 2 * ks ^ .. of a row, block dblk ^ .. of a transposed fragment, whose second read lies eight
+// rows further on with two chunks exchanged.  opaque(): computed where used.
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// (addresses in LDS bytes; tiles are aligned to 8 KiB, so the exclusive or leaves `at` alone)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 ktile_frag_at(uint32_t addr0, int ks, uint32_t at) {
+  return __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4 *)((addr0 ^ (uint32_t)(32 * ks)) + at));
+}
+__device__ __forceinline__ bf16x8 ttile_frag_at(uint32_t addr0, int dblk, int ks, uint32_t at) {
+  at += (uint32_t)(2 * 16 * ks * kHeadDim);
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) v4i16 *)((addr0 ^ (uint32_t)(64 * dblk)) + at));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) v4i16 *)((addr0 ^ (uint32_t)(64 * dblk + 32)) + at + 2 * 8 * kHeadDim));
+  Frag8 f;
+  f.d[0] = __builtin_bit_cast(uint2, lo);
+  f.d[1] = __builtin_bit_cast(uint2, hi);
+  return f.v;
+}
+
 struct MfmaChunk {
   int64_t cs, wb;   // chunk start, first window position
   int32_t nq, m;    // queries of the chunk, state rows it saw
   int32_t nq_ext;   // queries from the chunk start on that see the chunk's own tokens as window keys
   int32_t folded;   // the chunk's tokens were folded later on: their first gradient share is in the ring
   int32_t ring_row0;  // where in the ring ([U, ring rows, d]) the chunk's tokens have that share
-  int32_t section;    // roles dK, dV: kSecBoth, or only the window-key / only the state-row workgroups
+  int32_t section;    // role KV: kSecBoth, or only the window-key / only the state-row workgroups
 };
 
 
 template <int kRole>
 __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
   constexpr bool kKeysSta = kRole != kRoleDQ;
-  constexpr bool kWantDS = kRole != kRoleDV;  // dP^T, dS^T and the first result
   extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
-  float *rowsc = reinterpret_cast<float *>(lds + 4 * kTileElems);  // [stage][lse * log2e | D][64]
+  float *rowsc = reinterpret_cast<float *>(lds + 4 * kTileElems);  // [stage][lse * log2e | D][32]
   constexpr int D = kHeadDim;
+  constexpr int kRows = kKeysSta ? 32 : kTileKeys;  // rows of a streamed tile
+  constexpr int kTileE = kRows * D, kBlks = kRows / 32;
   const Dev &dv = a.dv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, l32 = lane & 31;
   const int G = dv.Hq / dv.Hkv;
-  const int n_keys_win = c.nq;  // roles dK, dV: the window keys of a launch are the chunk's own tokens
+  const int n_keys_win = c.nq;  // role KV: the window keys of a launch are the chunk's own tokens
   const int n_st_wg = (c.m + kStaPerWg - 1) / kStaPerWg;
   const int tpc = (c.nq + kStaPerWg - 1) / kStaPerWg;
   // Consecutive workgroup ids go round-robin over the 8 XCDs: a unit's workgroups share one L2.
-  // Roles dK, dV: the grid has two sections, the window-key workgroups of all units first and the
+  // Role KV: the grid has two sections, the window-key workgroups of all units first and the
   // state-row workgroups after them.  The former stream a whole window of queries and the latter
   // one chunk: started first, the long ones are done when the short ones have had two rounds
   // (interleaved unit by unit, the last long ones would start after the first round of short ones).
@@ -111,12 +160,13 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
 
   // ---- stationary vectors
   bool col_ok;
-  const uint16_t *sk_row, *sv_row;
+  const uint16_t *sk_row;
+  [[maybe_unused]] const uint16_t *sv_row = nullptr;
   int colq = 0;          // role dQ: the lane's query within the chunk
-  int64_t kpos = -1;     // roles dK, dV, window keys: the lane's key position
+  int64_t kpos = -1;     // role KV, window keys: the lane's key position
   int hq_sta = 0, st_row = 0;
   bool sta_state = false;
-  int wg_first = 0;      // roles dK, dV, window keys: first key position of the workgroup, relative to cs
+  int wg_first = 0;      // role KV, window keys: first key position of the workgroup, relative to cs
   if constexpr (!kKeysSta) {
     const int qt = member % tpc, gq = member / tpc;
     hq_sta = __builtin_amdgcn_readfirstlane(h * G + gq);
@@ -133,7 +183,6 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       col_ok = st_row < c.m;
       const int64_t ro = ((int64_t)u * dv.Mcap + (col_ok ? st_row : c.m - 1)) * D;
       sk_row = (const uint16_t *)a.khat + ro;
-      sv_row = (const uint16_t *)a.vhat + ro;
     } else {
       const int64_t first = c.cs + (int64_t)kStaPerWg * member;
       wg_first = (int)(first - c.cs);
@@ -141,15 +190,15 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       col_ok = kpos < c.cs + c.nq;
       const int64_t tok = ((int64_t)b * a.T + (col_ok ? kpos : c.cs + c.nq - 1)) * dv.Hkv + h;
       sk_row = (const uint16_t *)a.k + tok * D;
-      sv_row = (const uint16_t *)a.v + tok * D;
     }
   }
-  bf16x8 sk[8], sv[8];
+  bf16x8 sk[8];
+  [[maybe_unused]] bf16x8 sv[kKeysSta ? 1 : 8];
   float lse2_col = 0.f, d_col = 0.f;
 
   // ---- streamed tiles
   int n_st = 0, n_tiles, qt0 = 0, per_head = 1;
-  int nq_str = c.nq;  // roles dK, dV: queries streamed, from the chunk start on
+  int nq_str = c.nq;  // role KV: queries streamed, from the chunk start on
   if constexpr (!kKeysSta) {
     n_st = (c.m + kTileKeys - 1) / kTileKeys;
     const int qt = member % tpc;
@@ -157,8 +206,8 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     n_tiles = n_st + (int)((c.cs + qend - c.wb + kTileKeys - 1) / kTileKeys);
   } else {
     nq_str = sta_state ? c.nq : c.nq_ext;
-    const int n_qt = (nq_str + kTileKeys - 1) / kTileKeys;
-    qt0 = (!sta_state && wg_first > 0) ? wg_first / kTileKeys : 0;
+    const int n_qt = (nq_str + kRows - 1) / kRows;
+    qt0 = (!sta_state && wg_first > 0) ? wg_first / kRows : 0;
     per_head = n_qt - qt0;
     n_tiles = G * per_head;
     // Order of the streamed tiles: the last query tile first, and for each query tile the heads
@@ -171,10 +220,11 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
   n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
 
   uint32_t koff[8], toff[4][2];
-  ktile_offsets(lane, koff);
+  rtile_offsets(lane, koff);
   ttile_offsets(lane, toff);
-  const DmaLane dl = dma_lane(lane);
+  const DmaLane dl = dma_lane_both(lane);
   const uint32_t lds_addr = lds_addr_of(lds);
+  [[maybe_unused]] const uint32_t k_addr = lds_addr + 2 * koff[0], t_addr = lds_addr + 2 * toff[0][0];  // role KV
 
   auto issue_tile = [&](int it) {
     const char *xb, *yb;
@@ -197,45 +247,74 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       }
     } else {
       const int gq = it % G, qtile = qt0 + per_head - 1 - it / G;
-      const int64_t qrow = ((int64_t)b * a.T + c.cs + (int64_t)qtile * kTileKeys) * dv.Hq + h * G + gq;
+      const int64_t qrow = ((int64_t)b * a.T + c.cs + (int64_t)qtile * kRows) * dv.Hq + h * G + gq;
       xb = (const char *)a.q + qrow * D * 2;
       yb = (const char *)a.dout + qrow * D * 2;
       stride = (uint32_t)dv.Hq * D * 2;
-      valid = nq_str - qtile * kTileKeys;
+      valid = nq_str - qtile * kRows;
     }
-    const uint32_t at = lds_addr + (uint32_t)(2 * (it & 1)) * (kTileElems * 2);
-    tile_dma<false, 4>(xb, stride, valid, at, wave, dl);
-    tile_dma<false, 4>(yb, stride, valid, at + kTileElems * 2, wave, dl);
+    const uint32_t at = lds_addr + (uint32_t)(2 * (it & 1)) * (kTileE * 2);
+    if constexpr (kKeysSta) {
+      // half a tile: the first four of eight waves' shares
+      const DmaLane dl = dma_lane_both((int)opaque((uint32_t)lane));
+      const int v = valid >= kRows ? kTileKeys : valid;
+      tile_dma<false, 8>(xb, stride, v, at, wave, dl);
+      tile_dma<false, 8>(yb, stride, v, at + kTileE * 2, wave, dl);
+    } else {
+      tile_dma<false, 4>(xb, stride, valid, at, wave, dl);
+      tile_dma<false, 4>(yb, stride, valid, at + kTileE * 2, wave, dl);
+    }
   };
-  // roles dK, dV: lse and D of a tile's 64 query rows, fetched by the first wave a tile ahead and
-  // put into LDS just before the barrier that publishes the tile
-  float rs_lse = 0.f, rs_d = 0.f;
+  // role KV: lse and D of a tile's 32 query rows (a half of the wave each) and the head's temperature, asked for by
+  // the first wave a tile ahead and put into LDS just before the barrier that publishes the tile.  Nothing
+  // is done to the values before that: a use would wait for them, and for the tile loads with them.
+  float rs = 0.f, rs_tau = 1.f;
+  typedef const __attribute__((address_space(1))) float GlobalF32;
+  GlobalF32 *taus = nullptr;
+  if constexpr (kKeysSta) {   // wave-uniform, kept in scalar registers
+    const uint64_t x = (uint64_t)(sta_state ? dv.tau_state : dv.tau_bswa);
+    taus = (GlobalF32 *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x));
+  }
   auto fetch_rowsc = [&](int it) {
     if constexpr (kKeysSta) {
       if (wave == 0) {
         const int gq = it % G, qtile = qt0 + per_head - 1 - it / G;
-        int r = qtile * kTileKeys + lane;
+        const int ln = (int)opaque((uint32_t)lane);
+        int r = qtile * kRows + (ln & 31);
         r = r < nq_str ? r : nq_str - 1;
         const int64_t qrow = ((int64_t)b * a.T + c.cs + r) * dv.Hq + h * G + gq;
-        rs_lse = a.lse[qrow] * kLog2e;
-        rs_d = a.delta[qrow];
+        const float *src = ln < 32 ? a.lse : a.delta;
+        rs = src[qrow];
+        if (taus) rs_tau = taus[h * G + gq];
       }
     }
   };
   auto store_rowsc = [&](int it) {
     if constexpr (kKeysSta) {
       if (wave == 0) {
-        rowsc[(it & 1) * 128 + lane] = rs_lse;
-        rowsc[(it & 1) * 128 + 64 + lane] = rs_d;
+        rowsc[(it & 1) * kRowScalars + lane] = lane < 32 ? rs * kLog2e : rs;
+        if (lane == 0) rowsc[(it & 1) * kRowScalars + 64] = rs_tau;
       }
     }
   };
+  // role dQ: both temperatures of its one head
+  float tau_st = 1.f, tau_bs = 1.f;
+  if constexpr (!kKeysSta) {
+    auto uni = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    if (dv.tau_state) tau_st = uni(dv.tau_state[hq_sta]);
+    if (dv.tau_bswa) tau_bs = uni(dv.tau_bswa[hq_sta]);
+  }
 
-  f32x16 o1[4];  // the role's result, transposed: dq^T, dk^T or dv^T
+  f32x16 o1[4];                               // dq^T or dk^T
+  [[maybe_unused]] f32x16 o2[kKeysSta ? 4 : 1];  // role KV: dv^T
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o1[i][v] = 0.f;
+    for (int v = 0; v < 16; ++v) {
+      o1[i][v] = 0.f;
+      if constexpr (kKeysSta) o2[i][v] = 0.f;
+    }
   float tau_sum_state = 0.f, tau_sum_bswa = 0.f;  // role dQ: sum of dS * S over state / window keys
 
   auto tile_step = [&](int it, auto parity) {
@@ -246,16 +325,14 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       issue_tile(it + 1);
       fetch_rowsc(it + 1);
     }
-    const uint16_t *X = lds + (2 * decltype(parity)::value) * kTileElems;
-    const uint16_t *Y = X + kTileElems;
+    const uint16_t *X = lds + (2 * decltype(parity)::value) * kTileE;
+    const uint16_t *Y = X + kTileE;
     // what this tile is, and whether any of it is visible to this wave's columns
     bool tile_state;   // logits of this tile use the state temperature
     bool need_mask;    // wave-uniform: whether any pair of the tile is invisible to this wave
     int lim_lane = 0;  // role dQ: tile rows <= lim_lane are visible to the lane's query
-    int lo_lane = 0, hi_row = 0;  // roles dK, dV: tile rows lo_lane .. hi_row are visible to the lane's key
-    int hq;
+    int lo_lane = 0, hi_row = 0;  // role KV: tile rows lo_lane .. hi_row are visible to the lane's key
     if constexpr (!kKeysSta) {
-      hq = hq_sta;
       tile_state = it < n_st;
       const int wave_q0 = kStaPerWg * (member % tpc) + 32 * wave;  // the wave's first query
       if (tile_state) {
@@ -268,135 +345,219 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
         need_mask = p0rel + kTileKeys - 1 > wave_q0;
       }
     } else {
-      const int gq = it % G, qtile = qt0 + per_head - 1 - it / G;
-      hq = __builtin_amdgcn_readfirstlane(h * G + gq);
+      const int qtile = qt0 + per_head - 1 - it / G;
       tile_state = sta_state;
-      const int row_pos0 = qtile * kTileKeys;  // the tile's first query, relative to the chunk start
+      const int row_pos0 = qtile * kRows;  // the tile's first query, relative to the chunk start
       hi_row = nq_str - 1 - row_pos0;          // rows beyond the last query are padding
-      need_mask = hi_row < kTileKeys - 1;
+      need_mask = hi_row < kRows - 1;
       if (!sta_state) {
         const int wave_k0 = wg_first + 32 * wave;  // the wave's first key, relative to the chunk start
-        if (wave_k0 > row_pos0 + kTileKeys - 1) return;  // all queries before the wave's keys
+        if (wave_k0 > row_pos0 + kRows - 1) return;  // all queries before the wave's keys
         lo_lane = wave_k0 + l32 - row_pos0;              // visible rows: key position <= query position
         need_mask = need_mask || wave_k0 + 31 > row_pos0;
       }
     }
-    const float tau = tile_state ? (dv.tau_state ? dv.tau_state[hq] : 1.f) : (dv.tau_bswa ? dv.tau_bswa[hq] : 1.f);
+    float tau;
+    if constexpr (kKeysSta)
+      tau = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(rowsc[decltype(parity)::value * kRowScalars + 64])));
+    else tau = tile_state ? tau_st : tau_bs;
     const float cexp = tau * scale * kLog2e;
 
-    // Role dK takes the two 32-row halves of the tile one after the other -- logits and
-    // dout . v^T of the half, the elementwise step, then the half's share of the result -- so
-    // that half the logit registers are live; the other roles take them together.
-    f32x16 sacc[2], dacc[2];
-    Frag8 pP[4], pS[4];
+    f32x16 sacc[kBlks], dacc[kBlks];
+    [[maybe_unused]] Frag8 pP[2 * kBlks];
+    Frag8 pS[2 * kBlks];
     float tsum = 0.f;
+    // Role KV: P^T and dS^T are packed as they are made, four rows at a time, with the scalars of the next four
+    // asked for: the registers that all of a tile's scalars would take at once are not there.
     auto elementwise = [&](auto masked, auto blk_c) {
-      {
-        constexpr int blk = decltype(blk_c)::value;
-        float lse_r[16], d_r[16];
-        if constexpr (kKeysSta) {
-          const float *rl = rowsc + decltype(parity)::value * 128 + 32 * blk + 4 * g;
+      constexpr int blk = decltype(blk_c)::value;
+      if constexpr (kKeysSta) {
+        const float *rl = rowsc + decltype(parity)::value * kRowScalars + 4 * g;
+        float4 x = *reinterpret_cast<const float4 *>(rl), y = *reinterpret_cast<const float4 *>(rl + 32);
 #pragma unroll
-          for (int v4 = 0; v4 < 4; ++v4) {
-            const float4 x = *reinterpret_cast<const float4 *>(rl + 8 * v4);
-            const float4 y = *reinterpret_cast<const float4 *>(rl + 64 + 8 * v4);
-            lse_r[4 * v4] = x.x; lse_r[4 * v4 + 1] = x.y; lse_r[4 * v4 + 2] = x.z; lse_r[4 * v4 + 3] = x.w;
-            d_r[4 * v4] = y.x; d_r[4 * v4 + 1] = y.y; d_r[4 * v4 + 2] = y.z; d_r[4 * v4 + 3] = y.w;
+        for (int v4 = 0; v4 < 4; ++v4) {
+          const float lse4[4] = {x.x, x.y, x.z, x.w}, d4[4] = {y.x, y.y, y.z, y.w};
+          if (v4 < 3) {
+            x = *reinterpret_cast<const float4 *>(rl + 8 * v4 + 8);
+            y = *reinterpret_cast<const float4 *>(rl + 8 * v4 + 40);
           }
+          float p[4], ds[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int v = 4 * v4 + e, r = mfma_row(v, g);
+            bool vis = true;
+            if constexpr (decltype(masked)::value) vis = r >= lo_lane && r <= hi_row;
+            p[e] = vis ? __builtin_amdgcn_exp2f(fmaf(sacc[0][v], cexp, -lse4[e])) : 0.f;
+            ds[e] = p[e] * (dacc[0][v] - d4[e]) * tau;
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            pP[v4 >> 1].w[2 * (v4 & 1) + i] = pack_bf16(p[2 * i], p[2 * i + 1]);
+            pS[v4 >> 1].w[2 * (v4 & 1) + i] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
+      } else {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int r = 32 * blk + mfma_row(v, g);
           bool vis = true;
-          float lse2, dd;
-          if constexpr (!kKeysSta) {
-            if constexpr (decltype(masked)::value) vis = r <= lim_lane;
-            lse2 = lse2_col;
-            dd = d_col;
-          } else {
-            if constexpr (decltype(masked)::value) vis = r >= lo_lane && r <= hi_row;
-            lse2 = lse_r[v];
-            dd = d_r[v];
-          }
+          if constexpr (decltype(masked)::value) vis = r <= lim_lane;
           const float s = sacc[blk][v];
-          const float p = vis ? __builtin_amdgcn_exp2f(fmaf(s, cexp, -lse2)) : 0.f;
-          sacc[blk][v] = p;
-          if constexpr (kWantDS) {
-            const float ds = p * (dacc[blk][v] - dd);
-            tsum = fmaf(ds, s, tsum);
-            dacc[blk][v] = ds * tau;
-          }
+          const float p = vis ? __builtin_amdgcn_exp2f(fmaf(s, cexp, -lse2_col)) : 0.f;
+          const float ds = p * (dacc[blk][v] - d_col);
+          tsum = fmaf(ds, s, tsum);
+          dacc[blk][v] = ds * tau;
         }
+#pragma unroll
+        for (int ks = 2 * blk; ks < 2 * blk + 2; ++ks)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int v0 = (ks & 1) * 8 + 2 * e;
+            pS[ks].w[e] = pack_bf16(dacc[blk][v0], dacc[blk][v0 + 1]);
+          }
       }
     };
+    // The products of 32 streamed rows.  Fragments are read from LDS four steps ahead of the matrix instruction that
+    // takes them, and the first four of the second product while the first one ends; the order is pinned
+    // (0x100: LDS reads, 0x008: matrix instructions), or the compiler, short of registers, reads every
+    // fragment just before its use and each matrix instruction waits for LDS.
+    bf16x8 tf[4];
     auto first_products = [&](auto blk_c) {
+      __builtin_amdgcn_sched_barrier(0);
       constexpr int blk = decltype(blk_c)::value;
       const f32x16 zero = {0.f};
+      bf16x8 xf[4], yf[4];
+      if constexpr (kKeysSta) {
+        const uint32_t k0 = opaque(k_addr), v0 = k0 + 4 * kTileE * 2 + (uint32_t)wave * (32 * D * 2), t0 = opaque(t_addr);
+        constexpr uint32_t xa = decltype(parity)::value * (2 * kTileE * 2), ya = xa + kTileE * 2;
+        constexpr int kAhead = 4;   // steps of the second chain, two fragments each: four do not fit the registers
+        bf16x8 vf[kAhead];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        sacc[blk] = mfma32(ktile_frag(X, koff, blk, ks), sk[ks], ks == 0 ? zero : sacc[blk]);
-        if constexpr (kWantDS) dacc[blk] = mfma32(ktile_frag(Y, koff, blk, ks), sv[ks], ks == 0 ? zero : dacc[blk]);
+        for (int i = 0; i < 4; ++i) xf[i] = ktile_frag_at(k0, i, xa);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          sacc[blk] = mfma32(xf[ks & 3], sk[ks], ks == 0 ? zero : sacc[blk]);
+          if (ks < 4) xf[ks] = ktile_frag_at(k0, ks + 4, xa);
+          if (ks >= 8 - kAhead) {
+            yf[ks - (8 - kAhead)] = ktile_frag_at(k0, ks - (8 - kAhead), ya);
+            vf[ks - (8 - kAhead)] = ktile_frag_at(v0, ks - (8 - kAhead), 0);
+          }
+        }
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          dacc[blk] = mfma32(yf[ks % kAhead], vf[ks % kAhead], ks == 0 ? zero : dacc[blk]);
+          if (ks + kAhead < 8) {
+            yf[ks % kAhead] = ktile_frag_at(k0, ks + kAhead, ya);
+            vf[ks % kAhead] = ktile_frag_at(v0, ks + kAhead, 0);
+          } else {
+            tf[ks - (8 - kAhead)] = ttile_frag_at(t0, ks - (8 - kAhead), 0, ya);
+          }
+        }
+#pragma unroll
+        for (int i = kAhead; i < 4; ++i) tf[i] = ttile_frag_at(t0, i, 0, ya);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4 - kAhead, 0);
+#pragma unroll
+        for (int i = 0; i < 8 + kAhead; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * (4 - kAhead), 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          xf[i] = ktile_frag(X, koff, blk, i);
+          yf[i] = ktile_frag(Y, koff, blk, i);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          sacc[blk] = mfma32(xf[ks & 3], sk[ks], ks == 0 ? zero : sacc[blk]);
+          dacc[blk] = mfma32(yf[ks & 3], sv[ks], ks == 0 ? zero : dacc[blk]);
+          if (ks < 4) {
+            xf[ks] = ktile_frag(X, koff, blk, ks + 4);
+            yf[ks] = ktile_frag(Y, koff, blk, ks + 4);
+          } else {
+            tf[ks - 4] = ttile_frag(X, toff, ks - 4, 2 * blk);
+          }
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);
     };
     auto second_product = [&](auto blk_c) {
       constexpr int blk = decltype(blk_c)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (kKeysSta) {
+        const uint32_t t0 = opaque(t_addr);
+        constexpr uint32_t xa = decltype(parity)::value * (2 * kTileE * 2), ya = xa + kTileE * 2;
 #pragma unroll
-      for (int ks = 2 * blk; ks < 2 * blk + 2; ++ks) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v0 = (ks & 1) * 8 + 2 * e;
-          if constexpr (kWantDS)
-            pS[ks].w[e] = pack_bf16(dacc[blk][v0], dacc[blk][v0 + 1]);
-          else
-            pP[ks].w[e] = pack_bf16(sacc[blk][v0], sacc[blk][v0 + 1]);
+        for (int n = 0; n < 16; ++n) {   // eight of dv^T, then eight of dk^T
+          const int ks = (n >> 2) & 1, dblk = n & 3;
+          if (n < 8) o2[dblk] = mfma32(tf[dblk], pP[ks].v, o2[dblk]);
+          else o1[dblk] = mfma32(tf[dblk], pS[ks].v, o1[dblk]);
+          if (n < 12) tf[dblk] = ttile_frag_at(t0, dblk, ((n + 4) >> 2) & 1, n < 4 ? ya : xa);
         }
 #pragma unroll
-        for (int dblk = 0; dblk < 4; ++dblk) {
-          if constexpr (kWantDS)
-            o1[dblk] = mfma32(ttile_frag(X, toff, dblk, ks), pS[ks].v, o1[dblk]);
-          else
-            o1[dblk] = mfma32(ttile_frag(Y, toff, dblk, ks), pP[ks].v, o1[dblk]);
+        for (int i = 0; i < 12; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      } else {
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+          const int ks = 2 * blk + (n >> 2), dblk = n & 3;
+          o1[dblk] = mfma32(tf[dblk], pS[ks].v, o1[dblk]);
+          if (n < 4) tf[dblk] = ttile_frag(X, toff, dblk, ks + 1);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
     };
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
     using Masked = std::integral_constant<bool, true>;
     using Plain = std::integral_constant<bool, false>;
-    if constexpr (kRole == kRoleDK) {
-      first_products(B0{});
-      if (need_mask) elementwise(Masked{}, B0{}); else elementwise(Plain{}, B0{});
-      second_product(B0{});
-      first_products(B1{});
-      if (need_mask) elementwise(Masked{}, B1{}); else elementwise(Plain{}, B1{});
-      second_product(B1{});
-    } else if constexpr (kRole == kRoleDV) {
-      first_products(B0{});
-      first_products(B1{});
-      if (need_mask) {
-        elementwise(Masked{}, B0{});
-        elementwise(Masked{}, B1{});
-      } else {
-        elementwise(Plain{}, B0{});
-        elementwise(Plain{}, B1{});
-      }
-      second_product(B0{});
-      second_product(B1{});
-    } else {
-      // role dQ has no registers for two variants of the elementwise step: it always compares
-      (void)need_mask;
-      first_products(B0{});
-      first_products(B1{});
-      elementwise(Masked{}, B0{});
-      elementwise(Masked{}, B1{});
-      second_product(B0{});
-      second_product(B1{});
-    }
+    auto rows32 = [&](auto blk) {
+      first_products(blk);
+      if (need_mask) elementwise(Masked{}, blk); else elementwise(Plain{}, blk);
+      second_product(blk);
+    };
+    rows32(std::integral_constant<int, 0>{});
+    if constexpr (kBlks == 2) rows32(std::integral_constant<int, 1>{});
     if constexpr (!kKeysSta) {
       if (tile_state) tau_sum_state += tsum; else tau_sum_bswa += tsum;
     }
   };
 
+  // Role KV: the workgroup's 128 value rows go to LDS, in the layout of the tiles (a row block that
+  // starts beyond the last key repeats that key; nothing of it is kept).
+  if constexpr (kKeysSta) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int n_keys = sta_state ? c.m : c.nq;
+      int row0 = kStaPerWg * member + 64 * half;
+      row0 = row0 < n_keys ? row0 : n_keys - 1;
+      const int64_t first = sta_state ? (int64_t)u * dv.Mcap + row0 : ((int64_t)b * a.T + c.cs + row0) * dv.Hkv + h;
+      tile_dma<false, 4>((const char *)(sta_state ? a.vhat : (void *)a.v) + first * D * 2,
+                         (uint32_t)(sta_state ? 1 : dv.Hkv) * D * 2, n_keys - row0,
+                         lds_addr + 4 * kTileE * 2 + (uint32_t)half * (kTileElems * 2), wave, dl);
+    }
+  }
   // The first tile is asked for ahead of the stationary vectors, so that the two travel together
   // (short loops -- few streamed tiles per workgroup -- feel every round trip of the prologue).
   if (n_tiles > 0) {
@@ -408,7 +569,7 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     Frag8 f;
     f.q = *reinterpret_cast<const uint4 *>(sk_row + 16 * ks + 8 * g);
     sk[ks] = f.v;
-    if constexpr (kWantDS) {
+    if constexpr (!kKeysSta) {
       f.q = *reinterpret_cast<const uint4 *>(sv_row + 16 * ks + 8 * g);
       sv[ks] = f.v;
     }
@@ -433,7 +594,7 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       for (int e = 0; e < 8; ++e) part = fmaf(of[e], df[e], part);
     }
     d_col = xhalf_sum(part);
-    if (col_ok && g == 0) a.delta[qrow] = d_col;
+    if (col_ok && g == 0 && !a.delta_ready) a.delta[qrow] = d_col;
   }
 
   // the stationary vectors are in registers from here on (the compiler does not count the tile
@@ -473,23 +634,26 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
       // token got when its fold was undone (kept in fp32 in a ring of the last window's blocks and one more)
       // is added, and goes out in the I/O dtype.
       if (!sta_state) {
-        const float os = kRole == kRoleDK ? scale : 1.f;
         const int64_t tok = ((int64_t)b * a.T + kpos) * dv.Hkv + h;
-        uint16_t *orow = (uint16_t *)(kRole == kRoleDK ? a.dk : a.dv_out) + tok * D;
-        const float *ring = (kRole == kRoleDK ? a.dk_acc : a.dv_acc) +
-                            ((int64_t)u * a.ring_rows + c.ring_row0 + (int)(kpos - c.cs)) * D;
+        const int64_t ro = ((int64_t)u * a.ring_rows + c.ring_row0 + (int)(kpos - c.cs)) * D;
+        auto finish = [&](const f32x16 (&o)[4], float os, void *out, const float *acc) {
+          uint16_t *orow = (uint16_t *)out + tok * D;
+          const float *ring = acc + ro;
 #pragma unroll
-        for (int dblk = 0; dblk < 4; ++dblk)
+          for (int dblk = 0; dblk < 4; ++dblk)
 #pragma unroll
-          for (int vq = 0; vq < 4; ++vq) {
-            const int ch = 32 * dblk + 8 * vq + 4 * g;
-            float4 x4 = c.folded ? *reinterpret_cast<const float4 *>(ring + ch) : make_float4(0.f, 0.f, 0.f, 0.f);
-            x4.x += o1[dblk][4 * vq] * os;
-            x4.y += o1[dblk][4 * vq + 1] * os;
-            x4.z += o1[dblk][4 * vq + 2] * os;
-            x4.w += o1[dblk][4 * vq + 3] * os;
-            *reinterpret_cast<uint2 *>(orow + ch) = make_uint2(pack_bf16(x4.x, x4.y), pack_bf16(x4.z, x4.w));
-          }
+            for (int vq = 0; vq < 4; ++vq) {
+              const int ch = 32 * dblk + 8 * vq + 4 * g;
+              float4 x4 = c.folded ? *reinterpret_cast<const float4 *>(ring + ch) : make_float4(0.f, 0.f, 0.f, 0.f);
+              x4.x += o[dblk][4 * vq] * os;
+              x4.y += o[dblk][4 * vq + 1] * os;
+              x4.z += o[dblk][4 * vq + 2] * os;
+              x4.w += o[dblk][4 * vq + 3] * os;
+              *reinterpret_cast<uint2 *>(orow + ch) = make_uint2(pack_bf16(x4.x, x4.y), pack_bf16(x4.z, x4.w));
+            }
+        };
+        finish(o1, scale, a.dk, a.dk_acc);
+        finish(o2, 1.f, a.dv_out, a.dv_acc);
       }
     }
     // State rows: the readout's adjoint goes straight on into the adjoint of the sums.  A lane
@@ -498,7 +662,47 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     // exchange between the wave's halves.
     if (sta_state) {
       const int64_t ro = ((int64_t)u * dv.Mcap + (col_ok ? st_row : 0)) * D;
-      if constexpr (kRole == kRoleDK) {
+      {
+        // v-hat = rho * sV / max(|sV|, eps)
+        float svr[4][16];
+        float nn = 0.f, dot = 0.f;
+#pragma unroll
+        for (int dblk = 0; dblk < 4; ++dblk)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq) {
+            const float4 x4 = *reinterpret_cast<const float4 *>(a.wsV + ro + 32 * dblk + 8 * vq + 4 * g);
+            const float xs[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              svr[dblk][4 * vq + e] = xs[e];
+              nn += xs[e] * xs[e];
+              dot += o2[dblk][4 * vq + e] * xs[e];
+            }
+          }
+        const float nrm = sqrtf(xhalf_sum(nn));
+        const float den = fmaxf(nrm, dv.norm_eps);
+        dot = xhalf_sum(dot) / den;  // dv-hat . unit vector
+        const float rho = dv.rho[(int64_t)u * dv.Mcap + (col_ok ? st_row : 0)];
+        const float back = nrm > dv.norm_eps ? rho * dot / (den * den) : 0.f;
+        if (col_ok) {
+#pragma unroll
+          for (int dblk = 0; dblk < 4; ++dblk)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+              const int ch = 32 * dblk + 8 * vq + 4 * g;
+              float4 x4 = *reinterpret_cast<const float4 *>(a.dsV + ro + ch);
+              x4.x += rho / den * o2[dblk][4 * vq] - back * svr[dblk][4 * vq];
+              x4.y += rho / den * o2[dblk][4 * vq + 1] - back * svr[dblk][4 * vq + 1];
+              x4.z += rho / den * o2[dblk][4 * vq + 2] - back * svr[dblk][4 * vq + 2];
+              x4.w += rho / den * o2[dblk][4 * vq + 3] - back * svr[dblk][4 * vq + 3];
+              *reinterpret_cast<float4 *>(a.dsV + ro + ch) = x4;
+            }
+          if (g == 0) a.drho[(int64_t)u * dv.Mcap + st_row] += dot;
+        }
+      }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      {
         // k-hat = LN_s(sK) * gamma + beta.  The standardised sums x-hat and 1 / sqrt(var + eps) of
         // the visited version are kept beside its readout, so everything the row needs is asked
         // for at once: one memory round trip, not a chain of them.
@@ -595,43 +799,6 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
                              red[(4 * which + 3) * D + ch];
           if (sum4 != 0.f) atomicAdd(a.par64 + (which * dv.Hkv + h) * D + ch, (double)sum4);
         }
-      } else if constexpr (kRole == kRoleDV) {
-        // v-hat = rho * sV / max(|sV|, eps)
-        float svr[4][16];
-        float nn = 0.f, dot = 0.f;
-#pragma unroll
-        for (int dblk = 0; dblk < 4; ++dblk)
-#pragma unroll
-          for (int vq = 0; vq < 4; ++vq) {
-            const float4 x4 = *reinterpret_cast<const float4 *>(a.wsV + ro + 32 * dblk + 8 * vq + 4 * g);
-            const float xs[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              svr[dblk][4 * vq + e] = xs[e];
-              nn += xs[e] * xs[e];
-              dot += o1[dblk][4 * vq + e] * xs[e];
-            }
-          }
-        const float nrm = sqrtf(xhalf_sum(nn));
-        const float den = fmaxf(nrm, dv.norm_eps);
-        dot = xhalf_sum(dot) / den;  // dv-hat . unit vector
-        const float rho = dv.rho[(int64_t)u * dv.Mcap + (col_ok ? st_row : 0)];
-        const float back = nrm > dv.norm_eps ? rho * dot / (den * den) : 0.f;
-        if (col_ok) {
-#pragma unroll
-          for (int dblk = 0; dblk < 4; ++dblk)
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-              const int ch = 32 * dblk + 8 * vq + 4 * g;
-              float4 x4 = *reinterpret_cast<const float4 *>(a.dsV + ro + ch);
-              x4.x += rho / den * o1[dblk][4 * vq] - back * svr[dblk][4 * vq];
-              x4.y += rho / den * o1[dblk][4 * vq + 1] - back * svr[dblk][4 * vq + 1];
-              x4.z += rho / den * o1[dblk][4 * vq + 2] - back * svr[dblk][4 * vq + 2];
-              x4.w += rho / den * o1[dblk][4 * vq + 3] - back * svr[dblk][4 * vq + 3];
-              *reinterpret_cast<float4 *>(a.dsV + ro + ch) = x4;
-            }
-          if (g == 0) a.drho[(int64_t)u * dv.Mcap + st_row] += dot;
-        }
       }
     }
   }
@@ -641,14 +808,13 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
 
 bool backward_on_mfma(const Dev &dv) { return dv.io == 1 && dv.d == kHeadDim && dv.C % 64 == 0; }
 
-// The three launches of one chunk: dq (and the temperature sums), dk, dv (or the readout's adjoint).
+// The launches of one chunk: dq (and the temperature sums); dk and dv of its own tokens and of the state rows.
 hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
                                 hipStream_t st) {
   const Dev &dv = a.dv;
   static bool allowed = false;  // more than 64 KiB of LDS per workgroup has to be asked for once
   if (!allowed) {
-    const void *kernels[3] = {(const void *)bwd_mfma_kernel<kRoleDQ>, (const void *)bwd_mfma_kernel<kRoleDK>,
-                              (const void *)bwd_mfma_kernel<kRoleDV>};
+    const void *kernels[2] = {(const void *)bwd_mfma_kernel<kRoleDQ>, (const void *)bwd_mfma_kernel<kRoleKV>};
     for (const void *k : kernels) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes);
       if (e != hipSuccess) return e;
@@ -675,10 +841,7 @@ hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool fo
   }
   const int per_k = section == kSecBoth ? n_st_wg + n_win_wg : section == kSecState ? n_st_wg : n_win_wg;
   if (per_k == 0) return hipSuccess;
-  if (role == kRoleDK)
-    hipLaunchKernelGGL((bwd_mfma_kernel<kRoleDK>), dim3(groups * per_k), dim3(256), kBwdLdsBytes, st, a, c);
-  else
-    hipLaunchKernelGGL((bwd_mfma_kernel<kRoleDV>), dim3(groups * per_k), dim3(256), kBwdLdsBytes, st, a, c);
+  hipLaunchKernelGGL((bwd_mfma_kernel<kRoleKV>), dim3(groups * per_k), dim3(256), kBwdLdsBytes, st, a, c);
   return hipGetLastError();
 }
 

@@ -184,6 +184,7 @@ struct Bwd {
   float *dk_acc, *dv_acc;
   int32_t ring_rows;
   float *delta;          // [B, T, Hq] sum over channels of dout * out
+  int32_t delta_ready;   // it is there already: the dq role does not write it
   float *P, *dS;         // [U, G, C, Mcap + L] probabilities and logit adjoints of one chunk
   double *par64;         // [2 * Hkv * d + 2 * Hq] fp64 accumulators of dgamma, dbeta, dtau_state, dtau_bswa
 };
@@ -205,9 +206,9 @@ struct BwdStreams {
 hipError_t run_backward(const Bwd &a, const BwdChunk *chunks, int n_chunks, hipStream_t st, const BwdStreams &x);
 // backward_mfma.hip (bf16, d = 128): one chunk's dq, dk, dv and readout adjoint on the matrix cores
 bool backward_on_mfma(const Dev &dv);
-enum { kRoleDQ = 0, kRoleDK = 1, kRoleDV = 2 };
+enum { kRoleDQ = 0, kRoleKV = 1 };
 enum { kSecBoth = 0, kSecWindow = 1, kSecState = 2 };
-// one role of the matrix-core tile kernel over one chunk; roles dK, dV: all key workgroups, or only
+// one role of the matrix-core tile kernel over one chunk; role KV: all key workgroups, or only
 // those of the chunk's own tokens (window keys), or only those of the state rows
 hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
                                 hipStream_t st);

@@ -1,0 +1,23 @@
+"""The backward pass on the matrix cores at the edges of its tiles: 32-query and 64-key tiles, 128-key workgroups,
+one and several heads per KV head, D formed inside dq and by a pass ahead of the walk (256-token blocks and few
+workgroups).  Oracle and bars of test_gpu_backward."""
+import pytest
+
+from test_gpu_backward import run_backward_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,rows,T,heads", [
+    (64, 65, 64 * 4 + 1, (1, 1)),        # one query in the last tile, one state row beyond a tile
+    (64, 127, 64 * 5 + 33, (3, 1)),      # a query beyond a 32-row tile, three heads streamed one after the other
+    (128, 129, 128 * 4 + 31, (4, 2)),    # a workgroup with one state row
+    (192, 200, 192 * 3 + 95, (2, 2)),    # the block's second workgroup half empty
+    (256, 256, 256 * 3 + 1, (2, 1)),     # D ahead
+    (256, 300, 256 * 4, (4, 1)),
+])
+def test_tile_edges(C, rows, T, heads):
+    from paper_2605_09877_amd import synth as sy
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=heads[0], n_kv_heads=heads[1], seq=T, chunk_len=C,
+                  budget_fixed=rows)
+    run_backward_case(w, plain=False)
