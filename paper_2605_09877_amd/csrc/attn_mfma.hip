@@ -135,7 +135,7 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
 
   // Per-lane fragment offsets (elements) from the start of the K / V buffers.  K has two buffers
   // and its offsets flip after every tile; V buffers are addressed by tile number.
-  uint32_t koff[kKs], voff[2];
+  uint32_t koff[kKs], voff[kNb];
   const auto dl = [&] {
     if constexpr (D == 128) {
       ktile_offsets(lane, koff);

@@ -88,7 +88,11 @@ __device__ __forceinline__ bf16x8 tile_rows_frag(const uint16_t *lds, int blk, i
 // q ^ swz(r).  Rows are 256 B apart (a multiple of the bank cycle), the permutation is what keeps
 // the fragment reads below conflict-free.
 //   K tiles (read with ds_read_b128, lanes walk rows):        swz(r) = r & 15
-//   V tiles (read with ds_read_b64_tr_b16, 4 rows x 32 B):    swz(r) = 2 * (r & 3)
+//   V tiles (read with ds_read_b64_tr_b16, 4 rows x 64 B):    swz(r) = 4 * (r & 3)
+//   tiles that are read both ways (the backward pass):        swz(r) = 4 * (r & 3) + (r >> 2 & 3)
+// A transposing read serves 32 lanes at a time, 64 bytes (four chunks) of each of four consecutive rows: the
+// permutation has to send those four rows to four different quarters of the bank cycle.  Counted with
+// SQ_LDS_BANK_CONFLICT: 2 * (r & 3) costs 2 cycles more per read (4 instead of 2), r & 15 six more.
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 #define KVM_LDS_V4(p) ((__attribute__((address_space(3))) v4i16 *)(p))
 #define KVM_LDS_VOID(p) ((__attribute__((address_space(3))) void *)(p))
@@ -108,7 +112,7 @@ __device__ __forceinline__ DmaLane dma_lane(int lane) {
   d.rl = (uint32_t)rl;
 #pragma unroll
   for (int n = 0; n < 4; ++n) d.kcol[n] = (uint32_t)(16 * (c16 ^ (4 * n + rl)));
-  d.vcol = (uint32_t)(16 * (c16 ^ (2 * rl)));
+  d.vcol = (uint32_t)(16 * (c16 ^ (4 * rl)));
   return d;
 }
 
@@ -234,19 +238,18 @@ __device__ __forceinline__ bf16x8 ktile_frag(const uint16_t *lds_tile, const uin
 // (g = lane/32) -- the key order in which a lane holds P^T after the first product.
 // ds_read_b64_tr_b16: within 16 lanes, result element t of lane i = element i%4 of the 8 bytes
 // addressed by lane 4*t + i/4.  So lane j addresses key row K0 + j/4, channels dbase + 4*(j%4).
-// The per-lane part of the address depends on dblk only through its low bit (it meets the row
-// swizzle in one bit), so two offsets cover all sixteen fragments; the rest are constants.
-__device__ __forceinline__ void vtile_offsets(int lane, uint32_t (&off)[2]) {
+// The per-lane part of the address is one offset per channel block; the rest are constants.
+__device__ __forceinline__ void vtile_offsets(int lane, uint32_t (&off)[4]) {
   const int j = lane & 15, t = j >> 2, c = j & 3;
   const int g = lane >> 5, half = (lane >> 4) & 1;
 #pragma unroll
-  for (int odd = 0; odd < 2; ++odd) {
-    const int q = 4 * odd + 2 * half + (c >> 1);
-    off[odd] = (uint32_t)((4 * g + t) * kHeadDim + 8 * (q ^ (2 * t)) + 4 * (c & 1));
+  for (int dblk = 0; dblk < 4; ++dblk) {
+    const int q = 4 * dblk + 2 * half + (c >> 1);
+    off[dblk] = (uint32_t)((4 * g + t) * kHeadDim + 8 * (q ^ (4 * t)) + 4 * (c & 1));
   }
 }
-__device__ __forceinline__ bf16x8 vtile_frag(const uint16_t *lds_tile, const uint32_t (&off)[2], int dblk, int ks) {
-  const uint16_t *p = lds_tile + off[dblk & 1] + 16 * ks * kHeadDim + 64 * (dblk >> 1);
+__device__ __forceinline__ bf16x8 vtile_frag(const uint16_t *lds_tile, const uint32_t (&off)[4], int dblk, int ks) {
+  const uint16_t *p = lds_tile + off[dblk] + 16 * ks * kHeadDim;
   const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(p));
   const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(p + 8 * kHeadDim));
   Frag8 f;
