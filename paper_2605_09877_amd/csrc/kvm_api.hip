@@ -920,7 +920,13 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     const double copy_us = (double)dv.U * (double)m_max * (double)d * (double)es * 4.0 / 4.0e6;  // at ~4 TB/s
     const int forced = st->dbg[KVM_DEBUG_PREFILL_SCHEDULE];  // 1 serial, 2 pipelined: for comparisons
     // (and a call of a few chunks has nothing to pipeline: the events would cost more than they buy)
-    const bool serial = forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4);
+    // States without grouped launches (fp32, head_dim 64, odd blocks) pay the events for every chunk, some 20 us of it,
+    // and gain the shorter of a chunk's fold and its attention: with the block's similarity (C x rows x d) small both
+    // are a few launches of 5 to 10 us.  Serial against pipelined, us per call (blocks, rows): fp32 d 64 2 units
+    // (64, 64) 318 / 540, bf16 d 64 8 units (256, 256) 660 / 900, fp32 d 64 1 unit (256, 300: 20 MB) 402 / 450; but fp32
+    // d 128 1 unit (256, 300: 39 MB) 596 / 533, bf16 d 64 8 units (512, 1000: 66 MB) 1180 / 985.
+    const bool small_chunks = st->group == 1 && (double)C * (double)m_max * (double)d * (double)es <= 24.0e6;
+    const bool serial = forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks);
     if (serial) {
       for (const Chunk &ch : plan) {
         AttnArgs a;
