@@ -45,13 +45,15 @@ struct kvm_state {
   bool part_clean = false;  // the decode counters (Dev::part_cnt) have been zeroed
   uint32_t xchg = 2;
   int32_t *xerr_host = nullptr, *xerr_dev = nullptr;
+  int xerr_slot = -1;   // which of the devices' error words it is, -1: an allocation of the state's own
   // kvm_debug_set knobs (0 = the library's own choice)
   int dbg[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   int group = 1;      // chunks per attention launch in prefill; the readout has 2 * group slots
   // prefill pipeline: folds run ahead on a library-owned stream, attention follows in groups
   int64_t inplace = 0;  // folds done in place so far: version v lives in slot (v - inplace) mod NS
   static constexpr int kMaxChains = 2;
-  hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};
+  hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};   // on loan from the device's idle ones (take_stream)
+  int stream_dev = -1;
   hipEvent_t fold_done = nullptr;       // of the latest fold on a caller's stream whose workgroups wait for each other
   std::vector<hipEvent_t> sync_events;  // untimed events, reused call after call
   size_t sync_used = 0;
@@ -450,6 +452,95 @@ hipEvent_t keep_waiting_event(const kvm_state *st) {
   return kept;
 }
 
+// The library's streams go from state to state.  A training step makes a state, runs it forward and backward and
+// drops it: making two streams took 0.2 to 0.4 ms of host time each, dropping them 0.15 ms and a wait for the
+// device, of the 0.41 ms that a step on 43 tokens took.  At most kIdleStreams per device are kept.  Work that a
+// dropped state left on one only delays the next state's; it is ordered before that and depends on
+// nothing enqueued later.  A stream that is still part of a capture is destroyed as before.
+struct IdleStreams {
+  static constexpr int kMost = 8;
+  std::mutex lock;
+  hipStream_t idle[kMost];
+  int n = 0;
+};
+IdleStreams g_idle_streams[kMaxDevices];
+hipError_t take_stream(kvm_state *st, hipStream_t *out) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  st->stream_dev = dev;
+  if (dev < kMaxDevices) {
+    IdleStreams &p = g_idle_streams[dev];
+    std::lock_guard<std::mutex> hold(p.lock);
+    if (p.n > 0) {
+      *out = p.idle[--p.n];
+      return hipSuccess;
+    }
+  }
+  return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
+}
+void give_stream(int dev, hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (dev >= 0 && dev < kMaxDevices && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+    IdleStreams &p = g_idle_streams[dev];
+    std::lock_guard<std::mutex> hold(p.lock);
+    if (p.n < IdleStreams::kMost) {
+      p.idle[p.n++] = s;
+      return;
+    }
+  }
+  (void)hipStreamDestroy(s);
+}
+
+// Error words (host memory the device can write): a state takes one of a device's kWords and gives it back; one
+// block of host memory per device, made once.  A launch of a dropped state that is still running may raise
+// its word for the next holder: it does so only when its workgroups waited for seconds in vain, and then
+// an error is due there as well.  With no word left a state has its own allocation.
+struct ErrorWords {
+  static constexpr int kWords = 64;
+  std::mutex lock;
+  int32_t *host = nullptr, *dev = nullptr;
+  uint64_t used = 0;
+};
+ErrorWords g_error_words[kMaxDevices];
+int take_error_word(kvm_state *st) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  if (dev < kMaxDevices) {
+    ErrorWords &p = g_error_words[dev];
+    std::lock_guard<std::mutex> hold(p.lock);
+    if (!p.host) {
+      int32_t *h = nullptr;
+      HIP_TRY(hipHostMalloc((void **)&h, ErrorWords::kWords * sizeof(int32_t), hipHostMallocMapped));
+      HIP_TRY(hipHostGetDevicePointer((void **)&p.dev, h, 0));
+      p.host = h;
+    }
+    if (p.used != ~(uint64_t)0) {
+      const int i = __builtin_ctzll(~p.used);
+      p.used |= (uint64_t)1 << i;
+      st->xerr_slot = dev * ErrorWords::kWords + i;
+      st->xerr_host = p.host + i;
+      st->xerr_dev = p.dev + i;
+    }
+  }
+  if (!st->xerr_host) {
+    HIP_TRY(hipHostMalloc((void **)&st->xerr_host, sizeof(int32_t), hipHostMallocMapped));
+    HIP_TRY(hipHostGetDevicePointer((void **)&st->xerr_dev, st->xerr_host, 0));
+  }
+  *st->xerr_host = 0;
+  return KVM_OK;
+}
+void give_error_word(kvm_state *st) {
+  if (!st->xerr_host) return;
+  if (st->xerr_slot < 0) {
+    (void)hipHostFree(st->xerr_host);
+    return;
+  }
+  ErrorWords &p = g_error_words[st->xerr_slot / ErrorWords::kWords];
+  std::lock_guard<std::mutex> hold(p.lock);
+  p.used &= ~((uint64_t)1 << (st->xerr_slot % ErrorWords::kWords));
+}
+
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ull;
 }
@@ -482,9 +573,8 @@ int fused_run(kvm_state *st, bool in_place, hipStream_t stream, kvm::FoldRunArgs
   run.err = nullptr;
   if (run.split > 1) {
     if (!st->xerr_host) {
-      HIP_TRY(hipHostMalloc((void **)&st->xerr_host, sizeof(int32_t), hipHostMallocMapped));
-      *st->xerr_host = 0;
-      HIP_TRY(hipHostGetDevicePointer((void **)&st->xerr_dev, st->xerr_host, 0));
+      const int rc = take_error_word(st);
+      if (rc != KVM_OK) return rc;
     }
     if (!st->xtab_clean) {
       hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, stream, st->xtab, st->xtab_bytes / 8);
@@ -799,8 +889,8 @@ int kvm_state_destroy(kvm_state *st) {
       if (e != kept) (void)hipEventDestroy(e);
     if (st->fold_done && st->fold_done != kept) (void)hipEventDestroy(st->fold_done);
     for (hipStream_t fs : st->fold_streams)
-      if (fs) (void)hipStreamDestroy(fs);
-    if (st->xerr_host) (void)hipHostFree(st->xerr_host);
+      if (fs) give_stream(st->stream_dev, fs);
+    give_error_word(st);
   }
   delete st;
   return KVM_OK;
@@ -1003,7 +1093,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // memory keys of a run, which depend on k alone, are computed while the run before it folds.
   const int n_streams = fused_folds ? 2 : n_chains;
   for (int c2 = 0; c2 < n_streams; ++c2) {
-    if (!st->fold_streams[c2]) HIP_TRY(hipStreamCreateWithFlags(&st->fold_streams[c2], hipStreamNonBlocking));
+    if (!st->fold_streams[c2]) HIP_TRY(take_stream(st, &st->fold_streams[c2]));
     fstream[c2] = st->fold_streams[c2];
     if (c2 < n_chains) cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
   }
@@ -1517,7 +1607,7 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   kvm::BwdStreams x;
   if (on_mfma) {
     for (hipStream_t &fs : st->fold_streams)
-      if (!fs) HIP_TRY(hipStreamCreateWithFlags(&fs, hipStreamNonBlocking));
+      if (!fs) HIP_TRY(take_stream(st, &fs));
     x.side = st->fold_streams[0];
     x.side2 = st->fold_streams[1];
     st->sync_used = 0;
