@@ -373,7 +373,7 @@ int heads_together(const Dev &dv) {
 // a chain of memory round trips; the shares are at least one round of the loop.  Their results must
 // fit the state's scratch (gq heads' d sums and two words each).
 int shares_for(const Dev &dv, int gq, int n_groups, int keys, int round) {
-  if (n_groups >= kShareGroups) return 1;
+  if (n_groups > kShareGroups) return 1;
   const int64_t room = dv.kbar_bytes / (gq * (dv.d * 4 + 8));
   int s = (int)(room < kSplitWorkgroups ? room : kSplitWorkgroups) / n_groups;
   const int most = (keys + round - 1) / round;

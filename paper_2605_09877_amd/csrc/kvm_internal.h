@@ -136,7 +136,10 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
 hipError_t launch_score_mfma(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st);
 // attn_rows.hip
 constexpr int kSplitWorkgroups = 1024;  // workgroups of a decode launch whose keys are shared
-constexpr int kShareGroups = 512;      // from this many (sequence, head group) pairs on they are not
+// Up to this many (sequence, head group) pairs they are.  A step alone against shared, us: 128 pairs 10.7 / 10.8 (158 rows) to
+// 27.5 / 20.3 (1200 rows), 96 pairs of four heads 16.7 / 13.8 to 45.9 / 27.3; but 256 pairs 11.9 / 14.5 to 30.5 / 33.1, of
+// four heads 18.0 / 26.0 to 47.0 / 47.3.
+constexpr int kShareGroups = 128;
 hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st);
 // One decode step over sequences of several states (kvm_decode_step_multi): per sequence, where
 // its arrays start (its first KV head) and where it stands.
