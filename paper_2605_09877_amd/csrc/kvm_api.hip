@@ -48,6 +48,7 @@ struct kvm_state {
   int xerr_slot = -1;   // which of the devices' error words it is, -1: an allocation of the state's own
   // kvm_debug_set knobs (0 = the library's own choice)
   int dbg[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int64_t blocks = 0;  // what the state was made for, in blocks (kvm_state_grow does not change it)
   int group = 1;      // chunks per attention launch in prefill; the readout has 2 * group slots
   // prefill pipeline: folds run ahead on a library-owned stream, attention follows in groups
   int64_t inplace = 0;  // folds done in place so far: version v lives in slot (v - inplace) mod NS
@@ -382,7 +383,12 @@ int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hip
 // 256-token blocks: 8.4 ms for 65536 tokens against 10.6 with a kernel per step).  Otherwise a fold
 // is a kernel per step: with tiles that stream the shared launch lost (64 units of 1024 rows, 4
 // workgroups each: 13 ms for 32768 tokens against 10.9); so it is when kvm_debug_set asks for it.
-constexpr int kFusedMinUnits = 256;
+// Sharing is for states of 8 units and more, blocks of up to 256 tokens, and room for more than four blocks.  Us per call, a
+// kernel per step against shared: 2 units, 10 blocks of 256 tokens 208 / 247, of 512 256 / 316; 32 units, 10 blocks of 512
+// 425 / 461; 8 units, 38 blocks of 512 1007 / 1057; 8 units, prompts of 2 and 3 blocks of 128 (one or two folds, each a run of
+// its own) 49 / 53 and 77 / 87.  The choice holds for a state's life, prompt and generation alike: the two paths' readout
+// rows may differ in a last bit, and a state that is exported and imported goes on as it would have.
+constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareMinBlocks = 5;
 // Workgroups per unit on that path: 0 = a kernel per step.
 int fold_split(const kvm_state *st) {
   if (!st->mfma) return 0;
@@ -394,6 +400,7 @@ int fold_split(const kvm_state *st) {
   auto can_share = [&](int n) { return n > 1 && n <= most && kvm::fold_fused_fits(st->dv, n); };
   if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
   if (path == 1 || U >= kFusedMinUnits) return whole;
+  if (U < kShareMinUnits || st->dv.C > kShareMaxBlock || st->blocks < kShareMinBlocks) return 0;
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
 bool use_fused(const kvm_state *st) { return fold_split(st) > 0; }
@@ -871,6 +878,7 @@ int kvm_state_init(kvm_state **out, const kvm_config *cfg, void *dev_buf, size_t
     st->xtab_bytes = l.xtab_bytes;
     st->xtab_clean = false;
   }
+  st->blocks = (max_tokens + cfg->chunk_len - 1) / cfg->chunk_len;
   st->mfma = use_mfma(*cfg);
   st->group = group_of(*cfg);
   *out = st;

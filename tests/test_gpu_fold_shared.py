@@ -29,6 +29,16 @@ def make(sy, chunk, units, seq, budget, **kw):
                      **kind, **kw)
 
 
+def widest(w):
+    """The most workgroups that may share a unit's rows, forced: few units and long blocks are not shared by default."""
+    pkg, b, sy = kit()
+    tiles = pkg.state_for(w, device=DEV, **sy.make_params(w, DEV, plain=True)).capacity // 64
+    units, n = w.batch * w.n_kv_heads, 1
+    while 2 * n <= 16 and units * 2 * n <= 256 and tiles >= 2 * n:
+        n *= 2
+    return {b.KVM_DEBUG_FOLD_SPLIT: n}
+
+
 def run(w, knobs, decode_tail=0):
     pkg, binding, sy = kit()
     q, k, v = sy.make_qkv(w, DEV)
@@ -56,7 +66,7 @@ def same(a, b):
 
 
 STEP = (64, 64, 80, 81, 98, 162, 227, 227, 355, 355)   # appends of 16, 1, 17, 64, 65, 0, 128 rows at 128-token blocks
-CASES = {   # chunk, units, tokens, budget, other fields, forced split (0: the library's choice)
+CASES = {   # chunk, units, tokens, budget, other fields, forced split (0: the widest)
     "one tile each": (64, 2, 64 * 24, 1024, {}, 0),
     "four tiles each": (256, 64, 256 * 8, 1024, {}, 0),
     "sixteen workgroups": (256, 1, 256 * 9, 1024, {}, 16),
@@ -75,7 +85,7 @@ def test_shared_rows_agree_with_a_kernel_per_step(case):
     _, b, sy = kit()
     chunk, units, seq, budget, kw, split = CASES[case]
     w = make(sy, chunk, units, seq, budget, **kw)
-    knobs = {b.KVM_DEBUG_FOLD_SPLIT: split} if split else {}
+    knobs = {b.KVM_DEBUG_FOLD_SPLIT: split} if split else widest(w)
     got = run(w, knobs)
     assert got[0].fold_path == 1
     same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
@@ -86,7 +96,7 @@ def test_folds_in_place(tail):
     _, b, sy = kit()
     w = make(sy, 128, 2, 128 * 9, 512)
     w = sy.shrink(w, seq=w.seq // 128 * 128)
-    same(run(w, {}, tail), run(w, {b.KVM_DEBUG_FOLD_PATH: 2}, tail))
+    same(run(w, widest(w), tail), run(w, {b.KVM_DEBUG_FOLD_PATH: 2}, tail))
 
 
 def test_captured_step():
@@ -99,6 +109,8 @@ def test_captured_step():
     res = []
     for captured in (False, True):
         st = pkg.state_for(w, device=DEV, **p)
+        for knob, value in widest(w).items():
+            st.debug_set(knob, value)
         st.prefill(q[:, :n - 127].contiguous(), k[:, :n - 127].contiguous(), v[:, :n - 127].contiguous())
         one = lambda t: (q[:, t].contiguous(), k[:, t].contiguous(), v[:, t].contiguous())
         for t in range(n - 127, n):
@@ -145,3 +157,13 @@ def test_two_threads():
     for o in out:
         assert o is not None
         same(o, want)
+
+
+@pytest.mark.parametrize("chunk,units,blocks,path", [(128, 8, 5, 1), (128, 7, 5, 2), (128, 8, 4, 2), (512, 8, 6, 2)])
+def test_states_that_share_by_default(chunk, units, blocks, path):
+    """The edges of the default: 8 units, 256-token blocks, five blocks; results as a kernel per step either way."""
+    _, b, sy = kit()
+    w = make(sy, chunk, units, chunk * blocks, 2 * chunk)
+    got = run(w, {})
+    assert got[0].fold_path == path
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
