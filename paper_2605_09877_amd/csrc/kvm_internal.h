@@ -155,7 +155,12 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st);
 // attn_mfma.hip: prompts in bf16, d = 128 or 64, blocks of a multiple of 64 tokens (tiles of 64 keys neither cross
 // from the ring into the call's keys nor wrap in the ring); everything else is the row kernel's
-inline bool attention_on_mfma(const Dev &dv) { return dv.io == 1 && (dv.d == 128 || dv.d == 64) && dv.C % 64 == 0; }
+// With d = 64 and few queries in a chunk's launch the row kernel, a workgroup per query and head, still fills more of the
+// chip: 8192 of them 97 us against 19 on the matrix cores, but 1024 (one sequence, 2 heads, 512-token blocks) 23 us
+// less in a training call of 455 us.
+inline bool attention_on_mfma(const Dev &dv) {
+  return dv.io == 1 && dv.C % 64 == 0 && (dv.d == 128 || (dv.d == 64 && (int64_t)dv.B * dv.Hq * dv.C > 1024));
+}
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st);
 
 // backward.hip: the backward pass of a whole-sequence prefill that started from an empty state.

@@ -21,11 +21,13 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("signs", [(1, 1), (-1, 1), (1, -1)])
 def test_prefill_against_the_oracle(C, rows, T, heads, split, signs):
     from paper_2605_09877_amd import synth as sy
-    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64,
+    batch = 1024 // (C * heads[0]) + 1   # the fewest queries a launch takes to the matrix cores
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64,
                   rope_dims=16, seq=T, chunk_len=C, budget_fixed=rows)
 
     def tweak(params):
         params["tau_state"] *= signs[0]
         params["tau_bswa"] *= signs[1]
 
-    run_prefill_case(w, plain=False, split=split, tweak=tweak, case=f"head_dim_64[{C},{rows},{T},{heads},{signs}]")
+    run_prefill_case(w, plain=False, split=split, tweak=tweak, units=[(0, 0), (batch - 1, heads[1] - 1)],
+                     case=f"head_dim_64[{C},{rows},{T},{heads},{signs}]")
