@@ -680,16 +680,24 @@ __device__ __forceinline__ Row8 normalised16(const Dev &dv, const double (&sk)[8
   return r;
 }
 
+// Squared norm of a row of values, added up in the order of the kernel-per-step path (write_readout, create: pairs of
+// adjacent channels, then a balanced tree over the pairs): both paths have the same fp32 bits, and with them
+// the same readout.
+__device__ __forceinline__ float norm2_16(const float (&x)[8]) {
+  float half[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float *y = x + 4 * q;
+    half[q] = group_sum<16>(fmaf(y[1], y[1], y[0] * y[0]) + fmaf(y[3], y[3], y[2] * y[2]));
+  }
+  return half[0] + half[1];
+}
 // The readout row of value sums sv and radius rho whose normalised key is `khat`.  Rounding to bf16
 // is the hardware's (nearest even).
 __device__ __forceinline__ void store_readout16(const Dev &dv, int slot, int64_t ro, int c16, const Row8 &khat,
                                                 const float (&sv)[8], float rho) {
   constexpr int D = kHeadDim;
-  float nn = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) nn += sv[e] * sv[e];
-  // (hardware root and reciprocal, an ulp of fp32 each: far below the bf16 the result is rounded to)
-  const float vs = rho * __builtin_amdgcn_rcpf(fmaxf(__builtin_amdgcn_sqrtf(group_sum<16>(nn)), dv.norm_eps));
+  const float vs = rho / fmaxf(sqrtf(norm2_16(sv)), dv.norm_eps);
   Row8 v;
 #pragma unroll
   for (int q = 0; q < 2; ++q)
@@ -764,10 +772,7 @@ __device__ __forceinline__ void create_rows(const Dev &dv, const Ctx<NW> &cx, co
     if (fresh) store_tile_row(cx.s_fresh(), a - a_lo, c16, khat);
     if (!own) continue;
     const int64_t ro = (int64_t)cx.u * dv.Mcap + m + a;
-    float nn = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) nn += vf[e] * vf[e];
-    const float rho = sqrtf(group_sum<16>(nn));
+    const float rho = sqrtf(norm2_16(vf));
     store_sums(dv, ro, c16, sk, vf);
     if (c16 == 0) {
       dv.rho[ro] = rho;
