@@ -236,20 +236,18 @@ __global__ __launch_bounds__(64 * kUnfoldWaves) void bwd_unfold_kernel(Bwd a, in
       // the row as the earlier version had it: its sums, and its readout as the forward made it
       // (rows that the fold left alone keep the readout they have)
       double sm = 0.0;
-      float nn = 0.f;
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         a.wsK[ro + lane * CPL + c] = sk[c];
         a.wsV[ro + lane * CPL + c] = sv[c];
         sm += sk[c];
-        nn += sv[c] * sv[c];
       }
       const double mean = wave_sum(sm) / (double)D;
       double qq = 0.0;
 #pragma unroll
       for (int c = 0; c < CPL; ++c) qq += (sk[c] - mean) * (sk[c] - mean);
       const double rden = 1.0 / sqrt(wave_sum(qq) / (double)D + (double)dv.ln_eps);
-      const float vs = dv.rho[(int64_t)u * dv.Mcap + row] / fmaxf(sqrtf(wave_sum(nn)), dv.norm_eps);
+      const float vs = dv.rho[(int64_t)u * dv.Mcap + row] / fmaxf(sqrtf(wave_sum(lane_norm2<CPL>(sv))), dv.norm_eps);
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         const int ch = lane * CPL + c;
@@ -274,20 +272,19 @@ __global__ __launch_bounds__(256) void bwd_readout_kernel(Bwd a, int m) {
   if (row >= m) return;
   const int64_t ro = ((int64_t)u * dv.Mcap + row) * D;
   double sk[CPL], s = 0.0;
-  float sv[CPL], nn = 0.f;
+  float sv[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     sk[c] = a.wsK[ro + lane * CPL + c];
     sv[c] = a.wsV[ro + lane * CPL + c];
     s += sk[c];
-    nn += sv[c] * sv[c];
   }
   const double mean = wave_sum(s) / (double)D;
   double qq = 0.0;
 #pragma unroll
   for (int c = 0; c < CPL; ++c) qq += (sk[c] - mean) * (sk[c] - mean);
   const double rden = 1.0 / sqrt(wave_sum(qq) / (double)D + (double)dv.ln_eps);
-  const float vs = dv.rho[(int64_t)u * dv.Mcap + row] / fmaxf(sqrtf(wave_sum(nn)), dv.norm_eps);
+  const float vs = dv.rho[(int64_t)u * dv.Mcap + row] / fmaxf(sqrtf(wave_sum(lane_norm2<CPL>(sv))), dv.norm_eps);
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int ch = lane * CPL + c;

@@ -48,10 +48,7 @@ __device__ __forceinline__ void write_readout(const Dev &dv, int slot, int u, in
   // one fp64 reciprocal per row; (x - mean) * rden differs from (x - mean) / den by an ulp of
   // fp64 at most, far below what the rounding to the I/O dtype can see
   const double rden = 1.0 / sqrt(wave_sum(q) / (double)D + (double)dv.ln_eps);
-  float nn = 0.f;
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) nn += sv[c] * sv[c];
-  const float nrm = sqrtf(wave_sum(nn));
+  const float nrm = sqrtf(wave_sum(lane_norm2<CPL>(sv)));
   const float vs = rho / fmaxf(nrm, dv.norm_eps);
   T *kh = (T *)dv.khat + slot * dv.slot_elems + ((int64_t)u * dv.Mcap + row) * D;
   T *vh = (T *)dv.vhat + slot * dv.slot_elems + ((int64_t)u * dv.Mcap + row) * D;

@@ -687,8 +687,8 @@ __device__ __forceinline__ float norm2_16(const float (&x)[8]) {
   float half[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const float *y = x + 4 * q;
-    half[q] = group_sum<16>(fmaf(y[1], y[1], y[0] * y[0]) + fmaf(y[3], y[3], y[2] * y[2]));
+    const float y[2][2] = {{x[4 * q], x[4 * q + 1]}, {x[4 * q + 2], x[4 * q + 3]}};
+    half[q] = group_sum<16>(lane_norm2<2>(y[0]) + lane_norm2<2>(y[1]));
   }
   return half[0] + half[1];
 }

@@ -157,6 +157,17 @@ __device__ __forceinline__ V wave_sum(V x) {
   return group_sum<64>(x);
 }
 
+// A lane's share of a row's squared norm.  The readout's scale rests on it: every kernel that makes a readout (either
+// fold path, the refresh, the backward pass) rounds the same way, whatever the compiler would contract.
+template <int N>
+__device__ __forceinline__ float lane_norm2(const float (&x)[N]) {
+  static_assert(N == 1 || N == 2, "channels per lane");
+  if constexpr (N == 2)
+    return fmaf(x[0], x[0], x[1] * x[1]);
+  else
+    return x[0] * x[0];
+}
+
 template <typename V>
 __device__ __forceinline__ V wave_max(V x) {
 #pragma unroll
