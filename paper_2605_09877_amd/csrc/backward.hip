@@ -646,7 +646,9 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
   // D = dout . out per query.  The matrix-core dq kernel forms it for its own queries, which saves a pass over
   // out and dout but puts dq ahead of the state rows in the chain.
   const bool delta_first = !on_mfma || (use_side && delta_ahead(dv, chunks, n_chunks));
-  if (delta_first)
+  if (delta_first && on_mfma)
+    BWD_TRY(launch_delta_mfma(a, q_rows, st));   // (the order of dq's own sum: D is the same whoever forms it)
+  else if (delta_first)
     BWD_DISPATCH(dv, bwd_delta_kernel, dim3((unsigned)((q_rows + 3) / 4)), dim3(256), st, a.out, a.dout, a.delta, q_rows);
   a.delta_ready = delta_first ? 1 : 0;
   bool state_busy = false, window_busy[2] = {false, false};

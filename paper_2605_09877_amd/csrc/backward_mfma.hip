@@ -111,6 +111,41 @@ __device__ __forceinline__ bf16x8 ttile_frag_at(uint32_t addr0, int dblk, int ks
   return f.v;
 }
 
+// Half of a query's D = dout . out (the lane's channels; the lane 32 away has the others).  One order of the sum
+// for whoever forms D.
+__device__ __forceinline__ float delta_half(const uint16_t *o_row, const bf16x8 (&dout)[8], int g) {
+  float part = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    const uint4 ov = *reinterpret_cast<const uint4 *>(o_row + 16 * ks + 8 * g);
+    Frag8 f;
+    f.v = dout[ks];
+    float of[8], df[8];
+    unpack16<bf16_t>(ov, of);
+    unpack16<bf16_t>(f.q, df);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part = fmaf(of[e], df[e], part);
+  }
+  return part;
+}
+
+// D of every query ahead of the walk: 32 queries per wave, two lanes each.
+__global__ __launch_bounds__(256) void bwd_delta_mfma_kernel(const uint16_t *out, const uint16_t *dout, float *delta,
+                                                             int64_t rows) {
+  const int lane = threadIdx.x & 63, g = lane >> 5;
+  const int64_t row = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32 + (lane & 31);
+  const int64_t at = (row < rows ? row : rows - 1) * kHeadDim;
+  bf16x8 d[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    Frag8 f;
+    f.q = *reinterpret_cast<const uint4 *>(dout + at + 16 * ks + 8 * g);
+    d[ks] = f.v;
+  }
+  const float sum = xhalf_sum(delta_half(out + at, d, g));
+  if (row < rows && g == 0) delta[row] = sum;
+}
+
 struct MfmaChunk {
   int64_t cs, wb;   // chunk start, first window position
   int32_t nq, m;    // queries of the chunk, state rows it saw
@@ -578,23 +613,14 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     const int qc = col_ok ? colq : c.nq - 1;
     const int64_t qrow = ((int64_t)b * a.T + c.cs + qc) * dv.Hq + hq_sta;
     lse2_col = a.lse[qrow] * kLog2e;
-    // D = dout . out of the lane's query: the lane has half of the dout row already; the other
-    // roles, which run after this one, read D from memory
-    const uint16_t *o_row = (const uint16_t *)a.out + qrow * D;
-    float part = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const uint4 ov = *reinterpret_cast<const uint4 *>(o_row + 16 * ks + 8 * g);
-      Frag8 f;
-      f.v = sv[ks];
-      float of[8], df[8];
-      unpack16<bf16_t>(ov, of);
-      unpack16<bf16_t>(f.q, df);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) part = fmaf(of[e], df[e], part);
+    // D = dout . out of the lane's query: the lane has half of the dout row already.  Role KV, which
+    // runs after this one when D is formed here, reads it from memory
+    if (a.delta_ready) {
+      d_col = a.delta[qrow];
+    } else {
+      d_col = xhalf_sum(delta_half((const uint16_t *)a.out + qrow * D, sv, g));
+      if (col_ok && g == 0) a.delta[qrow] = d_col;
     }
-    d_col = xhalf_sum(part);
-    if (col_ok && g == 0 && !a.delta_ready) a.delta[qrow] = d_col;
   }
 
   // the stationary vectors are in registers from here on (the compiler does not count the tile
@@ -807,6 +833,12 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
 }  // namespace
 
 bool backward_on_mfma(const Dev &dv) { return dv.io == 1 && dv.d == kHeadDim && dv.C % 64 == 0; }
+
+hipError_t launch_delta_mfma(const Bwd &a, int64_t rows, hipStream_t st) {
+  hipLaunchKernelGGL(bwd_delta_mfma_kernel, dim3((unsigned)((rows + 127) / 128)), dim3(256), 0, st, (const uint16_t *)a.out,
+                     (const uint16_t *)a.dout, a.delta, rows);
+  return hipGetLastError();
+}
 
 // The launches of one chunk: dq (and the temperature sums); dk and dv of its own tokens and of the state rows.
 hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,

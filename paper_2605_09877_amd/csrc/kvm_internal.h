@@ -192,7 +192,7 @@ struct Bwd {
   float *dk_acc, *dv_acc;
   int32_t ring_rows;
   float *delta;          // [B, T, Hq] sum over channels of dout * out
-  int32_t delta_ready;   // it is there already: the dq role does not write it
+  int32_t delta_ready;   // it is there already: the dq role reads it
   float *P, *dS;         // [U, G, C, Mcap + L] probabilities and logit adjoints of one chunk
   double *par64;         // [2 * Hkv * d + 2 * Hq] fp64 accumulators of dgamma, dbeta, dtau_state, dtau_bswa
 };
@@ -214,6 +214,8 @@ struct BwdStreams {
 hipError_t run_backward(const Bwd &a, const BwdChunk *chunks, int n_chunks, hipStream_t st, const BwdStreams &x);
 // backward_mfma.hip (bf16, d = 128): one chunk's dq, dk, dv and readout adjoint on the matrix cores
 bool backward_on_mfma(const Dev &dv);
+// D = dout . out of `rows` queries, ahead of the walk
+hipError_t launch_delta_mfma(const Bwd &a, int64_t rows, hipStream_t st);
 enum { kRoleDQ = 0, kRoleKV = 1 };
 enum { kSecBoth = 0, kSecWindow = 1, kSecState = 2 };
 // one role of the matrix-core tile kernel over one chunk; role KV: all key workgroups, or only

@@ -2,6 +2,7 @@
 one and several heads per KV head, D formed inside dq and by a pass ahead of the walk (256-token blocks and few
 workgroups).  Oracle and bars of test_gpu_backward."""
 import pytest
+import torch
 
 from test_gpu_backward import run_backward_case
 
@@ -21,3 +22,18 @@ def test_tile_edges(C, rows, T, heads):
     w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=heads[0], n_kv_heads=heads[1], seq=T, chunk_len=C,
                   budget_fixed=rows)
     run_backward_case(w, plain=False)
+
+
+def test_gradients_do_not_depend_on_the_batch():
+    """Alone a sequence has D formed ahead of the walk, among 65 inside dq: the same gradients to the bit."""
+    import paper_2605_09877_amd as kvm
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    q, k, v, dout = (torch.randn(65, 256 * 3 + 1, 2, 128, generator=gen, device="cuda:0").bfloat16() for _ in range(4))
+
+    def grads(n):
+        leaves = [x[:n].contiguous().requires_grad_(True) for x in (q, k, v)]
+        out = kvm.kvm_attention(*leaves, chunk_len=256, rope_dims=32, budget_fixed=256)
+        return (out.detach(),) + torch.autograd.grad(out, leaves, dout[:n].contiguous())
+
+    for one, many in zip(grads(1), grads(65)):
+        assert torch.equal(one[0], many[0])
