@@ -245,14 +245,28 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     qt0 = (!sta_state && wg_first > 0) ? wg_first / kRows : 0;
     per_head = n_qt - qt0;
     n_tiles = G * per_head;
-    // Order of the streamed tiles: the last query tile first, and for each query tile the heads
-    // of the group one after the other.  The workgroups of a unit that share a stream differ in
+    // Order of the streamed tiles: the last 64 queries first, for each 64 the heads of the group one after
+    // the other, and a head's two tiles in ascending order (next_streamed).  The workgroups of a unit that share a stream differ in
     // where their first visible tile lies, not in where the last one does: walking backwards
     // they all start on the same tile and stay in step, so that one of them brings a tile into
     // the XCD's L2 and the others find it there (ascending, head by head, they ran up to six
     // tiles apart and the stream was fetched more than twice over).
   }
   n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+  // role KV: head and 32-query tile asked for last.  A tile without a partner (qt0 is even: workgroups start every 128
+  // keys) comes first.  dk and dv are sums in this order: that of 64-query tiles, with the same bits.
+  int str_gq = 0, str_qt = (qt0 + per_head - 1) & ~1;
+  auto next_streamed = [&]() {
+    if (!(str_qt & 1) && str_qt + 1 < qt0 + per_head) {
+      ++str_qt;
+    } else {
+      str_qt &= ~1;
+      if (++str_gq == G) {
+        str_gq = 0;
+        str_qt -= 2;
+      }
+    }
+  };
 
   uint32_t koff[8], toff[4][2];
   rtile_offsets(lane, koff);
@@ -281,12 +295,11 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
         valid = (int)(c.cs + c.nq - p0);
       }
     } else {
-      const int gq = it % G, qtile = qt0 + per_head - 1 - it / G;
-      const int64_t qrow = ((int64_t)b * a.T + c.cs + (int64_t)qtile * kRows) * dv.Hq + h * G + gq;
+      const int64_t qrow = ((int64_t)b * a.T + c.cs + (int64_t)str_qt * kRows) * dv.Hq + h * G + str_gq;
       xb = (const char *)a.q + qrow * D * 2;
       yb = (const char *)a.dout + qrow * D * 2;
       stride = (uint32_t)dv.Hq * D * 2;
-      valid = nq_str - qtile * kRows;
+      valid = nq_str - str_qt * kRows;
     }
     const uint32_t at = lds_addr + (uint32_t)(2 * (it & 1)) * (kTileE * 2);
     if constexpr (kKeysSta) {
@@ -311,17 +324,16 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     taus = (GlobalF32 *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
                            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x));
   }
-  auto fetch_rowsc = [&](int it) {
+  auto fetch_rowsc = [&]() {
     if constexpr (kKeysSta) {
       if (wave == 0) {
-        const int gq = it % G, qtile = qt0 + per_head - 1 - it / G;
         const int ln = (int)opaque((uint32_t)lane);
-        int r = qtile * kRows + (ln & 31);
+        int r = str_qt * kRows + (ln & 31);
         r = r < nq_str ? r : nq_str - 1;
-        const int64_t qrow = ((int64_t)b * a.T + c.cs + r) * dv.Hq + h * G + gq;
+        const int64_t qrow = ((int64_t)b * a.T + c.cs + r) * dv.Hq + h * G + str_gq;
         const float *src = ln < 32 ? a.lse : a.delta;
         rs = src[qrow];
-        if (taus) rs_tau = taus[h * G + gq];
+        if (taus) rs_tau = taus[h * G + str_gq];
       }
     }
   };
@@ -356,9 +368,11 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
     store_rowsc(it);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    [[maybe_unused]] const int qtile = str_qt;
     if (it + 1 < n_tiles) {
+      if constexpr (kKeysSta) next_streamed();
       issue_tile(it + 1);
-      fetch_rowsc(it + 1);
+      fetch_rowsc();
     }
     const uint16_t *X = lds + (2 * decltype(parity)::value) * kTileE;
     const uint16_t *Y = X + kTileE;
@@ -380,7 +394,6 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
         need_mask = p0rel + kTileKeys - 1 > wave_q0;
       }
     } else {
-      const int qtile = qt0 + per_head - 1 - it / G;
       tile_state = sta_state;
       const int row_pos0 = qtile * kRows;  // the tile's first query, relative to the chunk start
       hi_row = nq_str - 1 - row_pos0;          // rows beyond the last query are padding
@@ -597,7 +610,7 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
   // (short loops -- few streamed tiles per workgroup -- feel every round trip of the prologue).
   if (n_tiles > 0) {
     issue_tile(0);
-    fetch_rowsc(0);
+    fetch_rowsc();
   }
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) {
