@@ -24,9 +24,7 @@
  *    (KVM_ERR_ARG, KVM_ERR_STATE, KVM_ERR_CAPACITY, KVM_ERR_UNSUPPORTED, KVM_ERR_LIMIT) are detected
  *    before anything is enqueued: such a call leaves the state untouched.  KVM_ERR_HIP means a
  *    runtime call failed part-way: the streams are still joined back to the caller's, but the
- *    state's contents are undefined from then on (destroy it, or import a checkpoint).  The same
- *    code reports, on the next call on the state, that a fold kernel whose workgroups wait for
- *    each other (KVM_DEBUG_FOLD_SPLIT) ran into the time limit of such a wait.
+ *    state's contents are undefined from then on (destroy it, or import a checkpoint).
  *  - q and k arrive already prepared (normalised, partially RoPE-rotated on the first
  *    `rope_dims` channels) as the paper states at the end of "KVM weight preparation"; the
  *    library needs `rope_dims` only to zero the rotary sub-space of memory keys.
@@ -278,9 +276,11 @@ int kvm_state_import(kvm_state *st, const double *sK, const float *sV, const flo
  *   KVM_DEBUG_BACKWARD_PATH     1: attention adjoints on the vector ALU on every shape (it also
  *                               sizes kvm_backward_workspace_bytes: set it before asking)
  *   KVM_DEBUG_FOLD_SPLIT        1, 2, 4, 8 or 16: workgroups that share a unit's state rows on the
- *                               one-launch path (ignored where the shape does not allow it) */
+ *                               one-launch path (ignored where the shape does not allow it)
+ *   KVM_DEBUG_FOLD_PATIENCE     n: the workgroups that share a unit wait (n - 1) * 10 ns for all of
+ *                               them to have started before one takes the unit by itself */
 enum { KVM_DEBUG_FOLD_PATH = 0, KVM_DEBUG_FOLD_WAVES = 1, KVM_DEBUG_PREFILL_SCHEDULE = 2, KVM_DEBUG_FOLD_CHAINS = 3,
-       KVM_DEBUG_MERGE_COPY = 4, KVM_DEBUG_BACKWARD_PATH = 5, KVM_DEBUG_FOLD_SPLIT = 6, KVM_DEBUG_KNOBS = 8 };
+       KVM_DEBUG_MERGE_COPY = 4, KVM_DEBUG_BACKWARD_PATH = 5, KVM_DEBUG_FOLD_SPLIT = 6, KVM_DEBUG_FOLD_PATIENCE = 7, KVM_DEBUG_KNOBS = 8 };
 int kvm_debug_set(kvm_state *st, int knob, int value);
 
 /* Kernel timing for benchmarks (no passage of the paper: a measurement aid).  While enabled,

@@ -41,11 +41,15 @@
 // reads of the state it wrote itself, so the only data that crosses workgroups is each token's
 // partial winner: one exchange per fold through a small table in global memory.  An entry is one
 // 64-bit word (score, row, a 16-bit tag of the exchange it belongs to) written and read with relaxed
-// device-scope atomics: no fences, no flags beside the data; a reader spins on the tag, with a clock
-// limit that ends the wait and raises an error word instead of hanging.  The workgroups of a launch
-// must be able to be resident together (the host checks the grid against the chip and lets such
-// launches run one at a time); kernels that run beside it on other streams only delay a workgroup's
-// start, they never wait for this kernel.
+// device-scope atomics: no fences, no flags beside the data; a reader spins on the tag.
+//
+// Workgroups that wait for each other must all be running, and nothing promises that they are: there may be
+// fewer compute units than expected, or others' work on them.  So before any of them touches the
+// state they count themselves in (meet()), and when a unit's last one has not started within a time limit,
+// one of those that have takes the whole unit, as with one workgroup per unit, and the others leave,
+// late ones included.  Either way the fold's results are the same bits.  After that a workgroup waits for
+// running ones only, whose next exchange entry depends on nothing but entries already due: every wait ends, whatever
+// else the chip is doing.
 //
 // What bounds it: with shared rows, latency.  A fold of a 256-token block into some 300 rows (32 units x
 // 8 workgroups) takes 15 us without an append and 22 us with one, about 6 us more beside attention: an
@@ -71,8 +75,10 @@ constexpr int kNoRow = 0x7fffffff;
 constexpr int kTileBytes = kTileElems * 2;   // 16 KiB
 constexpr int kListMax = 16;                 // tokens of a row taken from its list in one go
 constexpr uint32_t kTokenBytes = 2 * kHeadDim * 2;   // memory key and value of a token
-// NW waves per workgroup; a stage of the K-hat stream is NW / 4 tiles, two stages are in LDS
+// NW waves per workgroup; a stage of the K-hat stream is NW / 4 tiles, two stages are in LDS.  A workgroup that takes
+// over a unit meant for several has the LDS of its share: stages of one tile, and the scratch is those two.
 __host__ __device__ constexpr int stage_tiles(int NW) { return NW / 4; }
+constexpr int kStageTaken = 1, kGatherTaken = (int)(2 * kStageTaken * kTileBytes / kTokenBytes);
 
 // LN_s parameters when the caller gave none (gamma = 1, beta = 0): read like given ones, so that
 // the kernels carry no per-element branches.
@@ -100,8 +106,8 @@ __device__ __forceinline__ bool beats(float sa, int ia, float sb, int ib) {
 //   then                int [local rows] last token pushed on the row's list or -1
 //   then (1-KiB bound)  scratch, one use after the other: the fresh tile (K-hat of the rows this fold creates); the
 //                       gathered tokens' memory keys and values
-//   then                K-hat tiles: this workgroup's own for the whole run (resident); otherwise a ring of 2 *
-//                       stage_tiles, which is the scratch as well (it is idle when that is needed)
+//   then                K-hat tiles: this workgroup's own for the whole run (resident); otherwise a ring of two
+//                       stages, which is the scratch as well (it is idle when that is needed)
 constexpr uint32_t kLdsCounters = 0, kLdsMerge = kLdsCounters + 32;
 __host__ __device__ constexpr uint32_t lds_tables(int NW) { return kLdsMerge + 3u * 4u * NW * 32; }
 __host__ __device__ constexpr uint32_t lds_fresh(int NW, int C, int own_tiles) {
@@ -118,6 +124,7 @@ struct Ctx {
   int u, tid, lane, wave;
   int part, split, shift;   // this workgroup's number among the unit's workgroups, how many they are, log2 of that
   bool resident;            // its K-hat tiles stay in LDS for the whole run
+  int stage;                // otherwise: tiles per stage of the ring, a power of two
   // the workgroup that owns a state row: 64-row tiles dealt round robin
   __device__ bool owns(int row) const { return ((row >> 6) & (split - 1)) == part; }
   __device__ int local(int row) const { return ((row >> (6 + shift)) << 6) | (row & 63); }
@@ -146,8 +153,9 @@ struct Ctx {
   __device__ int *s_cnt() const { return (int *)(smem + kLdsCounters); }
   __device__ unsigned char *s_merge() const { return smem + kLdsMerge; }
 };
-// counters: touched rows, near ties of the append, own merging tokens, a wait has given up, (stamps)
-enum { kCntRows = 0, kCntTies = 1, kCntOwn = 2, kCntGaveUp = 3, kCntStamps = 4 };
+// counters: touched rows, near ties of the append, own merging tokens, who folds the unit, (stamps)
+enum { kCntRows = 0, kCntTies = 1, kCntOwn = 2, kCntMeet = 3, kCntStamps = 4 };
+enum { kShared = 0, kWhole = 1, kLeave = 2 };   // with the others; this workgroup by itself; one of the others
 
 // Development aid (compiled in only with -DKVM_FOLD_STAMPS): the first workgroup leaves the clock
 // at its phase boundaries in the `creator` scratch, which this path does not use.
@@ -166,12 +174,14 @@ enum { kCntRows = 0, kCntTies = 1, kCntOwn = 2, kCntGaveUp = 3, kCntStamps = 4 }
 // ------------------------------------------------------------------------------------------------
 // The exchange after the scoring pass (split > 1): every workgroup of the unit publishes its own
 // winners and reads the others'; all of them end up with the same unit-wide result in LDS.
-// Table: [unit][exchange parity][workgroup][2][C] 64-bit words; word 0 of a token = (merge score,
+// Table, behind the arrival words: [unit][exchange parity][workgroup][2][C] 64-bit words; word 0 of a token = (merge score,
 // row in 16 bits, tag), word 1 = (append score, tag), the latter only from workgroups that own sink rows (elsewhere
 // every row may win, and the two scores are one).  A workgroup cannot be two exchanges ahead of
 // a sibling (it needs the sibling's entries of the exchange in between), so two parities suffice.
-// tag: the low 16 bits of the exchange's number, which the host never reuses within a state's life
-// before every entry has been rewritten many times; the table starts zeroed and 0 is never a tag.
+// tag: the exchange's number, 16 bits; the host zeroes the table before numbers repeat, and 0 is never a tag.
+__device__ __forceinline__ unsigned long long *exchange_table(const Dev &dv, const FoldRunArgs &run) {
+  return run.xtab + (size_t)dv.U * kArrivalWords;
+}
 __device__ __forceinline__ unsigned long long xchg_pack(float score, uint32_t low16, uint32_t tag) {
   return ((unsigned long long)__float_as_uint(score) << 32) | ((unsigned long long)(low16 & 0xffffu) << 16) |
          (unsigned long long)(tag & 0xffffu);
@@ -188,32 +198,44 @@ __device__ __forceinline__ void publish_winner(unsigned long long *mine, int C, 
                      __HIP_MEMORY_SCOPE_AGENT);
   if (with_all) __hip_atomic_store(mine + C + j, xchg_pack(all, 0, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// One entry, waited for.  gave_up: a word in LDS, set by the first wait of the workgroup that ran into
-// the limit; from then on its waits return at once (a workgroup loses at most one time limit, whatever
-// went wrong), with an entry that names no row, so that nothing downstream indexes with it.
-__device__ __forceinline__ unsigned long long xchg_wait(unsigned long long v, const unsigned long long *p, uint32_t tag,
-                                                        int32_t *err, volatile int *gave_up) {
-  if ((uint32_t)(v & 0xffffu) == tag) return v;
-  const unsigned long long t0 = wall_clock64();   // 100 MHz
-  while (*gave_up == 0) {
-    v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)(v & 0xffffu) == tag) return v;
+// One entry, waited for (the workgroup that owes it is running: meet()).
+__device__ __forceinline__ unsigned long long xchg_wait(unsigned long long v, const unsigned long long *p, uint32_t tag) {
+  while ((uint32_t)(v & 0xffffu) != tag) {
     __builtin_amdgcn_s_sleep(1);
-    if (wall_clock64() - t0 > 300000000ull) {   // 3 s: a sibling that never came
-      *gave_up = 1;
-      __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return v;
+}
+// Counts this workgroup in at its unit's arrival word (one thread) and says who folds the unit in this launch.  Low half of
+// the word: workgroups that have arrived since the table was zeroed, `before` of them in earlier launches; high
+// half: the last launch whose unit one workgroup took for itself.  The take is an exchange of the word as it was
+// seen incomplete: either it succeeds, and whoever comes or looks later sees this launch's number, or another
+// arrival came first.
+__device__ __forceinline__ int meet(unsigned long long *word, int split, uint32_t before, uint32_t launch, uint32_t patience) {
+  unsigned long long v = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((uint32_t)(v >> 32) == launch) return kLeave;
+  v += 1ull;
+  const unsigned long long t0 = wall_clock64();   // 100 MHz
+  for (;;) {
+    if ((uint32_t)(v >> 32) == launch) return kLeave;
+    if ((uint32_t)v - before == (uint32_t)split) return kShared;
+    if (wall_clock64() - t0 >= patience) {
+      const unsigned long long taken = ((unsigned long long)launch << 32) | (uint32_t)v;
+      if (__hip_atomic_compare_exchange_strong(word, &v, taken, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        return kWhole;
+    } else {
+      __builtin_amdgcn_s_sleep(1);
+      v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  return xchg_pack(-INFINITY, 0xffffu, tag);
 }
 // A pair of lanes per token: each reads half of the workgroups' entries, all of them asked for at once
 // (a read goes to memory, one or two microseconds away), waits for the stragglers one by one and
 // puts them together; then the two halves meet.
 template <int NW, int kHalf>   // kHalf: workgroups per lane
 __device__ __forceinline__ void exchange_half(const Dev &dv, const Ctx<NW> &cx, const unsigned long long *unit_tab,
-                                              uint32_t tag, int32_t *err) {
+                                              uint32_t tag) {
   const int C = cx.C, h = cx.tid & 1;
-  volatile int *gave_up = cx.s_cnt() + kCntGaveUp;
   const unsigned long long *theirs = unit_tab + (size_t)(h * kHalf) * 2 * C;
   const int n_sinks = (dv.S + kTileKeys - 1) / kTileKeys - h * kHalf;   // how many of this half own sink rows
 #pragma unroll 1
@@ -228,7 +250,7 @@ __device__ __forceinline__ void exchange_half(const Dev &dv, const Ctx<NW> &cx, 
     for (int o = 0; o < kHalf; ++o) late = late || (uint32_t)(w0[o] & 0xffffu) != tag;
     if (late) {
 #pragma unroll
-      for (int o = 0; o < kHalf; ++o) w0[o] = xchg_wait(w0[o], theirs + (size_t)o * 2 * C + j, tag, err, gave_up);
+      for (int o = 0; o < kHalf; ++o) w0[o] = xchg_wait(w0[o], theirs + (size_t)o * 2 * C + j, tag);
     }
     float best = -INFINITY, all = -INFINITY;
     int best_i = kNoRow;
@@ -245,7 +267,7 @@ __device__ __forceinline__ void exchange_half(const Dev &dv, const Ctx<NW> &cx, 
     take(dpp_get<0xB1>(best), dpp_int<0xB1>(best_i));   // the other lane of the pair
     // the append score counts sink rows too: their owners say what they are worth
     for (int o = 0; o < n_sinks && o < kHalf; ++o) {
-      w1 = xchg_wait(o == 0 ? w1 : 0ull, theirs + ((size_t)o * 2 + 1) * C + j, tag, err, gave_up);
+      w1 = xchg_wait(o == 0 ? w1 : 0ull, theirs + ((size_t)o * 2 + 1) * C + j, tag);
       all = fmaxf(all, __uint_as_float((uint32_t)(w1 >> 32)));
     }
     all = fmaxf(fmaxf(all, dpp_get<0xB1>(all)), best);
@@ -259,12 +281,12 @@ __device__ __forceinline__ void exchange_half(const Dev &dv, const Ctx<NW> &cx, 
 }
 template <int NW>
 __device__ __forceinline__ void exchange_winners(const Dev &dv, const Ctx<NW> &cx, const unsigned long long *unit_tab,
-                                                 uint32_t tag, int32_t *err) {
+                                                 uint32_t tag) {
   switch (cx.split) {
-    case 2: exchange_half<NW, 1>(dv, cx, unit_tab, tag, err); break;
-    case 4: exchange_half<NW, 2>(dv, cx, unit_tab, tag, err); break;
-    case 8: exchange_half<NW, 4>(dv, cx, unit_tab, tag, err); break;
-    default: exchange_half<NW, 8>(dv, cx, unit_tab, tag, err); break;
+    case 2: exchange_half<NW, 1>(dv, cx, unit_tab, tag); break;
+    case 4: exchange_half<NW, 2>(dv, cx, unit_tab, tag); break;
+    case 8: exchange_half<NW, 4>(dv, cx, unit_tab, tag); break;
+    default: exchange_half<NW, 8>(dv, cx, unit_tab, tag); break;
   }
 }
 
@@ -446,7 +468,8 @@ template <int NW>
 __device__ __forceinline__ void score_pass(const Dev &dv, const Ctx<NW> &cx, bool first, int slot, int m, int n, bool exact,
                                            const uint16_t *kbar_blk, bf16x8 (&kreg)[8], unsigned long long *mine,
                                            uint32_t tag) {
-  constexpr int D = kHeadDim, ST = stage_tiles(NW);
+  constexpr int D = kHeadDim;
+  const int ST = cx.stage;
   const int lane = cx.lane, wave = cx.wave, g = lane >> 5;
   const int C = cx.C;
   const bool ring = first && !cx.resident;
@@ -478,10 +501,10 @@ __device__ __forceinline__ void score_pass(const Dev &dv, const Ctx<NW> &cx, boo
     }
 #pragma unroll 1
     for (int t = 0; t < n_tiles; ++t) {
-      if (ring && t % ST == 0) {   // a stage has landed for every wave, and the other one has been read
+      if (ring && (t & (ST - 1)) == 0) {   // a stage has landed for every wave, and the other one has been read
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        issue_stage(t / ST + 1);
+        issue_stage((t >> __builtin_ctz(ST)) + 1);
       }
       if (tg.active && (t & (tg.wpg - 1)) == tg.sub)   // wpg is a power of two: NW and C / 32 are
         score_tile(w, Ks + (ring ? t & (2 * ST - 1) : t) * kTileElems, koff, kreg, first ? cx.global(64 * t) >> 5 : 0, row1,
@@ -1019,6 +1042,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
     cx.split = split;
     cx.shift = __builtin_ctz(split);
     cx.resident = a.run.resident > 0;
+    cx.stage = stage_tiles(NW);
     cx.tid = (int)threadIdx.x;
     cx.lane = cx.tid & 63;
     cx.wave = __builtin_amdgcn_readfirstlane(cx.tid >> 6);
@@ -1029,7 +1053,6 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
 #ifdef KVM_FOLD_STAMPS
   if (threadIdx.x == 0) cx.s_cnt()[kCntStamps] = 0;
 #endif
-  if (threadIdx.x == 0) cx.s_cnt()[kCntGaveUp] = 0;   // (read after barriers only)
   // the memory keys of a step's block: slab `kbar_block` of the scratch, this unit's C rows
   auto keys_of = [&](const FoldKernelArgs &a, int si) {
     return (const uint16_t *)a.dv.kbar + ((int64_t)a.run.s[si].kbar_block * a.dv.Ufull + cx.u) * cx.C * D;
@@ -1050,6 +1073,27 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
       const int base = cx.global(64 * t);
       fetch_tile<NW>(khat, base, m0 - base, at + (uint32_t)t * kTileBytes, cx.wave, dl);
     }
+  }
+  if (cx.split > 1) {   // the others are waited for while the tiles travel
+    if (cx.tid == 0) {
+      const FoldRunArgs &run = args_now().run;
+      cx.s_cnt()[kCntMeet] = meet(run.xtab + (size_t)cx.u * kArrivalWords, run.split, run.arrived, run.launch, run.patience);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const int who = __builtin_amdgcn_readfirstlane(cx.s_cnt()[kCntMeet]);
+    if (who == kLeave) return;
+    if (who == kWhole) {
+      const FoldKernelArgs &a = args_now();
+      cx.split = 1;
+      cx.part = cx.shift = 0;
+      cx.fresh_at = lds_fresh(NW, a.dv.C, own_tiles_most(a.dv.Mcap, 1));
+      cx.resident = false;
+      cx.stage = kStageTaken;
+      cx.gather = kGatherTaken;
+    }
+  }
+  if (cx.resident) {   // the tiles are there, every wave's share of them
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
@@ -1108,7 +1152,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
         const FoldKernelArgs &a = args_now();
         const Ctx<NW> c = phase(cx);
         const uint32_t xnum = a.run.s[si].xnum;
-        unsigned long long *mine = a.run.xtab + (((size_t)c.u * 2 + (xnum & 1u)) * c.split + c.part) * 2 * c.C;
+        unsigned long long *mine = exchange_table(a.dv, a.run) + (((size_t)c.u * 2 + (xnum & 1u)) * c.split + c.part) * 2 * c.C;
         score_pass<NW>(a.dv, c, a0 < 0, so, m + (a0 < 0 ? 0 : a0), a1 - a0, exact, keys_of(a, si), kreg, mine, xnum & 0xffffu);
       }
       if (begin && cx.resident && si > 0) copy_previous();
@@ -1121,8 +1165,8 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
           const FoldKernelArgs &a = args_now();
           const Ctx<NW> c = phase(cx);
           const uint32_t xnum = a.run.s[si].xnum;
-          exchange_winners<NW>(a.dv, c, a.run.xtab + (((size_t)c.u * 2 + (xnum & 1u)) * c.split) * 2 * c.C, xnum & 0xffffu,
-                               a.run.err);
+          exchange_winners<NW>(a.dv, c, exchange_table(a.dv, a.run) + (((size_t)c.u * 2 + (xnum & 1u)) * c.split) * 2 * c.C,
+                               xnum & 0xffffu);
           __syncthreads();
         }
         FOLD_STAMP();
@@ -1213,8 +1257,13 @@ int gather_tokens_most(const Dev &dv, int NW, int split, size_t limit) {
   return g > kGatherLeast ? g : kGatherLeast;
 }
 size_t lds_bytes(const Dev &dv, int NW, int split, size_t limit) {
-  return lds_fresh(NW, dv.C, own_tiles_most(dv.Mcap, split)) + (size_t)resident_tiles(dv, NW, split, limit) * kTileBytes +
-         (size_t)gather_tokens_most(dv, NW, split, limit) * kTokenBytes;
+  const size_t n = lds_fresh(NW, dv.C, own_tiles_most(dv.Mcap, split)) +
+                   (size_t)resident_tiles(dv, NW, split, limit) * kTileBytes +
+                   (size_t)gather_tokens_most(dv, NW, split, limit) * kTokenBytes;
+  if (split == 1) return n;
+  // (a workgroup that shares a unit must also be able to take over all of it)
+  const size_t taken = lds_fresh(NW, dv.C, own_tiles_most(dv.Mcap, 1)) + (size_t)kGatherTaken * kTokenBytes;
+  return n > taken ? n : taken;
 }
 
 }  // namespace
@@ -1232,7 +1281,7 @@ bool fold_fused_resident(const Dev &dv, int split, bool narrow) {
 }
 
 size_t fold_exchange_bytes(int64_t units, int C, int split) {
-  return split > 1 ? (size_t)units * 2 * split * 2 * C * sizeof(unsigned long long) : 0;
+  return split > 1 ? (size_t)units * (kArrivalWords + 2 * split * 2 * C) * sizeof(unsigned long long) : 0;
 }
 
 hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st) {
@@ -1252,16 +1301,7 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
   if (attr8 != hipSuccess) return attr8;
   FoldRunArgs run = run_;
   const int split = run.split, NW = narrow ? 8 : 16;
-  if (split < 1 || (split > 1 && (!run.xtab || !run.err))) return hipErrorInvalidValue;
-  if (split > 1) {
-    // the unit's workgroups wait for each other: all of the grid must fit the chip at once (one
-    // workgroup of either shape per compute unit at least)
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    if ((int64_t)dv.U * split > cus) return hipErrorInvalidValue;
-  }
+  if (split < 1 || (split > 1 && !run.xtab)) return hipErrorInvalidValue;
   const size_t limit = narrow ? kLdsNarrow : kLdsWide;
   run.resident = resident_tiles(dv, NW, split, limit);
   run.gather = gather_tokens_most(dv, NW, split, limit);

@@ -35,19 +35,16 @@ struct kvm_state {
   float *trace_score = nullptr;
   int64_t trace_max = 0;
   bool mfma = false;  // bf16, d = 128, C % 64 == 0: matrix-core kernels
-  // a unit's rows shared among several workgroups of that launch: the exchange table (part of the
-  // state buffer), whether it has been zeroed, the next exchange number (never reused: the
-  // table's entries are told apart by it), and the error word the kernel raises when a wait for a
-  // sibling workgroup ran into its time limit (host memory the device can write)
+  // a unit's rows shared among several workgroups of that launch: the table they meet at (part of the state buffer),
+  // whether it has been zeroed, and since then: the next exchange number (the table's entries are told
+  // apart by it), launches, and workgroups per unit of them
   unsigned long long *xtab = nullptr;
   size_t xtab_bytes = 0;
   bool xtab_clean = false;
   bool part_clean = false;  // the decode counters (Dev::part_cnt) have been zeroed
-  uint32_t xchg = 2;
-  int32_t *xerr_host = nullptr, *xerr_dev = nullptr;
-  int xerr_slot = -1;   // which of the devices' error words it is, -1: an allocation of the state's own
+  uint32_t xchg = 0, launches = 0, arrived = 0;
   // kvm_debug_set knobs (0 = the library's own choice)
-  int dbg[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int dbg[KVM_DEBUG_KNOBS] = {};
   int64_t blocks = 0;  // what the state was made for, in blocks (kvm_state_grow does not change it)
   int group = 1;      // chunks per attention launch in prefill; the readout has 2 * group slots
   // prefill pipeline: folds run ahead on a library-owned stream, attention follows in groups
@@ -429,7 +426,7 @@ struct WaitingLaunches {
 constexpr int kMaxDevices = 64;
 WaitingLaunches g_waiting[kMaxDevices];
 // done: an event of the state's, which stands for the end of this launch afterwards
-int launch_run(const kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
+int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
                hipStream_t stream) {
   if (run.split <= 1) {
     HIP_TRY(kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream));
@@ -441,7 +438,11 @@ int launch_run(const kvm_state *st, const Src &src, const kvm::FoldRunArgs &run,
   WaitingLaunches &w = g_waiting[dev];
   std::lock_guard<std::mutex> hold(w.lock);
   if (w.last && w.by != st->number) HIP_TRY(hipStreamWaitEvent(stream, w.last, 0));
-  HIP_TRY(kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream));
+  const hipError_t e = kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream);
+  if (e != hipSuccess) st->xtab_clean = false;   // nobody arrived
+  HIP_TRY(e);
+  st->launches += 1;
+  st->arrived += run.split;
   w.last = done;
   w.by = st->number;
   return KVM_OK;
@@ -499,55 +500,6 @@ void give_stream(int dev, hipStream_t s) {
   (void)hipStreamDestroy(s);
 }
 
-// Error words (host memory the device can write): a state takes one of a device's kWords and gives it back; one
-// block of host memory per device, made once.  A launch of a dropped state that is still running may raise
-// its word for the next holder: it does so only when its workgroups waited for seconds in vain, and then
-// an error is due there as well.  With no word left a state has its own allocation.
-struct ErrorWords {
-  static constexpr int kWords = 64;
-  std::mutex lock;
-  int32_t *host = nullptr, *dev = nullptr;
-  uint64_t used = 0;
-};
-ErrorWords g_error_words[kMaxDevices];
-int take_error_word(kvm_state *st) {
-  int dev = 0;
-  HIP_TRY(hipGetDevice(&dev));
-  if (dev < kMaxDevices) {
-    ErrorWords &p = g_error_words[dev];
-    std::lock_guard<std::mutex> hold(p.lock);
-    if (!p.host) {
-      int32_t *h = nullptr;
-      HIP_TRY(hipHostMalloc((void **)&h, ErrorWords::kWords * sizeof(int32_t), hipHostMallocMapped));
-      HIP_TRY(hipHostGetDevicePointer((void **)&p.dev, h, 0));
-      p.host = h;
-    }
-    if (p.used != ~(uint64_t)0) {
-      const int i = __builtin_ctzll(~p.used);
-      p.used |= (uint64_t)1 << i;
-      st->xerr_slot = dev * ErrorWords::kWords + i;
-      st->xerr_host = p.host + i;
-      st->xerr_dev = p.dev + i;
-    }
-  }
-  if (!st->xerr_host) {
-    HIP_TRY(hipHostMalloc((void **)&st->xerr_host, sizeof(int32_t), hipHostMallocMapped));
-    HIP_TRY(hipHostGetDevicePointer((void **)&st->xerr_dev, st->xerr_host, 0));
-  }
-  *st->xerr_host = 0;
-  return KVM_OK;
-}
-void give_error_word(kvm_state *st) {
-  if (!st->xerr_host) return;
-  if (st->xerr_slot < 0) {
-    (void)hipHostFree(st->xerr_host);
-    return;
-  }
-  ErrorWords &p = g_error_words[st->xerr_slot / ErrorWords::kWords];
-  std::lock_guard<std::mutex> hold(p.lock);
-  p.used &= ~((uint64_t)1 << (st->xerr_slot % ErrorWords::kWords));
-}
-
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ull;
 }
@@ -566,49 +518,40 @@ int clean_shares(kvm_state *st, hipStream_t stream) {
   return KVM_OK;
 }
 
-// Arguments of a one-launch run; with shared rows also what the exchange needs: the table zeroed
-// once (on `stream`, ahead of the first launch that uses it) and the error word.
+// How long the workgroups of a unit wait for each other to start before one of them takes the whole unit, in ticks of
+// 10 ns.  Beside attention the last one starts up to an attention launch (a millisecond or two) after the first.
+constexpr uint32_t kPatience = 1000000;
+// Arguments of a one-launch run; with shared rows also what the workgroups of a unit meet at: the table, zeroed (on
+// `stream`) ahead of the first launch that uses it and whenever the 16 bits of an exchange number run out.
 int fused_run(kvm_state *st, bool in_place, hipStream_t stream, kvm::FoldRunArgs *out) {
-  kvm::FoldRunArgs run;
-  run.n = 0;
+  kvm::FoldRunArgs run = {};
   run.in_place = in_place ? 1 : 0;
   run.trace_assign = st->trace_assign;
   run.trace_score = st->trace_score;
   run.trace_stride = (int64_t)st->dv.U * st->dv.C;
   run.split = fold_split(st);
-  run.xtab = nullptr;
-  run.err = nullptr;
   if (run.split > 1) {
-    if (!st->xerr_host) {
-      const int rc = take_error_word(st);
-      if (rc != KVM_OK) return rc;
-    }
-    if (!st->xtab_clean) {
+    if (!st->xtab_clean || st->xchg + kvm::kFoldMaxSteps > 0xffffu) {
       hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, stream, st->xtab, st->xtab_bytes / 8);
       HIP_TRY(hipGetLastError());
       st->xtab_clean = true;
+      st->xchg = 2;   // (0 is the tag of an empty entry)
+      st->launches = st->arrived = 0;
     }
     run.xtab = st->xtab;
-    run.err = st->xerr_dev;
+    run.launch = st->launches + 1;
+    run.arrived = st->arrived;
+    const int forced = st->dbg[KVM_DEBUG_FOLD_PATIENCE];
+    run.patience = forced ? (uint32_t)forced - 1u : kPatience;
   }
   *out = run;
   return KVM_OK;
 }
-// The exchange number of a fold (none is used up when the whole block is appended): consecutive,
-// never 0 in its low 16 bits.
+// The exchange number of a fold: consecutive (none is used up when the whole block is appended).
 uint32_t take_exchange(kvm_state *st, int64_t m, int64_t m_after) {
-  const int64_t n_app = m_after - m;
-  if ((st->xchg & 0xffffu) == 0u) st->xchg += 2u;   // skip the tag 0, keeping the parities alternating
   const uint32_t num = st->xchg;
-  st->xchg += n_app == st->dv.C ? 0u : 1u;
+  st->xchg += m_after - m == st->dv.C ? 0u : 1u;
   return num;
-}
-int cluster_error(const kvm_state *st) {
-  if (st->xerr_host && *(volatile int32_t *)st->xerr_host != 0) {
-    g_hip_error = "a fold workgroup waited for a sibling workgroup past its time limit; the state is undefined";
-    return KVM_ERR_HIP;
-  }
-  return KVM_OK;
 }
 
 int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, float *score_out,
@@ -898,7 +841,6 @@ int kvm_state_destroy(kvm_state *st) {
     if (st->fold_done && st->fold_done != kept) (void)hipEventDestroy(st->fold_done);
     for (hipStream_t fs : st->fold_streams)
       if (fs) give_stream(st->stream_dev, fs);
-    give_error_word(st);
   }
   delete st;
   return KVM_OK;
@@ -940,7 +882,6 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
                         const float *gate, void *out, float *lse, int64_t T,
                         const kvm_strides *sp, void *stream_) {
   if (!st || !q || !k || !v || !out || T <= 0) return KVM_ERR_ARG;
-  if (cluster_error(st) != KVM_OK) return KVM_ERR_HIP;
   hipStream_t stream = (hipStream_t)stream_;
   const kvm_config &c = st->cfg;
   const Dev &dv = st->dv;
@@ -1314,7 +1255,6 @@ int kvm_decode_step(kvm_state *st, const void *q, const void *k, const void *v,
                     const float *gate, void *out, void *stream_) {
   if (!st || !q || !k || !v || !out) return KVM_ERR_ARG;
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return KVM_ERR_ARG;
-  if (cluster_error(st) != KVM_OK) return KVM_ERR_HIP;
   hipStream_t stream = (hipStream_t)stream_;
   const kvm_config &c = st->cfg;
   const Dev &dv = st->dv;
@@ -1538,7 +1478,6 @@ int kvm_state_fold(kvm_state *st, const void *k_blk, const void *v_blk, const fl
   if (!st || !k_blk || !v_blk) return KVM_ERR_ARG;
   if (n_tokens != st->dv.C) return KVM_ERR_ARG;
   if (!aligned16(k_blk) || !aligned16(v_blk)) return KVM_ERR_ARG;
-  if (cluster_error(st) != KVM_OK) return KVM_ERR_HIP;
   const Dev &dv = st->dv;
   Src src;
   src.k = k_blk; src.v = v_blk; src.g = gate_blk;

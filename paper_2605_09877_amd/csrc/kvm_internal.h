@@ -116,12 +116,15 @@ struct FoldRunArgs {
   int32_t *trace_assign;
   float *trace_score;
   int64_t trace_stride;
-  int32_t split;               // workgroups per unit (a power of two); 1: none of the next two is used
-  unsigned long long *xtab;    // the exchange table, fold_exchange_bytes() of zeroed device memory
+  int32_t split;               // workgroups per unit (a power of two); 1: none of the next four is used
+  unsigned long long *xtab;    // arrival words and exchange table, fold_exchange_bytes() of zeroed device memory
+  uint32_t arrived;            // workgroups per unit of the earlier launches since the table was zeroed
+  uint32_t launch;             // number of this launch since then, from 1
+  uint32_t patience;           // how long a workgroup waits for its unit's others to start, ticks of 10 ns
   int32_t resident;            // (set by the launch) K-hat tiles a workgroup keeps in LDS, 0: they stream through a ring
   int32_t gather;              // (likewise) merging tokens the LDS scratch holds
-  int32_t *err;                // set to 1 when a wait for a sibling workgroup ran into its time limit
 };
+constexpr int kArrivalWords = 8;   // an arrival word of the table to itself in 64 bytes
 bool fold_fused_fits(const Dev &dv, int split = 1);
 // whether each of a unit's `split` workgroups keeps its normalised keys in LDS for a whole run
 bool fold_fused_resident(const Dev &dv, int split, bool narrow);

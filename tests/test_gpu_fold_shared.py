@@ -89,6 +89,19 @@ def test_shared_rows_agree_with_a_kernel_per_step(case):
     same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
 
 
+# patience 0: the first workgroup of a unit that finds itself alone takes all of it; 0.5 us: some units are taken, some shared
+@pytest.mark.parametrize("patience", [1, 51])
+@pytest.mark.parametrize("case", ["one tile each", "four tiles each", "long block", "appends", "growing", "sinks"])
+def test_units_whose_workgroups_do_not_all_start(case, patience):
+    """A unit that one workgroup takes over, because its others have not started in time, folds to the same bits."""
+    _, b, sy = kit()
+    chunk, units, seq, budget, kw, _ = CASES[case]
+    w = make(sy, chunk, units, seq, budget, **kw)
+    for tail in (0, chunk + 1):
+        got = run(w, {**widest(w), b.KVM_DEBUG_FOLD_PATIENCE: patience}, tail)
+        same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}, tail))
+
+
 @pytest.mark.parametrize("tail", [1, 128 + 3])
 def test_folds_in_place(tail):
     _, b, sy = kit()
