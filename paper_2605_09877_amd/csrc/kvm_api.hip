@@ -2,7 +2,6 @@
 // schedule (integer replay of the paper's budget rule) and the per-chunk launch sequence.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -20,11 +19,6 @@ using kvm::Dev;
 using kvm::Src;
 
 struct kvm_state {
-  const uint64_t number = next_number();   // tells the states of a process apart, also those of different times
-  static uint64_t next_number() {
-    static std::atomic<uint64_t> n{0};
-    return ++n;
-  }
   kvm_config cfg;
   std::vector<int64_t> table;
   Dev dv;
@@ -52,7 +46,6 @@ struct kvm_state {
   static constexpr int kMaxChains = 2;
   hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};   // on loan from the device's idle ones (take_stream)
   int stream_dev = -1;
-  hipEvent_t fold_done = nullptr;       // of the latest fold on a caller's stream whose workgroups wait for each other
   std::vector<hipEvent_t> sync_events;  // untimed events, reused call after call
   size_t sync_used = 0;
   // optional kernel timing: (start, stop, class) event pairs, events reused across reads
@@ -401,9 +394,8 @@ int fold_split(const kvm_state *st) {
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
 bool use_fused(const kvm_state *st) { return fold_split(st) > 0; }
-// The same for folds enqueued on `stream`: workgroups that wait for each other are ordered against
-// other streams by an event, which a stream that is being captured into a graph cannot take part in;
-// captured folds are a kernel per step.
+// The same for folds enqueued on `stream`: a launch whose workgroups meet carries numbers that hold once, so a graph
+// that is replayed cannot hold it; captured folds are a kernel per step (the same bits).
 int use_fused_on(const kvm_state *st, hipStream_t stream, bool *fused) {
   *fused = use_fused(st);
   if (*fused && fold_split(st) > 1) {
@@ -414,50 +406,18 @@ int use_fused_on(const kvm_state *st, hipStream_t stream, bool *fused) {
   return KVM_OK;
 }
 
-// Launches whose workgroups wait for each other run one after the other on a device, whichever
-// state, stream or thread of the process they come from: two of them on the chip at once could
-// each hold compute units that the other one's missing workgroups need.  The event of the latest one
-// per device; a state's own launches are in order already.
-struct WaitingLaunches {
-  std::mutex lock;
-  hipEvent_t last = nullptr, left = nullptr;   // left: `last` when the state it came from is gone
-  uint64_t by = 0;                             // number of the state that launched last
-};
 constexpr int kMaxDevices = 64;
-WaitingLaunches g_waiting[kMaxDevices];
-// done: an event of the state's, which stands for the end of this launch afterwards
+// done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
                hipStream_t stream) {
-  if (run.split <= 1) {
-    HIP_TRY(kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream));
-    return KVM_OK;
-  }
-  int dev = 0;
-  HIP_TRY(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices) return KVM_ERR_ARG;
-  WaitingLaunches &w = g_waiting[dev];
-  std::lock_guard<std::mutex> hold(w.lock);
-  if (w.last && w.by != st->number) HIP_TRY(hipStreamWaitEvent(stream, w.last, 0));
   const hipError_t e = kvm::launch_fold_fused(st->dv, src, run, narrow, done, stream);
   if (e != hipSuccess) st->xtab_clean = false;   // nobody arrived
   HIP_TRY(e);
-  st->launches += 1;
-  st->arrived += run.split;
-  w.last = done;
-  w.by = st->number;
-  return KVM_OK;
-}
-// A state's events are about to be destroyed: one that others may still have to wait for is kept
-// (at most one per device).
-hipEvent_t keep_waiting_event(const kvm_state *st) {
-  hipEvent_t kept = nullptr;
-  for (WaitingLaunches &w : g_waiting) {
-    std::lock_guard<std::mutex> hold(w.lock);
-    if (w.by != st->number || w.last == w.left) continue;
-    if (w.left) (void)hipEventDestroy(w.left);
-    w.left = kept = w.last;
+  if (run.split > 1) {
+    st->launches += 1;
+    st->arrived += run.split;
   }
-  return kept;
+  return KVM_OK;
 }
 
 // The library's streams go from state to state.  A training step makes a state, runs it forward and backward and
@@ -577,8 +537,7 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
     HIP_TRY(kvm::launch_memkey(dv, src, 1, stream));
     // a fold of its own (decode, the fold entry point, the chunk-by-chunk schedule): the narrow
     // workgroup, two to a compute unit, unless asked otherwise (measured 3 % ahead of the wide one)
-    if (run.split > 1 && !st->fold_done) HIP_TRY(hipEventCreateWithFlags(&st->fold_done, hipEventDisableTiming));
-    rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, run.split > 1 ? st->fold_done : nullptr, stream);
+    rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, nullptr, stream);
     if (rc_run != KVM_OK) return rc_run;
   } else {
     int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, stream);
@@ -835,10 +794,7 @@ int kvm_state_destroy(kvm_state *st) {
       (void)hipEventDestroy(sp.b);
     }
     for (auto e : st->free_events) (void)hipEventDestroy(e);
-    const hipEvent_t kept = keep_waiting_event(st);
-    for (auto e : st->sync_events)
-      if (e != kept) (void)hipEventDestroy(e);
-    if (st->fold_done && st->fold_done != kept) (void)hipEventDestroy(st->fold_done);
+    for (auto e : st->sync_events) (void)hipEventDestroy(e);
     for (hipStream_t fs : st->fold_streams)
       if (fs) give_stream(st->stream_dev, fs);
   }

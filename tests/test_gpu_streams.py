@@ -1,0 +1,73 @@
+"""Calls on different streams of a program do not wait for each other: not through the launches that share a unit
+among workgroups, and not through the library's own streams, which go from state to state."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def kit():
+    import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import synth
+    return pkg, synth
+
+
+def long_sleep(ms):
+    """Cycles of torch.cuda._sleep that last about so long."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for n in (1000, 100000):
+        a.record()
+        torch.cuda._sleep(n)
+        b.record()
+        torch.cuda.synchronize()
+    return int(100000 * ms / a.elapsed_time(b))
+
+
+def any_attempt_is_independent(attempt):
+    """attempt(held, free) enqueues work on both streams, that on `held` behind a sleep; whether `free` got done
+    meanwhile.  Streams share a few hardware queues, so a pair may be held up by chance: one of eight has to pass."""
+    cycles = long_sleep(60.0)
+    done = []
+    for _ in range(8):
+        held, free = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(held):
+            torch.cuda._sleep(cycles)
+            slept = torch.cuda.Event()
+            slept.record()
+        attempt(held, free)
+        free.synchronize()
+        done.append(not slept.query())
+        torch.cuda.synchronize()
+    assert any(done)
+
+
+def workload(**kw):
+    pkg, sy = kit()
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=8, n_kv_heads=8, chunk_len=128, seq=128 * 8,
+                  budget_fixed=256, **kw)
+    params = sy.make_params(w, DEV, plain=True)
+
+    def make(schedule):
+        st = pkg.state_for(w, device=DEV, **params)
+        st.debug_set(2, schedule)
+        return st
+
+    return make, sy.make_qkv(w, DEV)
+
+
+def test_shared_folds_of_two_states():
+    make, qkv = workload()
+    states = [make(1) for _ in range(2)]   # chunk by chunk: no streams but the caller's
+    assert states[0].fold_path == 1
+    for st in states:
+        st.prefill(*qkv)
+    torch.cuda.synchronize()
+
+    def attempt(held, free):
+        for st, stream in zip(states, (held, free)):
+            with torch.cuda.stream(stream):
+                st.reset()
+                st.prefill(*qkv)
+
+    any_attempt_is_independent(attempt)
