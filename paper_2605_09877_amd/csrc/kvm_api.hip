@@ -46,6 +46,7 @@ struct kvm_state {
   static constexpr int kMaxChains = 2;
   hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};   // on loan from the device's idle ones (take_stream)
   int stream_dev = -1;
+  hipStream_t stream_caller = nullptr;   // the caller's stream of the latest call that used them
   std::vector<hipEvent_t> sync_events;  // untimed events, reused call after call
   size_t sync_used = 0;
   // optional kernel timing: (start, stop, class) event pairs, events reused across reads
@@ -422,40 +423,50 @@ int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool 
 
 // The library's streams go from state to state.  A training step makes a state, runs it forward and backward and
 // drops it: making two streams took 0.2 to 0.4 ms of host time each, dropping them 0.15 ms and a wait for the
-// device, of the 0.41 ms that a step on 43 tokens took.  At most kIdleStreams per device are kept.  Work that a
-// dropped state left on one only delays the next state's; it is ordered before that and depends on
-// nothing enqueued later.  A stream that is still part of a capture is destroyed as before.
+// device, of the 0.41 ms that a step on 43 tokens took.  A stream goes to a state that is used on the caller's stream
+// its last holder was used on: that stream orders what was left on it anyway.  For any other caller it could hold
+// work that waits for something the caller knows nothing of.  At most kMost per device are kept, the latest ones.
+// A stream that is still part of a capture is destroyed.
 struct IdleStreams {
   static constexpr int kMost = 8;
   std::mutex lock;
-  hipStream_t idle[kMost];
+  struct {
+    hipStream_t s, caller;
+  } idle[kMost];   // oldest first
   int n = 0;
 };
 IdleStreams g_idle_streams[kMaxDevices];
-hipError_t take_stream(kvm_state *st, hipStream_t *out) {
+hipError_t take_stream(kvm_state *st, hipStream_t caller, hipStream_t *out) {
   int dev = 0;
   const hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   st->stream_dev = dev;
-  if (dev < kMaxDevices) {
+  if (dev >= 0 && dev < kMaxDevices) {
     IdleStreams &p = g_idle_streams[dev];
     std::lock_guard<std::mutex> hold(p.lock);
-    if (p.n > 0) {
-      *out = p.idle[--p.n];
-      return hipSuccess;
-    }
+    for (int i = p.n - 1; i >= 0; --i)
+      if (p.idle[i].caller == caller && caller != hipStreamPerThread) {   // (one handle, a stream per thread)
+        *out = p.idle[i].s;
+        for (--p.n; i < p.n; ++i) p.idle[i] = p.idle[i + 1];
+        return hipSuccess;
+      }
   }
   return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
 }
-void give_stream(int dev, hipStream_t s) {
+void give_stream(int dev, hipStream_t caller, hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (dev >= 0 && dev < kMaxDevices && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
     IdleStreams &p = g_idle_streams[dev];
     std::lock_guard<std::mutex> hold(p.lock);
-    if (p.n < IdleStreams::kMost) {
-      p.idle[p.n++] = s;
-      return;
-    }
+    const hipStream_t oldest = p.idle[0].s;
+    const bool full = p.n == IdleStreams::kMost;
+    if (full)
+      for (int i = 0; i + 1 < p.n; ++i) p.idle[i] = p.idle[i + 1];
+    else
+      ++p.n;
+    p.idle[p.n - 1] = {s, caller};
+    if (!full) return;
+    s = oldest;
   }
   (void)hipStreamDestroy(s);
 }
@@ -796,7 +807,7 @@ int kvm_state_destroy(kvm_state *st) {
     for (auto e : st->free_events) (void)hipEventDestroy(e);
     for (auto e : st->sync_events) (void)hipEventDestroy(e);
     for (hipStream_t fs : st->fold_streams)
-      if (fs) give_stream(st->stream_dev, fs);
+      if (fs) give_stream(st->stream_dev, st->stream_caller, fs);
   }
   delete st;
   return KVM_OK;
@@ -997,8 +1008,9 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // Streams of the library: one per chain; the one-launch folds have a second one on which the
   // memory keys of a run, which depend on k alone, are computed while the run before it folds.
   const int n_streams = fused_folds ? 2 : n_chains;
+  st->stream_caller = stream;
   for (int c2 = 0; c2 < n_streams; ++c2) {
-    if (!st->fold_streams[c2]) HIP_TRY(take_stream(st, &st->fold_streams[c2]));
+    if (!st->fold_streams[c2]) HIP_TRY(take_stream(st, stream, &st->fold_streams[c2]));
     fstream[c2] = st->fold_streams[c2];
     if (c2 < n_chains) cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
   }
@@ -1509,8 +1521,9 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   a.par64 = (double *)(w + l.par64);
   kvm::BwdStreams x;
   if (on_mfma) {
+    st->stream_caller = (hipStream_t)stream;
     for (hipStream_t &fs : st->fold_streams)
-      if (!fs) HIP_TRY(take_stream(st, &fs));
+      if (!fs) HIP_TRY(take_stream(st, (hipStream_t)stream, &fs));
     x.side = st->fold_streams[0];
     x.side2 = st->fold_streams[1];
     st->sync_used = 0;

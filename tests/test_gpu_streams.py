@@ -71,3 +71,15 @@ def test_shared_folds_of_two_states():
                 st.prefill(*qkv)
 
     any_attempt_is_independent(attempt)
+
+
+def test_streams_of_a_dropped_state():
+    make, qkv = workload(io="f32")
+    torch.cuda.synchronize()
+
+    def attempt(held, free):
+        for stream in (held, free):
+            with torch.cuda.stream(stream):
+                make(2).prefill(*qkv)   # the state is dropped at once, its work still waiting
+
+    any_attempt_is_independent(attempt)
