@@ -159,12 +159,12 @@ bool use_mfma(const kvm_config &c) {
 // a launch has thousands of workgroups; the generic path launches chunk by chunk.
 int group_of(const kvm_config &c) { return use_mfma(c) ? 8 : 1; }
 static_assert(2 * kvm::kFoldMaxSteps <= 8, "two runs of one-launch folds have their memory keys in a group's scratch");
-constexpr int kClusterBelowUnits = 256;  // compute units of the chip this library is written for
+constexpr int kComputeUnits = 256;  // of the chip this library is written for
 // Workgroups that may share a unit's rows (a power of two): at most kFoldMaxSplit, one 64-row tile each, and
-// a compute unit for every one of them, because they wait for each other.
-int most_split(int64_t U, int64_t Mcap) {
+// together no more than `cus` compute units (beyond that a unit's workgroups start far apart).
+int most_split(int64_t U, int64_t Mcap, int cus) {
   int n = 1;
-  while (2 * n <= kvm::kFoldMaxSplit && U * 2 * n <= kClusterBelowUnits && Mcap / 64 >= 2 * n) n *= 2;
+  while (2 * n <= kvm::kFoldMaxSplit && U * 2 * n <= cus && Mcap / 64 >= 2 * n) n *= 2;
   return n;
 }
 
@@ -194,7 +194,7 @@ Layout layout_of(const kvm_config &c, int64_t Mcap) {
   l.pi = take(U * C * 4);
   l.app = take(U * C * 4);
   // exchange table of the one-launch fold when a unit's rows are shared among workgroups
-  l.xtab_bytes = use_mfma(c) ? kvm::fold_exchange_bytes((int64_t)U, (int)C, most_split((int64_t)U, Mcap)) : 0;
+  l.xtab_bytes = use_mfma(c) ? kvm::fold_exchange_bytes((int64_t)U, (int)C, most_split((int64_t)U, Mcap, kComputeUnits)) : 0;
   l.xtab = take(l.xtab_bytes);
   l.part_cnt = take((size_t)kvm::kShareGroups * 4);
   l.creator = take(U * C * 4);
@@ -379,6 +379,16 @@ int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hip
 // 425 / 461; 8 units, 38 blocks of 512 1007 / 1057; 8 units, prompts of 2 and 3 blocks of 128 (one or two folds, each a run of
 // its own) 49 / 53 and 77 / 87.  The choice holds for a state's life, prompt and generation alike: the two paths' readout
 // rows may differ in a last bit, and a state that is exported and imported goes on as it would have.
+// The device may have fewer compute units than the chip (a partition of it): what there is is asked for.
+int compute_units(const kvm_state *st) {
+  int dev = 0, n = st->dbg[KVM_DEBUG_COMPUTE_UNITS];
+  if (n == 0 && (hipGetDevice(&dev) != hipSuccess ||
+                 hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)) {
+    (void)hipGetLastError();
+    return kComputeUnits;
+  }
+  return n < kComputeUnits ? n : kComputeUnits;
+}
 constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareMinBlocks = 5;
 // Workgroups per unit on that path: 0 = a kernel per step.
 int fold_split(const kvm_state *st) {
@@ -387,7 +397,7 @@ int fold_split(const kvm_state *st) {
   if (path == 2) return 0;
   const int U = st->dv.U, forced = st->dbg[KVM_DEBUG_FOLD_SPLIT];
   const int whole = kvm::fold_fused_fits(st->dv, 1) ? 1 : 0;
-  const int most = most_split(U, st->dv.Mcap);
+  const int most = most_split(U, st->dv.Mcap, compute_units(st));
   auto can_share = [&](int n) { return n > 1 && n <= most && kvm::fold_fused_fits(st->dv, n); };
   if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
   if (path == 1 || U >= kFusedMinUnits) return whole;

@@ -205,3 +205,13 @@ def test_a_grown_and_an_imported_state_continue_to_the_bit(first):
         got, ref = st.export(), whole.export()
         for key in ("sK", "sV", "rho", "n", "w", "khat", "vhat"):
             assert torch.equal(got[key], ref[key]), key
+
+
+@pytest.mark.parametrize("compute_units,path", [(32, 1), (8, 2)])
+def test_fewer_compute_units(compute_units, path):
+    """A device with fewer compute units than the widest launch has workgroups folds all the same."""
+    _, b, sy = kit()
+    w = make(sy, 128, 8, 128 * 8, 512)
+    got = run(w, {b.KVM_DEBUG_COMPUTE_UNITS: compute_units})
+    assert got[0].fold_path == path
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))

@@ -86,6 +86,21 @@ def test_state_bytes_cover_the_layout():
         lib.kvm_state_bytes(C.byref(cfg(budget_kind=kb.KVM_BUDGET_SQRT, budget_scale=4.0)), 4096)
 
 
+def test_fold_path_follows_the_compute_units_there_are():
+    """Rows are shared among workgroups only as far as the device has compute units for them all: a partition of the
+    chip folds with fewer of them, or with a kernel per step."""
+    lib = kb.load_library()
+    c = cfg(batch=4, n_q_heads=2, n_kv_heads=2)   # 8 units, 512 rows
+    h = C.c_void_p()
+    nbytes = lib.kvm_state_bytes(C.byref(c), 8192)
+    assert lib.kvm_state_init(C.byref(h), C.byref(c), FAKE_DEV_PTR, nbytes, 8192) == kb.KVM_OK
+    v = C.c_int64(-1)
+    for units, path in ((256, 1), (100000, 1), (32, 1), (16, 1), (15, 2), (1, 2)):
+        assert lib.kvm_debug_set(h, kb.KVM_DEBUG_COMPUTE_UNITS, units) == kb.KVM_OK
+        assert lib.kvm_state_fold_path(h, C.byref(v)) == 0 and v.value == path, (units, v.value)
+    assert lib.kvm_state_destroy(h) == 0
+
+
 def test_argument_and_capacity_errors_before_any_launch():
     lib = kb.load_library()
     c = cfg(budget_kind=kb.KVM_BUDGET_SQRT, budget_scale=4.0)
