@@ -1307,9 +1307,11 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
   run.gather = gather_tokens_most(dv, NW, split, limit);
   FoldKernelArgs args{dv, src, run};
   void *argv[] = {&args};
-  const hipError_t e = hipExtLaunchKernel(narrow ? (const void *)fold_fused_kernel<8> : (const void *)fold_fused_kernel<16>,
-                                          dim3((unsigned)(dv.U * split)), dim3(64 * NW), argv,
-                                          lds_bytes(dv, NW, split, limit), st, nullptr, done, 0);
+  const void *kernel = narrow ? (const void *)fold_fused_kernel<8> : (const void *)fold_fused_kernel<16>;
+  const dim3 grid((unsigned)(dv.U * split)), block(64 * NW);
+  const size_t lds = lds_bytes(dv, NW, split, limit);
+  const hipError_t e = done ? hipExtLaunchKernel(kernel, grid, block, argv, lds, st, nullptr, done, 0)
+                            : hipLaunchKernel(kernel, grid, block, argv, lds, st);
   if (e != hipSuccess) return e;
   return hipGetLastError();
 }

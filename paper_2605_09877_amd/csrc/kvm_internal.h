@@ -132,7 +132,7 @@ size_t fold_exchange_bytes(int64_t units, int C, int split);
 // readout rows [0, m) recomputed from the sums with the one-launch path's arithmetic
 hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st);
 // done: an event that stands for the end of the launch (the kernel's own completion signal: nothing more is put on the
-// stream), or null
+// stream; not on a stream under capture), or null
 hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run, bool narrow, hipEvent_t done,
                              hipStream_t st);
 // score_mfma.hip (bf16, d = 128)
