@@ -31,6 +31,9 @@
  *  - Shapes: B batch, H_q query heads, H_kv key/value heads (H_q % H_kv == 0; a group of
  *    H_q/H_kv query heads shares one KV head's state, window, gate and LN_s), d = head_dim
  *    (64 or 128), C = chunk_len, L = n_bswa_chunks * C.  A "unit" is one (batch, KV head).
+ *  - Values that are not finite reach the queries that see them, except in prefills of bf16 with
+ *    head_dim 128 and C % 64 == 0: there keys are taken 64 at a time, and a NaN or an infinity in a
+ *    later token's v makes NaN of that channel for earlier queries of the same 64 positions too.
  *  - I/O dtype: KVM_F32 or KVM_BF16 for q, k, v, out, the memory keys and the normalised
  *    readout rows.  State key sums are fp64 (they feed the slot argmax, which has to be
  *    reproducible), value sums and radii fp32.

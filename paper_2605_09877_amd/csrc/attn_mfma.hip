@@ -373,7 +373,80 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
     tile_step(it, std::integral_constant<int, 0>{});
     if (it + 1 < n_tiles) tile_step(it + 1, std::integral_constant<int, 1>{});
   }
-  const float l = xhalf_sum(l_part);
+  float l = xhalf_sum(l_part);
+  if constexpr (kSplitP) {
+    // A key that a query does not see enters the second product with p = 0, and a value that is not finite makes that
+    // NaN; so does the rest of a split p, 0, with a value the query sees.  A query whose result is not
+    // finite is therefore done again, one visible key after the other, in fp32.
+    float bad = 0.f * l;
+#pragma unroll
+    for (int i = 0; i < kNb; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) bad = fmaf(oacc[i][v], 0.f, bad);
+    if (myq < nq && !(xhalf_sum(bad) == 0.f)) {
+      // channels of a lane: 32 * dblk + 8 * vq + 4 * g .. + 3, as in the accumulators
+      auto load4 = [&](const char *row, int dblk, int vq, float *f) {
+        const uint2 x = *reinterpret_cast<const uint2 *>(row + 2 * (32 * dblk + 8 * vq + 4 * g));
+        f[0] = __uint_as_float(x.x << 16);
+        f[1] = __uint_as_float(x.x & 0xffff0000u);
+        f[2] = __uint_as_float(x.y << 16);
+        f[3] = __uint_as_float(x.y & 0xffff0000u);
+      };
+      const char *qrow = (const char *)((const uint16_t *)a.q + b * a.q_b + ((int64_t)ci * dv.C + myq) * a.q_t + hq * a.q_h);
+      float qf[kNb][16];
+#pragma unroll
+      for (int i = 0; i < 4 * kNb; ++i) load4(qrow, i >> 2, i & 3, &qf[i >> 2][4 * (i & 3)]);
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[i][v] = 0.f;
+      m_run = -INFINITY;
+      l = 0.f;
+      const float f_state = neg_bits & 1 ? -c_state : c_state, f_bswa = neg_bits & 2 ? -c_bswa : c_bswa;
+      const int n_keys = m + (int)(cs + myq - wb) + 1;
+#pragma unroll 1
+      for (int n = 0; n < n_keys; ++n) {
+        const char *kr, *vr;
+        if (n < m) {
+          kr = khat + (uint32_t)n * (D * 2);
+          vr = vhat + (uint32_t)n * (D * 2);
+        } else {
+          const int prel = wrel + (n - m);
+          if (prel >= t0rel) {
+            kr = in_k + (int64_t)prel * (int64_t)kst_in;
+            vr = in_v + (int64_t)prel * (int64_t)vst_in;
+          } else {
+            int slot = ring_slot0 + (n - m);
+            slot = slot >= dv.L ? slot - dv.L : slot;
+            kr = ring_k + (uint32_t)slot * (D * 2);
+            vr = ring_v + (uint32_t)slot * (D * 2);
+          }
+        }
+        float dot = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4 * kNb; ++i) {
+          float x[4];
+          load4(kr, i >> 2, i & 3, x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dot = fmaf(qf[i >> 2][4 * (i & 3) + e], x[e], dot);
+        }
+        const float t = xhalf_sum(dot) * (n < m ? f_state : f_bswa);
+        const float m_new = fmaxf(m_run, t);
+        if (m_new == -INFINITY) continue;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new), pr = __builtin_amdgcn_exp2f(t - m_new);
+        m_run = m_new;
+        l = fmaf(l, alpha, pr);
+#pragma unroll
+        for (int i = 0; i < 4 * kNb; ++i) {
+          float x[4];
+          load4(vr, i >> 2, i & 3, x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            oacc[i >> 2][4 * (i & 3) + e] = fmaf(pr, x[e], oacc[i >> 2][4 * (i & 3) + e] * alpha);
+        }
+      }
+    }
+  }
   if (myq < nq) {
     const float inv = 1.f / l;
     uint16_t *orow = (uint16_t *)a.out + b * a.o_b + ((int64_t)ci * dv.C + myq) * a.o_t + hq * a.o_h;
