@@ -16,9 +16,11 @@
  *  - Every call orders its work on the caller's stream (`void *stream` is a hipStream_t passed as
  *    a plain pointer so that this header needs no HIP header; NULL = the default stream) and
  *    returns without synchronising the host: work the caller enqueues on that stream afterwards
- *    sees all of it.  kvm_prefill_chunked and kvm_prefill_backward also use two streams the state
- *    owns (default priority, non-blocking, created at first use): part of their kernels runs there,
- *    forked from and joined back to the caller's stream by events inside the call.  Calls on one
+ *    sees all of it.  kvm_prefill_chunked and kvm_prefill_backward also use two streams of the
+ *    library's (default priority, non-blocking, made at first use; a dropped state's go to the next
+ *    state on the same caller's stream): part of their kernels runs there, forked from and joined
+ *    back to the caller's stream by events inside the call.  Calls on different streams do not
+ *    wait for each other.  Calls on one
  *    state must be issued in order on one stream (or be ordered by the caller).
  *  - Return value: KVM_OK (0) or a negative kvm_status.  Argument, state and capacity errors
  *    (KVM_ERR_ARG, KVM_ERR_STATE, KVM_ERR_CAPACITY, KVM_ERR_UNSUPPORTED, KVM_ERR_LIMIT) are detected
@@ -210,7 +212,7 @@ int kvm_state_fold(kvm_state *st, const void *k_blk, const void *v_blk, const fl
  *     overwritten (sums over the batch for the parameters).  All device pointers, the caller's.
  *   - workspace: device, 256-byte aligned, kvm_backward_workspace_bytes(st, T) bytes; rewritten.
  * Work is enqueued on `stream`; the host is not blocked (with bf16 and head_dim 128 part of each
- * chunk's work runs on the state's own two streams, the ones a prefill's folds use, forked from
+ * chunk's work runs on the two streams that a prefill's folds use, forked from
  * and joined to `stream` by events inside the call: later work on `stream` sees all of it).
  * Parameter gradients are summed with fp64 atomics (their last fp32 bit can differ from run to
  * run). */
@@ -230,7 +232,7 @@ int kvm_state_tokens(const kvm_state *st, int64_t *tokens_seen);
 int kvm_state_capacity(const kvm_state *st, int64_t *rows_out);   /* rows the bound buffer holds */
 int kvm_state_folds(const kvm_state *st, int64_t *folds_out);     /* folds done so far */
 /* Which code path this state's folds take as things stand (its shape, the debug knobs):
- * 1 = a run of folds in one launch, one workgroup per unit; 2 = one kernel per fold step.
+ * 1 = a run of folds in one launch, one workgroup per unit or several; 2 = one kernel per fold step.
  * For reports (bench.py names the kernels it timed); both paths compute the same fold. */
 int kvm_state_fold_path(const kvm_state *st, int64_t *path_out);
 

@@ -291,7 +291,7 @@ class KVMState:
 
     @property
     def fold_path(self) -> int:
-        """1: a run of folds is one launch (one workgroup per unit); 2: one kernel per fold step."""
+        """1: a run of folds is one launch (one workgroup per unit or several); 2: one kernel per fold step."""
         return self._i64(self.lib.kvm_state_fold_path)
 
     def rows_for(self, max_tokens: int) -> int:

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void gate_mfma_kernel(const uint16_t *x, const
   uint32_t koff[8];
   ktile_offsets(lane, koff);
   auto issue = [&](int c0, int stage) {
-    // (rows past the end repeat the last one: a second half without tokens repeats the first half's)
+    // (rows past the end repeat the last one; a second half without tokens is not loaded, nothing of it is stored)
     const uint32_t at = xs_addr + (uint32_t)stage * (2 * kTileElems * 2);
     const char *from = xb + (size_t)c0 * 2;
     tile_dma<false, 4>(from, stride, valid, at, wave, dl);

@@ -142,13 +142,14 @@ def test_captured_step():
 
 
 def test_two_threads():
-    """Two states driven from two threads on streams of their own: their launches take turns."""
+    """Two states driven from two threads on streams of their own: their launches meet on the chip."""
     pkg, b, sy = kit()
     w = make(sy, 256, 16, 256 * 16, 1024)
     q, k, v = sy.make_qkv(w, DEV)
     want = run(sy.shrink(w), {b.KVM_DEBUG_FOLD_PATH: 2})
     p = sy.make_params(w, DEV, plain=False)
     torch.cuda.synchronize()
+    assert pkg.state_for(w, device=DEV, **p).fold_path == 1 and want[0].fold_path == 2
     out = [None, None]
 
     def work(i):

@@ -86,6 +86,17 @@ def test_state_bytes_cover_the_layout():
         lib.kvm_state_bytes(C.byref(cfg(budget_kind=kb.KVM_BUDGET_SQRT, budget_scale=4.0)), 4096)
 
 
+def test_the_library_allocates_no_memory():
+    """Buffers and workspaces are the caller's: no source of the library names an allocation, on the device or pinned on
+    the host (kvm_decode_step_multi_static promises it for code that cannot have one)."""
+    from paper_2605_09877_amd import build
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            text = f.read()
+        for call in ("hipMalloc", "hipHostMalloc", "hipHostAlloc", "hipExtMalloc", "hipFree", "hipHostFree"):
+            assert call not in text, (name, call)
+
+
 def test_fold_path_follows_the_compute_units_there_are():
     """Rows are shared among workgroups only as far as the device has compute units for them all: a partition of the
     chip folds with fewer of them, or with a kernel per step."""
