@@ -942,7 +942,12 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     // (64, 64) 318 / 540, bf16 d 64 8 units (256, 256) 660 / 900, fp32 d 64 1 unit (256, 300: 20 MB) 402 / 450; but fp32
     // d 128 1 unit (256, 300: 39 MB) 596 / 533, bf16 d 64 8 units (512, 1000: 66 MB) 1180 / 985.
     const bool small_chunks = st->group == 1 && (double)C * (double)m_max * (double)d * (double)es <= 24.0e6;
-    const bool serial = forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks);
+    // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
+    // wait for each other have crashed the runtime, at the end of the capture and at a replay.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap));
+    const bool captured = cap != hipStreamCaptureStatusNone;
+    const bool serial = captured || (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks));
     if (serial) {
       for (const Chunk &ch : plan) {
         AttnArgs a;
@@ -1016,20 +1021,14 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   Dev cdv[kvm_state::kMaxChains];
   const int cb = dv.B / n_chains;  // sequences per chain
   // Streams of the library: one per chain; the one-launch folds have a second one on which the
-  // memory keys of a run, which depend on k alone, are computed while the run before it folds.  These two
-  // wait for each other in turn, which a capture of the call does not survive (the runtime crashes when the
-  // capture ends); captured, the keys are computed on the folds' stream.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIP_TRY(hipStreamIsCapturing(stream, &cap));
-  const bool captured = cap != hipStreamCaptureStatusNone;
-  const int n_streams = fused_folds && !captured ? 2 : n_chains;
+  // memory keys of a run, which depend on k alone, are computed while the run before it folds.
+  const int n_streams = fused_folds ? 2 : n_chains;
   st->stream_caller = stream;
   for (int c2 = 0; c2 < n_streams; ++c2) {
     if (!st->fold_streams[c2]) HIP_TRY(take_stream(st, stream, &st->fold_streams[c2]));
     fstream[c2] = st->fold_streams[c2];
     if (c2 < n_chains) cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
   }
-  const hipStream_t key_stream = fstream[n_streams - 1];   // of one-launch folds
   // From here on work is forked onto the fold streams.  Whatever happens, the caller's stream
   // waits for them before the call returns: they may still be reading the caller's k, v and gate.
   auto forked = [&]() -> int {
@@ -1084,7 +1083,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           for (int k2 = 0; k2 < n_waited && !seen; ++k2) seen = waited[k2] == e;
           if (!seen) {
             if (fused_folds)   // (the folds wait for the memory keys anyway: no second wait in the chain)
-              HIP_TRY(hipStreamWaitEvent(key_stream, e, 0));
+              HIP_TRY(hipStreamWaitEvent(fstream[1], e, 0));
             else
               for (int c2 = 0; c2 < n_chains; ++c2) HIP_TRY(hipStreamWaitEvent(fstream[c2], e, 0));
             waited[n_waited++] = e;
@@ -1114,14 +1113,12 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         const int half = runs++ & 1, slab0 = half * kvm::kFoldMaxSteps;
         Dev kdv = dv;
         kdv.kbar = (char *)dv.kbar + (size_t)slab0 * dv.Ufull * C * d * es;
-        if (key_stream != fstream[0] && keys_read_ev[half]) HIP_TRY(hipStreamWaitEvent(key_stream, keys_read_ev[half], 0));
-        HIP_TRY(kvm::launch_memkey(kdv, fsrc, run, key_stream));
-        if (key_stream != fstream[0]) {
-          hipEvent_t keys_ev;
-          HIP_TRY(next_sync_event(st, &keys_ev));
-          HIP_TRY(hipEventRecord(keys_ev, key_stream));
-          HIP_TRY(hipStreamWaitEvent(fstream[0], keys_ev, 0));
-        }
+        if (keys_read_ev[half]) HIP_TRY(hipStreamWaitEvent(fstream[1], keys_read_ev[half], 0));
+        HIP_TRY(kvm::launch_memkey(kdv, fsrc, run, fstream[1]));
+        hipEvent_t keys_ev;
+        HIP_TRY(next_sync_event(st, &keys_ev));
+        HIP_TRY(hipEventRecord(keys_ev, fstream[1]));
+        HIP_TRY(hipStreamWaitEvent(fstream[0], keys_ev, 0));
         {
           ProfileSpan span(st, 1, fstream[0], run);
           kvm::FoldRunArgs fr;
@@ -1137,10 +1134,9 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           }
           // (an event recorded behind the launch costs the chain some 4 us: 64 runs 8.12 ms, with it 8.50)
           HIP_TRY(next_sync_event(st, &last_fold_ev[0]));
-          rc_run = launch_run(st, fsrc, fr, narrow_folds, captured ? nullptr : last_fold_ev[0], fstream[0]);
+          rc_run = launch_run(st, fsrc, fr, narrow_folds, last_fold_ev[0], fstream[0]);
           if (rc_run != KVM_OK) return rc_run;
         }
-        if (captured) HIP_TRY(hipEventRecord(last_fold_ev[0], fstream[0]));
         keys_read_ev[half] = last_fold_ev[0];
       } else
       for (int c2 = 0; c2 < n_chains; ++c2) {
@@ -1540,7 +1536,9 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   a.P = (float *)(w + l.P); a.dS = (float *)(w + l.dS);
   a.par64 = (double *)(w + l.par64);
   kvm::BwdStreams x;
-  if (on_mfma) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
+  if (on_mfma && cap == hipStreamCaptureStatusNone) {   // (a captured call keeps to the caller's stream)
     st->stream_caller = (hipStream_t)stream;
     for (hipStream_t &fs : st->fold_streams)
       if (!fs) HIP_TRY(take_stream(st, (hipStream_t)stream, &fs));
