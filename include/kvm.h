@@ -231,7 +231,8 @@ int kvm_state_rows(const kvm_state *st, int64_t *m_out);          /* current m, 
 int kvm_state_tokens(const kvm_state *st, int64_t *tokens_seen);
 int kvm_state_capacity(const kvm_state *st, int64_t *rows_out);   /* rows the bound buffer holds */
 int kvm_state_folds(const kvm_state *st, int64_t *folds_out);     /* folds done so far */
-/* Which code path this state's folds take as things stand (its shape, the debug knobs):
+/* Which code path this state's folds take as things stand (its shape, the debug knobs), in a prompt
+ * of the length it was made for (shorter calls and single folds may take the other):
  * 1 = a run of folds in one launch, one workgroup per unit or several; 2 = one kernel per fold step.
  * For reports (bench.py names the kernels it timed); both paths compute the same fold. */
 int kvm_state_fold_path(const kvm_state *st, int64_t *path_out);

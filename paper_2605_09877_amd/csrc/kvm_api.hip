@@ -374,11 +374,23 @@ int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hip
 // 256-token blocks: 8.4 ms for 65536 tokens against 10.6 with a kernel per step).  Otherwise a fold
 // is a kernel per step: with tiles that stream the shared launch lost (64 units of 1024 rows, 4
 // workgroups each: 13 ms for 32768 tokens against 10.9); so it is when kvm_debug_set asks for it.
-// Sharing is for states of 8 units and more, blocks of up to 256 tokens, and room for more than four blocks.  Us per call, a
-// kernel per step against shared: 2 units, 10 blocks of 256 tokens 208 / 247, of 512 256 / 316; 32 units, 10 blocks of 512
-// 425 / 461; 8 units, 38 blocks of 512 1007 / 1057; 8 units, prompts of 2 and 3 blocks of 128 (one or two folds, each a run of
-// its own) 49 / 53 and 77 / 87.  The choice holds for a state's life, prompt and generation alike: the two paths' readout
-// rows may differ in a last bit, and a state that is exported and imported goes on as it would have.
+// Sharing is for states of 8 units and more, blocks of up to 256 tokens, and calls of 7 blocks and more, of 5 from 64 units
+// on, or any into a state of 1024 rows and more.  Us per call, a kernel per step / shared, by blocks of the call:
+//   units, block, rows     5              6              7              8              12
+//    8,    128,   256      109 / 122      121 / 126      138 / 134      152 / 147      223 / 208
+//    8,    256,  1024      129 / 139      144 / 145      165 / 155      185 / 165      287 / 236
+//   16,     64,   128      109 / 123      116 / 123      131 / 129      145 / 141      209 / 201
+//   32,    256,   512      152 / 151      176 / 157      201 / 172      226 / 186      340 / 265
+//   64,     64,   128      224 / 162      255 / 167      238 / 158      286 / 156      339 / 254
+//  128,    256,  1024      356 / 310      494 / 411      598 / 492      699 / 589     1125 / 906
+// (4 units: 256, 1024: 126 / 134 at 5 blocks, 175 / 160 at 8; 128, 256: 147 / 145 and 212 / 203 at 8 and 12.  512-token
+// blocks, 32 units, 10 blocks 425 / 461; 8 units, 38 blocks 1007 / 1057; 8 units, 5 and 8 blocks 170 / 182 and
+// 226 / 214: undecided, not shared.)
+// A fold by itself (decode, the fold entry point, chunk by chunk) is shared from units x block = 8192 or 1024 rows on.  Us
+// alone: 8 units of 128-token blocks on 256 rows 45 / 48, 16 of 256 on 256 47 / 49, 32 of 128 on 512 48 / 48; 32 of 256
+// on 512 52 / 49, 64 of 128 on 512 50 / 49, 128 of 256 on 512 75 / 70, 128 of 64 on 256 50 / 50; 8 of 128 on 768, 1024,
+// 2048 rows 46 / 47, 47 / 46, 52 / 46, 16 of 256 48 / 49, 50 / 49, 55 / 49.
+// Either path gives the same bits, so the choice may differ from call to call.
 // The device may have fewer compute units than the chip (a partition of it): what there is is asked for.
 int compute_units(const kvm_state *st) {
   int dev = 0, n = st->dbg[KVM_DEBUG_COMPUTE_UNITS];
@@ -389,30 +401,32 @@ int compute_units(const kvm_state *st) {
   }
   return n < kComputeUnits ? n : kComputeUnits;
 }
-constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareMinBlocks = 5;
-// Workgroups per unit on that path: 0 = a kernel per step.
-int fold_split(const kvm_state *st) {
+constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareAlone = 8192,
+              kShareAnyRows = 1024;
+// Workgroups per unit on that path, for the folds of a call of `blocks` blocks (1: a fold by itself) into the state as it
+// stands: 0 = a kernel per step.
+int fold_split(const kvm_state *st, int64_t blocks) {
   if (!st->mfma) return 0;
   const int path = st->dbg[KVM_DEBUG_FOLD_PATH];
   if (path == 2) return 0;
-  const int U = st->dv.U, forced = st->dbg[KVM_DEBUG_FOLD_SPLIT];
+  const int U = st->dv.U, C = st->dv.C, forced = st->dbg[KVM_DEBUG_FOLD_SPLIT];
   const int whole = kvm::fold_fused_fits(st->dv, 1) ? 1 : 0;
   const int most = most_split(U, st->dv.Mcap, compute_units(st));
   auto can_share = [&](int n) { return n > 1 && n <= most && kvm::fold_fused_fits(st->dv, n); };
   if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
   if (path == 1 || U >= kFusedMinUnits) return whole;
-  if (U < kShareMinUnits || st->dv.C > kShareMaxBlock || st->blocks < kShareMinBlocks) return 0;
+  if (U < kShareMinUnits || C > kShareMaxBlock) return 0;
+  if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) return 0;
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
-bool use_fused(const kvm_state *st) { return fold_split(st) > 0; }
 // The same for folds enqueued on `stream`: a launch whose workgroups meet carries numbers that hold once, so a graph
 // that is replayed cannot hold it; captured folds are a kernel per step (the same bits).
-int use_fused_on(const kvm_state *st, hipStream_t stream, bool *fused) {
-  *fused = use_fused(st);
-  if (*fused && fold_split(st) > 1) {
+int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream, int *split) {
+  *split = fold_split(st, blocks);
+  if (*split > 1) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(stream, &cap));
-    if (cap != hipStreamCaptureStatusNone) *fused = false;
+    if (cap != hipStreamCaptureStatusNone) *split = 0;
   }
   return KVM_OK;
 }
@@ -504,13 +518,13 @@ int clean_shares(kvm_state *st, hipStream_t stream) {
 constexpr uint32_t kPatience = 1000000;
 // Arguments of a one-launch run; with shared rows also what the workgroups of a unit meet at: the table, zeroed (on
 // `stream`) ahead of the first launch that uses it and whenever the 16 bits of an exchange number run out.
-int fused_run(kvm_state *st, bool in_place, hipStream_t stream, kvm::FoldRunArgs *out) {
+int fused_run(kvm_state *st, int split, bool in_place, hipStream_t stream, kvm::FoldRunArgs *out) {
   kvm::FoldRunArgs run = {};
   run.in_place = in_place ? 1 : 0;
   run.trace_assign = st->trace_assign;
   run.trace_score = st->trace_score;
   run.trace_stride = (int64_t)st->dv.U * st->dv.C;
-  run.split = fold_split(st);
+  run.split = split;
   if (run.split > 1) {
     if (!st->xtab_clean || st->xchg + kvm::kFoldMaxSteps > 0xffffu) {
       hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, stream, st->xtab, st->xtab_bytes / 8);
@@ -545,12 +559,12 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
   const Dev &dv = st->dv;
   const int so = slot_of(st, st->folds), sn = in_place ? so : slot_of(st, st->folds + 1);
   const size_t ntok = (size_t)dv.U * dv.C;
-  bool fused;
-  int rc_run = use_fused_on(st, stream, &fused);
+  int split;
+  int rc_run = fold_split_on(st, 1, stream, &split);
   if (rc_run != KVM_OK) return rc_run;
-  if (fused) {
+  if (split > 0) {
     kvm::FoldRunArgs run;
-    rc_run = fused_run(st, in_place, stream, &run);
+    rc_run = fused_run(st, split, in_place, stream, &run);
     if (rc_run != KVM_OK) return rc_run;
     run.n = 1;
     run.s[0] = {(int32_t)m, (int32_t)m_after, so, sn, 0, st->folds < st->trace_max ? (int32_t)st->folds : -1, 0,
@@ -997,11 +1011,12 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // whose chains run side by side on streams of their own (units are independent).  Two, not
   // more: with four chains the step was measured 40 % to 100 % slower, with four, eight and
   // sixteen hardware queues alike.
-  bool fused_folds;
+  int split;
   {
-    const int rc = use_fused_on(st, stream, &fused_folds);
+    const int rc = fold_split_on(st, (int64_t)plan.size(), stream, &split);
     if (rc != KVM_OK) return rc;
   }
+  const bool fused_folds = split > 0;
   int n_chains = 1;
   {
     int64_t m_max = 0;
@@ -1016,7 +1031,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // unit) unless asked otherwise: measured 7 % to 11 % ahead of the narrow one beside attention.
   // With a unit's rows shared among workgroups the narrow one is the default: it is the shape that
   // fits beside an attention workgroup, and sharing is chosen where the folds are to run hidden.
-  const bool narrow_folds = st->dbg[KVM_DEBUG_FOLD_WAVES] == 8 || (st->dbg[KVM_DEBUG_FOLD_WAVES] == 0 && fold_split(st) > 1);
+  const bool narrow_folds = st->dbg[KVM_DEBUG_FOLD_WAVES] == 8 || (st->dbg[KVM_DEBUG_FOLD_WAVES] == 0 && split > 1);
   hipStream_t fstream[kvm_state::kMaxChains];
   Dev cdv[kvm_state::kMaxChains];
   const int cb = dv.B / n_chains;  // sequences per chain
@@ -1122,7 +1137,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         {
           ProfileSpan span(st, 1, fstream[0], run);
           kvm::FoldRunArgs fr;
-          int rc_run = fused_run(st, false, fstream[0], &fr);
+          int rc_run = fused_run(st, split, false, fstream[0], &fr);
           if (rc_run != KVM_OK) return rc_run;
           fr.n = run;
           for (int i = 0; i < run; ++i) {
@@ -1578,7 +1593,7 @@ int kvm_state_capacity(const kvm_state *st, int64_t *rows_out) {
 }
 int kvm_state_fold_path(const kvm_state *st, int64_t *path_out) {
   if (!st || !path_out) return KVM_ERR_ARG;
-  *path_out = use_fused(st) ? 1 : 2;
+  *path_out = fold_split(st, st->blocks) > 0 ? 1 : 2;
   return KVM_OK;
 }
 int kvm_state_folds(const kvm_state *st, int64_t *folds_out) {
@@ -1690,7 +1705,7 @@ int kvm_state_import(kvm_state *st, const double *sK, const float *sV, const flo
   if (win_k) HIP_TRY(hipMemcpyAsync(dv.winK, win_k, win, hipMemcpyDeviceToDevice, stream));
   if (win_v) HIP_TRY(hipMemcpyAsync(dv.winV, win_v, win, hipMemcpyDeviceToDevice, stream));
   if (win_g) HIP_TRY(hipMemcpyAsync(dv.winG, win_g, U * dv.L * 4, hipMemcpyDeviceToDevice, stream));
-  if (use_fused(st))
+  if (fold_split(st, st->blocks) > 0)
     HIP_TRY(kvm::launch_refresh16(dv, (int)m, slot_of(st, folds), stream));
   else
     HIP_TRY(kvm::launch_refresh(dv, (int)m, slot_of(st, folds), stream));

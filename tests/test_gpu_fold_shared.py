@@ -171,9 +171,11 @@ def test_two_threads():
         same(o, want)
 
 
-@pytest.mark.parametrize("chunk,units,blocks,path", [(128, 8, 5, 1), (128, 7, 5, 2), (128, 8, 4, 2), (512, 8, 6, 2)])
+@pytest.mark.parametrize("chunk,units,blocks,path", [(128, 8, 7, 1), (128, 7, 7, 2), (128, 8, 6, 2), (512, 8, 8, 2),
+                                                     (64, 64, 5, 1), (64, 64, 4, 2), (64, 63, 5, 2)])
 def test_states_that_share_by_default(chunk, units, blocks, path):
-    """The edges of the default: 8 units, 256-token blocks, five blocks; results as a kernel per step either way."""
+    """The edges of the default: 8 units, 256-token blocks, seven blocks, five from 64 units on; results as a kernel per
+    step either way."""
     _, b, sy = kit()
     w = make(sy, chunk, units, chunk * blocks, 2 * chunk)
     got = run(w, {})
@@ -183,7 +185,7 @@ def test_states_that_share_by_default(chunk, units, blocks, path):
 
 @pytest.mark.parametrize("first", [4, 7])
 def test_a_grown_and_an_imported_state_continue_to_the_bit(first):
-    """States of 8 units made for fewer blocks than share rows (4) and for more (7), then grown or carried over into a
+    """States of 8 units made for fewer blocks than share rows (4) and for as many (7), then grown or carried over into a
     state of full size: outputs and state of the rest of the prompt are those of one that was whole from the start."""
     pkg, b, sy = kit()
     w = make(sy, 128, 8, 128 * 24, None)

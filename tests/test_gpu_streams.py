@@ -44,8 +44,8 @@ def any_attempt_is_independent(attempt):
 
 def workload(**kw):
     pkg, sy = kit()
-    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=8, n_kv_heads=8, chunk_len=128, seq=128 * 8,
-                  budget_fixed=256, **kw)
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=32, n_kv_heads=32, chunk_len=256, seq=256 * 8,
+                  budget_fixed=512, **kw)
     params = sy.make_params(w, DEV, plain=True)
 
     def make(schedule):
@@ -58,7 +58,7 @@ def workload(**kw):
 
 def test_shared_folds_of_two_states():
     make, qkv = workload()
-    states = [make(1) for _ in range(2)]   # chunk by chunk: no streams but the caller's
+    states = [make(1) for _ in range(2)]   # chunk by chunk: no streams but the caller's; 32 units of 256 share a fold
     assert states[0].fold_path == 1
     for st in states:
         st.prefill(*qkv)
