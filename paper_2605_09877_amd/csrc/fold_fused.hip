@@ -52,11 +52,11 @@
 // else the chip is doing.
 //
 // What bounds it: with shared rows, latency.  A fold of a 256-token block into some 300 rows (32 units x
-// 8 workgroups) takes 15 us without an append and 22 us with one, about 6 us more beside attention: an
+// 8 workgroups) takes 15 us without an append and 22 us with one, 29 us on average beside attention: an
 // exchange, two more round trips to memory (values of untouched rows, sums of touched rows), ten
 // barriers.  A kernel per step took 38 us and 62 us for the same.  Prefill of 65536 tokens with a
-// growing state (B 1 x H 32, 256-token blocks): 10.6 to 13.5 ms before (the box decides), 8.4 ms now; of a
-// layer's 16384 tokens with 256 rows: 3.3 ms before, 2.8 ms now.  With one workgroup per unit (256 units
+// growing state (B 2 x H 16, 256-token blocks): 10.6 to 13.5 ms before (the box decides), 8.0 to 8.2 ms now; of a
+// layer's 16384 tokens with 512 rows: 3.3 ms before, 2.8 ms now.  With one workgroup per unit (256 units
 // and more) by the tiles' and rows' traffic: B 16 x H 16, 8192 tokens, 5.06 ms before, 4.61 ms now
 // (keys of the next run computed beside the folds, gathered tokens, no separate copy pass).
 #include <cstddef>

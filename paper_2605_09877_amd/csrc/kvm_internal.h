@@ -158,9 +158,10 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st);
 // attn_mfma.hip: prompts in bf16, d = 128 or 64, blocks of a multiple of 64 tokens (tiles of 64 keys neither cross
 // from the ring into the call's keys nor wrap in the ring); everything else is the row kernel's
-// With d = 64 and few queries in a chunk's launch the row kernel, a workgroup per query and head, still fills more of the
-// chip: 8192 of them 97 us against 19 on the matrix cores, but 1024 (one sequence, 2 heads, 512-token blocks) 23 us
-// less in a training call of 455 us.
+// With d = 64 and few queries in a chunk's launch the row kernel, a workgroup per query and head, fills more of the chip.
+// Attention us a launch, row kernel / tiles, by queries x heads of the chunk (64-, 256-, 512-token blocks, rows = block):
+// 512: 8.8 / 10.3, 12.8 / 19.4, 20.5 / 32.0; 1024: 10.7 / 10.2, 18.0 / 19.5, 29.0 / 32.8; 2048: 15.5 / 10.2, 27.2 / 19.4,
+// 46.4 / 33.0; 8192: 80.6 / 19.5 (256), 140.5 / 33.2 (512); with 1000 rows the same order at every one of them.
 inline bool attention_on_mfma(const Dev &dv) {
   return dv.io == 1 && dv.C % 64 == 0 && (dv.d == 128 || (dv.d == 64 && (int64_t)dv.B * dv.Hq * dv.C > 1024));
 }

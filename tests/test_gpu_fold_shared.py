@@ -218,3 +218,49 @@ def test_fewer_compute_units(compute_units, path):
     got = run(w, {b.KVM_DEBUG_COMPUTE_UNITS: compute_units})
     assert got[0].fold_path == path
     same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
+
+
+def test_exchange_numbers_run_out():
+    """A state's shared folds are told apart by 16-bit numbers; the table is cleared before they repeat (after some 65530
+    folds: in the 129th of these prompts)."""
+    pkg, b, sy = kit()
+    w = make(sy, 64, 2, 64 * 512, 128)
+    q, k, v = sy.make_qkv(w, DEV)
+    p = sy.make_params(w, DEV, plain=False)
+    ref = pkg.state_for(w, device=DEV, **p)
+    ref.debug_set(b.KVM_DEBUG_FOLD_PATH, 2)
+    want = ref.prefill(q, k, v, p["gate"])
+    st = pkg.state_for(w, device=DEV, **p)
+    st.debug_set(b.KVM_DEBUG_FOLD_SPLIT, 2)
+    assert st.fold_path == 1
+    for i in range(132):
+        st.reset()
+        got = st.prefill(q, k, v, p["gate"])
+        if i == 0 or i > 124:
+            assert torch.equal(got, want), i
+    a, e = st.export(), ref.export()
+    for key in ("sK", "sV", "rho", "n", "w", "khat", "vhat"):
+        assert torch.equal(a[key], e[key]), key
+
+
+def test_arrangement_changes_between_calls():
+    """The workgroups' meeting counts on over launches of different widths, taken-over units among them."""
+    pkg, b, sy = kit()
+    w = make(sy, 128, 4, 128 * 24, 1024)
+    q, k, v = sy.make_qkv(w, DEV)
+    p = sy.make_params(w, DEV, plain=False)
+    part = lambda x, lo, hi: x[:, lo:hi].contiguous()
+    ref = pkg.state_for(w, device=DEV, **p)
+    ref.debug_set(b.KVM_DEBUG_FOLD_PATH, 2)
+    want = ref.prefill(q, k, v, p["gate"])
+    st = pkg.state_for(w, device=DEV, **p)
+    out = []
+    for i, (split, patience) in enumerate([(2, 0), (16, 0), (4, 1), (8, 51), (1, 0), (16, 1), (2, 0), (4, 0)]):
+        st.debug_set(b.KVM_DEBUG_FOLD_SPLIT, split)
+        st.debug_set(b.KVM_DEBUG_FOLD_PATIENCE, patience)
+        lo, hi = 384 * i, 384 * (i + 1)
+        out.append(st.prefill(part(q, lo, hi), part(k, lo, hi), part(v, lo, hi), part(p["gate"], lo, hi)))
+    assert torch.equal(torch.cat(out, dim=1), want)
+    a, e = st.export(), ref.export()
+    for key in ("sK", "sV", "rho", "n", "w", "khat", "vhat"):
+        assert torch.equal(a[key], e[key]), key
