@@ -390,7 +390,9 @@ int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hip
 // alone: 8 units of 128-token blocks on 256 rows 45 / 48, 16 of 256 on 256 47 / 49, 32 of 128 on 512 48 / 48; 32 of 256
 // on 512 52 / 49, 64 of 128 on 512 50 / 49, 128 of 256 on 512 75 / 70, 128 of 64 on 256 50 / 50; 8 of 128 on 768, 1024,
 // 2048 rows 46 / 47, 47 / 46, 52 / 46, 16 of 256 48 / 49, 50 / 49, 55 / 49.
-// Either path gives the same bits, so the choice may differ from call to call.
+// Either path leaves the same state to the bit (of the record, the winning score of a token that moved to a row of the same
+// fold may be another fp32 sum), so the choice may differ from call to call.
+
 // The device may have fewer compute units than the chip (a partition of it): what there is is asked for.
 int compute_units(const kvm_state *st) {
   int dev = 0, n = st->dbg[KVM_DEBUG_COMPUTE_UNITS];
@@ -419,16 +421,19 @@ int fold_split(const kvm_state *st, int64_t blocks) {
   if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) return 0;
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
+// Whether work put on `stream` goes into a graph.  (The query fails for the legacy stream while another thread captures:
+// that stream is not captured.)
+bool captured(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
 // The same for folds enqueued on `stream`: a launch whose workgroups meet carries numbers that hold once, so a graph
 // that is replayed cannot hold it; captured folds are a kernel per step (the same bits).
-int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream, int *split) {
-  *split = fold_split(st, blocks);
-  if (*split > 1) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(stream, &cap));
-    if (cap != hipStreamCaptureStatusNone) *split = 0;
-  }
-  return KVM_OK;
+int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
+  const int split = fold_split(st, blocks);
+  return split > 1 && captured(stream) ? 0 : split;
 }
 
 constexpr int kMaxDevices = 64;
@@ -507,9 +512,7 @@ int clean_shares(kvm_state *st, hipStream_t stream) {
   hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, stream, (unsigned long long *)st->dv.part_cnt,
                      (size_t)kvm::kShareGroups / 2);
   HIP_TRY(hipGetLastError());
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIP_TRY(hipStreamIsCapturing(stream, &cap));
-  st->part_clean = cap == hipStreamCaptureStatusNone;
+  st->part_clean = !captured(stream);
   return KVM_OK;
 }
 
@@ -542,10 +545,10 @@ int fused_run(kvm_state *st, int split, bool in_place, hipStream_t stream, kvm::
   *out = run;
   return KVM_OK;
 }
-// The exchange number of a fold: consecutive (none is used up when the whole block is appended).
-uint32_t take_exchange(kvm_state *st, int64_t m, int64_t m_after) {
+// The exchange number of a fold: consecutive (none is used up without an exchange).
+uint32_t take_exchange(kvm_state *st, int split, int64_t m, int64_t m_after) {
   const uint32_t num = st->xchg;
-  st->xchg += m_after - m == st->dv.C ? 0u : 1u;
+  st->xchg += split <= 1 || m_after - m == st->dv.C ? 0u : 1u;
   return num;
 }
 
@@ -559,16 +562,14 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
   const Dev &dv = st->dv;
   const int so = slot_of(st, st->folds), sn = in_place ? so : slot_of(st, st->folds + 1);
   const size_t ntok = (size_t)dv.U * dv.C;
-  int split;
-  int rc_run = fold_split_on(st, 1, stream, &split);
-  if (rc_run != KVM_OK) return rc_run;
+  const int split = fold_split_on(st, 1, stream);
   if (split > 0) {
     kvm::FoldRunArgs run;
-    rc_run = fused_run(st, split, in_place, stream, &run);
+    int rc_run = fused_run(st, split, in_place, stream, &run);
     if (rc_run != KVM_OK) return rc_run;
     run.n = 1;
     run.s[0] = {(int32_t)m, (int32_t)m_after, so, sn, 0, st->folds < st->trace_max ? (int32_t)st->folds : -1, 0,
-                take_exchange(st, m, m_after), 0u};
+                take_exchange(st, split, m, m_after), 0u};
     HIP_TRY(kvm::launch_memkey(dv, src, 1, stream));
     // a fold of its own (decode, the fold entry point, the chunk-by-chunk schedule): the narrow
     // workgroup, two to a compute unit, unless asked otherwise (measured 3 % ahead of the wide one)
@@ -958,10 +959,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     const bool small_chunks = st->group == 1 && (double)C * (double)m_max * (double)d * (double)es <= 24.0e6;
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(stream, &cap));
-    const bool captured = cap != hipStreamCaptureStatusNone;
-    const bool serial = captured || (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks));
+    const bool serial = captured(stream) || (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks));
     if (serial) {
       for (const Chunk &ch : plan) {
         AttnArgs a;
@@ -1011,11 +1009,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // whose chains run side by side on streams of their own (units are independent).  Two, not
   // more: with four chains the step was measured 40 % to 100 % slower, with four, eight and
   // sixteen hardware queues alike.
-  int split;
-  {
-    const int rc = fold_split_on(st, (int64_t)plan.size(), stream, &split);
-    if (rc != KVM_OK) return rc;
-  }
+  const int split = fold_split_on(st, (int64_t)plan.size(), stream);
   const bool fused_folds = split > 0;
   int n_chains = 1;
   {
@@ -1145,7 +1139,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
             const int64_t fold_no = st->folds + i;
             fr.s[i] = {(int32_t)steps[i].m, (int32_t)steps[i].m_after, steps[i].so, steps[i].sn,
                        batched ? lo - lo0 : 0, fold_no < st->trace_max ? (int32_t)fold_no : -1, slab0 + i,
-                       take_exchange(st, steps[i].m, steps[i].m_after), 0u};
+                       take_exchange(st, split, steps[i].m, steps[i].m_after), 0u};
           }
           // (an event recorded behind the launch costs the chain some 4 us: 64 runs 8.12 ms, with it 8.50)
           HIP_TRY(next_sync_event(st, &last_fold_ev[0]));
@@ -1551,9 +1545,7 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   a.P = (float *)(w + l.P); a.dS = (float *)(w + l.dS);
   a.par64 = (double *)(w + l.par64);
   kvm::BwdStreams x;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
-  if (on_mfma && cap == hipStreamCaptureStatusNone) {   // (a captured call keeps to the caller's stream)
+  if (on_mfma && !captured((hipStream_t)stream)) {   // (a captured call keeps to the caller's stream)
     st->stream_caller = (hipStream_t)stream;
     for (hipStream_t &fs : st->fold_streams)
       if (!fs) HIP_TRY(take_stream(st, (hipStream_t)stream, &fs));

@@ -39,6 +39,7 @@ def any_attempt_is_independent(attempt):
         free.synchronize()
         done.append(not slept.query())
         torch.cuda.synchronize()
+    print('independent attempts:', sum(done), 'of', len(done))
     assert any(done)
 
 
