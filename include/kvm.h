@@ -17,9 +17,9 @@
  *    a plain pointer so that this header needs no HIP header; NULL = the default stream) and
  *    returns without synchronising the host: work the caller enqueues on that stream afterwards
  *    sees all of it.  kvm_prefill_chunked and kvm_prefill_backward also use two streams of the
- *    library's (default priority, non-blocking, made at first use; a dropped state's go to the next
- *    state on the same caller's stream): part of their kernels runs there, forked from and joined
- *    back to the caller's stream by events inside the call.  Calls on different streams do not
+ *    library's (default priority, non-blocking, made at first use, the same two for all states on
+ *    one caller's stream): part of their kernels runs there, forked from and joined back to the
+ *    caller's stream by events inside the call, except under capture into a graph.  Calls on different streams do not
  *    wait for each other.  Calls on one
  *    state must be issued in order on one stream (or be ordered by the caller).
  *  - Return value: KVM_OK (0) or a negative kvm_status.  Argument, state and capacity errors

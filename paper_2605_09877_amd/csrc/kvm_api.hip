@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -17,6 +18,15 @@
 using kvm::AttnArgs;
 using kvm::Dev;
 using kvm::Src;
+
+// The library's two streams beside a caller's stream.  All states that are used on a caller's stream share them: their calls
+// are in order there, every call forks from it and joins it, and so the two streams order nothing that it does not.
+struct SideStreams {
+  hipStream_t caller, s[2];
+  int dev, states;       // how many states hold them
+  uint64_t let_go;       // when the last one did, by a count
+  SideStreams *next;
+};
 
 struct kvm_state {
   kvm_config cfg;
@@ -44,9 +54,7 @@ struct kvm_state {
   // prefill pipeline: folds run ahead on a library-owned stream, attention follows in groups
   int64_t inplace = 0;  // folds done in place so far: version v lives in slot (v - inplace) mod NS
   static constexpr int kMaxChains = 2;
-  hipStream_t fold_streams[kMaxChains] = {nullptr, nullptr};   // on loan from the device's idle ones (take_stream)
-  int stream_dev = -1;
-  hipStream_t stream_caller = nullptr;   // the caller's stream of the latest call that used them
+  SideStreams *side = nullptr;   // of the caller's stream that the latest call used them on (use_side_streams)
   std::vector<hipEvent_t> sync_events;  // untimed events, reused call after call
   size_t sync_used = 0;
   // optional kernel timing: (start, stop, class) event pairs, events reused across reads
@@ -436,7 +444,6 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
   return split > 1 && captured(stream) ? 0 : split;
 }
 
-constexpr int kMaxDevices = 64;
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
                hipStream_t stream) {
@@ -450,54 +457,74 @@ int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool 
   return KVM_OK;
 }
 
-// The library's streams go from state to state.  A training step makes a state, runs it forward and backward and
-// drops it: making two streams took 0.2 to 0.4 ms of host time each, dropping them 0.15 ms and a wait for the
-// device, of the 0.41 ms that a step on 43 tokens took.  A stream goes to a state that is used on the caller's stream
-// its last holder was used on: that stream orders what was left on it anyway.  For any other caller it could hold
-// work that waits for something the caller knows nothing of.  At most kMost per device are kept, the latest ones.
-// A stream that is still part of a capture is destroyed.
-struct IdleStreams {
-  static constexpr int kMost = 8;
-  std::mutex lock;
-  struct {
-    hipStream_t s, caller;
-  } idle[kMost];   // oldest first
-  int n = 0;
-};
-IdleStreams g_idle_streams[kMaxDevices];
-hipError_t take_stream(kvm_state *st, hipStream_t caller, hipStream_t *out) {
+// A training step makes a state, runs it forward and backward and drops it: making two streams for it took 0.2 to 0.4 ms of
+// host time each, dropping them 0.15 ms and a wait for the device, of the 0.41 ms that a step on 43 tokens took.  So
+// a caller's stream keeps its two when the last of its states is gone, as long as there are no more than kIdleMost such pairs
+// on the device (the ones let go first are destroyed).  One pair for all states also keeps the two apart from each other and from
+// the caller on the few hardware queues: streams get queues in turn, and pairs mixed from what dropped states
+// had left shared one at times (12 blocks of 512 tokens, 8 units, two fold chains: 870 us, with both on one queue 1140).
+constexpr int kIdleMost = 4;
+std::mutex g_side_lock;
+SideStreams *g_side = nullptr;
+uint64_t g_side_count = 0;
+
+void destroy_side(SideStreams *x) {
+  for (hipStream_t s : x->s)
+    if (s) (void)hipStreamDestroy(s);
+  delete x;
+}
+void let_side_streams_go(kvm_state *st) {
+  SideStreams *gone = nullptr;
+  {
+    std::lock_guard<std::mutex> hold(g_side_lock);
+    SideStreams *x = st->side;
+    st->side = nullptr;
+    if (!x || --x->states > 0) return;
+    x->let_go = ++g_side_count;
+    int idle = 0;
+    SideStreams **oldest = nullptr;
+    for (SideStreams **p = &g_side; *p; p = &(*p)->next)
+      if ((*p)->states == 0 && (*p)->dev == x->dev) {
+        ++idle;
+        if (!oldest || (*p)->let_go < (*oldest)->let_go) oldest = p;
+      }
+    if (idle > kIdleMost) {
+      gone = *oldest;
+      *oldest = gone->next;
+    }
+  }
+  if (gone) destroy_side(gone);
+}
+// st->side: the two streams beside `caller`.
+int use_side_streams(kvm_state *st, hipStream_t caller) {
   int dev = 0;
-  const hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  st->stream_dev = dev;
-  if (dev >= 0 && dev < kMaxDevices) {
-    IdleStreams &p = g_idle_streams[dev];
-    std::lock_guard<std::mutex> hold(p.lock);
-    for (int i = p.n - 1; i >= 0; --i)
-      if (p.idle[i].caller == caller && caller != hipStreamPerThread) {   // (one handle, a stream per thread)
-        *out = p.idle[i].s;
-        for (--p.n; i < p.n; ++i) p.idle[i] = p.idle[i + 1];
-        return hipSuccess;
+  HIP_TRY(hipGetDevice(&dev));
+  if (st->side && st->side->caller == caller && st->side->dev == dev) return KVM_OK;
+  let_side_streams_go(st);
+  {
+    std::lock_guard<std::mutex> hold(g_side_lock);
+    for (SideStreams *x = g_side; x; x = x->next)
+      if (x->caller == caller && x->dev == dev && caller != hipStreamPerThread) {   // (one handle, a stream per thread)
+        ++x->states;
+        st->side = x;
+        return KVM_OK;
       }
   }
-  return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
-}
-void give_stream(int dev, hipStream_t caller, hipStream_t s) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (dev >= 0 && dev < kMaxDevices && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-    IdleStreams &p = g_idle_streams[dev];
-    std::lock_guard<std::mutex> hold(p.lock);
-    const hipStream_t oldest = p.idle[0].s;
-    const bool full = p.n == IdleStreams::kMost;
-    if (full)
-      for (int i = 0; i + 1 < p.n; ++i) p.idle[i] = p.idle[i + 1];
-    else
-      ++p.n;
-    p.idle[p.n - 1] = {s, caller};
-    if (!full) return;
-    s = oldest;
+  SideStreams *x = new (std::nothrow) SideStreams{caller, {nullptr, nullptr}, dev, 1, 0, nullptr};
+  if (!x) return KVM_ERR_HIP;
+  for (hipStream_t &s : x->s) {
+    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) {
+      s = nullptr;
+      destroy_side(x);
+      HIP_TRY(e);
+    }
   }
-  (void)hipStreamDestroy(s);
+  std::lock_guard<std::mutex> hold(g_side_lock);
+  x->next = g_side;
+  g_side = x;
+  st->side = x;
+  return KVM_OK;
 }
 
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long *p, size_t n) {
@@ -831,8 +858,7 @@ int kvm_state_destroy(kvm_state *st) {
     }
     for (auto e : st->free_events) (void)hipEventDestroy(e);
     for (auto e : st->sync_events) (void)hipEventDestroy(e);
-    for (hipStream_t fs : st->fold_streams)
-      if (fs) give_stream(st->stream_dev, st->stream_caller, fs);
+    let_side_streams_go(st);
   }
   delete st;
   return KVM_OK;
@@ -1032,10 +1058,12 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // Streams of the library: one per chain; the one-launch folds have a second one on which the
   // memory keys of a run, which depend on k alone, are computed while the run before it folds.
   const int n_streams = fused_folds ? 2 : n_chains;
-  st->stream_caller = stream;
+  {
+    const int rc = use_side_streams(st, stream);
+    if (rc != KVM_OK) return rc;
+  }
   for (int c2 = 0; c2 < n_streams; ++c2) {
-    if (!st->fold_streams[c2]) HIP_TRY(take_stream(st, stream, &st->fold_streams[c2]));
-    fstream[c2] = st->fold_streams[c2];
+    fstream[c2] = st->side->s[c2];
     if (c2 < n_chains) cdv[c2] = n_chains == 1 ? dv : batch_view(dv, c2 * cb, cb, es);
   }
   // From here on work is forked onto the fold streams.  Whatever happens, the caller's stream
@@ -1546,11 +1574,10 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   a.par64 = (double *)(w + l.par64);
   kvm::BwdStreams x;
   if (on_mfma && !captured((hipStream_t)stream)) {   // (a captured call keeps to the caller's stream)
-    st->stream_caller = (hipStream_t)stream;
-    for (hipStream_t &fs : st->fold_streams)
-      if (!fs) HIP_TRY(take_stream(st, (hipStream_t)stream, &fs));
-    x.side = st->fold_streams[0];
-    x.side2 = st->fold_streams[1];
+    const int rc = use_side_streams(st, (hipStream_t)stream);
+    if (rc != KVM_OK) return rc;
+    x.side = st->side->s[0];
+    x.side2 = st->side->s[1];
     st->sync_used = 0;
     for (hipEvent_t *e : {&x.fork, &x.dq_done, &x.join_state, &x.join_window[0], &x.join_window[1]})
       HIP_TRY(next_sync_event(st, e));
