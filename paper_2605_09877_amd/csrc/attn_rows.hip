@@ -96,7 +96,10 @@ __device__ __forceinline__ void combine_shares(const RowQuery<T> &rq) {
   }
 }
 
-template <typename T, int D, int GQ>
+// kShared: the keys may be shared among workgroups.  A kernel of its own, because what sharing adds costs registers, in bf16
+// one head at a time 82 instead of 79 and with them a wave per SIMD (five instead of six): 40 sequences of 16 heads on
+// 328 rows, their fold included, 31.2 instead of 30.5 us a token, 10 of 32 heads on 16 17.0 instead of 16.7.
+template <typename T, int D, int GQ, bool kShared>
 __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
   constexpr int VEC = Vec16<T>::kN;
   constexpr int LPR = D / VEC;   // lanes per key row
@@ -129,7 +132,7 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
   const int m = rq.m;
   int total = m + (int)(pos - wb + 1);
   int n_first = 0;
-  if (rq.n_split > 1) {
+  if constexpr (kShared) {
     // this workgroup's share: whole rounds of the loop below (a share can be empty)
     constexpr int kRound = 4 * RPW * KB;
     const int per = ((total + rq.n_split - 1) / rq.n_split + kRound - 1) / kRound * kRound;
@@ -242,12 +245,12 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
 #pragma unroll
       for (int wv = 0; wv < 4; ++wv) {
         // a wave that saw no key has max -inf -> 0 (none of them did: an empty share)
-        const float sc = mm == -INFINITY ? 0.f : exp2f(sh_m[hh][wv] - mm);
+        const float sc = kShared && mm == -INFINITY ? 0.f : exp2f(sh_m[hh][wv] - mm);
         l += sh_l[hh][wv] * sc;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) o[i] += sh_acc[hh][wv][cl * VEC + i] * sc;
       }
-      if (rq.n_split > 1) {
+      if constexpr (kShared) {
         // a share's maximum is -inf when it was empty (then l and o are 0 * finite = 0)
         const int slot = rq.split * GQ + hh;
 #pragma unroll
@@ -262,7 +265,7 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
       if (rq.lse && cl == 0) rq.lse[hh * rq.lse_h] = (mm + log2f(l)) * kLn2;
     }
   }
-  if (rq.n_split > 1) combine_shares<T, D, GQ>(rq);
+  if constexpr (kShared) combine_shares<T, D, GQ>(rq);
 }
 
 // Where the shares of query-head group number `group` of the launch go.
@@ -274,12 +277,12 @@ __device__ __forceinline__ void set_share(RowQuery<T> &rq, const Dev &dv, int gr
   rq.part_cnt = dv.part_cnt + group;
 }
 
-// One workgroup per (query, group of GQ query heads, sequence) of one state; in a decode step
-// several per group, sharing its keys.
-template <typename T, int D, int GQ>
+// One workgroup per (query, group of GQ query heads, sequence) of one state; shared, a decode step's:
+// several per group.
+template <typename T, int D, int GQ, bool kShared>
 __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
   // a decode step has one query per sequence, and the x dimension counts the shares of its keys
-  const int qi = a.put_token ? 0 : blockIdx.x, hq = blockIdx.y * GQ, b = blockIdx.z;
+  const int qi = kShared ? 0 : blockIdx.x, hq = blockIdx.y * GQ, b = blockIdx.z;
   const int hkv = hq / (dv.Hq / dv.Hkv);
   const int u = b * dv.Hkv + hkv;
   RowQuery<T> rq;
@@ -305,22 +308,22 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
   rq.put_k = rq.put_v = nullptr;
   rq.put_g = nullptr;
   rq.gate = 1.f;
-  rq.split = blockIdx.x;
-  rq.n_split = a.put_token ? gridDim.x : 1;
-  set_share<T, D, GQ>(rq, dv, b * gridDim.y + blockIdx.y);
+  rq.split = kShared ? blockIdx.x : 0;
+  rq.n_split = kShared ? gridDim.x : 1;
+  if constexpr (kShared) set_share<T, D, GQ>(rq, dv, b * gridDim.y + blockIdx.y);
   if (a.put_token && rq.split == 0 && hq == hkv * (dv.Hq / dv.Hkv)) {
     rq.put_k = (T *)dv.winK + (int64_t)u * dv.L * D;
     rq.put_v = (T *)dv.winV + (int64_t)u * dv.L * D;
     rq.put_g = dv.winG + (int64_t)u * dv.L;
     rq.gate = a.in.g ? a.in.g[b * a.in.g_b + hkv * a.in.g_h + (rq.pos - a.t0) * a.in.g_t] : 1.f;
   }
-  attn_row<T, D, GQ>(dv, rq);
+  attn_row<T, D, GQ, kShared>(dv, rq);
 }
 
 // Decode over sequences that live in different states (each at its own position, with its own
 // number of state rows): one workgroup, or several sharing the keys, per (group of GQ query heads,
 // sequence); sequence s reads seq[s].  dv is the states' common configuration (heads, chunk, window, temperatures).
-template <typename T, int D, int GQ>
+template <typename T, int D, int GQ, bool kShared>
 __global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, const void *q,
                                                               const void *k, const void *v, const float *gate,
                                                               void *out) {
@@ -348,16 +351,16 @@ __global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqD
   rq.put_k = rq.put_v = nullptr;
   rq.put_g = nullptr;
   rq.gate = 1.f;
-  rq.split = blockIdx.x;
-  rq.n_split = gridDim.x;
-  set_share<T, D, GQ>(rq, dv, s * gridDim.y + blockIdx.y);
+  rq.split = kShared ? blockIdx.x : 0;
+  rq.n_split = kShared ? gridDim.x : 1;
+  if constexpr (kShared) set_share<T, D, GQ>(rq, dv, s * gridDim.y + blockIdx.y);
   if (rq.split == 0 && hq == hkv * (dv.Hq / dv.Hkv)) {
     rq.put_k = (T *)sd.winK + (int64_t)hkv * dv.L * D;
     rq.put_v = (T *)sd.winV + (int64_t)hkv * dv.L * D;
     rq.put_g = sd.winG + (int64_t)hkv * dv.L;
     rq.gate = gate ? gate[(int64_t)s * dv.Hkv + hkv] : 1.f;
   }
-  attn_row<T, D, GQ>(dv, rq);
+  attn_row<T, D, GQ, kShared>(dv, rq);
 }
 
 // Query heads a decode workgroup takes together: the KV head's whole group when it has 2 or 4
@@ -385,18 +388,27 @@ int round_keys(const Dev &dv) { return 16 * 64 / (dv.d / (dv.io == 0 ? 4 : 8)); 
 
 }  // namespace
 
-#define KVM_ROWS_DISPATCH(KERNEL, GQV, grid, ...)                                                   \
+#define KVM_ROWS_DISPATCH(KERNEL, GQV, SHARED, grid, ...)                                           \
   do {                                                                                              \
     if (dv.io == 0 && dv.d == 64)                                                                   \
-      hipLaunchKernelGGL((KERNEL<float, 64, GQV>), grid, dim3(256), 0, st, __VA_ARGS__);            \
+      hipLaunchKernelGGL((KERNEL<float, 64, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);    \
     else if (dv.io == 0 && dv.d == 128)                                                             \
-      hipLaunchKernelGGL((KERNEL<float, 128, GQV>), grid, dim3(256), 0, st, __VA_ARGS__);           \
+      hipLaunchKernelGGL((KERNEL<float, 128, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);   \
     else if (dv.io == 1 && dv.d == 64)                                                              \
-      hipLaunchKernelGGL((KERNEL<bf16_t, 64, GQV>), grid, dim3(256), 0, st, __VA_ARGS__);           \
+      hipLaunchKernelGGL((KERNEL<bf16_t, 64, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);   \
     else if (dv.io == 1 && dv.d == 128)                                                             \
-      hipLaunchKernelGGL((KERNEL<bf16_t, 128, GQV>), grid, dim3(256), 0, st, __VA_ARGS__);          \
+      hipLaunchKernelGGL((KERNEL<bf16_t, 128, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);  \
     else                                                                                            \
       return hipErrorInvalidValue;                                                                  \
+  } while (0)
+#define KVM_ROWS_LAUNCH(KERNEL, SHARED, grid, ...)             \
+  do {                                                         \
+    if (gq == 4)                                               \
+      KVM_ROWS_DISPATCH(KERNEL, 4, SHARED, grid, __VA_ARGS__); \
+    else if (gq == 2)                                          \
+      KVM_ROWS_DISPATCH(KERNEL, 2, SHARED, grid, __VA_ARGS__); \
+    else                                                       \
+      KVM_ROWS_DISPATCH(KERNEL, 1, SHARED, grid, __VA_ARGS__); \
   } while (0)
 
 hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
@@ -410,12 +422,10 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
     nx = shares_for(dv, gq, dv.Hq / gq * dv.B, a.m[0] + (int)win, round_keys(dv));
   }
   dim3 grid(nx, dv.Hq / gq, dv.B);
-  if (gq == 4)
-    KVM_ROWS_DISPATCH(attn_rows_kernel, 4, grid, dv, a);
-  else if (gq == 2)
-    KVM_ROWS_DISPATCH(attn_rows_kernel, 2, grid, dv, a);
+  if (a.put_token && nx > 1)
+    KVM_ROWS_LAUNCH(attn_rows_kernel, true, grid, dv, a);
   else
-    KVM_ROWS_DISPATCH(attn_rows_kernel, 1, grid, dv, a);
+    KVM_ROWS_LAUNCH(attn_rows_kernel, false, grid, dv, a);
   return hipGetLastError();
 }
 
@@ -424,12 +434,10 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
   if (n_seq <= 0) return hipSuccess;
   const int gq = heads_together(dv);
   dim3 agrid(shares_for(dv, gq, dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
-  if (gq == 4)
-    KVM_ROWS_DISPATCH(attn_rows_multi_kernel, 4, agrid, dv, seq, q, k, v, gate, out);
-  else if (gq == 2)
-    KVM_ROWS_DISPATCH(attn_rows_multi_kernel, 2, agrid, dv, seq, q, k, v, gate, out);
+  if (agrid.x > 1)
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, true, agrid, dv, seq, q, k, v, gate, out);
   else
-    KVM_ROWS_DISPATCH(attn_rows_multi_kernel, 1, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, agrid, dv, seq, q, k, v, gate, out);
   return hipGetLastError();
 }
 

@@ -985,7 +985,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     const bool small_chunks = st->group == 1 && (double)C * (double)m_max * (double)d * (double)es <= 24.0e6;
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.
-    const bool serial = captured(stream) || (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks));
+    const bool serial = (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks)) || captured(stream);
     if (serial) {
       for (const Chunk &ch : plan) {
         AttnArgs a;
