@@ -485,7 +485,10 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel_d64(Dev dv, AttnArgs 
 
 }  // namespace
 
-hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st) {
+hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st) {
+  static const hipError_t attr = hipFuncSetAttribute((const void *)attn_mfma_kernel_q128,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBesideFoldLds);
+  if (attr != hipSuccess) return attr;
   if (a.nq_total <= 0) return hipSuccess;
   const int Gq = dv.Hq / dv.Hkv;
   const bool by_head = Gq % 4 == 0;  // as in the kernel: four heads x 32 positions, or 128 positions of one head
@@ -496,7 +499,7 @@ hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   if (dv.d == 64)
     hipLaunchKernelGGL(attn_mfma_kernel_d64, grid, dim3(256), 0, st, dv, a);
   else
-    hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), 0, st, dv, a);
+    hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), beside_folds ? kBesideFoldLds : 0, st, dv, a);
   return hipGetLastError();
 }
 

@@ -1049,6 +1049,7 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
     run_n = a.run.n;
     run_in_place = a.run.in_place;
   }
+  __builtin_amdgcn_s_setprio(3);   // ahead of an attention workgroup's waves on the same compute unit: the chain waits for this one
   const float qnan = __uint_as_float(0x7fc00000u);
 #ifdef KVM_FOLD_STAMPS
   if (threadIdx.x == 0) cx.s_cnt()[kCntStamps] = 0;
@@ -1279,6 +1280,10 @@ bool fold_fused_fits(const Dev &dv, int split) {
 bool fold_fused_resident(const Dev &dv, int split, bool narrow) {
   return fold_fused_fits(dv, split) && resident_tiles(dv, narrow ? 8 : 16, split, narrow ? kLdsNarrow : kLdsWide) > 0;
 }
+bool fold_fused_beside(const Dev &dv, int split) {
+  return split > 1 && fold_fused_fits(dv, split) && resident_tiles(dv, 8, split, kLdsBesideAttention) > 0 &&
+         lds_bytes(dv, 8, split, kLdsBesideAttention) <= kLdsBesideAttention;
+}
 
 size_t fold_exchange_bytes(int64_t units, int C, int split) {
   return split > 1 ? (size_t)units * (kArrivalWords + 2 * split * 2 * C) * sizeof(unsigned long long) : 0;
@@ -1302,7 +1307,8 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
   FoldRunArgs run = run_;
   const int split = run.split, NW = narrow ? 8 : 16;
   if (split < 1 || (split > 1 && !run.xtab)) return hipErrorInvalidValue;
-  const size_t limit = narrow ? kLdsNarrow : kLdsWide;
+  const size_t limit = run.beside ? kLdsBesideAttention : narrow ? kLdsNarrow : kLdsWide;
+  if (run.beside && (!narrow || !fold_fused_beside(dv, split))) return hipErrorInvalidValue;
   run.resident = resident_tiles(dv, NW, split, limit);
   run.gather = gather_tokens_most(dv, NW, split, limit);
   FoldKernelArgs args{dv, src, run};

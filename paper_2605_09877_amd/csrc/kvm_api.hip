@@ -166,7 +166,8 @@ bool use_mfma(const kvm_config &c) {
 // Chunks per prefill attention launch.  The matrix-core path launches groups of chunks so that
 // a launch has thousands of workgroups; the generic path launches chunk by chunk.
 int group_of(const kvm_config &c) { return use_mfma(c) ? 8 : 1; }
-static_assert(2 * kvm::kFoldMaxSteps <= 8, "two runs of one-launch folds have their memory keys in a group's scratch");
+// Blocks whose memory keys the scratch holds: a group's, or two runs of one-launch folds.
+int key_blocks(const kvm_config &c) { return use_mfma(c) ? 2 * kvm::kFoldMaxSteps : group_of(c); }
 constexpr int kComputeUnits = 256;  // of the chip this library is written for
 // Workgroups that may share a unit's rows (a power of two): at most kFoldMaxSplit, one 64-row tile each, and
 // together no more than `cus` compute units (beyond that a unit's workgroups start far apart).
@@ -197,7 +198,7 @@ Layout layout_of(const kvm_config &c, int64_t Mcap) {
   l.winK = take(U * L * d * es);
   l.winV = take(U * L * d * es);
   l.winG = take(U * L * 4);
-  l.kbar = take((size_t)group_of(c) * U * C * d * es);
+  l.kbar = take((size_t)key_blocks(c) * U * C * d * es);
   l.score = take(U * C * 8);
   l.pi = take(U * C * 4);
   l.app = take(U * C * 4);
@@ -228,7 +229,7 @@ void bind(Dev &dv, const kvm_config &c, void *buf, int64_t Mcap) {
   dv.pi = (int32_t *)(p + l.pi);
   dv.app = (int32_t *)(p + l.app);
   dv.creator = (int32_t *)(p + l.creator);
-  dv.kbar_bytes = (int64_t)group_of(c) * c.batch * c.n_kv_heads * c.chunk_len * c.head_dim * (int64_t)esize(c.io_dtype);
+  dv.kbar_bytes = (int64_t)key_blocks(c) * c.batch * c.n_kv_heads * c.chunk_len * c.head_dim * (int64_t)esize(c.io_dtype);
   dv.part_cnt = (unsigned *)(p + l.part_cnt);
   dv.gamma = c.ln_gamma;
   dv.beta = c.ln_beta;
@@ -443,6 +444,24 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
   const int split = fold_split(st, blocks);
   return split > 1 && captured(stream) ? 0 : split;
 }
+
+// Whether the attention launches of a prefill leave room on every compute unit for the workgroup of a shared fold.
+// Two attention workgroups fill a compute unit's LDS but for 32 KiB: a run of folds then waits, all of its workgroups for the
+// last, until one has left everywhere.  With one (kBesideFoldLds) attention has three quarters of its rate
+// and the chain starts at once: worth it while the chain is the longer of the two, some 22 us a fold against a chunk's
+// attention at 0.9 PFLOP/s.  Us per call of 8192 tokens, two / one per compute unit (GFLOP a chunk): 2 x 16 heads, growing,
+// 65536 tokens (5.8) 7570 / 6350; 64 units of 64-token blocks (0.8) 2300 / 1976; 32 units, 2 heads each, growing (2.9)
+// 1865 / 1610; 64 units, 512 rows, 2 heads each (15) 1280 / 1165; 16 units, 4 heads each (7.5) 672 / 639; but 32 units, 900 rows,
+// 4 heads each (21.5) 1270 / 1290, 64 units, 512 rows, 4 heads each (30) 1790 / 1805.
+constexpr double kBesideMostFlops = 18e9;
+bool attention_beside(const kvm_state *st, int split, int64_t m) {
+  const Dev &dv = st->dv;
+  const double keys = (double)m + (double)dv.L - 0.5 * (double)dv.C;
+  return kvm::fold_fused_beside(dv, split) && 4.0 * dv.d * dv.B * dv.Hq * dv.C * keys <= kBesideMostFlops;
+}
+// Folds of a run: a group's where they run beside attention; half of one elsewhere (the launch waits for attention to leave, and
+// attention for the launch: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight).
+constexpr int kFoldRunApart = 4;
 
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
@@ -1008,7 +1027,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         {
           ProfileSpan span(st, 0, stream);
           if (kvm::attention_on_mfma(dv))
-            HIP_TRY(kvm::launch_attn_mfma(dv, a, stream));
+            HIP_TRY(kvm::launch_attn_mfma(dv, a, false, stream));
           else
             HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
         }
@@ -1038,9 +1057,9 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   const int split = fold_split_on(st, (int64_t)plan.size(), stream);
   const bool fused_folds = split > 0;
   int n_chains = 1;
+  int64_t m_max = 0;
+  for (const Chunk &ch : plan) m_max = ch.m > m_max ? ch.m : m_max;
   {
-    int64_t m_max = 0;
-    for (const Chunk &ch : plan) m_max = ch.m > m_max ? ch.m : m_max;
     const double fold_mb = (double)dv.U * ((double)m_max * d * es * 5.0 + (double)C * d * es * 4.0) / 1.0e6;
     if (fold_mb < 96.0 && dv.B % 2 == 0) n_chains = 2;
     const int forced = st->dbg[KVM_DEBUG_FOLD_CHAINS];  // 1 or 2: for comparisons
@@ -1052,6 +1071,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // With a unit's rows shared among workgroups the narrow one is the default: it is the shape that
   // fits beside an attention workgroup, and sharing is chosen where the folds are to run hidden.
   const bool narrow_folds = st->dbg[KVM_DEBUG_FOLD_WAVES] == 8 || (st->dbg[KVM_DEBUG_FOLD_WAVES] == 0 && split > 1);
+  const bool beside = narrow_folds && attention_beside(st, split, m_max);
   hipStream_t fstream[kvm_state::kMaxChains];
   Dev cdv[kvm_state::kMaxChains];
   const int cb = dv.B / n_chains;  // sequences per chain
@@ -1099,7 +1119,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       // keys are computed by one launch (blocks taken from the ring go one at a time)
       const int64_t lo0 = plan[next_fold].s + C - L;
       int run = 1;
-      const int run_cap = fused_folds ? kvm::kFoldMaxSteps : G;
+      const int run_cap = beside ? kvm::kFoldMaxSteps : fused_folds ? kFoldRunApart : G;
       if (lo0 >= t0)
         while (run < run_cap && next_fold + run <= last_chunk && next_fold + run < n_chunks &&
                plan[next_fold + run].folds)
@@ -1162,6 +1182,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           int rc_run = fused_run(st, split, false, fstream[0], &fr);
           if (rc_run != KVM_OK) return rc_run;
           fr.n = run;
+          fr.beside = beside ? 1 : 0;
           for (int i = 0; i < run; ++i) {
             const int64_t lo = plan[next_fold + i].s + C - L;
             const int64_t fold_no = st->folds + i;
@@ -1238,7 +1259,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     {
       ProfileSpan span(st, 0, stream);
       if (kvm::attention_on_mfma(dv))
-        HIP_TRY(kvm::launch_attn_mfma(dv, a, stream));
+        HIP_TRY(kvm::launch_attn_mfma(dv, a, beside, stream));
       else
         HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
     }

@@ -102,7 +102,11 @@ hipError_t launch_ring_copy(const Dev &dv, const Src &src, int64_t src_t0, int64
 // scores also go to trace_assign / trace_score at that fold index (trace_stride = tokens of one
 // fold over all units).  narrow: the 8-wave workgroup that fits beside an attention workgroup on
 // a compute unit; otherwise 16 waves and the unit to itself.
-constexpr int kFoldMaxSteps = 4;   // half of a group: the other half of the key scratch is the next run's
+constexpr int kFoldMaxSteps = 8;   // a group's worth.  A run's border costs the chain some 15 us (launch, keys and tiles
+                                   // fetched anew): 65536 tokens, growing state, 32 units: 6.85 ms in runs of 4, 6.35 in runs of 8
+// LDS of a shared fold's workgroup and of an attention workgroup launched with kBesideFoldLds more: one of each fills a
+// compute unit, and a second attention workgroup does not fit (attn_mfma.hip: launch_attn_mfma)
+constexpr size_t kLdsBesideAttention = 78 * 1024, kBesideFoldLds = 17 * 1024;
 constexpr int kFoldMaxSplit = 16;  // workgroups that may share a unit's rows
 struct FoldStep {
   int32_t m, m_after, so, sn;
@@ -121,6 +125,7 @@ struct FoldRunArgs {
   uint32_t arrived;            // workgroups per unit of the earlier launches since the table was zeroed
   uint32_t launch;             // number of this launch since then, from 1
   uint32_t patience;           // how long a workgroup waits for its unit's others to start, ticks of 10 ns
+  int32_t beside;              // the launch runs beside attention: LDS of at most kLdsBesideAttention where the tiles fit that
   int32_t resident;            // (set by the launch) K-hat tiles a workgroup keeps in LDS, 0: they stream through a ring
   int32_t gather;              // (likewise) merging tokens the LDS scratch holds
 };
@@ -128,6 +133,8 @@ constexpr int kArrivalWords = 8;   // an arrival word of the table to itself in 
 bool fold_fused_fits(const Dev &dv, int split = 1);
 // whether each of a unit's `split` workgroups keeps its normalised keys in LDS for a whole run
 bool fold_fused_resident(const Dev &dv, int split, bool narrow);
+// whether they do so within kLdsBesideAttention
+bool fold_fused_beside(const Dev &dv, int split);
 size_t fold_exchange_bytes(int64_t units, int C, int split);
 // readout rows [0, m) recomputed from the sums with the one-launch path's arithmetic
 hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st);
@@ -165,7 +172,8 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
 inline bool attention_on_mfma(const Dev &dv) {
   return dv.io == 1 && dv.C % 64 == 0 && (dv.d == 128 || (dv.d == 64 && (int64_t)dv.B * dv.Hq * dv.C > 1024));
 }
-hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, hipStream_t st);
+// beside_folds: one workgroup per compute unit, so that those of shared folds find theirs free at any time
+hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st);
 
 // backward.hip: the backward pass of a whole-sequence prefill that started from an empty state.
 // Dense operands: q, out, dout, dq [B, T, Hq, d]; k, v, dk, dv [B, T, Hkv, d]; gate, dgate
