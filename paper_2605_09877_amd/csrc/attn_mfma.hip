@@ -33,6 +33,78 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kXcds = 8;  // accelerator dies, each with its own L2
 
+// One query (the lane's, half of its channels) over its visible keys one after the other, in fp32: what is left to do when
+// a product with a masked key's value, 0 x something that is not finite, has spoilt the result.
+struct KeyWalk {
+  const char *khat, *vhat, *ring_k, *ring_v, *in_k, *in_v;   // (in_k, in_v: at the chunk's first position)
+  uint32_t kst, vst;
+  int m, wrel, t0rel, ring_slot0, L;
+  float c_state, c_bswa;   // logit scales, signs included
+};
+template <int D>
+__device__ __forceinline__ void attend_one_by_one(const KeyWalk &w, const char *qrow, int n_keys, int g, f32x16 (&oacc)[D / 32],
+                                                  float &m_run, float &l) {
+  constexpr int kNb = D / 32;
+  // channels of a lane: 32 * dblk + 8 * vq + 4 * g .. + 3, as in the accumulators
+  auto load4 = [&](const char *row, int dblk, int vq, float *f) {
+    const uint2 x = *reinterpret_cast<const uint2 *>(row + 2 * (32 * dblk + 8 * vq + 4 * g));
+    f[0] = __uint_as_float(x.x << 16);
+    f[1] = __uint_as_float(x.x & 0xffff0000u);
+    f[2] = __uint_as_float(x.y << 16);
+    f[3] = __uint_as_float(x.y & 0xffff0000u);
+  };
+  float qf[kNb][16];
+#pragma unroll
+  for (int i = 0; i < 4 * kNb; ++i) load4(qrow, i >> 2, i & 3, &qf[i >> 2][4 * (i & 3)]);
+#pragma unroll
+  for (int i = 0; i < kNb; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) oacc[i][v] = 0.f;
+  m_run = -INFINITY;
+  l = 0.f;
+#pragma unroll 1
+  for (int n = 0; n < n_keys; ++n) {
+    const char *kr, *vr;
+    if (n < w.m) {
+      kr = w.khat + (uint32_t)n * (D * 2);
+      vr = w.vhat + (uint32_t)n * (D * 2);
+    } else {
+      const int prel = w.wrel + (n - w.m);
+      if (prel >= w.t0rel) {
+        kr = w.in_k + (int64_t)prel * (int64_t)w.kst;
+        vr = w.in_v + (int64_t)prel * (int64_t)w.vst;
+      } else {
+        int slot = w.ring_slot0 + (n - w.m);
+        slot = slot >= w.L ? slot - w.L : slot;
+        kr = w.ring_k + (uint32_t)slot * (D * 2);
+        vr = w.ring_v + (uint32_t)slot * (D * 2);
+      }
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4 * kNb; ++i) {
+      float x[4];
+      load4(kr, i >> 2, i & 3, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dot = fmaf(qf[i >> 2][4 * (i & 3) + e], x[e], dot);
+    }
+    const float t = xhalf_sum(dot) * (n < w.m ? w.c_state : w.c_bswa);
+    const float m_new = fmaxf(m_run, t);
+    if (m_new == -INFINITY) continue;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new), pr = __builtin_amdgcn_exp2f(t - m_new);
+    m_run = m_new;
+    l = fmaf(l, alpha, pr);
+#pragma unroll
+    for (int i = 0; i < 4 * kNb; ++i) {
+      float x[4];
+      load4(vr, i >> 2, i & 3, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        oacc[i >> 2][4 * (i & 3) + e] = fmaf(pr, x[e], oacc[i >> 2][4 * (i & 3) + e] * alpha);
+    }
+  }
+}
+
 template <int NW, int D>
 __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint16_t *Ks, uint16_t *Vs) {
   static_assert((D == 128 || D == 64) && (D == 128 || NW == 4), "");
@@ -384,67 +456,13 @@ __device__ __forceinline__ void attn_body(const Dev &dv, const AttnArgs &a, uint
 #pragma unroll
       for (int v = 0; v < 16; ++v) bad = fmaf(oacc[i][v], 0.f, bad);
     if (myq < nq && !(xhalf_sum(bad) == 0.f)) {
-      // channels of a lane: 32 * dblk + 8 * vq + 4 * g .. + 3, as in the accumulators
-      auto load4 = [&](const char *row, int dblk, int vq, float *f) {
-        const uint2 x = *reinterpret_cast<const uint2 *>(row + 2 * (32 * dblk + 8 * vq + 4 * g));
-        f[0] = __uint_as_float(x.x << 16);
-        f[1] = __uint_as_float(x.x & 0xffff0000u);
-        f[2] = __uint_as_float(x.y << 16);
-        f[3] = __uint_as_float(x.y & 0xffff0000u);
-      };
+      KeyWalk w;
+      w.khat = khat; w.vhat = vhat; w.ring_k = ring_k; w.ring_v = ring_v; w.in_k = in_k; w.in_v = in_v;
+      w.kst = kst_in; w.vst = vst_in; w.m = m; w.wrel = wrel; w.t0rel = t0rel; w.ring_slot0 = ring_slot0; w.L = dv.L;
+      w.c_state = neg_bits & 1 ? -c_state : c_state;
+      w.c_bswa = neg_bits & 2 ? -c_bswa : c_bswa;
       const char *qrow = (const char *)((const uint16_t *)a.q + b * a.q_b + ((int64_t)ci * dv.C + myq) * a.q_t + hq * a.q_h);
-      float qf[kNb][16];
-#pragma unroll
-      for (int i = 0; i < 4 * kNb; ++i) load4(qrow, i >> 2, i & 3, &qf[i >> 2][4 * (i & 3)]);
-#pragma unroll
-      for (int i = 0; i < kNb; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[i][v] = 0.f;
-      m_run = -INFINITY;
-      l = 0.f;
-      const float f_state = neg_bits & 1 ? -c_state : c_state, f_bswa = neg_bits & 2 ? -c_bswa : c_bswa;
-      const int n_keys = m + (int)(cs + myq - wb) + 1;
-#pragma unroll 1
-      for (int n = 0; n < n_keys; ++n) {
-        const char *kr, *vr;
-        if (n < m) {
-          kr = khat + (uint32_t)n * (D * 2);
-          vr = vhat + (uint32_t)n * (D * 2);
-        } else {
-          const int prel = wrel + (n - m);
-          if (prel >= t0rel) {
-            kr = in_k + (int64_t)prel * (int64_t)kst_in;
-            vr = in_v + (int64_t)prel * (int64_t)vst_in;
-          } else {
-            int slot = ring_slot0 + (n - m);
-            slot = slot >= dv.L ? slot - dv.L : slot;
-            kr = ring_k + (uint32_t)slot * (D * 2);
-            vr = ring_v + (uint32_t)slot * (D * 2);
-          }
-        }
-        float dot = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4 * kNb; ++i) {
-          float x[4];
-          load4(kr, i >> 2, i & 3, x);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dot = fmaf(qf[i >> 2][4 * (i & 3) + e], x[e], dot);
-        }
-        const float t = xhalf_sum(dot) * (n < m ? f_state : f_bswa);
-        const float m_new = fmaxf(m_run, t);
-        if (m_new == -INFINITY) continue;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new), pr = __builtin_amdgcn_exp2f(t - m_new);
-        m_run = m_new;
-        l = fmaf(l, alpha, pr);
-#pragma unroll
-        for (int i = 0; i < 4 * kNb; ++i) {
-          float x[4];
-          load4(vr, i >> 2, i & 3, x);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            oacc[i >> 2][4 * (i & 3) + e] = fmaf(pr, x[e], oacc[i >> 2][4 * (i & 3) + e] * alpha);
-        }
-      }
+      attend_one_by_one<D>(w, qrow, m + (int)(cs + myq - wb) + 1, g, oacc, m_run, l);
     }
   }
   if (myq < nq) {
@@ -483,12 +501,575 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel_d64(Dev dv, AttnArgs 
   attn_body<4, 64>(dv, a, Ks, Vs);
 }
 
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // until N of this wave's loads are under way
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// ------------------------------------------------------------------------------------------------
+// head_dim 128, launches of few queries: the four waves of a workgroup take the same 32 queries of one head and four
+// tiles of 64 keys at a time.  Each wave scores a tile (first product, maximum, exponentials) and leaves P^T in LDS in the
+// second product's operand layout; then each wave adds all four tiles, in order, to a quarter of the channels.  The
+// reference point of the exponentials moves tile by tile as in the tile kernel, decided by every wave from the
+// tiles' maxima, and the sums are added up in the same order: the results have that kernel's bits, so a
+// sequence's do not depend on the batch it is in.
+// What bounds it: latencies, 1.2 us for four tiles where a workgroup of the tile kernel, alone on its compute unit, takes
+// some 1.6 us for each.  A wave's K tile and its channels of the four V tiles are its own (no barrier
+// but the two of the exchange); K of the next four is asked for as soon as the first product has read
+// this one's, V as soon as the second has.
+constexpr int kQuadK = 4 * kTileElems, kQuadV = 4 * 4 * kTileKeys * 32, kQuadP = 4 * 4 * 64 * 8;   // elements
+constexpr int kQuadLds = (kQuadK + kQuadV + kQuadP) * 2 + 4 * 32 * 4;
+
+__global__ __launch_bounds__(256, 2) void attn_quad_kernel_d128(Dev dv, AttnArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
+  constexpr int D = 128;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, l32 = lane & 31;
+  // workgroup -> work item as in the tile kernel, a member being 32 positions of one head
+  const int Gq = dv.Hq / dv.Hkv, tpc = dv.C / 32;
+  const int per_group = tpc * Gq;
+  const int n_groups = a.n_chunks * dv.Hkv * dv.B;
+  const int xcd = blockIdx.x % kXcds, seq = blockIdx.x / kXcds;
+  const int group = (seq / per_group) * kXcds + xcd;
+  if (group >= n_groups) return;
+  const int member = seq % per_group;
+  const int ci = group % a.n_chunks;
+  const int hkv = (group / a.n_chunks) % dv.Hkv;
+  const int b = group / (a.n_chunks * dv.Hkv);
+  const int hq = __builtin_amdgcn_readfirstlane(hkv * Gq + member / tpc);
+  const int u = b * dv.Hkv + hkv;
+  const int Q0 = (tpc - 1 - member % tpc) * 32;                          // longest causal part first
+  const int nq = ci == a.n_chunks - 1 ? a.nq_total - ci * dv.C : dv.C;
+  if (Q0 >= nq) return;
+  const int64_t cs = a.s + (int64_t)ci * dv.C;
+  const int64_t wb = cs + dv.C - dv.L > 0 ? cs + dv.C - dv.L : 0;
+  const int myq = Q0 + l32, m = a.m[ci];
+  auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  auto uni_ptr = [](const char *p_) {
+    const uint64_t x = (uint64_t)p_;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return (const char *)(((uint64_t)hi << 32) | (uint64_t)lo);
+  };
+  KeyWalk w;
+  w.khat = uni_ptr((const char *)dv.khat + (a.slot[ci] * dv.slot_elems + (int64_t)u * dv.Mcap * D) * 2);
+  w.vhat = uni_ptr((const char *)dv.vhat + (a.slot[ci] * dv.slot_elems + (int64_t)u * dv.Mcap * D) * 2);
+  w.ring_k = uni_ptr((const char *)dv.winK + (int64_t)u * dv.L * D * 2);
+  w.ring_v = uni_ptr((const char *)dv.winV + (int64_t)u * dv.L * D * 2);
+  w.kst = (uint32_t)uni((int)(a.in.k_t * 2));
+  w.vst = (uint32_t)uni((int)(a.in.v_t * 2));
+  w.in_k = uni_ptr((const char *)a.in.k + (b * a.in.k_b + hkv * a.in.k_h + (cs - a.t0) * a.in.k_t) * 2);
+  w.in_v = uni_ptr((const char *)a.in.v + (b * a.in.v_b + hkv * a.in.v_h + (cs - a.t0) * a.in.v_t) * 2);
+  w.m = m;
+  w.wrel = uni((int)(wb - cs));
+  w.t0rel = uni(a.t0 - cs < -(1 << 30) ? -(1 << 30) : (int)(a.t0 - cs));
+  w.ring_slot0 = uni((int)(wb % dv.L));
+  w.L = dv.L;
+  const int qend = Q0 + 32 < nq ? Q0 + 32 : nq;
+  const int n_st = uni((m + kTileKeys - 1) / kTileKeys);
+  const int n_tiles = uni(n_st + (qend - w.wrel + kTileKeys - 1) / kTileKeys);
+
+  uint16_t *Kt = lds + wave * kTileElems;
+  uint16_t *Vt = lds + kQuadK + wave * (4 * kTileKeys * 32);   // [tile][key][32 channels]
+  uint16_t *Pt = lds + kQuadK + kQuadV;                        // [tile][16 keys][lane][8]
+  float *tops = reinterpret_cast<float *>(lds + kQuadK + kQuadV + kQuadP);   // [tile][query]
+  const uint32_t k_addr = lds_addr_of(Kt), v_addr = lds_addr_of(Vt);
+  uint32_t koff[8];
+  ktile_offsets(lane, koff);
+  const DmaLane dl = dma_lane(lane);
+  // where V^T fragments are read: row 4 g + j / 4 (+ 8), channels 16 half + 4 (j % 4); four rows are a bank cycle
+  const uint32_t voff = (uint32_t)((4 * g + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  struct TileSrc {
+    const char *k, *v;
+    uint32_t kst, vst;
+    int valid;
+  };
+  auto tile_src = [&](int it) {
+    TileSrc t;
+    if (it < n_st) {
+      t.k = w.khat + (uint32_t)(it * kTileKeys) * (D * 2);
+      t.v = w.vhat + (uint32_t)(it * kTileKeys) * (D * 2);
+      t.kst = t.vst = D * 2;
+      t.valid = m - it * kTileKeys;
+    } else {
+      const int prel = w.wrel + (it - n_st) * kTileKeys;
+      t.valid = nq - prel;
+      if (prel >= w.t0rel) {
+        t.k = w.in_k + (int64_t)prel * (int64_t)w.kst;
+        t.v = w.in_v + (int64_t)prel * (int64_t)w.vst;
+        t.kst = w.kst;
+        t.vst = w.vst;
+      } else {
+        int slot = w.ring_slot0 + (it - n_st) * kTileKeys;
+        slot = slot >= dv.L ? slot - dv.L : slot;   // a window is at most L long: one wrap
+        t.k = w.ring_k + (uint32_t)slot * (D * 2);
+        t.v = w.ring_v + (uint32_t)slot * (D * 2);
+        t.kst = t.vst = D * 2;
+      }
+    }
+    return t;
+  };
+  auto issue_k = [&](int it) {   // 16 loads
+    const TileSrc t = tile_src(it);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile_dma<false, 4>(t.k, t.kst, t.valid, k_addr, q, dl);
+  };
+  auto issue_v = [&](int it0) {   // 16 loads: this wave's channels of four tiles (of the last one, where there are fewer)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const TileSrc t = tile_src(it0 + i < n_tiles ? it0 + i : n_tiles - 1);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        int r = 16 * n + (lane >> 2);
+        r = r < t.valid ? r : t.valid - 1;
+        dma16(t.v, (uint32_t)r * t.vst + (uint32_t)(64 * wave + 16 * (lane & 3)), v_addr + (uint32_t)(4 * i + n) * 1024u);
+      }
+    }
+  };
+  issue_k(wave < n_tiles ? wave : n_tiles - 1);   // (a wave without a tile: loads to count, not read)
+  issue_v(0);
+  const char *qrow = (const char *)((const uint16_t *)a.q + b * a.q_b +
+                                    ((int64_t)ci * dv.C + (myq < nq ? myq : nq - 1)) * a.q_t + hq * a.q_h);
+  bf16x8 qreg[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    Frag8 f;
+    f.q = *reinterpret_cast<const uint4 *>(qrow + 32 * ks + 16 * g);
+    qreg[ks] = f.v;
+  }
+  const float rs = kLog2e * rsqrtf((float)D);
+  w.c_state = (dv.tau_state ? dv.tau_state[hq] : 1.f) * rs;
+  w.c_bswa = (dv.tau_bswa ? dv.tau_bswa[hq] : 1.f) * rs;
+  const int neg_bits = uni((w.c_state < 0.f ? 1 : 0) | (w.c_bswa < 0.f ? 2 : 0));   // as in the tile kernel
+  __builtin_amdgcn_s_waitcnt(0);   // no load that the compiler counts is under way in the loop
+
+  f32x16 oacc = {0.f};
+  float m_run = -INFINITY, l_part = 0.f;
+  bool q_negated = false;
+#pragma unroll 1
+  for (int it0 = 0; it0 < n_tiles; it0 += 4) {
+    const int it = it0 + wave;
+    const bool mine = it < n_tiles, more = it0 + 4 < n_tiles, is_state = it < n_st;
+    if (((neg_bits & (is_state ? 1 : 2)) != 0) != q_negated) {
+      asm volatile("" ::: "memory");  // stays a (rarely taken) branch
+      q_negated = !q_negated;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        Frag8 f;
+        f.v = qreg[ks];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f.w[e] ^= 0x80008000u;
+        qreg[ks] = f.v;
+      }
+    }
+    wait_loads<16>();   // K is there; V, asked for after it, may still be under way
+    f32x16 sacc[2];
+    float smax = -INFINITY;
+    const float scale = fabsf(is_state ? w.c_state : w.c_bswa);
+    if (mine) {
+      bf16x8 kf[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) kf[i] = ktile_frag(Kt, koff, i & 1, i >> 1);
+      const f32x16 zero = {0.f};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) sacc[blk] = mfma32(kf[2 * ks + blk], qreg[ks], ks == 0 ? zero : sacc[blk]);
+    }
+    wait_lds();
+    if (more) issue_k(it + 4 < n_tiles ? it + 4 : n_tiles - 1);
+    if (mine) {
+      const int row0 = it * kTileKeys, prel = w.wrel + (it - n_st) * kTileKeys;
+      if (is_state ? m - row0 < kTileKeys : prel + kTileKeys - 1 > Q0) {
+        const int lim = is_state ? m - row0 - 1 : myq - prel;   // keys up to it are visible to the lane's query
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sacc[blk][v] = (32 * blk + mfma_row(v, g)) <= lim ? sacc[blk][v] : -INFINITY;
+      }
+      smax = sacc[0][0];
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) smax = fmaxf(smax, sacc[blk][v]);
+      smax = xhalf_max(smax);
+      if (g == 0) tops[wave * 32 + l32] = smax * scale;
+    }
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // the reference point after each of the four tiles, and what is accumulated is multiplied by ahead of it
+    constexpr float kSlack = 8.f;   // as in the tile kernel
+    float alpha[4], m_mine = m_run;
+    int moved = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      alpha[t] = 1.f;
+      if (it0 + t < n_tiles) {
+        const float m_new = fmaxf(m_run, tops[t * 32 + l32]);
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run + kSlack) != 0) {
+          alpha[t] = __builtin_amdgcn_exp2f(m_run - m_new);
+          m_run = m_new;
+          moved |= 1 << t;
+        }
+      }
+      if (t == wave) m_mine = m_run;
+    }
+    if (mine) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        Frag8 p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int v = (ks & 1) * 8 + 2 * e;
+          p.w[e] = pack_bf16(__builtin_amdgcn_exp2f(fmaf(sacc[ks >> 1][v], scale, -m_mine)),
+                             __builtin_amdgcn_exp2f(fmaf(sacc[ks >> 1][v + 1], scale, -m_mine)));
+        }
+        *reinterpret_cast<uint4 *>(Pt + ((wave * 4 + ks) * 64 + lane) * 8) = p.q;
+      }
+    }
+    if (more) wait_loads<16>(); else wait_loads<0>();   // V is there
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (it0 + t < n_tiles) {
+        Frag8 p[4];
+        bf16x8 vf[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          p[ks].q = *reinterpret_cast<const uint4 *>(Pt + ((t * 4 + ks) * 64 + lane) * 8);
+          const uint16_t *vp = Vt + (t * kTileKeys + 16 * ks) * 32 + voff;
+          Frag8 f;
+          f.d[0] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(vp)));
+          f.d[1] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(KVM_LDS_V4(vp + 8 * 32)));
+          vf[ks] = f.v;
+        }
+        if (moved & (1 << t)) {
+          l_part *= alpha[t];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) oacc[v] *= alpha[t];
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          oacc = mfma32(vf[ks], p[ks].v, oacc);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            l_part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p[ks].w[e]), ones, l_part, false);
+        }
+      }
+    }
+    wait_lds();
+    if (more) issue_v(it0 + 4);
+  }
+  const float l = xhalf_sum(l_part);
+  if (myq < nq) {
+    const float inv = 1.f / l;
+    uint16_t *orow = (uint16_t *)a.out + b * a.o_b + ((int64_t)ci * dv.C + myq) * a.o_t + hq * a.o_h;
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq)
+      *reinterpret_cast<uint2 *>(orow + 32 * wave + 8 * vq + 4 * g) =
+          make_uint2(pack_bf16(oacc[4 * vq] * inv, oacc[4 * vq + 1] * inv), pack_bf16(oacc[4 * vq + 2] * inv, oacc[4 * vq + 3] * inv));
+    if (a.lse && wave == 0 && g == 0)
+      a.lse[b * a.lse_b + ((int64_t)ci * dv.C + myq) * a.lse_t + hq * a.lse_h] = (m_run + log2f(l)) * kLn2;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// head_dim 64, launches of few queries: the four waves of a workgroup take the same 32 queries of one head and every
+// fourth tile of 32 keys each, and put their results together at the end.  Four times as many
+// workgroups as above, a quarter of the tiles in a row: what bounds such a launch is that chain (a wave alone on its SIMD
+// takes two thirds of a 64-key tile's time for latencies).  A wave has its tiles to itself (no
+// barriers in the loop), one K and one V buffer: K of the next tile is asked for as soon as the first
+// product has read this one's, V as soon as the second has.
+__device__ __forceinline__ void attn_split_d64(const Dev &dv, const AttnArgs &a, uint16_t *tiles, float2 *sh_ml, int *sh_bad) {
+  constexpr int D = 64, kKs = D / 16, kNb = D / 32, kTK = 32, kTileE = kTK * D, kLoads = kTileE * 2 / 1024;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, l32 = lane & 31;
+  // workgroup -> work item as above, a member being 32 positions of one head
+  const int Gq = dv.Hq / dv.Hkv, tpc = dv.C / 32;
+  const int per_group = tpc * Gq;
+  const int n_groups = a.n_chunks * dv.Hkv * dv.B;
+  const int xcd = blockIdx.x % kXcds, seq = blockIdx.x / kXcds;
+  const int group = (seq / per_group) * kXcds + xcd;
+  if (group >= n_groups) return;
+  const int member = seq % per_group;
+  const int ci = group % a.n_chunks;
+  const int hkv = (group / a.n_chunks) % dv.Hkv;
+  const int b = group / (a.n_chunks * dv.Hkv);
+  const int hq = __builtin_amdgcn_readfirstlane(hkv * Gq + member / tpc);
+  const int u = b * dv.Hkv + hkv;
+  const int Q0 = (tpc - 1 - member % tpc) * 32;                          // longest causal part first
+  const int nq = ci == a.n_chunks - 1 ? a.nq_total - ci * dv.C : dv.C;
+  if (Q0 >= nq) return;
+  const int64_t cs = a.s + (int64_t)ci * dv.C;
+  const int64_t wb = cs + dv.C - dv.L > 0 ? cs + dv.C - dv.L : 0;
+  const int myq = Q0 + l32, m = a.m[ci];
+  auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  auto uni_ptr = [](const char *p_) {
+    const uint64_t x = (uint64_t)p_;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return (const char *)(((uint64_t)hi << 32) | (uint64_t)lo);
+  };
+  KeyWalk w;
+  w.khat = uni_ptr((const char *)dv.khat + (a.slot[ci] * dv.slot_elems + (int64_t)u * dv.Mcap * D) * 2);
+  w.vhat = uni_ptr((const char *)dv.vhat + (a.slot[ci] * dv.slot_elems + (int64_t)u * dv.Mcap * D) * 2);
+  w.ring_k = uni_ptr((const char *)dv.winK + (int64_t)u * dv.L * D * 2);
+  w.ring_v = uni_ptr((const char *)dv.winV + (int64_t)u * dv.L * D * 2);
+  w.kst = (uint32_t)uni((int)(a.in.k_t * 2));
+  w.vst = (uint32_t)uni((int)(a.in.v_t * 2));
+  w.in_k = uni_ptr((const char *)a.in.k + (b * a.in.k_b + hkv * a.in.k_h + (cs - a.t0) * a.in.k_t) * 2);
+  w.in_v = uni_ptr((const char *)a.in.v + (b * a.in.v_b + hkv * a.in.v_h + (cs - a.t0) * a.in.v_t) * 2);
+  w.m = m;
+  w.wrel = uni((int)(wb - cs));
+  w.t0rel = uni(a.t0 - cs < -(1 << 30) ? -(1 << 30) : (int)(a.t0 - cs));
+  w.ring_slot0 = uni((int)(wb % dv.L));
+  w.L = dv.L;
+  const int qend = Q0 + 32 < nq ? Q0 + 32 : nq;
+  const int n_st = uni((m + kTK - 1) / kTK);
+  const int n_tiles = uni(n_st + (qend - w.wrel + kTK - 1) / kTK);
+
+  uint32_t koff[kKs], voff[kNb];
+  ktile_offsets64(lane, koff);
+  vtile_offsets64(lane, voff);
+  const DmaLane64 dl = dma_lane64(lane);
+  uint16_t *Kt = tiles + wave * 2 * kTileE, *Vt = Kt + kTileE;
+  const uint32_t k_addr = lds_addr_of(Kt), v_addr = lds_addr_of(Vt);
+  // 32 rows of a tile, all of them by this wave; rows beyond the last repeat it
+  auto load_tile = [&](const char *base, uint32_t stride, int valid, uint32_t at, auto vswz) {
+    constexpr bool kV = decltype(vswz)::value;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      int r = 8 * n + (int)dl.rl;
+      r = r < valid ? r : valid - 1;
+      dma16(base, (uint32_t)r * stride + (kV ? dl.vcol : dl.kcol[n & 1]), at + (uint32_t)n * 1024u);
+    }
+  };
+  auto issue = [&](int it, auto values) {
+    constexpr bool kV = decltype(values)::value;
+    const uint32_t at = kV ? v_addr : k_addr;
+    if (it < n_st) {
+      load_tile((kV ? w.vhat : w.khat) + (uint32_t)(it * kTK) * (D * 2), D * 2, m - it * kTK, at, values);
+    } else {
+      const int prel = w.wrel + (it - n_st) * kTK, valid = nq - prel;
+      if (prel >= w.t0rel) {
+        const uint32_t st = kV ? w.vst : w.kst;
+        load_tile((kV ? w.in_v : w.in_k) + (int64_t)prel * (int64_t)st, st, valid, at, values);
+      } else {
+        int slot = w.ring_slot0 + (it - n_st) * kTK;
+        slot = slot >= dv.L ? slot - dv.L : slot;   // a window is at most L long: one wrap
+        load_tile((kV ? w.ring_v : w.ring_k) + (uint32_t)slot * (D * 2), D * 2, valid, at, values);
+      }
+    }
+  };
+  using Keys = std::integral_constant<bool, false>;
+  using Values = std::integral_constant<bool, true>;
+  if (wave < n_tiles) {   // the first tile and the queries travel together
+    issue(wave, Keys{});
+    issue(wave, Values{});
+  }
+  const char *qrow = (const char *)((const uint16_t *)a.q + b * a.q_b +
+                                    ((int64_t)ci * dv.C + (myq < nq ? myq : nq - 1)) * a.q_t + hq * a.q_h);
+  bf16x8 qreg[kKs];
+#pragma unroll
+  for (int ks = 0; ks < kKs; ++ks) {
+    Frag8 f;
+    f.q = *reinterpret_cast<const uint4 *>(qrow + 32 * ks + 16 * g);
+    qreg[ks] = f.v;
+  }
+  const float rs = kLog2e * rsqrtf((float)D);
+  w.c_state = (dv.tau_state ? dv.tau_state[hq] : 1.f) * rs;
+  w.c_bswa = (dv.tau_bswa ? dv.tau_bswa[hq] : 1.f) * rs;
+  const int neg_bits = uni((w.c_state < 0.f ? 1 : 0) | (w.c_bswa < 0.f ? 2 : 0));   // as above
+  if (tid < 32) sh_bad[tid] = 0;
+  __builtin_amdgcn_s_waitcnt(0);   // no load that the compiler counts is under way in the loop
+
+  f32x16 oacc[kNb];
+#pragma unroll
+  for (int i = 0; i < kNb; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) oacc[i][v] = 0.f;
+  float m_run = -INFINITY, l_part = 0.f;
+  bool q_negated = false;
+  for (int it = wave; it < n_tiles; it += 4) {
+    const bool is_state = it < n_st, more = it + 4 < n_tiles;
+    if (((neg_bits & (is_state ? 1 : 2)) != 0) != q_negated) {
+      asm volatile("" ::: "memory");  // stays a (rarely taken) branch
+      q_negated = !q_negated;
+#pragma unroll
+      for (int ks = 0; ks < kKs; ++ks) {
+        Frag8 f;
+        f.v = qreg[ks];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f.w[e] ^= 0x80008000u;
+        qreg[ks] = f.v;
+      }
+    }
+    wait_loads<kLoads>();   // K is there; V, asked for after it, may still be under way
+    f32x16 sacc = {0.f};
+    {
+      bf16x8 kf[kKs];
+#pragma unroll
+      for (int ks = 0; ks < kKs; ++ks) kf[ks] = ktile_frag64(Kt, koff, 0, ks);
+      wait_lds();
+      if (more) issue(it + 4, Keys{});
+#pragma unroll
+      for (int ks = 0; ks < kKs; ++ks) sacc = mfma32(kf[ks], qreg[ks], sacc);
+    }
+    const int prel = w.wrel + (it - n_st) * kTK;
+    const int lim = is_state ? m - it * kTK - 1 : myq - prel;   // keys up to it are visible to the lane's query
+    if (is_state ? m - it * kTK < kTK : prel + kTK - 1 > Q0) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sacc[v] = mfma_row(v, g) <= lim ? sacc[v] : -INFINITY;
+    }
+    const float scale = fabsf(is_state ? w.c_state : w.c_bswa);
+    float smax = sacc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) smax = fmaxf(smax, sacc[v]);
+    smax = xhalf_max(smax);
+    constexpr float kSlack = 8.f;   // as above
+    const float m_new = fmaxf(m_run, smax * scale);
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run + kSlack) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_part *= alpha;
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[i][v] *= alpha;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale, -m_run));
+    Frag8 pb[2], pl[2], pll[2];   // P as the sum of three bf16 numbers, as above
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float p0 = sacc[ks * 8 + 2 * e], p1 = sacc[ks * 8 + 2 * e + 1];
+        auto rest = [](float x, float y, uint32_t ww, float &rx, float &ry) {   // exact
+          rx = x - __uint_as_float(ww << 16);
+          ry = y - __uint_as_float(ww & 0xffff0000u);
+        };
+        float r0, r1;
+        pb[ks].w[e] = pack_bf16(p0, p1);
+        rest(p0, p1, pb[ks].w[e], r0, r1);
+        pl[ks].w[e] = pack_bf16(r0, r1);
+        rest(r0, r1, pl[ks].w[e], r0, r1);
+        pll[ks].w[e] = pack_bf16(r0, r1);
+        l_part += p0 + p1;
+      }
+    if (more) wait_loads<kLoads>(); else wait_loads<0>();   // V is there
+    bf16x8 vf[2][kNb];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dblk = 0; dblk < kNb; ++dblk) vf[ks][dblk] = vtile_frag64(Vt, voff, dblk, ks);
+    wait_lds();
+    if (more) issue(it + 4, Values{});
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dblk = 0; dblk < kNb; ++dblk) {
+        oacc[dblk] = mfma32(vf[ks][dblk], pb[ks].v, oacc[dblk]);
+        oacc[dblk] = mfma32(vf[ks][dblk], pl[ks].v, oacc[dblk]);
+        oacc[dblk] = mfma32(vf[ks][dblk], pll[ks].v, oacc[dblk]);
+      }
+  }
+
+  // The four results: a wave's own go where its tiles were (as many bytes: 32 x D floats), and every wave puts a
+  // quarter of the channels together.
+  float *mine = reinterpret_cast<float *>(Kt);
+#pragma unroll
+  for (int p = 0; p < 4 * kNb; ++p)
+    *reinterpret_cast<float4 *>(mine + (p * 64 + lane) * 4) =
+        make_float4(oacc[p >> 2][4 * (p & 3)], oacc[p >> 2][4 * (p & 3) + 1], oacc[p >> 2][4 * (p & 3) + 2],
+                    oacc[p >> 2][4 * (p & 3) + 3]);
+  {
+    const float l_wave = xhalf_sum(l_part);
+    if (g == 0) sh_ml[wave * 32 + l32] = make_float2(m_run, l_wave);
+  }
+  __syncthreads();
+  float f[4], top = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) top = fmaxf(top, sh_ml[o * 32 + l32].x);
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const float2 ml = sh_ml[o * 32 + l32];
+    f[o] = __builtin_amdgcn_exp2f(ml.x - top);
+    l = fmaf(ml.y, f[o], l);
+  }
+  float4 x[kNb];
+#pragma unroll
+  for (int i = 0; i < kNb; ++i) {
+    const int p = wave * kNb + i;
+    x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      const float4 y = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(tiles + o * 2 * kTileE) + (p * 64 + lane) * 4);
+      x[i].x = fmaf(y.x, f[o], x[i].x);
+      x[i].y = fmaf(y.y, f[o], x[i].y);
+      x[i].z = fmaf(y.z, f[o], x[i].z);
+      x[i].w = fmaf(y.w, f[o], x[i].w);
+    }
+  }
+  uint16_t *orow = (uint16_t *)a.out + b * a.o_b + ((int64_t)ci * dv.C + myq) * a.o_t + hq * a.o_h;
+  auto store4 = [&](int p, float x0, float x1, float x2, float x3, float inv) {
+    *reinterpret_cast<uint2 *>(orow + 32 * (p >> 2) + 8 * (p & 3) + 4 * g) =
+        make_uint2(pack_bf16(x0 * inv, x1 * inv), pack_bf16(x2 * inv, x3 * inv));
+  };
+  // a query whose result is not finite, as above: the first wave does it again
+  float bad = 0.f * l;
+#pragma unroll
+  for (int i = 0; i < kNb; ++i) bad = fmaf(x[i].x, 0.f, fmaf(x[i].y, 0.f, fmaf(x[i].z, 0.f, fmaf(x[i].w, 0.f, bad))));
+  if (!(bad == 0.f)) sh_bad[l32] = 1;
+  __syncthreads();
+  const bool again = sh_bad[l32] != 0;
+  if (myq < nq && !again) {
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int i = 0; i < kNb; ++i) store4(wave * kNb + i, x[i].x, x[i].y, x[i].z, x[i].w, inv);
+  }
+  if (wave == 0 && again && myq < nq) {
+    attend_one_by_one<D>(w, qrow, m + myq - w.wrel + 1, g, oacc, top, l);
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int p = 0; p < 4 * kNb; ++p)
+      store4(p, oacc[p >> 2][4 * (p & 3)], oacc[p >> 2][4 * (p & 3) + 1], oacc[p >> 2][4 * (p & 3) + 2],
+             oacc[p >> 2][4 * (p & 3) + 3], inv);
+  }
+  if (a.lse && wave == 0 && g == 0 && myq < nq)
+    a.lse[b * a.lse_b + ((int64_t)ci * dv.C + myq) * a.lse_t + hq * a.lse_h] = (top + log2f(l)) * kLn2;
+}
+
+__global__ __launch_bounds__(256, 2) void attn_split_kernel_d64(Dev dv, AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t tiles[4 * 2 * 32 * 64];
+  __shared__ float2 ml[4 * 32];
+  __shared__ int bad[32];
+  attn_split_d64(dv, a, tiles, ml, bad);
+}
+
 }  // namespace
+
+// Launches of up to so many workgroups of the tile kernels go to the others: as many of theirs, four times the number, as find a
+// place at once.  head_dim 128 (one per compute unit), us per call, tiles / four at a time: 64 workgroups: 3 x 8 heads on 2,
+// 904 tokens 105 / 90; 4 heads, 4000 tokens 297 / 290; but 128: 2 x 16 heads, 612 tokens 41.7 / 44.4, 256: 8 x 8 heads on 2, 587 tokens
+// 40 / 57.  head_dim 64 (two and more per compute unit): 128 workgroups: 2 x 16 heads on 4, 4173 tokens 655 / 522; but 256: 8 x 16
+// heads, 2000 tokens 470 / 483.
+constexpr unsigned kQuadMost = 64, kSplitMost = 128;
 
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute((const void *)attn_mfma_kernel_q128,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBesideFoldLds);
+  static const hipError_t attr_quad = hipFuncSetAttribute((const void *)attn_quad_kernel_d128,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kQuadLds);
   if (attr != hipSuccess) return attr;
+  if (attr_quad != hipSuccess) return attr_quad;
   if (a.nq_total <= 0) return hipSuccess;
   const int Gq = dv.Hq / dv.Hkv;
   const bool by_head = Gq % 4 == 0;  // as in the kernel: four heads x 32 positions, or 128 positions of one head
@@ -496,7 +1077,12 @@ hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds,
   const int per_group = ((dv.C + span - 1) / span) * (by_head ? Gq / 4 : Gq);
   const int n_groups = a.n_chunks * dv.Hkv * dv.B;
   dim3 grid((unsigned)((n_groups + kXcds - 1) / kXcds * kXcds * per_group));
-  if (dv.d == 64)
+  const dim3 sgrid((unsigned)((n_groups + kXcds - 1) / kXcds * kXcds * (dv.C / 32) * Gq));
+  if (dv.d == 128 && grid.x <= kQuadMost && !beside_folds) {
+    hipLaunchKernelGGL(attn_quad_kernel_d128, sgrid, dim3(256), kQuadLds, st, dv, a);
+  } else if (dv.d == 64 && grid.x <= kSplitMost) {
+    hipLaunchKernelGGL(attn_split_kernel_d64, sgrid, dim3(256), 0, st, dv, a);
+  } else if (dv.d == 64)
     hipLaunchKernelGGL(attn_mfma_kernel_d64, grid, dim3(256), 0, st, dv, a);
   else
     hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), beside_folds ? kBesideFoldLds : 0, st, dv, a);
