@@ -24,6 +24,7 @@
 #include "kvm_device.h"
 #include "kvm_internal.h"
 #include "kvm_mfma.h"
+#include "kvm_score.h"
 
 namespace kvm {
 
@@ -1053,6 +1054,19 @@ __global__ __launch_bounds__(256, 2) void attn_split_kernel_d64(Dev dv, AttnArgs
   __shared__ int bad[32];
   attn_split_d64(dv, a, tiles, ml, bad);
 }
+// The same with the scores of the block that is folded after the chunk in further workgroups (attn_rows_score_kernel).  Here
+// attention is the longer part and goes first: the call above 338 us, 365 the other way round.
+__global__ __launch_bounds__(256, 2) void attn_split_score_kernel_d64(Dev dv, AttnArgs a, int n_att, int slot, int m) {
+  __shared__ __attribute__((aligned(1024))) uint16_t tiles[4 * 2 * 32 * 64];
+  __shared__ float2 ml[4 * 32];
+  __shared__ int bad[32];
+  if ((int)blockIdx.x < n_att) {
+    attn_split_d64(dv, a, tiles, ml, bad);
+  } else {
+    const int id = (int)blockIdx.x - n_att, per_unit = (dv.C + 3) / 4;
+    score_tokens<bf16_t, 64>(dv, slot, 0, m, 1, id % per_unit, id / per_unit);
+  }
+}
 
 }  // namespace
 
@@ -1063,6 +1077,31 @@ __global__ __launch_bounds__(256, 2) void attn_split_kernel_d64(Dev dv, AttnArgs
 // heads, 2000 tokens 470 / 483.
 constexpr unsigned kQuadMost = 64, kSplitMost = 128;
 
+// Workgroups of the tile kernels (four heads x 32 positions, or 128 positions of one head, each) and of the others.
+static unsigned tile_workgroups(const Dev &dv, const AttnArgs &a, unsigned *of_32) {
+  const int Gq = dv.Hq / dv.Hkv;
+  const bool by_head = Gq % 4 == 0;
+  const int span = by_head ? 32 : 128;
+  const int per_group = ((dv.C + span - 1) / span) * (by_head ? Gq / 4 : Gq);
+  const int n_groups = (a.n_chunks * dv.Hkv * dv.B + kXcds - 1) / kXcds * kXcds;
+  *of_32 = (unsigned)(n_groups * (dv.C / 32) * Gq);
+  return (unsigned)(n_groups * per_group);
+}
+
+bool attention_takes_scores(const Dev &dv, const AttnArgs &a) {
+  unsigned of_32;
+  return !attention_on_mfma(dv) || (dv.d == 64 && tile_workgroups(dv, a, &of_32) <= kSplitMost);
+}
+
+hipError_t launch_attn_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st) {
+  if (!attention_on_mfma(dv)) return launch_attn_rows_score(dv, a, slot, m, st);
+  unsigned of_32;
+  (void)tile_workgroups(dv, a, &of_32);
+  const dim3 grid(of_32 + (unsigned)((dv.C + 3) / 4 * dv.U));
+  hipLaunchKernelGGL(attn_split_score_kernel_d64, grid, dim3(256), 0, st, dv, a, (int)of_32, slot, m);
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute((const void *)attn_mfma_kernel_q128,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBesideFoldLds);
@@ -1071,17 +1110,12 @@ hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds,
   if (attr != hipSuccess) return attr;
   if (attr_quad != hipSuccess) return attr_quad;
   if (a.nq_total <= 0) return hipSuccess;
-  const int Gq = dv.Hq / dv.Hkv;
-  const bool by_head = Gq % 4 == 0;  // as in the kernel: four heads x 32 positions, or 128 positions of one head
-  const int span = by_head ? 32 : 128;
-  const int per_group = ((dv.C + span - 1) / span) * (by_head ? Gq / 4 : Gq);
-  const int n_groups = a.n_chunks * dv.Hkv * dv.B;
-  dim3 grid((unsigned)((n_groups + kXcds - 1) / kXcds * kXcds * per_group));
-  const dim3 sgrid((unsigned)((n_groups + kXcds - 1) / kXcds * kXcds * (dv.C / 32) * Gq));
+  unsigned of_32;
+  const dim3 grid(tile_workgroups(dv, a, &of_32));
   if (dv.d == 128 && grid.x <= kQuadMost && !beside_folds) {
-    hipLaunchKernelGGL(attn_quad_kernel_d128, sgrid, dim3(256), kQuadLds, st, dv, a);
+    hipLaunchKernelGGL(attn_quad_kernel_d128, dim3(of_32), dim3(256), kQuadLds, st, dv, a);
   } else if (dv.d == 64 && grid.x <= kSplitMost) {
-    hipLaunchKernelGGL(attn_split_kernel_d64, sgrid, dim3(256), 0, st, dv, a);
+    hipLaunchKernelGGL(attn_split_kernel_d64, dim3(of_32), dim3(256), 0, st, dv, a);
   } else if (dv.d == 64)
     hipLaunchKernelGGL(attn_mfma_kernel_d64, grid, dim3(256), 0, st, dv, a);
   else

@@ -8,6 +8,7 @@
 // (running max, sum, output fragment) and the groups are merged at the end.
 #include "kvm_device.h"
 #include "kvm_internal.h"
+#include "kvm_score.h"
 
 namespace kvm {
 
@@ -280,9 +281,9 @@ __device__ __forceinline__ void set_share(RowQuery<T> &rq, const Dev &dv, int gr
 // One workgroup per (query, group of GQ query heads, sequence) of one state; shared, a decode step's:
 // several per group.
 template <typename T, int D, int GQ, bool kShared>
-__global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
+__device__ __forceinline__ void attn_rows_of(const Dev &dv, const AttnArgs &a, int x, int y, int b) {
   // a decode step has one query per sequence, and the x dimension counts the shares of its keys
-  const int qi = kShared ? 0 : blockIdx.x, hq = blockIdx.y * GQ, b = blockIdx.z;
+  const int qi = kShared ? 0 : x, hq = y * GQ;
   const int hkv = hq / (dv.Hq / dv.Hkv);
   const int u = b * dv.Hkv + hkv;
   RowQuery<T> rq;
@@ -308,9 +309,9 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
   rq.put_k = rq.put_v = nullptr;
   rq.put_g = nullptr;
   rq.gate = 1.f;
-  rq.split = kShared ? blockIdx.x : 0;
+  rq.split = kShared ? x : 0;
   rq.n_split = kShared ? gridDim.x : 1;
-  if constexpr (kShared) set_share<T, D, GQ>(rq, dv, b * gridDim.y + blockIdx.y);
+  if constexpr (kShared) set_share<T, D, GQ>(rq, dv, b * gridDim.y + y);
   if (a.put_token && rq.split == 0 && hq == hkv * (dv.Hq / dv.Hkv)) {
     rq.put_k = (T *)dv.winK + (int64_t)u * dv.L * D;
     rq.put_v = (T *)dv.winV + (int64_t)u * dv.L * D;
@@ -318,6 +319,28 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
     rq.gate = a.in.g ? a.in.g[b * a.in.g_b + hkv * a.in.g_h + (rq.pos - a.t0) * a.in.g_t] : 1.f;
   }
   attn_row<T, D, GQ, kShared>(dv, rq);
+}
+
+template <typename T, int D, int GQ, bool kShared>
+__global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
+  attn_rows_of<T, D, GQ, kShared>(dv, a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// A chunk's attention and, in further workgroups, the scores of the block that is folded after it: both read the same state
+// version and neither writes what the other reads, so the chain from chunk to chunk is a launch shorter.  Us per call, apart /
+// in one launch: fp32, 2 heads of 64 channels, 1024 tokens in 64-token chunks, 64 rows 305 / 211; fp32, 4 units of 128
+// channels, 1500 tokens in 64-token chunks, 100 rows 655 / 523; bf16, 96-token chunks, 200 rows 437 / 355.
+// The scores' workgroups come first: they are the longer ones (the last of these calls 390 us the other way round).
+template <typename T, int D, bool kTwo>
+__global__ __launch_bounds__(256) void attn_rows_score_kernel(Dev dv, AttnArgs a, int slot, int m) {
+  const int per_unit = (dv.C + 3) / 4, n_score = per_unit * dv.U;
+  int id = blockIdx.x;
+  if (id < n_score) {
+    score_tokens<T, D, kTwo>(dv, slot, 0, m, 1, id % per_unit, id / per_unit);
+  } else {
+    id -= n_score;
+    attn_rows_of<T, D, 1, false>(dv, a, id % a.nq_total, id / a.nq_total % dv.Hq, id / a.nq_total / dv.Hq);
+  }
 }
 
 // Decode over sequences that live in different states (each at its own position, with its own
@@ -426,6 +449,24 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
     KVM_ROWS_LAUNCH(attn_rows_kernel, true, grid, dv, a);
   else
     KVM_ROWS_LAUNCH(attn_rows_kernel, false, grid, dv, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st) {
+  const dim3 grid((unsigned)((int64_t)a.nq_total * dv.Hq * dv.B + (int64_t)(dv.C + 3) / 4 * dv.U));
+  // (a state of up to 64 rows has one for each lane: 223 us for the first of the calls above with a second one asked for, 211 now)
+#define KVM_ROWS_SCORE(T, D)                                                                                 \
+  do {                                                                                                       \
+    if (m > 64)                                                                                              \
+      hipLaunchKernelGGL((attn_rows_score_kernel<T, D, true>), grid, dim3(256), 0, st, dv, a, slot, m);      \
+    else                                                                                                     \
+      hipLaunchKernelGGL((attn_rows_score_kernel<T, D, false>), grid, dim3(256), 0, st, dv, a, slot, m);     \
+  } while (0)
+  if (dv.io == 0 && dv.d == 64) KVM_ROWS_SCORE(float, 64);
+  else if (dv.io == 0) KVM_ROWS_SCORE(float, 128);
+  else if (dv.d == 64) KVM_ROWS_SCORE(bf16_t, 64);
+  else KVM_ROWS_SCORE(bf16_t, 128);
+#undef KVM_ROWS_SCORE
   return hipGetLastError();
 }
 

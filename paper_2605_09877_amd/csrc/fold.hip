@@ -15,6 +15,7 @@
 
 #include "kvm_device.h"
 #include "kvm_internal.h"
+#include "kvm_score.h"
 
 namespace kvm {
 
@@ -123,73 +124,9 @@ __global__ __launch_bounds__(256) void memkey_kernel(Dev dv, Src src, int n_bloc
 }
 
 // ------------------------------------------------------------------ similarity + winners (generic)
-// One wave per token; lanes stride over state rows [row0, row1); each dot product is an fp64 sum
-// of the I/O-dtype operands.  first_pass: rows are the pre-append state, writes s_j (all rows)
-// and the best eligible row.  Otherwise rows are the ones appended in this fold and only tokens
-// that were not appended themselves may move to them (strictly larger score only).
-template <typename T, int D>
+template <typename T, int D, bool kTwo>
 __global__ __launch_bounds__(256) void score_kernel(Dev dv, int slot, int row0, int row1, int first_pass) {
-  __shared__ double kb[4][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int u = blockIdx.y;
-  const int j = blockIdx.x * 4 + wave;
-  const int64_t tj = (int64_t)u * dv.C + j;
-  const bool active = j < dv.C && (first_pass || dv.app[tj] < 0);
-  if (active) {
-    const T *kbar = (const T *)dv.kbar + tj * D;
-    for (int c = lane; c < D; c += 64) kb[wave][c] = (double)Io<T>::load(kbar + c);
-  }
-  __syncthreads();
-  if (!active) return;
-  double best_all = -INFINITY, best = -INFINITY;
-  int best_i = 0x7fffffff;
-  const T *kh = (const T *)dv.khat + slot * dv.slot_elems + (int64_t)u * dv.Mcap * D;
-  for (int i = row0 + lane; i < row1; i += 64) {
-    // (a lane owns a row: a load touches 64 rows, and the load unit, a row at a time, is what bounds the
-    // launch; element by element the 256 tokens and 256 rows of four bf16 / 64 units took 47 us)
-    const T *row = kh + (int64_t)i * D;
-    double acc = 0.0;
-    constexpr int VEC = Vec16<T>::kN, kInFlight = D / VEC < 16 ? D / VEC : 16;
-#pragma unroll 1
-    for (int c0 = 0; c0 < D; c0 += kInFlight * VEC) {
-      uint4 raw[kInFlight];
-#pragma unroll
-      for (int n = 0; n < kInFlight; ++n) raw[n] = *reinterpret_cast<const uint4 *>(row + c0 + n * VEC);
-#pragma unroll
-      for (int n = 0; n < kInFlight; ++n) {
-        float x[VEC];
-        unpack16<T>(raw[n], x);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) acc += kb[wave][c0 + n * VEC + e] * (double)x[e];
-      }
-    }
-    best_all = acc > best_all ? acc : best_all;
-    if (i >= dv.S && acc > best) {
-      best = acc;
-      best_i = i;
-    }
-  }
-  best_all = wave_max(best_all);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double ob = __shfl_xor(best, o, kWave);
-    const int oi = __shfl_xor(best_i, o, kWave);
-    if (ob > best || (ob == best && oi < best_i)) {
-      best = ob;
-      best_i = oi;
-    }
-  }
-  if (lane == 0) {
-    if (first_pass) {
-      dv.score[tj] = make_float2((float)best_all, (float)best);
-      dv.pi[tj] = best_i;
-      dv.app[tj] = -1;
-    } else if (best_i != 0x7fffffff && (float)best > dv.score[tj].y) {
-      // compare in the stored (fp32) precision so both passes rank alike
-      dv.score[tj].y = (float)best;
-      dv.pi[tj] = best_i;
-    }
-  }
+  score_tokens<T, D, kTwo>(dv, slot, row0, row1, first_pass, blockIdx.x, blockIdx.y);
 }
 
 // ------------------------------------------------------------------ append selection
@@ -780,9 +717,22 @@ hipError_t launch_memkey(const Dev &dv, const Src &src, int n_blocks, hipStream_
   return hipGetLastError();
 }
 
+// Workgroups up to which a lane of the scoring kernel has two rows under way (kvm_score.h).
+constexpr unsigned kScoreTwoMost = 1024;
 hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st) {
   dim3 grid((dv.C + 3) / 4, dv.U);
-  KVM_DISPATCH(dv, score_kernel, grid, dim3(256), 0, st, dv, slot, row0, row1, first_pass ? 1 : 0);
+#define KVM_SCORE(T, D)                                                                                                  \
+  do {                                                                                                                   \
+    if (grid.x * grid.y <= kScoreTwoMost)                                                                                \
+      hipLaunchKernelGGL((score_kernel<T, D, true>), grid, dim3(256), 0, st, dv, slot, row0, row1, first_pass ? 1 : 0);  \
+    else                                                                                                                 \
+      hipLaunchKernelGGL((score_kernel<T, D, false>), grid, dim3(256), 0, st, dv, slot, row0, row1, first_pass ? 1 : 0); \
+  } while (0)
+  if (dv.io == 0 && dv.d == 64) KVM_SCORE(float, 64);
+  else if (dv.io == 0) KVM_SCORE(float, 128);
+  else if (dv.d == 64) KVM_SCORE(bf16_t, 64);
+  else KVM_SCORE(bf16_t, 128);
+#undef KVM_SCORE
   return hipGetLastError();
 }
 

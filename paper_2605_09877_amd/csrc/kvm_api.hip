@@ -166,8 +166,8 @@ bool use_mfma(const kvm_config &c) {
 // Chunks per prefill attention launch.  The matrix-core path launches groups of chunks so that
 // a launch has thousands of workgroups; the generic path launches chunk by chunk.
 int group_of(const kvm_config &c) { return use_mfma(c) ? 8 : 1; }
-// Blocks whose memory keys the scratch holds: a group's, or two runs of one-launch folds.
-int key_blocks(const kvm_config &c) { return use_mfma(c) ? 2 * kvm::kFoldMaxSteps : group_of(c); }
+// Blocks whose memory keys the scratch holds: two runs of one-launch folds, or what one launch makes of them ahead.
+int key_blocks(const kvm_config &c) { return use_mfma(c) ? 2 * kvm::kFoldMaxSteps : 8; }
 constexpr int kComputeUnits = 256;  // of the chip this library is written for
 // Workgroups that may share a unit's rows (a power of two): at most kFoldMaxSplit, one 64-row tile each, and
 // together no more than `cus` compute units (beyond that a unit's workgroups start far apart).
@@ -287,7 +287,8 @@ int slot_of(const kvm_state *st, int64_t ver) {
 // Reads readout version `folds` and writes version folds + 1: into the next slot, with untouched
 // rows copied over (prefill, where attention launches still read the older versions), or, in_place,
 // over the version it read (decode and the fold entry point: nothing else is in flight).
-// kbar_block >= 0: the block's memory keys were already computed into that slab of the scratch.
+// kbar_block >= 0: the block's memory keys were already computed into that slab of the scratch; scored: and so were the
+// scores of the first pass, by the attention launch ahead of it.
 // The sequences [b0, b0 + nb) of a state as a state of their own: same strides, moved pointers.
 Dev batch_view(const Dev &full, int b0, int nb, size_t es) {
   Dev v = full;
@@ -322,7 +323,7 @@ Src batch_view(const Src &s, int b0, size_t es) {
 // The launches of one fold over the units of `dv` (the whole state or a view of part of its
 // batch), from m to m_after rows, reading readout slot so and writing slot sn.
 int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_t m_after, int so, int sn,
-                  bool in_place, int kbar_block, hipStream_t stream) {
+                  bool in_place, int kbar_block, bool scored, hipStream_t stream) {
   const kvm_config &c = st->cfg;
   const int n_app = (int)(m_after - m);
   if (kbar_block < 0) {
@@ -336,7 +337,9 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
     HIP_TRY(kvm::launch_select(dv, (int)m, n_app, true, stream));
     HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, 0, true, false, copy, false, so, sn, stream));
   } else {
-    if (st->mfma)
+    if (scored)
+      ;   // by the attention launch ahead of the fold
+    else if (st->mfma)
       HIP_TRY(kvm::launch_score_mfma(dv, so, 0, (int)m, true, stream));
     else
       HIP_TRY(kvm::launch_score(dv, so, 0, (int)m, true, stream));
@@ -599,7 +602,7 @@ uint32_t take_exchange(kvm_state *st, int split, int64_t m, int64_t m_after) {
 }
 
 int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, float *score_out,
-               hipStream_t stream, bool in_place, int kbar_block = -1) {
+               hipStream_t stream, bool in_place, int kbar_block = -1, bool scored = false) {
   const kvm_config &c = st->cfg;
   if (c.budget_kind == KVM_BUDGET_NONE) return KVM_OK;
   const int64_t m = st->m;
@@ -614,15 +617,15 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
     int rc_run = fused_run(st, split, in_place, stream, &run);
     if (rc_run != KVM_OK) return rc_run;
     run.n = 1;
-    run.s[0] = {(int32_t)m, (int32_t)m_after, so, sn, 0, st->folds < st->trace_max ? (int32_t)st->folds : -1, 0,
-                take_exchange(st, split, m, m_after), 0u};
-    HIP_TRY(kvm::launch_memkey(dv, src, 1, stream));
+    run.s[0] = {(int32_t)m, (int32_t)m_after, so, sn, 0, st->folds < st->trace_max ? (int32_t)st->folds : -1,
+                kbar_block < 0 ? 0 : kbar_block, take_exchange(st, split, m, m_after), 0u};
+    if (kbar_block < 0) HIP_TRY(kvm::launch_memkey(dv, src, 1, stream));
     // a fold of its own (decode, the fold entry point, the chunk-by-chunk schedule): the narrow
     // workgroup, two to a compute unit, unless asked otherwise (measured 3 % ahead of the wide one)
     rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, nullptr, stream);
     if (rc_run != KVM_OK) return rc_run;
   } else {
-    int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, stream);
+    int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, scored, stream);
     if (rc != KVM_OK) return rc;
     if (st->trace_assign && st->folds < st->trace_max)
       HIP_TRY(hipMemcpyAsync(st->trace_assign + st->folds * ntok, dv.pi, ntok * 4,
@@ -996,17 +999,35 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     const double copy_us = (double)dv.U * (double)m_max * (double)d * (double)es * 4.0 / 4.0e6;  // at ~4 TB/s
     const int forced = st->dbg[KVM_DEBUG_PREFILL_SCHEDULE];  // 1 serial, 2 pipelined: for comparisons
     // (and a call of a few chunks has nothing to pipeline: the events would cost more than they buy)
-    // States without grouped launches (fp32, head_dim 64, odd blocks) pay the events for every chunk, some 20 us of it,
-    // and gain the shorter of a chunk's fold and its attention: with the block's similarity (C x rows x d) small both
-    // are a few launches of 5 to 10 us.  Serial against pipelined, us per call (blocks, rows): fp32 d 64 2 units
-    // (64, 64) 318 / 540, bf16 d 64 8 units (256, 256) 660 / 900, fp32 d 64 1 unit (256, 300: 20 MB) 402 / 450; but fp32
-    // d 128 1 unit (256, 300: 39 MB) 596 / 533, bf16 d 64 8 units (512, 1000: 66 MB) 1180 / 985.
-    const bool small_chunks = st->group == 1 && (double)C * (double)m_max * (double)d * (double)es <= 24.0e6;
+    // So do states without grouped launches (fp32, head_dim 64, odd blocks) whose attention takes the scores of a chunk's fold
+    // along (launch_attn_score): the events would cost some 20 us a chunk.  Pipelined / serial, us per call (blocks, rows): bf16 d 64
+    // 8 units (256, 700) 238 / 143, 8 units (512, 1000) 567 / 558; fp32 d 64 4 units (512, 1000) 1312 / 938; fp32 d 128 8 units (128,
+    // 1000) 968 / 794, 8 units (512, 2000) 8900 / 7120, 1 unit (512, 900) 456 / 451.  A single unit whose block and state are larger
+    // still leaves room for both at once, 1 unit (1000, 1100) 1496 / 1555; and where attention goes by itself the small ones alone
+    // are serial, bf16 d 64 32 units, 4 heads each (320, 1100) 1846 / 2141.
+    const double similarity = (double)C * (double)m_max * (double)d * (double)es;
+    AttnArgs one;
+    one.n_chunks = 1;
+    const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one) && (dv.U > 1 || similarity <= 240.0e6)));
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.
-    const bool serial = (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || small_chunks)) || captured(stream);
+    const bool serial = (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || apart)) || captured(stream);
     if (serial) {
-      for (const Chunk &ch : plan) {
+      size_t keys_from = 0, keys_to = 0;   // chunks whose blocks' memory keys are in the scratch, one after the other
+      for (size_t i_ch = 0; i_ch < plan.size(); ++i_ch) {
+        const Chunk &ch = plan[i_ch];
+        const int64_t ce = ch.s + C, lo = ce - L;
+        const Src block = lo >= t0 ? advance(in, lo - t0, es) : advance(ring, lo % L, es);
+        if (ch.folds && i_ch >= keys_to) {
+          // memory keys depend on k alone: of as many blocks as the scratch holds at once (those in the ring one by one)
+          size_t n = 1;
+          while (lo >= t0 && (int)n < key_blocks(c) && i_ch + n < plan.size() && plan[i_ch + n].folds) ++n;
+          ProfileSpan span(st, 1, stream, 0);
+          HIP_TRY(kvm::launch_memkey(dv, block, (int)n, stream));
+          keys_from = i_ch;
+          keys_to = i_ch + n;
+        }
+        const int slab = (int)(i_ch - keys_from);
         AttnArgs a;
         a.put_token = 0;
         a.q = (const char *)q + (ch.s - t0) * s.q_t * (int64_t)es;
@@ -1024,18 +1045,22 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           a.m[i] = (int32_t)st->m;
           a.slot[i] = (int32_t)slot_of(st, st->folds);
         }
+        const int64_t n_app = ch.folds ? rows_after(c, st->table, st->m, ce) - st->m : C;
+        const bool scored = !st->mfma && n_app < C && kvm::attention_takes_scores(dv, a);
         {
           ProfileSpan span(st, 0, stream);
-          if (kvm::attention_on_mfma(dv))
+          if (scored) {
+            Dev kdv = dv;
+            kdv.kbar = (char *)dv.kbar + (size_t)slab * dv.Ufull * C * d * es;
+            HIP_TRY(kvm::launch_attn_score(kdv, a, slot_of(st, st->folds), (int)st->m, stream));
+          } else if (kvm::attention_on_mfma(dv))
             HIP_TRY(kvm::launch_attn_mfma(dv, a, false, stream));
           else
             HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
         }
         if (ch.folds) {
-          const int64_t ce = ch.s + C, lo = ce - L;
           ProfileSpan span(st, 1, stream);
-          const int rc = lo >= t0 ? fold_block(st, advance(in, lo - t0, es), ce, nullptr, nullptr, stream, true)
-                                  : fold_block(st, advance(ring, lo % L, es), ce, nullptr, nullptr, stream, true);
+          const int rc = fold_block(st, block, ce, nullptr, nullptr, stream, true, slab, scored);
           if (rc != KVM_OK) return rc;
         }
       }
@@ -1205,9 +1230,9 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         for (int i = 0; i < run; ++i) {
           const int64_t lo = plan[next_fold + i].s + C - L;  // first token of the overflow block
           const int rc = batched ? fold_launches(st, cdv[c2], advance(cin, lo - t0, es), steps[i].m, steps[i].m_after,
-                                                 steps[i].so, steps[i].sn, false, i, fstream[c2])
+                                                 steps[i].so, steps[i].sn, false, i, false, fstream[c2])
                                  : fold_launches(st, cdv[c2], advance(cring, lo % L, es), steps[i].m,
-                                                 steps[i].m_after, steps[i].so, steps[i].sn, false, -1, fstream[c2]);
+                                                 steps[i].m_after, steps[i].so, steps[i].sn, false, -1, false, fstream[c2]);
           if (rc != KVM_OK) return rc;
           const int rt = fold_trace(st, cdv[c2], (int64_t)c2 * cb * dv.Hkv, st->folds + i, fstream[c2]);
           if (rt != KVM_OK) return rt;

@@ -175,6 +175,12 @@ inline bool attention_on_mfma(const Dev &dv) {
 // beside_folds: one workgroup per compute unit, so that those of shared folds find theirs free at any time
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st);
 
+// A chunk's attention with the first scoring pass of the fold after it (rows [0, m) of readout slot `slot`, memory keys at
+// dv.kbar), one launch: for states without the matrix-core folds.
+bool attention_takes_scores(const Dev &dv, const AttnArgs &a);
+hipError_t launch_attn_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st);
+hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st);
+
 // backward.hip: the backward pass of a whole-sequence prefill that started from an empty state.
 // Dense operands: q, out, dout, dq [B, T, Hq, d]; k, v, dk, dv [B, T, Hkv, d]; gate, dgate
 // [B, T, Hkv]; lse [B, T, Hq]; assign [folds, U, C].  The work arrays have the state's row
