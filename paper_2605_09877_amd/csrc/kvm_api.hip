@@ -366,16 +366,15 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
   return KVM_OK;
 }
 
-// What a fold leaves for the parity tests: its assignments and scores, for the units of `dv`
-// (unit u0 on of the state), into the trace buffers at fold number `fold`.
-int fold_trace(const kvm_state *st, const Dev &dv, int64_t u0, int64_t fold, hipStream_t stream) {
-  const size_t ntok_all = (size_t)st->dv.U * dv.C, ntok = (size_t)dv.U * dv.C, off = (size_t)u0 * dv.C;
-  if (st->trace_assign && fold < st->trace_max)
-    HIP_TRY(hipMemcpyAsync(st->trace_assign + fold * ntok_all + off, dv.pi, ntok * 4, hipMemcpyDeviceToDevice, stream));
-  if (st->trace_score && fold < st->trace_max)
-    HIP_TRY(hipMemcpyAsync(st->trace_score + (fold * ntok_all + off) * 2, dv.score, ntok * 8, hipMemcpyDeviceToDevice,
-                           stream));
-  return KVM_OK;
+// The record of a fold (kvm_state_trace), for the units of `dv` (unit u0 on of the state): where the kernel-per-step path is
+// to leave its assignments and scores, the caller's buffers at fold number `fold` instead of the scratch.  (Copied there
+// behind every fold they were two more launches in the chain: 126 of 5.6 us, 0.7 ms, of a training step on 8 x 32768 tokens.)
+Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
+  if (fold >= st->trace_max) return dv;
+  const int64_t at = (fold * st->dv.U + u0) * dv.C;
+  if (st->trace_assign) dv.pi = st->trace_assign + at;
+  if (st->trace_score) dv.score = (float2 *)(st->trace_score + 2 * at);
+  return dv;
 }
 
 // The one-launch fold path (a run of folds in one kernel; bf16, d = 128 states whose tables fit LDS)
@@ -612,6 +611,7 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
   const int so = slot_of(st, st->folds), sn = in_place ? so : slot_of(st, st->folds + 1);
   const size_t ntok = (size_t)dv.U * dv.C;
   const int split = fold_split_on(st, 1, stream);
+  Dev rdv = dv;
   if (split > 0) {
     kvm::FoldRunArgs run;
     int rc_run = fused_run(st, split, in_place, stream, &run);
@@ -625,19 +625,14 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
     rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, nullptr, stream);
     if (rc_run != KVM_OK) return rc_run;
   } else {
-    int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, scored, stream);
+    rdv = recorded(st, dv, 0, st->folds);
+    int rc = fold_launches(st, rdv, src, m, m_after, so, sn, in_place, kbar_block, scored, stream);
     if (rc != KVM_OK) return rc;
-    if (st->trace_assign && st->folds < st->trace_max)
-      HIP_TRY(hipMemcpyAsync(st->trace_assign + st->folds * ntok, dv.pi, ntok * 4,
-                             hipMemcpyDeviceToDevice, stream));
-    if (st->trace_score && st->folds < st->trace_max)
-      HIP_TRY(hipMemcpyAsync(st->trace_score + st->folds * ntok * 2, dv.score, ntok * 8,
-                             hipMemcpyDeviceToDevice, stream));
   }
   if (assign_out)
-    HIP_TRY(hipMemcpyAsync(assign_out, dv.pi, ntok * 4, hipMemcpyDeviceToDevice, stream));
+    HIP_TRY(hipMemcpyAsync(assign_out, rdv.pi, ntok * 4, hipMemcpyDeviceToDevice, stream));
   if (score_out)
-    HIP_TRY(hipMemcpyAsync(score_out, dv.score, ntok * 8, hipMemcpyDeviceToDevice, stream));
+    HIP_TRY(hipMemcpyAsync(score_out, rdv.score, ntok * 8, hipMemcpyDeviceToDevice, stream));
   st->m = m_after;
   st->folds += 1;
   if (in_place) st->inplace += 1;
@@ -1050,7 +1045,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         {
           ProfileSpan span(st, 0, stream);
           if (scored) {
-            Dev kdv = dv;
+            Dev kdv = recorded(st, dv, 0, st->folds);
             kdv.kbar = (char *)dv.kbar + (size_t)slab * dv.Ufull * C * d * es;
             HIP_TRY(kvm::launch_attn_score(kdv, a, slot_of(st, st->folds), (int)st->m, stream));
           } else if (kvm::attention_on_mfma(dv))
@@ -1229,13 +1224,12 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         if (batched) HIP_TRY(kvm::launch_memkey(cdv[c2], advance(cin, lo0 - t0, es), run, fstream[c2]));
         for (int i = 0; i < run; ++i) {
           const int64_t lo = plan[next_fold + i].s + C - L;  // first token of the overflow block
-          const int rc = batched ? fold_launches(st, cdv[c2], advance(cin, lo - t0, es), steps[i].m, steps[i].m_after,
-                                                 steps[i].so, steps[i].sn, false, i, false, fstream[c2])
-                                 : fold_launches(st, cdv[c2], advance(cring, lo % L, es), steps[i].m,
-                                                 steps[i].m_after, steps[i].so, steps[i].sn, false, -1, false, fstream[c2]);
+          const Dev rdv = recorded(st, cdv[c2], (int64_t)c2 * cb * dv.Hkv, st->folds + i);
+          const int rc = batched ? fold_launches(st, rdv, advance(cin, lo - t0, es), steps[i].m, steps[i].m_after, steps[i].so,
+                                                 steps[i].sn, false, i, false, fstream[c2])
+                                 : fold_launches(st, rdv, advance(cring, lo % L, es), steps[i].m, steps[i].m_after, steps[i].so,
+                                                 steps[i].sn, false, -1, false, fstream[c2]);
           if (rc != KVM_OK) return rc;
-          const int rt = fold_trace(st, cdv[c2], (int64_t)c2 * cb * dv.Hkv, st->folds + i, fstream[c2]);
-          if (rt != KVM_OK) return rt;
         }
       }
       st->m = steps[run - 1].m_after;
