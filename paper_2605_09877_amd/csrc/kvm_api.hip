@@ -166,8 +166,6 @@ bool use_mfma(const kvm_config &c) {
 // Chunks per prefill attention launch.  The matrix-core path launches groups of chunks so that
 // a launch has thousands of workgroups; the generic path launches chunk by chunk.
 int group_of(const kvm_config &c) { return use_mfma(c) ? 8 : 1; }
-// Blocks whose memory keys the scratch holds: two runs of one-launch folds, or what one launch makes of them ahead.
-int key_blocks(const kvm_config &c) { return use_mfma(c) ? 2 * kvm::kFoldMaxSteps : 8; }
 constexpr int kComputeUnits = 256;  // of the chip this library is written for
 // Workgroups that may share a unit's rows (a power of two): at most kFoldMaxSplit, one 64-row tile each, and
 // together no more than `cus` compute units (beyond that a unit's workgroups start far apart).
@@ -176,6 +174,18 @@ int most_split(int64_t U, int64_t Mcap, int cus) {
   while (2 * n <= kvm::kFoldMaxSplit && U * 2 * n <= cus && Mcap / 64 >= 2 * n) n *= 2;
   return n;
 }
+
+// States whose folds may be shared among workgroups (fold_split, below).
+constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareAlone = 8192,
+              kShareAnyRows = 1024;
+bool may_share(const kvm_config &c) {
+  const int64_t U = (int64_t)c.batch * c.n_kv_heads;
+  return use_mfma(c) && U >= kShareMinUnits && U < kFusedMinUnits && c.chunk_len <= kShareMaxBlock;
+}
+// Folds of a run: a group's where they run beside attention (attention_beside), half of one elsewhere.  Blocks whose memory
+// keys the scratch holds: two runs'.
+constexpr int kFoldRunApart = 4;
+int key_blocks(const kvm_config &c) { return may_share(c) ? 2 * kvm::kFoldMaxSteps : 2 * kFoldRunApart; }
 
 Layout layout_of(const kvm_config &c, int64_t Mcap) {
   const size_t U = (size_t)c.batch * c.n_kv_heads, d = c.head_dim, C = c.chunk_len;
@@ -414,8 +424,6 @@ int compute_units(const kvm_state *st) {
   }
   return n < kComputeUnits ? n : kComputeUnits;
 }
-constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareAlone = 8192,
-              kShareAnyRows = 1024;
 // Workgroups per unit on that path, for the folds of a call of `blocks` blocks (1: a fold by itself) into the state as it
 // stands: 0 = a kernel per step.
 int fold_split(const kvm_state *st, int64_t blocks) {
@@ -455,16 +463,14 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
 // 65536 tokens (5.8) 7570 / 6350; 64 units of 64-token blocks (0.8) 2300 / 1976; 32 units, 2 heads each, growing (2.9)
 // 1865 / 1610; 64 units, 512 rows, 2 heads each (15) 1280 / 1165; 16 units, 4 heads each (7.5) 672 / 639; but 32 units, 900 rows,
 // 4 heads each (21.5) 1270 / 1290, 64 units, 512 rows, 4 heads each (30) 1790 / 1805.
+// The runs of folds are a group's eight then.  Elsewhere the launch waits for attention to leave and attention for the launch, and
+// they are half as long: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight.
 constexpr double kBesideMostFlops = 18e9;
 bool attention_beside(const kvm_state *st, int split, int64_t m) {
   const Dev &dv = st->dv;
   const double keys = (double)m + (double)dv.L - 0.5 * (double)dv.C;
-  return kvm::fold_fused_beside(dv, split) && 4.0 * dv.d * dv.B * dv.Hq * dv.C * keys <= kBesideMostFlops;
+  return may_share(st->cfg) && kvm::fold_fused_beside(dv, split) && 4.0 * dv.d * dv.B * dv.Hq * dv.C * keys <= kBesideMostFlops;
 }
-// Folds of a run: a group's where they run beside attention; half of one elsewhere (the launch waits for attention to leave, and
-// attention for the launch: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight).
-constexpr int kFoldRunApart = 4;
-
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
                hipStream_t stream) {
@@ -1187,7 +1193,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       }
       if (fused_folds) {
         const Src fsrc = batched ? advance(in, lo0 - t0, es) : advance(ring, lo0 % L, es);
-        const int half = runs++ & 1, slab0 = half * kvm::kFoldMaxSteps;
+        const int half = runs++ & 1, slab0 = half * run_cap;
         Dev kdv = dv;
         kdv.kbar = (char *)dv.kbar + (size_t)slab0 * dv.Ufull * C * d * es;
         if (keys_read_ev[half]) HIP_TRY(hipStreamWaitEvent(fstream[1], keys_read_ev[half], 0));
