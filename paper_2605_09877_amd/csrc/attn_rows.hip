@@ -97,11 +97,12 @@ __device__ __forceinline__ void combine_shares(const RowQuery<T> &rq) {
   }
 }
 
-// kShared: the keys may be shared among workgroups.  A kernel of its own, because what sharing adds costs registers, in bf16
+// NW: waves per workgroup.  kShared: the keys may be shared among workgroups.  A kernel of its own, because what sharing adds costs registers, in bf16
 // one head at a time 82 instead of 79 and with them a wave per SIMD (five instead of six): 40 sequences of 16 heads on
 // 328 rows, their fold included, 31.2 instead of 30.5 us a token, 10 of 32 heads on 16 17.0 instead of 16.7.
-template <typename T, int D, int GQ, bool kShared>
+template <typename T, int D, int GQ, bool kShared, int NW = 4>
 __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
+  static_assert(NW == 4 || !kShared, "shares are put together by four waves");
   constexpr int VEC = Vec16<T>::kN;
   constexpr int LPR = D / VEC;   // lanes per key row
   constexpr int RPW = 64 / LPR;  // key rows per wave step
@@ -152,12 +153,12 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
     for (int i = 0; i < VEC; ++i) acc[hh][i] = 0.f;
   }
 
-  for (int n0 = n_first; n0 < total; n0 += 4 * RPW * KB) {
+  for (int n0 = n_first; n0 < total; n0 += NW * RPW * KB) {
     float kf[KB][VEC], vf[KB][VEC];
     bool is_state[KB], on[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      const int n = n0 + (kb * 4 + wave) * RPW + sub;
+      const int n = n0 + (kb * NW + wave) * RPW + sub;
       const int nc = n < total ? n : total - 1;
       const T *kp, *vp;
       if (nc < m) {
@@ -209,7 +210,7 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
     }
   }
 
-  __shared__ float sh_m[GQ][4], sh_l[GQ][4], sh_acc[GQ][4][D];
+  __shared__ float sh_m[GQ][NW], sh_l[GQ][NW], sh_acc[GQ][NW][D];
 #pragma unroll
   for (int hh = 0; hh < GQ; ++hh) {
     // merge the lane groups of this wave
@@ -235,16 +236,18 @@ __device__ __forceinline__ void attn_row(const Dev &dv, const RowQuery<T> &rq) {
     }
   }
   __syncthreads();
-  // merge the four waves: wave hh % 4 finishes head hh
+  // merge the waves: wave hh % 4 finishes head hh
 #pragma unroll
   for (int hh = 0; hh < GQ; ++hh) {
     if (wave == (hh & 3) && sub == 0) {
-      const float mm = fmaxf(fmaxf(sh_m[hh][0], sh_m[hh][1]), fmaxf(sh_m[hh][2], sh_m[hh][3]));
+      float mm = fmaxf(fmaxf(sh_m[hh][0], sh_m[hh][1]), fmaxf(sh_m[hh][2], sh_m[hh][3]));
+#pragma unroll
+      for (int wv = 4; wv < NW; ++wv) mm = fmaxf(mm, sh_m[hh][wv]);
       float l = 0.f, o[VEC];
 #pragma unroll
       for (int i = 0; i < VEC; ++i) o[i] = 0.f;
 #pragma unroll
-      for (int wv = 0; wv < 4; ++wv) {
+      for (int wv = 0; wv < NW; ++wv) {
         // a wave that saw no key has max -inf -> 0 (none of them did: an empty share)
         const float sc = kShared && mm == -INFINITY ? 0.f : exp2f(sh_m[hh][wv] - mm);
         l += sh_l[hh][wv] * sc;
@@ -280,7 +283,7 @@ __device__ __forceinline__ void set_share(RowQuery<T> &rq, const Dev &dv, int gr
 
 // One workgroup per (query, group of GQ query heads, sequence) of one state; shared, a decode step's:
 // several per group.
-template <typename T, int D, int GQ, bool kShared>
+template <typename T, int D, int GQ, bool kShared, int NW = 4>
 __device__ __forceinline__ void attn_rows_of(const Dev &dv, const AttnArgs &a, int x, int y, int b) {
   // a decode step has one query per sequence, and the x dimension counts the shares of its keys
   const int qi = kShared ? 0 : x, hq = y * GQ;
@@ -318,12 +321,12 @@ __device__ __forceinline__ void attn_rows_of(const Dev &dv, const AttnArgs &a, i
     rq.put_g = dv.winG + (int64_t)u * dv.L;
     rq.gate = a.in.g ? a.in.g[b * a.in.g_b + hkv * a.in.g_h + (rq.pos - a.t0) * a.in.g_t] : 1.f;
   }
-  attn_row<T, D, GQ, kShared>(dv, rq);
+  attn_row<T, D, GQ, kShared, NW>(dv, rq);
 }
 
-template <typename T, int D, int GQ, bool kShared>
-__global__ __launch_bounds__(256) void attn_rows_kernel(Dev dv, AttnArgs a) {
-  attn_rows_of<T, D, GQ, kShared>(dv, a, blockIdx.x, blockIdx.y, blockIdx.z);
+template <typename T, int D, int GQ, bool kShared, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_rows_kernel(Dev dv, AttnArgs a) {
+  attn_rows_of<T, D, GQ, kShared, NW>(dv, a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // A chunk's attention and, in further workgroups, the scores of the block that is folded after it: both read the same state
@@ -346,8 +349,8 @@ __global__ __launch_bounds__(256) void attn_rows_score_kernel(Dev dv, AttnArgs a
 // Decode over sequences that live in different states (each at its own position, with its own
 // number of state rows): one workgroup, or several sharing the keys, per (group of GQ query heads,
 // sequence); sequence s reads seq[s].  dv is the states' common configuration (heads, chunk, window, temperatures).
-template <typename T, int D, int GQ, bool kShared>
-__global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, const void *q,
+template <typename T, int D, int GQ, bool kShared, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, const void *q,
                                                               const void *k, const void *v, const float *gate,
                                                               void *out) {
   const int hq = blockIdx.y * GQ, s = blockIdx.z;
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(256) void attn_rows_multi_kernel(Dev dv, const SeqD
     rq.put_g = sd.winG + (int64_t)hkv * dv.L;
     rq.gate = gate ? gate[(int64_t)s * dv.Hkv + hkv] : 1.f;
   }
-  attn_row<T, D, GQ, kShared>(dv, rq);
+  attn_row<T, D, GQ, kShared, NW>(dv, rq);
 }
 
 // Query heads a decode workgroup takes together: the KV head's whole group when it has 2 or 4
@@ -407,31 +410,37 @@ int shares_for(const Dev &dv, int gq, int n_groups, int keys, int round) {
   s = s < kMaxSplit ? s : kMaxSplit;
   return s > 1 ? s : 1;
 }
+// Eight waves per workgroup where a decode launch, one workgroup per (sequence, head group), has no more of them than compute
+// units: a workgroup walks its keys alone on its unit, and loads and sums wait for each other.  Us per step with four /
+// eight waves, 2048 rows in bf16: 256 workgroups of four heads 81 / 60, of one 58 / 45, 192 of two (845 rows) 24 / 20,
+// 160 of one (500) 17 / 13; but 320 of four heads (1000) 58 / 63, of two 37 / 43, of one 33 / 35, 512 of four (2048) 116 / 120.
+constexpr int kWavesFew = 8, kFewGroups = 256;
+bool many_waves(int n_groups) { return n_groups <= kFewGroups; }
 int round_keys(const Dev &dv) { return 16 * 64 / (dv.d / (dv.io == 0 ? 4 : 8)); }
 
 }  // namespace
 
-#define KVM_ROWS_DISPATCH(KERNEL, GQV, SHARED, grid, ...)                                           \
+#define KVM_ROWS_DISPATCH(KERNEL, GQV, SHARED, NWV, grid, ...)                                           \
   do {                                                                                              \
     if (dv.io == 0 && dv.d == 64)                                                                   \
-      hipLaunchKernelGGL((KERNEL<float, 64, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);    \
+      hipLaunchKernelGGL((KERNEL<float, 64, GQV, SHARED, NWV>), grid, dim3(64 * NWV), 0, st, __VA_ARGS__);    \
     else if (dv.io == 0 && dv.d == 128)                                                             \
-      hipLaunchKernelGGL((KERNEL<float, 128, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);   \
+      hipLaunchKernelGGL((KERNEL<float, 128, GQV, SHARED, NWV>), grid, dim3(64 * NWV), 0, st, __VA_ARGS__);   \
     else if (dv.io == 1 && dv.d == 64)                                                              \
-      hipLaunchKernelGGL((KERNEL<bf16_t, 64, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);   \
+      hipLaunchKernelGGL((KERNEL<bf16_t, 64, GQV, SHARED, NWV>), grid, dim3(64 * NWV), 0, st, __VA_ARGS__);   \
     else if (dv.io == 1 && dv.d == 128)                                                             \
-      hipLaunchKernelGGL((KERNEL<bf16_t, 128, GQV, SHARED>), grid, dim3(256), 0, st, __VA_ARGS__);  \
+      hipLaunchKernelGGL((KERNEL<bf16_t, 128, GQV, SHARED, NWV>), grid, dim3(64 * NWV), 0, st, __VA_ARGS__);  \
     else                                                                                            \
       return hipErrorInvalidValue;                                                                  \
   } while (0)
-#define KVM_ROWS_LAUNCH(KERNEL, SHARED, grid, ...)             \
+#define KVM_ROWS_LAUNCH(KERNEL, SHARED, NWV, grid, ...)             \
   do {                                                         \
     if (gq == 4)                                               \
-      KVM_ROWS_DISPATCH(KERNEL, 4, SHARED, grid, __VA_ARGS__); \
+      KVM_ROWS_DISPATCH(KERNEL, 4, SHARED, NWV, grid, __VA_ARGS__); \
     else if (gq == 2)                                          \
-      KVM_ROWS_DISPATCH(KERNEL, 2, SHARED, grid, __VA_ARGS__); \
+      KVM_ROWS_DISPATCH(KERNEL, 2, SHARED, NWV, grid, __VA_ARGS__); \
     else                                                       \
-      KVM_ROWS_DISPATCH(KERNEL, 1, SHARED, grid, __VA_ARGS__); \
+      KVM_ROWS_DISPATCH(KERNEL, 1, SHARED, NWV, grid, __VA_ARGS__); \
   } while (0)
 
 hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
@@ -446,9 +455,11 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   }
   dim3 grid(nx, dv.Hq / gq, dv.B);
   if (a.put_token && nx > 1)
-    KVM_ROWS_LAUNCH(attn_rows_kernel, true, grid, dv, a);
+    KVM_ROWS_LAUNCH(attn_rows_kernel, true, 4, grid, dv, a);
+  else if (a.put_token && many_waves(dv.Hq / gq * dv.B))
+    KVM_ROWS_LAUNCH(attn_rows_kernel, false, kWavesFew, grid, dv, a);
   else
-    KVM_ROWS_LAUNCH(attn_rows_kernel, false, grid, dv, a);
+    KVM_ROWS_LAUNCH(attn_rows_kernel, false, 4, grid, dv, a);
   return hipGetLastError();
 }
 
@@ -476,9 +487,11 @@ hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int
   const int gq = heads_together(dv);
   dim3 agrid(shares_for(dv, gq, dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
   if (agrid.x > 1)
-    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, true, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, true, 4, agrid, dv, seq, q, k, v, gate, out);
+  else if (many_waves(dv.Hq / gq * n_seq))
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, kWavesFew, agrid, dv, seq, q, k, v, gate, out);
   else
-    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, 4, agrid, dv, seq, q, k, v, gate, out);
   return hipGetLastError();
 }
 
