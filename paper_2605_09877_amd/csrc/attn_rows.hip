@@ -349,13 +349,37 @@ __global__ __launch_bounds__(256) void attn_rows_score_kernel(Dev dv, AttnArgs a
 // Decode over sequences that live in different states (each at its own position, with its own
 // number of state rows): one workgroup, or several sharing the keys, per (group of GQ query heads,
 // sequence); sequence s reads seq[s].  dv is the states' common configuration (heads, chunk, window, temperatures).
+template <typename T, int D>
+__device__ __forceinline__ SeqDesc seq_of(const Dev &dv, const SeqPack &pk, int s) {
+  int i = s;
+  if (pk.seq0[pk.n] != pk.n) {   // some state has several sequences
+    int hi = pk.n;
+    i = 0;
+    while (hi - i > 1) {
+      const int mid = (i + hi) / 2;
+      if (pk.seq0[mid] <= s) i = mid; else hi = mid;
+    }
+  }
+  const int64_t es = sizeof(T), U = (int64_t)(pk.seq0[i + 1] - pk.seq0[i]) * dv.Hkv, u0 = (int64_t)(s - pk.seq0[i]) * dv.Hkv;
+  const int64_t ring = decode_ring_offset(U, dv.L, D, es);
+  SeqDesc sd;
+  sd.m = pk.m[i];
+  sd.Mcap = pk.Mcap[i];
+  sd.pos = pk.pos[i];
+  sd.khat = (const char *)pk.khat[i] + u0 * sd.Mcap * D * es;
+  sd.vhat = (const char *)sd.khat + decode_value_offset(dv.NS, U, sd.Mcap, D, es);
+  sd.winK = (char *)pk.winK[i] + u0 * dv.L * D * es;
+  sd.winV = (char *)sd.winK + ring;
+  sd.winG = (float *)((char *)pk.winK[i] + 2 * ring) + u0 * dv.L;
+  return sd;
+}
 template <typename T, int D, int GQ, bool kShared, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, const void *q,
+__global__ __launch_bounds__(64 * NW) void attn_rows_multi_kernel(Dev dv, const SeqDesc *seq, SeqPack pk, const void *q,
                                                               const void *k, const void *v, const float *gate,
                                                               void *out) {
   const int hq = blockIdx.y * GQ, s = blockIdx.z;
   const int hkv = hq / (dv.Hq / dv.Hkv);
-  const SeqDesc sd = seq[s];
+  const SeqDesc sd = seq ? seq[s] : seq_of<T, D>(dv, pk, s);
   RowQuery<T> rq;
   rq.pos = sd.pos;
   rq.q = (const T *)q + ((int64_t)s * dv.Hq + hq) * D;
@@ -481,17 +505,17 @@ hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, in
   return hipGetLastError();
 }
 
-hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int most_keys, const void *q,
+hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, const SeqPack &pack, int n_seq, int most_keys, const void *q,
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st) {
   if (n_seq <= 0) return hipSuccess;
   const int gq = heads_together(dv);
   dim3 agrid(shares_for(dv, gq, dv.Hq / gq * n_seq, most_keys, round_keys(dv)), dv.Hq / gq, n_seq);
   if (agrid.x > 1)
-    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, true, 4, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, true, 4, agrid, dv, seq, pack, q, k, v, gate, out);
   else if (many_waves(dv.Hq / gq * n_seq))
-    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, kWavesFew, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, kWavesFew, agrid, dv, seq, pack, q, k, v, gate, out);
   else
-    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, 4, agrid, dv, seq, q, k, v, gate, out);
+    KVM_ROWS_LAUNCH(attn_rows_multi_kernel, false, 4, agrid, dv, seq, pack, q, k, v, gate, out);
   return hipGetLastError();
 }
 

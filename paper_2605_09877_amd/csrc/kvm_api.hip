@@ -83,7 +83,6 @@ int hip_fail(hipError_t e, const char *what) {
   } while (0)
 
 inline size_t esize(int io) { return io == KVM_BF16 ? 2 : 4; }
-inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 int64_t ceil_sqrt(int64_t e) {
   if (e <= 0) return 0;
@@ -194,7 +193,7 @@ Layout layout_of(const kvm_config &c, int64_t Mcap) {
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
-    o += up256(bytes);
+    o += (size_t)kvm::up256((int64_t)bytes);
     return at;
   };
   l.sK = take(U * M * d * 8);
@@ -671,7 +670,7 @@ BwdLayout bwd_layout(const kvm_config &c, int64_t Mcap, int64_t T, bool mfma_pat
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
-    o += up256(bytes);
+    o += (size_t)kvm::up256((int64_t)bytes);
     return at;
   };
   l.wsK = take(U * M * d * 8);
@@ -783,17 +782,41 @@ int most_keys(kvm_state *const *states, int n_states) {
   return (int)most;
 }
 
-// Up to kPackStates states' worth of descriptors per launch, handed over as a kernel argument
+// What a launch over up to kPackStates states needs to know of them, as a kernel argument; false: they are too many.
+bool pack_states(kvm_state *const *states, int n_states, kvm::SeqPack *pack) {
+  pack->n = 0;
+  pack->seq0[0] = 0;
+  if (n_states > kvm::kPackStates) return false;
+  for (int i = 0; i < n_states; ++i) {
+    const kvm_state *st = states[i];
+    const Dev &dv = st->dv;
+    const int64_t es = (int64_t)esize(st->cfg.io_dtype), ring = kvm::decode_ring_offset(dv.U, dv.L, dv.d, es);
+    // (the arrays' order in the buffer: layout_of)
+    if ((const char *)dv.vhat - (const char *)dv.khat != kvm::decode_value_offset(dv.NS, dv.U, dv.Mcap, dv.d, es) ||
+        (const char *)dv.winV - (const char *)dv.winK != ring || (const char *)dv.winG - (const char *)dv.winV != ring)
+      return false;
+    pack->khat[i] = (const char *)dv.khat + slot_of(st, st->folds) * dv.slot_elems * es;
+    pack->winK[i] = dv.winK;
+    pack->pos[i] = st->tokens;
+    pack->m[i] = (int32_t)st->m;
+    pack->Mcap[i] = dv.Mcap;
+    pack->seq0[i + 1] = pack->seq0[i] + dv.B;
+  }
+  pack->n = n_states;
+  return true;
+}
+
+// Up to kFillStates states' worth of descriptors per launch, handed over as a kernel argument
 // (no host-to-device copy, no host buffer): per state where its arrays start and where it stands;
 // thread i of the launch writes the descriptor of sequence pack.seq0[0] + i.
-constexpr int kPackStates = 32;
+constexpr int kFillStates = 32;
 struct StatePack {
-  const void *khat[kPackStates], *vhat[kPackStates];  // current readout version, first unit
-  void *winK[kPackStates], *winV[kPackStates];
-  float *winG[kPackStates];
-  int64_t pos[kPackStates];
-  int32_t m[kPackStates], Mcap[kPackStates];
-  int32_t seq0[kPackStates + 1];  // first sequence of each state; [n] = one past the last
+  const void *khat[kFillStates], *vhat[kFillStates];  // current readout version, first unit
+  void *winK[kFillStates], *winV[kFillStates];
+  float *winG[kFillStates];
+  int64_t pos[kFillStates];
+  int32_t m[kFillStates], Mcap[kFillStates];
+  int32_t seq0[kFillStates + 1];  // first sequence of each state; [n] = one past the last
   int32_t n;
 };
 __global__ __launch_bounds__(256) void seqdesc_fill_kernel(StatePack pk, kvm::SeqDesc *table, int Hkv, int L, int d,
@@ -1406,35 +1429,39 @@ int kvm_decode_step_multi(kvm_state *const *states, int32_t n_states, const void
     if ((u + 1) % C == 0 && u + 1 >= L && rows_after(st->cfg, st->table, st->m, u + 1) > st->dv.Mcap)
       return KVM_ERR_CAPACITY;
   }
-  std::vector<kvm::SeqDesc> desc((size_t)n_seq);
-  size_t s = 0;
-  for (int i = 0; i < n_states; ++i) {
-    const kvm_state *st = states[i];
-    const Dev &dv = st->dv;
-    const int64_t slot = slot_of(st, st->folds);
-    for (int b = 0; b < dv.B; ++b, ++s) {
-      const int64_t u0 = (int64_t)b * dv.Hkv;
-      kvm::SeqDesc &sd = desc[s];
-      sd.khat = (const char *)dv.khat + (slot * dv.slot_elems + u0 * dv.Mcap * d) * es;
-      sd.vhat = (const char *)dv.vhat + (slot * dv.slot_elems + u0 * dv.Mcap * d) * es;
-      sd.winK = (char *)dv.winK + u0 * L * d * es;
-      sd.winV = (char *)dv.winV + u0 * L * d * es;
-      sd.winG = dv.winG + u0 * L;
-      sd.pos = st->tokens;
-      sd.m = (int32_t)st->m;
-      sd.Mcap = dv.Mcap;
-    }
-  }
   {
     const int rc = clean_shares(states[0], stream);
     if (rc != KVM_OK) return rc;
   }
-  // pageable source: the copy is staged before the call returns, and ordered on the stream
-  HIP_TRY(hipMemcpyAsync(workspace, desc.data(), desc.size() * sizeof(kvm::SeqDesc), hipMemcpyHostToDevice,
-                         stream));
+  kvm::SeqPack pack;
+  const bool packed = pack_states(states, n_states, &pack);
+  if (!packed) {
+    std::vector<kvm::SeqDesc> desc((size_t)n_seq);
+    size_t s = 0;
+    for (int i = 0; i < n_states; ++i) {
+      const kvm_state *st = states[i];
+      const Dev &dv = st->dv;
+      const int64_t slot = slot_of(st, st->folds);
+      for (int b = 0; b < dv.B; ++b, ++s) {
+        const int64_t u0 = (int64_t)b * dv.Hkv;
+        kvm::SeqDesc &sd = desc[s];
+        sd.khat = (const char *)dv.khat + (slot * dv.slot_elems + u0 * dv.Mcap * d) * es;
+        sd.vhat = (const char *)dv.vhat + (slot * dv.slot_elems + u0 * dv.Mcap * d) * es;
+        sd.winK = (char *)dv.winK + u0 * L * d * es;
+        sd.winV = (char *)dv.winV + u0 * L * d * es;
+        sd.winG = dv.winG + u0 * L;
+        sd.pos = st->tokens;
+        sd.m = (int32_t)st->m;
+        sd.Mcap = dv.Mcap;
+      }
+    }
+    // pageable source: the copy is staged before the call returns, and ordered on the stream
+    HIP_TRY(hipMemcpyAsync(workspace, desc.data(), desc.size() * sizeof(kvm::SeqDesc), hipMemcpyHostToDevice,
+                           stream));
+  }
   {
     ProfileSpan span(states[0], 2, stream);
-    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)workspace, (int)n_seq,
+    HIP_TRY(kvm::launch_decode_multi(first->dv, packed ? nullptr : (const kvm::SeqDesc *)workspace, pack, (int)n_seq,
                                      most_keys(states, n_states), q, k, v, gate, out, stream));
   }
   for (int i = 0; i < n_states; ++i) {
@@ -1492,10 +1519,12 @@ int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, con
     if (rc == KVM_OK) rc = clean_shares(states[0], stream);
     if (rc != KVM_OK) return rc;
   }
-  // the descriptor table, kPackStates states per launch
-  for (int i0 = 0, seq0 = 0; i0 < n_states; i0 += kPackStates) {
+  kvm::SeqPack pack;
+  const bool packed = pack_states(states, n_states, &pack);
+  // the descriptor table, kFillStates states per launch
+  for (int i0 = 0, seq0 = 0; !packed && i0 < n_states; i0 += kFillStates) {
     StatePack pk;
-    pk.n = n_states - i0 < kPackStates ? n_states - i0 : kPackStates;
+    pk.n = n_states - i0 < kFillStates ? n_states - i0 : kFillStates;
     int sq = seq0;
     for (int i = 0; i < pk.n; ++i) {
       const kvm_state *st = states[i0 + i];
@@ -1513,7 +1542,7 @@ int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, con
       sq += dv.B;
     }
     pk.seq0[pk.n] = sq;
-    for (int i = pk.n + 1; i <= kPackStates; ++i) pk.seq0[i] = sq;
+    for (int i = pk.n + 1; i <= kFillStates; ++i) pk.seq0[i] = sq;
     const int n_here = sq - seq0;
     hipLaunchKernelGGL(seqdesc_fill_kernel, dim3((n_here + 255) / 256), dim3(256), 0, stream, pk,
                        (kvm::SeqDesc *)table, (int)first->dv.Hkv, (int)L, (int)d, (int)es);
@@ -1522,8 +1551,8 @@ int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, con
   }
   {
     ProfileSpan span(states[0], 2, stream);
-    HIP_TRY(kvm::launch_decode_multi(first->dv, (const kvm::SeqDesc *)table, (int)n_seq, most_keys(states, n_states), q,
-                                     k, v, gate, out, stream));
+    HIP_TRY(kvm::launch_decode_multi(first->dv, packed ? nullptr : (const kvm::SeqDesc *)table, pack, (int)n_seq,
+                                     most_keys(states, n_states), q, k, v, gate, out, stream));
   }
   for (int i = 0; i < n_states; ++i) {
     kvm_state *st = states[i];

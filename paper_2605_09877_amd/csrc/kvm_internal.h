@@ -160,8 +160,24 @@ struct SeqDesc {
   int64_t pos;              // position of the token being decoded
   int32_t m, Mcap;          // state rows now, rows per unit in the buffer
 };
-// most_keys: the largest number of keys (state rows and window) any of the sequences attends to
-hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, int n_seq, int most_keys, const void *q,
+// The same of up to kPackStates states as a kernel argument: no table to write ahead of the launch (copied from the host it was a
+// launch of its own of 4.8 us and as much of host time; 3 x 4 heads on 2, 353 rows: 12.4 us a step, with it @A).
+constexpr int kPackStates = 64;
+struct SeqPack {
+  const void *khat[kPackStates];   // current readout version, first unit; v-hat is decode_value_offset() bytes further on
+  void *winK[kPackStates];         // first unit; the rings of values and gates follow, decode_ring_offset() bytes apart
+  int64_t pos[kPackStates];
+  int32_t m[kPackStates], Mcap[kPackStates];
+  int32_t seq0[kPackStates + 1];   // first sequence of each state; [n] = one past the last
+  int32_t n;
+};
+__host__ __device__ inline int64_t up256(int64_t x) { return (x + 255) & ~(int64_t)255; }
+__host__ __device__ inline int64_t decode_value_offset(int64_t NS, int64_t U, int64_t Mcap, int64_t d, int64_t es) {
+  return up256(NS * U * Mcap * d * es);
+}
+__host__ __device__ inline int64_t decode_ring_offset(int64_t U, int64_t L, int64_t d, int64_t es) { return up256(U * L * d * es); }
+// seq: the table, or null: pack.  most_keys: the largest number of keys (state rows and window) any of the sequences attends to
+hipError_t launch_decode_multi(const Dev &dv, const SeqDesc *seq, const SeqPack &pack, int n_seq, int most_keys, const void *q,
                                const void *k, const void *v, const float *gate, void *out, hipStream_t st);
 // attn_mfma.hip: prompts in bf16, d = 128 or 64, blocks of a multiple of 64 tokens (tiles of 64 keys neither cross
 // from the ring into the call's keys nor wrap in the ring); everything else is the row kernel's
