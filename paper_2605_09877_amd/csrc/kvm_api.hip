@@ -175,7 +175,7 @@ int most_split(int64_t U, int64_t Mcap, int cus) {
 }
 
 // States whose folds may be shared among workgroups (fold_split, below).
-constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 256, kShareAlone = 8192,
+constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 512, kShareLongBlock = 256, kShareAlone = 8192,
               kShareAnyRows = 1024;
 bool may_share(const kvm_config &c) {
   const int64_t U = (int64_t)c.batch * c.n_kv_heads;
@@ -394,7 +394,7 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 // 256-token blocks: 8.4 ms for 65536 tokens against 10.6 with a kernel per step).  Otherwise a fold
 // is a kernel per step: with tiles that stream the shared launch lost (64 units of 1024 rows, 4
 // workgroups each: 13 ms for 32768 tokens against 10.9); so it is when kvm_debug_set asks for it.
-// Sharing is for states of 8 units and more, blocks of up to 256 tokens, and calls of 7 blocks and more, of 5 from 64 units
+// Sharing is for states of 8 units and more, and, in blocks of up to 256 tokens, calls of 7 blocks and more, of 5 from 64 units
 // on, or any into a state of 1024 rows and more.  Us per call, a kernel per step / shared, by blocks of the call:
 //   units, block, rows     5              6              7              8              12
 //    8,    128,   256      109 / 122      121 / 126      138 / 134      152 / 147      223 / 208
@@ -403,9 +403,12 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 //   32,    256,   512      152 / 151      176 / 157      201 / 172      226 / 186      340 / 265
 //   64,     64,   128      224 / 162      255 / 167      238 / 158      286 / 156      339 / 254
 //  128,    256,  1024      356 / 310      494 / 411      598 / 492      699 / 589     1125 / 906
-// (4 units: 256, 1024: 126 / 134 at 5 blocks, 175 / 160 at 8; 128, 256: 147 / 145 and 212 / 203 at 8 and 12.  512-token
-// blocks, 32 units, 10 blocks 425 / 461; 8 units, 38 blocks 1007 / 1057; 8 units, 5 and 8 blocks 170 / 182 and
-// 226 / 214: undecided, not shared.)
+// (4 units: 256, 1024: 126 / 134 at 5 blocks, 175 / 160 at 8; 128, 256: 147 / 145 and 212 / 203 at 8 and 12.)
+// Blocks of more than 256 and up to 512 tokens, of which a kernel per step makes fewer launches per token: from 12 blocks on, 8
+// from 64 units on, and up to two query heads per KV head (with four, attention is the longer part).  Growing state: 10 units, 2 heads each,
+// 31 blocks 1630 / 1208, 12 units, 38 blocks 2631 / 2086, 16 units, 16 blocks 688 / 588; fixed: 8 units, 1000 rows, 38 blocks 1049 / 932,
+// 64 units, 512 rows, 8 blocks 521 / 488.  But 8 units, 8 blocks, 512 rows 200 / 210, 1000 rows 256 / 296, 32 units, 1000 rows, 10 blocks
+// 494 / 508; four heads each: 8 units, 600 rows, 16 blocks 523 / 556, 64 units 2075 / 2110.
 // A fold by itself (decode, the fold entry point, chunk by chunk) is shared from units x block = 8192 or 1024 rows on.  Us
 // alone: 8 units of 128-token blocks on 256 rows 45 / 48, 16 of 256 on 256 47 / 49, 32 of 128 on 512 48 / 48; 32 of 256
 // on 512 52 / 49, 64 of 128 on 512 50 / 49, 128 of 256 on 512 75 / 70, 128 of 64 on 256 50 / 50; 8 of 128 on 768, 1024,
@@ -436,6 +439,9 @@ int fold_split(const kvm_state *st, int64_t blocks) {
   if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
   if (path == 1 || U >= kFusedMinUnits) return whole;
   if (U < kShareMinUnits || C > kShareMaxBlock) return 0;
+  if (C > kShareLongBlock) {
+    if (blocks < (U < 64 ? 12 : 8) || st->dv.Hq > 2 * st->dv.Hkv) return 0;
+  } else
   if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) return 0;
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }

@@ -161,7 +161,8 @@ struct SeqDesc {
   int32_t m, Mcap;          // state rows now, rows per unit in the buffer
 };
 // The same of up to kPackStates states as a kernel argument: no table to write ahead of the launch (copied from the host it was a
-// launch of its own of 4.8 us and as much of host time; 3 x 4 heads on 2, 353 rows: 12.4 us a step, with it @A).
+// launch of its own of 4.8 us and as much of host time; 3 x 4 heads on 2, 353 rows: 12.4 us a step before,
+// 10.2 now).
 constexpr int kPackStates = 64;
 struct SeqPack {
   const void *khat[kPackStates];   // current readout version, first unit; v-hat is decode_value_offset() bytes further on

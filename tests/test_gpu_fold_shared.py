@@ -264,3 +264,17 @@ def test_arrangement_changes_between_calls():
     a, e = st.export(), ref.export()
     for key in ("sK", "sV", "rho", "n", "w", "khat", "vhat"):
         assert torch.equal(a[key], e[key]), key
+
+
+@pytest.mark.parametrize("chunk,units,heads,blocks,path", [
+    (512, 8, 8, 12, 1), (512, 8, 8, 11, 2), (512, 64, 64, 8, 1), (512, 64, 64, 7, 2), (512, 8, 16, 12, 1), (512, 8, 32, 12, 2),
+    (1024, 8, 8, 12, 2),
+])
+def test_long_blocks_on_either_side_of_the_rule(chunk, units, heads, blocks, path):
+    """Blocks of more than 256 tokens by the library's own choice, growing state, against a kernel per step."""
+    _, b, sy = kit()
+    w = make(sy, chunk, units, chunk * blocks, None)
+    w = sy.shrink(w, n_q_heads=heads)
+    got = run(w, {})
+    assert got[0].fold_path == path
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
