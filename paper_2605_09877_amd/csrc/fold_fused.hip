@@ -52,12 +52,13 @@
 // else the chip is doing.
 //
 // What bounds it: with shared rows, latency.  A fold of a 256-token block into some 300 rows (32 units x
-// 8 workgroups) takes 15 us without an append and 22 us with one, 29 us on average beside attention: an
-// exchange, two more round trips to memory (values of untouched rows, sums of touched rows), ten
-// barriers.  A kernel per step took 38 us and 62 us for the same.  Prefill of 65536 tokens with a
-// growing state (B 2 x H 16, 256-token blocks): 10.6 to 13.5 ms before (the box decides), 8.0 to 8.2 ms now; of a
-// layer's 16384 tokens with 512 rows: 3.3 ms before, 2.8 ms now.  With one workgroup per unit (256 units
-// and more) by the tiles' and rows' traffic: B 16 x H 16, 8192 tokens, 5.06 ms before, 4.61 ms now
+// 8 workgroups) takes 15 us without an append and 18 us with one of a few rows, 23 us on average beside attention: scores and copies of
+// the fold before 6.5, exchange 1, lists 1.5, merge 5.5 (of which a round trip to the sums 2), another 4 to select, create and
+// score again.  A kernel per step took 38 us and 62 us for the same.  Prefill of 65536 tokens with a growing state
+// (B 2 x H 16, 256-token blocks): 10.6 to 13.5 ms with a kernel per step (the box decides), 7.6 shared, 6.35 with one
+// attention workgroup beside each of these and runs of eight folds, 5.95 with few new rows selected one by one; a
+// layer's 16384 tokens with 512 rows: 3.3, 2.7 and 2.3 ms.  With one workgroup per unit (256 units and more)
+// by the tiles' and rows' traffic: B 16 x H 16, 8192 tokens, 5.06 ms before, 4.61 ms
 // (keys of the next run computed beside the folds, gathered tokens, no separate copy pass).
 #include <cstddef>
 
@@ -98,7 +99,7 @@ __device__ __forceinline__ bool beats(float sa, int ia, float sb, int ib) {
 // rows are the rows of this workgroup's own 64-row tiles, numbered through (all rows when a unit
 // has one workgroup).
 //   0                   int [8] counters
-//   kLdsMerge           float/int [3][NW * 32] partial winners of waves that share tokens
+//   kLdsMerge           float/int [3][NW * 32] partial winners of waves that share tokens; then the block's merge gates
 //   tables(NW)          eight arrays of C words: append score s_j, winning merge score, target row, rank among
 //                       the appended tokens or -1, next token on the same row's list or -1, token that creates
 //                       new row number a (later: where a merging token has been gathered to), local rows
@@ -150,6 +151,9 @@ struct Ctx {
   __device__ int *s_slot() const { return table<int>(5); }
   __device__ int *s_own() const { return table<int>(7); }
   __device__ int *s_head() const { return table<int>(8); }
+  // the block's merge gates, while its tokens merge: where the partial winners were, if they fit there
+  __device__ bool gates_in_lds() const { return C <= 3 * NW * 32; }
+  __device__ float *s_gate() const { return (float *)(smem + kLdsMerge); }
   __device__ int *s_cnt() const { return (int *)(smem + kLdsCounters); }
   __device__ unsigned char *s_merge() const { return smem + kLdsMerge; }
 };
@@ -580,53 +584,137 @@ __device__ __forceinline__ void settle_ties(const Dev &dv, const Ctx<NW> &cx, in
 // the taken ones, in position order, is the new row it creates.  Every wave finds the n_app-th smallest
 // score for itself, bit by bit from the top, counting with ballots over scores it holds in registers (no
 // barriers, no table: comparing every token with every other one through LDS took 7 us for 256 tokens,
-// this takes 1.5).
+// this takes 1.5).  A few (a growing state appends at most folds, some four rows) are taken one by one, the smallest that is left
+// each time, some 130 cycles, where the bits take 3.9 us: 65536 tokens, growing state, 32 units 6.34 -> 6.03 ms.
+// (Up to 12 of 256 tokens, 32 of 512: with 32 of 256 a call of 8 x 32 heads, 16 or 32 rows a fold, was 1 % slower.)
 constexpr int kMaxBlock = 1024;
+constexpr int select_few(int pieces) { return pieces <= 4 ? 12 : 32; }
+// Minimum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
+  auto mn = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+  x = mn(x, (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true));
+  x = mn(x, (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true));
+  x = mn(x, (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true));
+  x = mn(x, (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true));
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = mn(r[0], r[1]);
+  const auto t = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return mn(t[0], t[1]);
+}
+// A score's bits made monotonic as an unsigned number.
+__device__ __forceinline__ uint32_t score_key(float s) {
+  uint32_t f = __float_as_uint(s);
+  f = f == 0x80000000u ? 0u : f;   // -0 and +0 are one score
+  return (f & 0x80000000u) ? ~f : (f | 0x80000000u);
+}
 template <int NW, int kQ>   // kQ: 64-token pieces, at least C / 64
 __device__ __forceinline__ void select_tokens(const Ctx<NW> &cx, int m, int n_app) {
   const int C = cx.C, lane = cx.lane;
-  uint32_t key[kQ];   // the float's bits made monotonic as an unsigned number; the largest number beyond the block
+  uint32_t key[kQ];   // (the largest number beyond the block)
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
     key[q] = 0xffffffffu;
     if (64 * q < C) {
-      uint32_t f = __float_as_uint(cx.s_app()[64 * q + lane]);
-      f = f == 0x80000000u ? 0u : f;   // -0 and +0 are one score
-      key[q] = (f & 0x80000000u) ? ~f : (f | 0x80000000u);
+      key[q] = score_key(cx.s_app()[64 * q + lane]);
     }
   }
-  uint32_t T = 0;   // largest number that fewer than n_app scores lie below: the n_app-th smallest score
+  unsigned long long taken[kQ];   // tokens taken, by piece
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) taken[q] = 0ull;
+  if (n_app <= select_few(kQ)) {
 #pragma unroll 1
-  for (int bit = 30; bit >= 0; bit -= 2) {   // two bits at a time
-    const uint32_t c1 = T | (1u << bit), c2 = T | (2u << bit), c3 = T | (3u << bit);
-    int n1 = 0, n2 = 0, n3 = 0;
+    for (int a = 0; a < n_app; ++a) {
+      uint32_t least = key[0];
+#pragma unroll
+      for (int q = 1; q < kQ; ++q) least = key[q] < least ? key[q] : least;
+      least = wave_min_u32(least);
+      bool found = false;
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {   // the earliest of those with this score
+        const unsigned long long eq = __builtin_amdgcn_ballot_w64(key[q] == least) & ~taken[q];
+        if (!found && eq != 0 && 64 * q < C) {
+          found = true;
+          const unsigned long long bit = eq & (0ull - eq);
+          taken[q] |= bit;
+          key[q] = (bit >> lane) & 1ull ? 0xffffffffu : key[q];
+        }
+      }
+    }
+  } else {
+    uint32_t T = 0;   // largest number that fewer than n_app scores lie below: the n_app-th smallest score
+#pragma unroll 1
+    for (int bit = 30; bit >= 0; bit -= 2) {   // two bits at a time
+      const uint32_t c1 = T | (1u << bit), c2 = T | (2u << bit), c3 = T | (3u << bit);
+      int n1 = 0, n2 = 0, n3 = 0;
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        n1 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c1));
+        n2 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c2));
+        n3 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c3));
+      }
+      T = n3 < n_app ? c3 : n2 < n_app ? c2 : n1 < n_app ? c1 : T;
+    }
+    int equal = n_app;   // how many of the scores equal to it are taken: the earliest
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) equal -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < T));
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-      n1 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c1));
-      n2 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c2));
-      n3 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < c3));
+      unsigned long long eq = __builtin_amdgcn_ballot_w64(key[q] == T);
+      while (__builtin_popcountll(eq) > equal) eq &= ~(1ull << (63 - __builtin_clzll(eq)));
+      equal -= __builtin_popcountll(eq);
+      taken[q] = __builtin_amdgcn_ballot_w64(key[q] < T) | eq;
     }
-    T = n3 < n_app ? c3 : n2 < n_app ? c2 : n1 < n_app ? c1 : T;
   }
-  int equal = n_app;   // how many of the scores equal to it are taken: the earliest
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) equal -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[q] < T));
   int base = 0;
 #pragma unroll
   for (int q = 0; q < kQ; ++q) {
-    unsigned long long eq = __builtin_amdgcn_ballot_w64(key[q] == T);
-    while (__builtin_popcountll(eq) > equal) eq &= ~(1ull << (63 - __builtin_clzll(eq)));
-    equal -= __builtin_popcountll(eq);
-    const unsigned long long taken = __builtin_amdgcn_ballot_w64(key[q] < T) | eq;
     if (q % NW == cx.wave) {   // a wave per 64 tokens writes what they all know
       const int j = 64 * q + lane;
-      if ((taken >> lane) & 1ull) {
-        const int a = base + __builtin_popcountll(taken & ((1ull << lane) - 1ull));
+      if ((taken[q] >> lane) & 1ull) {
+        const int a = base + __builtin_popcountll(taken[q] & ((1ull << lane) - 1ull));
         cx.s_rank()[j] = a;
         cx.s_pi()[j] = m + a;
         cx.s_best()[j] = __uint_as_float(0x7fc00000u);
         cx.s_creator()[a] = j;
       }
+    }
+    base += __builtin_popcountll(taken[q]);
+  }
+  __syncthreads();
+}
+
+// The same for blocks of more than 512 tokens, whose scores stay in LDS: a loop instead of registers, for the rare block that is
+// so long (sixteen pieces in registers made the whole kernel's code slower: 8 x 32 heads, 8192 tokens 4.51 -> 4.60 ms).
+template <int NW>
+__device__ __forceinline__ void select_long(const Ctx<NW> &cx, int m, int n_app) {
+  const int pieces = cx.C / 64, lane = cx.lane;
+  uint32_t T = 0;   // as above
+#pragma unroll 1
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = T | (1u << bit);
+    int n = 0;
+#pragma unroll 1
+    for (int q = 0; q < pieces; ++q) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(score_key(cx.s_app()[64 * q + lane]) < c));
+    T = n < n_app ? c : T;
+  }
+  int equal = n_app;
+#pragma unroll 1
+  for (int q = 0; q < pieces; ++q) equal -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(score_key(cx.s_app()[64 * q + lane]) < T));
+  int base = 0;
+#pragma unroll 1
+  for (int q = 0; q < pieces; ++q) {
+    const int j = 64 * q + lane;
+    const uint32_t k = score_key(cx.s_app()[j]);
+    unsigned long long eq = __builtin_amdgcn_ballot_w64(k == T);
+    while (__builtin_popcountll(eq) > equal) eq &= ~(1ull << (63 - __builtin_clzll(eq)));
+    equal -= __builtin_popcountll(eq);
+    const unsigned long long taken = __builtin_amdgcn_ballot_w64(k < T) | eq;
+    if (q % NW == cx.wave && ((taken >> lane) & 1ull)) {
+      const int a = base + __builtin_popcountll(taken & ((1ull << lane) - 1ull));
+      cx.s_rank()[j] = a;
+      cx.s_pi()[j] = m + a;
+      cx.s_best()[j] = __uint_as_float(0x7fc00000u);
+      cx.s_creator()[a] = j;
     }
     base += __builtin_popcountll(taken);
   }
@@ -853,6 +941,12 @@ __device__ __forceinline__ void build_lists(const Dev &dv, const Ctx<NW> &cx) {
 // several tokens is a chain of memory round trips.)
 template <int NW>
 __device__ __forceinline__ void gather_tokens(const Ctx<NW> &cx, const Block &blk) {
+  if (blk.gsrc && cx.gates_in_lds()) {   // the gates of the whole block, 64 per instruction (taken where they are used, each was a round trip)
+    const uint32_t gates = lds_addr_of(cx.s_gate());
+    for (int j0 = 64 * cx.wave; j0 < cx.C; j0 += 64 * NW) {   // (C is a multiple of 64)
+      dma4_from(blk.gsrc + (int64_t)(j0 + cx.lane) * blk.g_t, gates + 4u * (uint32_t)j0);
+    }
+  }
   int n = cx.s_cnt()[kCntOwn];
   n = n < cx.gather ? n : cx.gather;
   const int c16 = cx.lane & 15;
@@ -899,16 +993,18 @@ __device__ __forceinline__ void merge_rows(const Dev &dv, const Ctx<NW> &cx, con
       w = dv.w[ro];
       n = dv.n[ro];
     }
+    // lane i of the group keeps the i-th token of the list (any order)
+    int mine = kNoRow, len = 0;
+    if (on) {
+      for (int t = cx.s_head()[lr]; t >= 0 && len <= kListMax; t = next[t], ++len)
+        if (len == c16) mine = t;
+    }
     if (!landed) {   // the gathered tokens are there, every wave's share of them
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
       landed = true;
     }
     if (!on) break;
-    // lane i of the group keeps the i-th token of the list (any order)
-    int mine = kNoRow, len = 0;
-    for (int t = cx.s_head()[lr]; t >= 0 && len <= kListMax; t = next[t], ++len)
-      if (len == c16) mine = t;
     // The row's tokens in ascending position: from the lanes' tokens, or, when a list is longer than
     // the lanes (many tokens on one row), from the block's targets, 16 positions at a time.
     auto after = [&](int t) {
@@ -923,7 +1019,7 @@ __device__ __forceinline__ void merge_rows(const Dev &dv, const Ctx<NW> &cx, con
     for (int t = after(-1); t != kNoRow; t = after(t)) {
       const int slot = cx.s_slot()[t];
       float gt = 1.f, kf[8], vf[8];
-      if (blk.gsrc) gt = blk.gsrc[(int64_t)t * blk.g_t];
+      if (blk.gsrc) gt = cx.gates_in_lds() ? cx.s_gate()[t] : blk.gsrc[(int64_t)t * blk.g_t];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         if (slot < cx.gather) {
@@ -1158,24 +1254,29 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
       }
       if (begin && cx.resident && si > 0) copy_previous();
       if (!live) return;
-      begin = false;
-      __syncthreads();
+      // (nothing waits for a barrier between a wave's own winners and its reading of the others': each entry is waited
+      // for by itself)
+      const bool meet_now = a0 < 0 && cx.split > 1;
+      if (!meet_now) __syncthreads();
       FOLD_STAMP();
+      if (meet_now) {
+        const FoldKernelArgs &a = args_now();
+        const Ctx<NW> c = phase(cx);
+        const uint32_t xnum = a.run.s[si].xnum;
+        exchange_winners<NW>(a.dv, c, exchange_table(a.dv, a.run) + (((size_t)c.u * 2 + (xnum & 1u)) * c.split) * 2 * c.C,
+                             xnum & 0xffffu);
+        __syncthreads();
+      }
+      begin = false;
       if (a0 < 0) {
-        if (cx.split > 1) {
-          const FoldKernelArgs &a = args_now();
-          const Ctx<NW> c = phase(cx);
-          const uint32_t xnum = a.run.s[si].xnum;
-          exchange_winners<NW>(a.dv, c, exchange_table(a.dv, a.run) + (((size_t)c.u * 2 + (xnum & 1u)) * c.split) * 2 * c.C,
-                               xnum & 0xffffu);
-          __syncthreads();
-        }
         FOLD_STAMP();
         if (n_app > 0) {
           if (cx.C <= 256)
             select_tokens<NW, 4>(phase(cx), m, n_app);
+          else if (cx.C <= 512)
+            select_tokens<NW, 8>(phase(cx), m, n_app);
           else
-            select_tokens<NW, kMaxBlock / 64>(phase(cx), m, n_app);
+            select_long<NW>(phase(cx), m, n_app);
           FOLD_STAMP();
         }
       }
@@ -1218,9 +1319,16 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
           reinterpret_cast<float2 *>(a.run.trace_score)[trace * a.run.trace_stride + base + j] = sc;
       }
     }
-    // the next fold of the run reads what this one wrote (this workgroup's own stores)
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    // The next fold of the run reads what this one wrote, this workgroup's own stores: with resident tiles behind
+    // barriers of its own that wait for them, so that this one is for LDS alone.
+    if (cx.resident) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    } else {
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }
   }
 }
 

@@ -149,6 +149,17 @@ __device__ __forceinline__ void dma16_from(const void *p, uint32_t lds_addr) {
       : "v"(p), "s"(lds_addr)
       : "memory", "m0");
 }
+// And with four bytes per lane: lane i's word lands at lds_addr + 4 * i.
+__device__ __forceinline__ void dma4_from(const void *p, uint32_t lds_addr) {
+  lds_addr = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_addr);
+  asm volatile(
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %0, off"
+      :
+      : "v"(p), "s"(lds_addr)
+      : "memory", "m0");
+}
 // Four such loads from one scalar base into four consecutive 1-KiB pieces of LDS: M0 is written
 // once, load n carries the immediate 1024 * n, which the hardware adds to the LDS address and to
 // the global address alike.  One instruction sequence, so nothing can come between the write of

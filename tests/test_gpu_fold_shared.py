@@ -278,3 +278,28 @@ def test_long_blocks_on_either_side_of_the_rule(chunk, units, heads, blocks, pat
     got = run(w, {})
     assert got[0].fold_path == path
     same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
+
+
+@pytest.mark.parametrize("chunk,steps", [(128, (12, 13, 1, 0, 40)), (256, (11, 12, 13)), (512, (32, 33, 1, 100)), (1024, (5, 33, 300))])
+def test_selection_forms_agree_with_a_kernel_per_step(chunk, steps):
+    """Appends on either side of the lines between the forms of the selection (one by one, bit by bit in registers, from
+    LDS), every block holding its first half twice, so that scores are equal and the earliest of them have to be taken."""
+    pkg, b, sy = kit()
+    rows = [chunk, chunk]
+    for n in steps:
+        rows.append(rows[-1] + n)
+    w = make(sy, chunk, 3, chunk * len(rows), tuple(rows))
+    q, k, v = sy.make_qkv(w, DEV)
+    for c in range(len(rows)):
+        k[:, c * chunk + chunk // 2:(c + 1) * chunk] = k[:, c * chunk:c * chunk + chunk // 2]
+    p = sy.make_params(w, DEV, plain=False)
+    res = []
+    for knobs in (widest(w), {b.KVM_DEBUG_FOLD_PATH: 2}):
+        st = pkg.state_for(w, device=DEV, **p)
+        for knob, value in knobs.items():
+            st.debug_set(knob, value)
+        assign, _ = st.trace(len(rows))
+        st.prefill(q, k, v, p["gate"])
+        torch.cuda.synchronize()
+        res.append((st, assign[:st.folds].clone(), st.export()))
+    same(*res)
