@@ -261,9 +261,10 @@ __global__ __launch_bounds__(64 * kUnfoldWaves) void bwd_unfold_kernel(Bwd a, in
   block_param_add<D, kUnfoldWaves>(a, h, dga_sum, dbe_sum, red);
 }
 
-// Readout of the visited version: rows [0, m) of every unit, as the forward computes it.
+// Rows [0, m) of the last version, ahead of the walk: the sums as the forward left them, the readout as it computes it, and
+// adjoints of zero (rows beyond are never looked at).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_readout_kernel(Bwd a, int m) {
+__global__ __launch_bounds__(256) void bwd_begin_kernel(Bwd a, int m) {
   constexpr int CPL = D / 64;
   const Dev &dv = a.dv;
   const int lane = threadIdx.x & 63;
@@ -275,8 +276,13 @@ __global__ __launch_bounds__(256) void bwd_readout_kernel(Bwd a, int m) {
   float sv[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
-    sk[c] = a.wsK[ro + lane * CPL + c];
-    sv[c] = a.wsV[ro + lane * CPL + c];
+    const int64_t at = ro + lane * CPL + c;
+    sk[c] = dv.sK[at];
+    sv[c] = dv.sV[at];
+    a.wsK[at] = sk[c];
+    a.wsV[at] = sv[c];
+    a.dsK[at] = 0.f;
+    a.dsV[at] = 0.f;
     s += sk[c];
   }
   const double mean = wave_sum(s) / (double)D;
@@ -294,7 +300,10 @@ __global__ __launch_bounds__(256) void bwd_readout_kernel(Bwd a, int m) {
     Io<T>::store((T *)a.vhat + ro + ch, sv[c] * vs);
     a.xhat[ro + ch] = (float)((sk[c] - mean) * rden);
   }
-  if (lane == 0) a.rden[(int64_t)u * dv.Mcap + row] = (float)rden;
+  if (lane == 0) {
+    a.rden[(int64_t)u * dv.Mcap + row] = (float)rden;
+    a.drho[(int64_t)u * dv.Mcap + row] = 0.f;
+  }
 }
 
 // Adjoint of the readout into the adjoint of the sums: rows [0, m).
@@ -545,10 +554,11 @@ __global__ __launch_bounds__(256) void bwd_cast_kernel(const float *src, T *dst,
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_zero_floats_kernel(float *p, int64_t n) {
+// dgate, whose size need not be a multiple of 16 bytes, and the parameter gradients' accumulators
+__global__ __launch_bounds__(256) void bwd_zero_sums_kernel(float *dgate, int64_t n_gate, double *par64, int n_par) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.f;
+  if (i < n_gate) dgate[i] = 0.f;
+  if (i < n_par) par64[i] = 0.0;
 }
 
 // Zero fill with a kernel of the library's own (a caller may capture the call in a graph, where
@@ -610,30 +620,21 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
   // of a launch; until then only what the token got when its fold was undone is kept, for the
   // blocks of one window.  Elsewhere dk, dv are summed in full-size fp32 accumulators.
   a.ring_rows = on_mfma ? dv.L + dv.C : 0;
-  const int64_t state_elems = (int64_t)dv.U * dv.Mcap * D;
   const int64_t kv_elems = (int64_t)dv.B * a.T * dv.Hkv * D;
   const int64_t q_rows = (int64_t)dv.B * a.T * dv.Hq;
-  // everything that is accumulated starts at zero; the sums start as the forward left them
-  BWD_TRY(zero_fill(a.dsK, state_elems * 4, st));
-  BWD_TRY(zero_fill(a.dsV, state_elems * 4, st));
-  BWD_TRY(zero_fill(a.drho, (size_t)dv.U * dv.Mcap * 4, st));
-  if (!on_mfma) {
-    BWD_TRY(zero_fill(a.dk_acc, kv_elems * 4, st));
-    BWD_TRY(zero_fill(a.dv_acc, kv_elems * 4, st));
+  // everything that is accumulated starts at zero; the sums start as the forward left them; the readout of the last version,
+  // of which undoing a fold then rewrites the rows it touched
+  if (!on_mfma)   // (dk and dv lie one after the other)
+    BWD_TRY(zero_fill(a.dk_acc, (size_t)((char *)a.dv_acc - (char *)a.dk_acc) + kv_elems * 4, st));
+  {
+    const int64_t n_gate = (int64_t)dv.B * a.T * dv.Hkv, n_par = 2 * (int64_t)dv.Hkv * D + 2 * dv.Hq;
+    hipLaunchKernelGGL(bwd_zero_sums_kernel, dim3((unsigned)(((n_gate > n_par ? n_gate : n_par) + 255) / 256)), dim3(256), 0, st,
+                       a.dgate, n_gate, a.par64, (int)n_par);
+    BWD_TRY(hipGetLastError());
   }
-  BWD_TRY(zero_fill(a.par64, (size_t)(2 * dv.Hkv * D + 2 * dv.Hq) * 8, st));
-  // dgate is the caller's tensor: its size need not be a multiple of 16 bytes
-  BWD_DISPATCH(dv, bwd_zero_floats_kernel, dim3((unsigned)(((int64_t)dv.B * a.T * dv.Hkv + 255) / 256)), dim3(256), st,
-               a.dgate, (int64_t)dv.B * a.T * dv.Hkv);
-  if (dv.sK) {
-    BWD_TRY(hipMemcpyAsync(a.wsK, dv.sK, state_elems * 8, hipMemcpyDeviceToDevice, st));
-    BWD_TRY(hipMemcpyAsync(a.wsV, dv.sV, state_elems * 4, hipMemcpyDeviceToDevice, st));
-  }
-
-  // the readout of the last version; undoing a fold then rewrites the rows it touched
   if (n_chunks > 0 && chunks[n_chunks - 1].m_after > 0) {
     const int m_end = chunks[n_chunks - 1].m_after;
-    BWD_DISPATCH(dv, bwd_readout_kernel, dim3((m_end + 3) / 4, dv.U), dim3(256), st, a, m_end);
+    BWD_DISPATCH(dv, bwd_begin_kernel, dim3((m_end + 3) / 4, dv.U), dim3(256), st, a, m_end);
   }
   // Matrix-core path, three streams.  The caller's carries the chain that the state imposes: undo the
   // fold, (dq,) dk and dv of the state rows.  dk and dv of the chunk's own tokens (window keys) need D and
@@ -641,11 +642,16 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
   // walk is on the other two, which is what fills the chip while a fold is undone.  The ring holds one
   // block more than a window so that the fold undone then writes another slot than they read; they
   // must be done before the fold after that.
-  const bool use_side = on_mfma && x.side && x.side2 && x.fork && x.dq_done && x.join_state && x.join_window[0] &&
+  // Where a chunk has few workgroups (kBwdOneLaunch), those of all roles are one launch on the caller's stream, behind D from a pass
+  // of its own: the events between three streams cost 8 to 16 us a chunk, twice.
+  int m_max = 0;
+  for (int i = 0; i < n_chunks; ++i) m_max = chunks[i].m > m_max ? chunks[i].m : m_max;
+  const bool one_launch = on_mfma && backward_fits_one_launch(dv, m_max);
+  const bool use_side = on_mfma && !one_launch && x.side && x.side2 && x.fork && x.dq_done && x.join_state && x.join_window[0] &&
                         x.join_window[1];
   // D = dout . out per query.  The matrix-core dq kernel forms it for its own queries, which saves a pass over
   // out and dout but puts dq ahead of the state rows in the chain.
-  const bool delta_first = !on_mfma || (use_side && delta_ahead(dv, chunks, n_chunks));
+  const bool delta_first = !on_mfma || one_launch || (use_side && delta_ahead(dv, chunks, n_chunks));
   if (delta_first && on_mfma)
     BWD_TRY(launch_delta_mfma(a, q_rows, st));   // (the order of dq's own sum: D is the same whoever forms it)
   else if (delta_first)
@@ -683,7 +689,9 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
       // the chunk's own block was folded after the last chunk that had it in its window
       const int cj = ci + dv.L / dv.C - 1;
       const bool folded = cj < n_chunks && chunks[cj].fold >= 0;
-      if (use_side && delta_first) {
+      if (one_launch) {
+        BWD_TRY(launch_backward_mfma_both(a, ch.s, ch.nq, ch.m, folded, st));
+      } else if (use_side && delta_first) {
         BWD_TRY(hipEventRecord(x.fork, st));
         BWD_TRY(hipStreamWaitEvent(x.side, x.fork, 0));
         BWD_TRY(hipStreamWaitEvent(x.side2, x.fork, 0));

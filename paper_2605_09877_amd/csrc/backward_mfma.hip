@@ -157,7 +157,7 @@ struct MfmaChunk {
 
 
 template <int kRole>
-__global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
+__device__ __forceinline__ void bwd_mfma_role(Bwd a, MfmaChunk c, int block) {   // (by reference the loops spill two registers more)
   constexpr bool kKeysSta = kRole != kRoleDQ;
   extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
   float *rowsc = reinterpret_cast<float *>(lds + 4 * kTileElems);  // [stage][lse * log2e | D][32]
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
   // (interleaved unit by unit, the last long ones would start after the first round of short ones).
   const int n_win_wg = (n_keys_win + kStaPerWg - 1) / kStaPerWg;
   const int groups8 = (dv.U + kXcds - 1) / kXcds * kXcds;
-  int wg = blockIdx.x, per_group = G * tpc;
+  int wg = block, per_group = G * tpc;
   bool section_state = false;
   if constexpr (kKeysSta) {
     section_state = c.section == kSecState || (c.section == kSecBoth && wg >= groups8 * n_win_wg);
@@ -843,6 +843,18 @@ __global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
   }
 }
 
+template <int kRole>
+__global__ __launch_bounds__(256, 2) void bwd_mfma_kernel(Bwd a, MfmaChunk c) {
+  bwd_mfma_role<kRole>(a, c, blockIdx.x);
+}
+// Both roles of a chunk in one launch, n_dq workgroups of dQ first (D is there already): see launch_backward_mfma_both.
+__global__ __launch_bounds__(256, 2) void bwd_mfma_both_kernel(Bwd a, MfmaChunk c, int n_dq) {
+  if ((int)blockIdx.x < n_dq)
+    bwd_mfma_role<kRoleDQ>(a, c, blockIdx.x);
+  else
+    bwd_mfma_role<kRoleKV>(a, c, (int)blockIdx.x - n_dq);
+}
+
 }  // namespace
 
 bool backward_on_mfma(const Dev &dv) { return dv.io == 1 && dv.d == kHeadDim && dv.C % 64 == 0; }
@@ -853,19 +865,21 @@ hipError_t launch_delta_mfma(const Bwd &a, int64_t rows, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The launches of one chunk: dq (and the temperature sums); dk and dv of its own tokens and of the state rows.
-hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
-                                hipStream_t st) {
-  const Dev &dv = a.dv;
-  static bool allowed = false;  // more than 64 KiB of LDS per workgroup has to be asked for once
-  if (!allowed) {
-    const void *kernels[2] = {(const void *)bwd_mfma_kernel<kRoleDQ>, (const void *)bwd_mfma_kernel<kRoleKV>};
+namespace {
+hipError_t allow_lds() {   // more than 64 KiB of LDS per workgroup has to be asked for once
+  static const hipError_t rc = [] {
+    const void *kernels[3] = {(const void *)bwd_mfma_kernel<kRoleDQ>, (const void *)bwd_mfma_kernel<kRoleKV>,
+                              (const void *)bwd_mfma_both_kernel};
     for (const void *k : kernels) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes);
       if (e != hipSuccess) return e;
     }
-    allowed = true;
-  }
+    return hipSuccess;
+  }();
+  return rc;
+}
+MfmaChunk chunk_of(const Bwd &a, int64_t cs, int nq, int m, bool folded, int section) {
+  const Dev &dv = a.dv;
   MfmaChunk c;
   c.cs = cs;
   c.wb = cs + dv.C - dv.L > 0 ? cs + dv.C - dv.L : 0;
@@ -877,16 +891,44 @@ hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool fo
   c.folded = folded ? 1 : 0;
   c.ring_row0 = (int)((cs / dv.C) % (a.ring_rows / dv.C)) * dv.C;
   c.section = section;
-  const int G = dv.Hq / dv.Hkv;
+  return c;
+}
+struct Grids {
+  unsigned dq, window, state;   // workgroups
+};
+Grids grids_of(const Dev &dv, int nq, int m) {
   const unsigned groups = (unsigned)((dv.U + kXcds - 1) / kXcds * kXcds);
-  const int n_win_wg = (nq + kStaPerWg - 1) / kStaPerWg, n_st_wg = (m + kStaPerWg - 1) / kStaPerWg;
+  const unsigned n_win = (unsigned)((nq + kStaPerWg - 1) / kStaPerWg), n_st = (unsigned)((m + kStaPerWg - 1) / kStaPerWg);
+  return {groups * (unsigned)(dv.Hq / dv.Hkv) * n_win, groups * n_win, groups * n_st};
+}
+}  // namespace
+
+// The launches of one chunk: dq (and the temperature sums); dk and dv of its own tokens and of the state rows.
+hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
+                                hipStream_t st) {
+  if (const hipError_t e = allow_lds(); e != hipSuccess) return e;
+  const MfmaChunk c = chunk_of(a, cs, nq, m, folded, section);
+  const Grids g = grids_of(a.dv, nq, m);
   if (role == kRoleDQ) {
-    hipLaunchKernelGGL((bwd_mfma_kernel<kRoleDQ>), dim3(groups * G * n_win_wg), dim3(256), kBwdLdsBytes, st, a, c);
+    hipLaunchKernelGGL((bwd_mfma_kernel<kRoleDQ>), dim3(g.dq), dim3(256), kBwdLdsBytes, st, a, c);
     return hipGetLastError();
   }
-  const int per_k = section == kSecBoth ? n_st_wg + n_win_wg : section == kSecState ? n_st_wg : n_win_wg;
-  if (per_k == 0) return hipSuccess;
-  hipLaunchKernelGGL((bwd_mfma_kernel<kRoleKV>), dim3(groups * per_k), dim3(256), kBwdLdsBytes, st, a, c);
+  const unsigned n = section == kSecBoth ? g.state + g.window : section == kSecState ? g.state : g.window;
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL((bwd_mfma_kernel<kRoleKV>), dim3(n), dim3(256), kBwdLdsBytes, st, a, c);
+  return hipGetLastError();
+}
+
+// All of them at once.
+bool backward_fits_one_launch(const Dev &dv, int m) {
+  const Grids g = grids_of(dv, dv.C, m);
+  return g.dq + g.window + g.state <= (dv.Hq <= 2 * dv.Hkv ? kBwdOneLaunch : kBwdOneLaunchHeads);
+}
+hipError_t launch_backward_mfma_both(const Bwd &a, int64_t cs, int nq, int m, bool folded, hipStream_t st) {
+  if (const hipError_t e = allow_lds(); e != hipSuccess) return e;
+  const Grids g = grids_of(a.dv, nq, m);
+  hipLaunchKernelGGL(bwd_mfma_both_kernel, dim3(g.dq + g.window + g.state), dim3(256), kBwdLdsBytes, st, a,
+                     chunk_of(a, cs, nq, m, folded, kSecBoth), (int)g.dq);
   return hipGetLastError();
 }
 

@@ -257,5 +257,13 @@ enum { kSecBoth = 0, kSecWindow = 1, kSecState = 2 };
 // those of the chunk's own tokens (window keys), or only those of the state rows
 hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
                                 hipStream_t st);
+// both roles in one launch, where a whole chunk's workgroups into m state rows are few enough; needs D.  Whole calls of training,
+// launches of their own on three streams / one, us (workgroups): 224 of 32 units 1050 / 801, 8 units, growing, 8465 tokens (up to 128)
+// 3990 / 2960, 12 units of 64-token chunks, 20764 tokens (120) 27300 / 17500, 512 of 96 units 2118 / 1972, 704 of 128 units 2550 / 2474;
+// with four heads per KV head: 96 of 8 units 4110 / 2750, 224 of 16 1632 / 1619, but 336 of 24 1737 / 1776, 448 of 32 1910 / 2050 (their
+// loops are long, and the kernel of both roles spills more in them).
+constexpr unsigned kBwdOneLaunch = 1024, kBwdOneLaunchHeads = 256;   // (up to two query heads per KV head; more)
+bool backward_fits_one_launch(const Dev &dv, int m);
+hipError_t launch_backward_mfma_both(const Bwd &a, int64_t cs, int nq, int m, bool folded, hipStream_t st);
 
 }  // namespace kvm

@@ -37,3 +37,22 @@ def test_gradients_do_not_depend_on_the_batch():
 
     for one, many in zip(grads(1), grads(65)):
         assert torch.equal(one[0], many[0])
+
+
+@pytest.mark.parametrize("heads,many", [((2, 2), 200), ((2, 1), 200), ((4, 1), 70), ((4, 1), 24)])
+@pytest.mark.parametrize("C,rows", [(64, 70), (256, 256)])
+def test_gradients_of_one_launch_and_of_several(heads, many, C, rows):
+    """A sequence alone, whose chunks are one launch each, and the same one among so many that they are not: the same
+    gradients to the bit."""
+    import paper_2605_09877_amd as kvm
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    mk = lambda h: torch.randn(many, C * 3 + 33, h, 128, generator=gen, device="cuda:0").bfloat16()
+    q, k, v, dout = mk(heads[0]), mk(heads[1]), mk(heads[1]), mk(heads[0])
+
+    def grads(n):
+        leaves = [x[:n].contiguous().requires_grad_(True) for x in (q, k, v)]
+        out = kvm.kvm_attention(*leaves, chunk_len=C, rope_dims=32, budget_fixed=rows)
+        return (out.detach(),) + torch.autograd.grad(out, leaves, dout[:n].contiguous())
+
+    for one, all_ in zip(grads(1), grads(many)):
+        assert torch.equal(one[0], all_[0])
