@@ -155,7 +155,8 @@ int kvm_decode_step(kvm_state *st, const void *q, const void *k, const void *v,
  *   q, out: [sum of batches, H_q, d]; k, v: [sum, H_kv, d]; gate: [sum, H_kv] or NULL; rows in
  *   the order of `states`, each state's sequences together.
  *   workspace: device memory, 16-byte aligned, kvm_decode_multi_workspace_bytes(sum of batches)
- *   bytes, owned by the caller; rewritten by every call (stream-ordered).
+ *   bytes, owned by the caller; rewritten by every call over more than 64 states (stream-ordered;
+ *   what is needed of fewer goes along with the launch).
  * KVM_ERR_CAPACITY (nothing enqueued) if any state's fold would exceed its buffer; KVM_ERR_ARG on
  * mismatched configurations. */
 size_t kvm_decode_multi_workspace_bytes(int64_t n_sequences);
@@ -168,11 +169,11 @@ int kvm_decode_step_multi(kvm_state *const *states, int32_t n_states, const void
  * workspace, same effect, same results to the bit (the same attention and fold kernels run).  The
  * per-sequence descriptor table lives in a device array inside the library, fixed at
  * KVM_STATIC_MAX_SEQUENCES sequences per call (about 224 KiB on every GPU the library runs on,
- * held until the process ends); it is filled by a small kernel from values passed as kernel
- * arguments, so the call makes no hipMalloc / hipFree, no host-to-device copy and no host heap
+ * held until the process ends); for more than 64 states it is filled by a small kernel from values passed as kernel
+ * arguments (what is needed of fewer goes along with the launch itself), so the call makes no hipMalloc / hipFree, no host-to-device copy and no host heap
  * allocation (with kvm_state_profile off).  More sequences than the maximum: KVM_ERR_LIMIT,
  * nothing enqueued (kvm_last_hip_error() says how many were asked for).  The table is rewritten
- * by every call: calls on one GPU must be ordered (one stream, or events); calls that overlap on
+ * by every call over more than 64 states: such calls on one GPU must be ordered (one stream, or events); calls that overlap on
  * one GPU race on it. */
 #define KVM_STATIC_MAX_SEQUENCES 4096
 int kvm_decode_step_multi_static(kvm_state *const *states, int32_t n_states, const void *q, const void *k,

@@ -404,6 +404,8 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 //   64,     64,   128      224 / 162      255 / 167      238 / 158      286 / 156      339 / 254
 //  128,    256,  1024      356 / 310      494 / 411      598 / 492      699 / 589     1125 / 906
 // (4 units: 256, 1024: 126 / 134 at 5 blocks, 175 / 160 at 8; 128, 256: 147 / 145 and 212 / 203 at 8 and 12.)
+// (Measured with runs of four folds and no room kept for them beside attention; the shared side has since gained, the most,
+// a fifth, in calls of many blocks.)
 // Blocks of more than 256 and up to 512 tokens, of which a kernel per step makes fewer launches per token: from 12 blocks on, 8
 // from 64 units on, and up to two query heads per KV head (with four, attention is the longer part).  Growing state: 10 units, 2 heads each,
 // 31 blocks 1630 / 1208, 12 units, 38 blocks 2631 / 2086, 16 units, 16 blocks 688 / 588; fixed: 8 units, 1000 rows, 38 blocks 1049 / 932,
