@@ -175,16 +175,18 @@ int most_split(int64_t U, int64_t Mcap, int cus) {
 }
 
 // States whose folds may be shared among workgroups (fold_split, below).
-constexpr int kFusedMinUnits = 256, kShareMinUnits = 8, kShareMaxBlock = 512, kShareLongBlock = 256, kShareAlone = 8192,
+constexpr int kFusedMinUnits = 256, kShareFewUnits = 8, kShareMaxBlock = 512, kShareLongBlock = 256, kShareAlone = 8192,
               kShareAnyRows = 1024;
 bool may_share(const kvm_config &c) {
   const int64_t U = (int64_t)c.batch * c.n_kv_heads;
-  return use_mfma(c) && U >= kShareMinUnits && U < kFusedMinUnits && c.chunk_len <= kShareMaxBlock;
+  return use_mfma(c) && U < kFusedMinUnits && c.chunk_len <= (U < kShareFewUnits ? kShareLongBlock : kShareMaxBlock);
 }
 // Folds of a run: a group's where they run beside attention (attention_beside), half of one elsewhere.  Blocks whose memory
-// keys the scratch holds: two runs'.
+// keys the scratch holds: two runs' (of fewer than 8 units half as many in either case).
 constexpr int kFoldRunApart = 4;
-int key_blocks(const kvm_config &c) { return may_share(c) ? 2 * kvm::kFoldMaxSteps : 2 * kFoldRunApart; }
+int key_blocks(const kvm_config &c) {
+  return may_share(c) && (int64_t)c.batch * c.n_kv_heads >= kShareFewUnits ? 2 * kvm::kFoldMaxSteps : 2 * kFoldRunApart;
+}
 
 Layout layout_of(const kvm_config &c, int64_t Mcap) {
   const size_t U = (size_t)c.batch * c.n_kv_heads, d = c.head_dim, C = c.chunk_len;
@@ -394,8 +396,8 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 // 256-token blocks: 8.4 ms for 65536 tokens against 10.6 with a kernel per step).  Otherwise a fold
 // is a kernel per step: with tiles that stream the shared launch lost (64 units of 1024 rows, 4
 // workgroups each: 13 ms for 32768 tokens against 10.9); so it is when kvm_debug_set asks for it.
-// Sharing is for states of 8 units and more, and, in blocks of up to 256 tokens, calls of 7 blocks and more, of 5 from 64 units
-// on, or any into a state of 1024 rows and more.  Us per call, a kernel per step / shared, by blocks of the call:
+// Sharing is, in blocks of up to 256 tokens, for calls of 7 blocks and more, of 5 from 64 units
+// on, or any into a state of 1024 rows and more.  (Fewer than 8 units: below.)  Us per call, a kernel per step / shared, by blocks of the call:
 //   units, block, rows     5              6              7              8              12
 //    8,    128,   256      109 / 122      121 / 126      138 / 134      152 / 147      223 / 208
 //    8,    256,  1024      129 / 139      144 / 145      165 / 155      185 / 165      287 / 236
@@ -403,7 +405,6 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 //   32,    256,   512      152 / 151      176 / 157      201 / 172      226 / 186      340 / 265
 //   64,     64,   128      224 / 162      255 / 167      238 / 158      286 / 156      339 / 254
 //  128,    256,  1024      356 / 310      494 / 411      598 / 492      699 / 589     1125 / 906
-// (4 units: 256, 1024: 126 / 134 at 5 blocks, 175 / 160 at 8; 128, 256: 147 / 145 and 212 / 203 at 8 and 12.)
 // (Measured with runs of four folds and no room kept for them beside attention; the shared side has since gained, the most,
 // a fifth, in calls of many blocks.)
 // Blocks of more than 256 and up to 512 tokens, of which a kernel per step makes fewer launches per token: from 12 blocks on, 8
@@ -411,6 +412,13 @@ Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
 // 31 blocks 1630 / 1208, 12 units, 38 blocks 2631 / 2086, 16 units, 16 blocks 688 / 588; fixed: 8 units, 1000 rows, 38 blocks 1049 / 932,
 // 64 units, 512 rows, 8 blocks 521 / 488.  But 8 units, 8 blocks, 512 rows 200 / 210, 1000 rows 256 / 296, 32 units, 1000 rows, 10 blocks
 // 494 / 508; four heads each: 8 units, 600 rows, 16 blocks 523 / 556, 64 units 2075 / 2110.
+// Fewer than 8 units, of which a kernel per step keeps a few compute units busy: blocks of up to 256 tokens, calls of 32 blocks and more
+// into a state with room for 256 rows, of 20 with room for 512 (runs of four: the scratch holds no more keys).  Us per call, a kernel per
+// step / shared: 32 blocks of 256, 200 rows: 2 units 556 / 556, 4 units 585 / 565, with 8 heads each 642 / 602; 20 of 256, 512 rows: 2 units 382 / 359,
+// 4 units 395 / 366; 20 of 64, 520 rows, 4 units 360 / 310; 20 of 128, 1000 rows, one unit 396 / 330.  Growing: 32 of 256, up to 362 rows, 2 units
+// 845 / 680; 20 of 256, up to 1150 rows, 2 units 835 / 555; 78 of 256, 4 units of two heads 4050 / 2127.  But 32 of 64, 128 rows: one
+// unit 450 / 481, 4 units 469 / 491.
+// Longer blocks lost with fixed rows: 512 tokens, 512 rows, 24 blocks, 2 units 532 / 557, 4 units 552 / 560.
 // A fold by itself (decode, the fold entry point, chunk by chunk) is shared from units x block = 8192 or 1024 rows on.  Us
 // alone: 8 units of 128-token blocks on 256 rows 45 / 48, 16 of 256 on 256 47 / 49, 32 of 128 on 512 48 / 48; 32 of 256
 // on 512 52 / 49, 64 of 128 on 512 50 / 49, 128 of 256 on 512 75 / 70, 128 of 64 on 256 50 / 50; 8 of 128 on 768, 1024,
@@ -440,11 +448,14 @@ int fold_split(const kvm_state *st, int64_t blocks) {
   auto can_share = [&](int n) { return n > 1 && n <= most && kvm::fold_fused_fits(st->dv, n); };
   if (forced != 0) return (forced == 2 || forced == 4 || forced == 8 || forced == 16) && can_share(forced) ? forced : whole;
   if (path == 1 || U >= kFusedMinUnits) return whole;
-  if (U < kShareMinUnits || C > kShareMaxBlock) return 0;
-  if (C > kShareLongBlock) {
+  if (!may_share(st->cfg)) return 0;
+  if (U < kShareFewUnits) {
+    if (st->dv.Mcap < 256 || blocks < (st->dv.Mcap >= 512 ? 20 : 32)) return 0;
+  } else if (C > kShareLongBlock) {
     if (blocks < (U < 64 ? 12 : 8) || st->dv.Hq > 2 * st->dv.Hkv) return 0;
-  } else
-  if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) return 0;
+  } else if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) {
+    return 0;
+  }
   return can_share(most) && kvm::fold_fused_resident(st->dv, most, true) ? most : 0;
 }
 // Whether work put on `stream` goes into a graph.  (The query fails for the legacy stream while another thread captures:
@@ -1176,7 +1187,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       // keys are computed by one launch (blocks taken from the ring go one at a time)
       const int64_t lo0 = plan[next_fold].s + C - L;
       int run = 1;
-      const int run_cap = beside ? kvm::kFoldMaxSteps : fused_folds ? kFoldRunApart : G;
+      const int run_cap = beside ? key_blocks(c) / 2 : fused_folds ? kFoldRunApart : G;
       if (lo0 >= t0)
         while (run < run_cap && next_fold + run <= last_chunk && next_fold + run < n_chunks &&
                plan[next_fold + run].folds)

@@ -280,6 +280,20 @@ def test_long_blocks_on_either_side_of_the_rule(chunk, units, heads, blocks, pat
     same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
 
 
+@pytest.mark.parametrize("chunk,units,heads,blocks,budget,path", [
+    (64, 1, 1, 32, 256, 1), (64, 7, 7, 31, 256, 2), (64, 4, 4, 32, 192, 2), (128, 2, 8, 20, 512, 1), (128, 2, 8, 19, 512, 2), (256, 4, 4, 20, 448, 2),
+    (256, 3, 6, 32, None, 1), (64, 5, 5, 32, (64, 64, 65, 130, 190, 254, 300) + (300,) * 25, 1), (512, 4, 4, 32, 512, 2),
+])
+def test_few_units_on_either_side_of_the_rule(chunk, units, heads, blocks, budget, path):
+    """Fewer than 8 units by the library's own choice, with two decoded tokens behind the prompt, against a kernel per step."""
+    _, b, sy = kit()
+    w = make(sy, chunk, units, chunk * blocks, budget)
+    w = sy.shrink(w, n_q_heads=heads)
+    got = run(w, {}, 2)
+    assert got[0].fold_path == path
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}, 2))
+
+
 @pytest.mark.parametrize("chunk,steps", [(128, (12, 13, 1, 0, 40)), (256, (11, 12, 13)), (512, (32, 33, 1, 100)), (1024, (5, 33, 300))])
 def test_selection_forms_agree_with_a_kernel_per_step(chunk, steps):
     """Appends on either side of the lines between the forms of the selection (one by one, bit by bit in registers, from
