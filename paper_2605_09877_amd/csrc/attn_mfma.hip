@@ -1089,8 +1089,9 @@ static unsigned tile_workgroups(const Dev &dv, const AttnArgs &a, unsigned *of_3
 }
 
 bool attention_takes_scores(const Dev &dv, const AttnArgs &a) {
+  if (!attention_on_mfma(dv)) return attn_rows_score_workgroups(dv, a) <= kMostWorkgroups;
   unsigned of_32;
-  return !attention_on_mfma(dv) || (dv.d == 64 && tile_workgroups(dv, a, &of_32) <= kSplitMost);
+  return dv.d == 64 && tile_workgroups(dv, a, &of_32) <= kSplitMost;
 }
 
 hipError_t launch_attn_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st) {

@@ -487,8 +487,11 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
+int64_t attn_rows_score_workgroups(const Dev &dv, const AttnArgs &a) {
+  return (int64_t)a.nq_total * dv.Hq * dv.B + (int64_t)(dv.C + 3) / 4 * dv.U;
+}
 hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st) {
-  const dim3 grid((unsigned)((int64_t)a.nq_total * dv.Hq * dv.B + (int64_t)(dv.C + 3) / 4 * dv.U));
+  const dim3 grid((unsigned)attn_rows_score_workgroups(dv, a));
   // (a state of up to 64 rows has one for each lane: 223 us for the first of the calls above with a second one asked for, 211 now)
 #define KVM_ROWS_SCORE(T, D)                                                                                 \
   do {                                                                                                       \

@@ -1051,6 +1051,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     const double similarity = (double)C * (double)m_max * (double)d * (double)es;
     AttnArgs one;
     one.n_chunks = 1;
+    one.nq_total = (int32_t)C;
     const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one) && (dv.U > 1 || similarity <= 240.0e6)));
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.

@@ -25,3 +25,24 @@ def test_prefill_against_the_oracle(io, d, C, rows, blocks, tail, heads, split, 
                   seq=C * blocks + tail, chunk_len=C, budget_fixed=rows)
     run_prefill_case(w, plain=False, split=split, units=[(0, 0), (batch - 1, heads[1] - 1)],
                      case=f"chunk_by_chunk[{io},{d},{C},{rows},{batch}]")
+
+
+@pytest.mark.parametrize("batch", [4064, 4096])
+def test_more_workgroups_than_a_dimension_holds(batch):
+    """64 heads x 64 queries x 4096 sequences are 2^24 attention workgroups: with those of the scores beside them (4064: just
+    below, 4096: above) more than one dimension of a launch takes.  Every sequence has the inputs, and so the bits, of
+    one alone."""
+    import torch
+    import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import synth as sy
+    w1 = sy.shrink(sy.WORKLOADS["tiny_f32"], batch=1, n_q_heads=64, n_kv_heads=1, seq=128, n_bswa_chunks=1)
+    qkv = sy.make_qkv(w1, "cuda:0")
+    res = []
+    for n in (1, batch):
+        st = pkg.state_for(sy.shrink(w1, batch=n), device="cuda:0")
+        out = st.prefill(*(x.expand(n, -1, -1, -1) for x in qkv))
+        state = st.export()
+        assert st.folds == 2 and st.rows == 64
+        res.append((out, *(state[key] for key in ("sK", "sV", "n", "khat", "vhat"))))
+    for one, many in zip(*res):
+        assert bool((many == one).all())
