@@ -155,8 +155,8 @@ int kvm_decode_step(kvm_state *st, const void *q, const void *k, const void *v,
  *   q, out: [sum of batches, H_q, d]; k, v: [sum, H_kv, d]; gate: [sum, H_kv] or NULL; rows in
  *   the order of `states`, each state's sequences together.
  *   workspace: device memory, 16-byte aligned, kvm_decode_multi_workspace_bytes(sum of batches)
- *   bytes, owned by the caller; rewritten by every call over more than 64 states (stream-ordered;
- *   what is needed of fewer goes along with the launch).
+ *   bytes, owned by the caller; rewritten by every call over more than 64 states (stream-ordered, so such calls
+ *   that may overlap need one each; what is needed of fewer goes along with the launch).
  * KVM_ERR_CAPACITY (nothing enqueued) if any state's fold would exceed its buffer; KVM_ERR_ARG on
  * mismatched configurations. */
 size_t kvm_decode_multi_workspace_bytes(int64_t n_sequences);

@@ -525,7 +525,20 @@ class KVMState:
                                              _stream()), "kvm_state_import")
 
 
-_multi_workspace: dict = {}
+_PACKED_STATES = 64           # states up to which kvm_decode_step_multi writes nothing into its workspace
+_unwritten: dict = {}         # by device: a workspace for those calls
+
+
+def _multi_workspace(device: torch.device, nbytes: int, n_states: int) -> torch.Tensor:
+    """The workspace of one decode_multi call.  More than 64 states: a table that the call writes and its kernels read, so
+    every call has one of its own, freed in stream order (calls on other streams and threads would write over a table
+    that is kept while it is read).  Fewer: memory that is passed and never touched."""
+    if n_states > _PACKED_STATES:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    ws = _unwritten.get(device)
+    if ws is None or ws.numel() < nbytes:
+        ws = _unwritten[device] = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return ws
 
 
 def decode_multi(states, q, k, v, gate=None, out=None):
@@ -544,9 +557,7 @@ def decode_multi(states, q, k, v, gate=None, out=None):
         out = torch.empty_like(q)
     first._chk(out, q.shape, first.dtype, "out")
     nbytes = first.lib.kvm_decode_multi_workspace_bytes(n)
-    ws = _multi_workspace.get((str(first.device), nbytes))
-    if ws is None:
-        ws = _multi_workspace[(str(first.device), nbytes)] = torch.empty(nbytes, dtype=torch.uint8, device=first.device)
+    ws = _multi_workspace(first.device, nbytes, len(states))
     handles = (C.c_void_p * len(states))(*[st.handle for st in states])
     with _on_device(first.device):
         _check(first.lib.kvm_decode_step_multi(handles, len(states), q.data_ptr(), k.data_ptr(), v.data_ptr(),

@@ -114,3 +114,40 @@ def test_ragged_decode_rejects_mismatched_states():
         binding.decode_multi([s1, s2], q, q.clone(), q.clone())
     with pytest.raises(binding.KVMError):
         binding.decode_multi([s1, s1], q, q.clone(), q.clone())
+
+
+def test_batches_of_many_states_on_two_streams():
+    """Two batches of 65 states, each on a stream of its own with nothing between the streams, calls in turn: outputs of
+    the same calls one after the other, to the bit."""
+    pkg, sy = kvm(), synth()
+    from paper_2605_09877_amd import binding
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=1, n_q_heads=4, n_kv_heads=2, chunk_len=64, seq=64 * 4, budget_fixed=100)
+    n, steps = 65, 40
+    data = [sy.make_qkv(sy.shrink(w, batch=n), DEV, seed_offset=i) for i in range(2)]
+
+    def batches():
+        res = []
+        for i, (q, k, v) in enumerate(data):
+            states = [pkg.state_for(w, device=DEV) for _ in range(n)]
+            for j, st in enumerate(states):
+                Tp = 64 * (1 + (i + j) % 3)
+                st.prefill(*(x[j:j + 1, :Tp].contiguous() for x in (q, k, v)))
+            res.append(states)
+        torch.cuda.synchronize()
+        return res
+
+    tokens = [[[x[:, 200 + t].contiguous() for x in qkv] for qkv in data] for t in range(steps)]
+    one = batches()
+    want = [[binding.decode_multi(one[i], *tokens[t][i]) for i in range(2)] for t in range(steps)]
+    torch.cuda.synchronize()
+    two, streams = batches(), [torch.cuda.Stream() for _ in range(2)]
+    got = []
+    for t in range(steps):
+        row = []
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                row.append(binding.decode_multi(two[i], *tokens[t][i]))
+        got.append(row)
+    torch.cuda.synchronize()
+    for a, b in zip(want, got):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
