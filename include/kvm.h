@@ -240,7 +240,8 @@ int kvm_state_fold_path(const kvm_state *st, int64_t *path_out);
 
 /* Record every later fold's assignments and scores: fold number f (0 = the creation fold of
  * this state, counted over its whole life) writes assign[f] as int32 [B, H_kv, C] and
- * score[f] as fp32 [B, H_kv, C, 2].  Folds beyond `max_folds` are not recorded.  NULLs stop it. */
+ * score[f] as fp32 [B, H_kv, C, 2].  Folds beyond `max_folds` are not recorded.  NULLs stop it.
+ * Device memory, written in the order of the calls' streams and never read: the folds do not depend on it. */
 int kvm_state_trace(kvm_state *st, int32_t *assign, float *score, int64_t max_folds);
 
 /* Move the state into a larger buffer sized for `new_max_tokens` (growth scheduler: called

@@ -332,9 +332,9 @@ Src batch_view(const Src &s, int b0, size_t es) {
 }
 
 // The launches of one fold over the units of `dv` (the whole state or a view of part of its
-// batch), from m to m_after rows, reading readout slot so and writing slot sn.
+// batch), from m to m_after rows, reading readout slot so and writing slot sn; `rec`: of these units.
 int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_t m_after, int so, int sn,
-                  bool in_place, int kbar_block, bool scored, hipStream_t stream) {
+                  bool in_place, int kbar_block, bool scored, const kvm::Record &rec, hipStream_t stream) {
   const kvm_config &c = st->cfg;
   const int n_app = (int)(m_after - m);
   if (kbar_block < 0) {
@@ -346,7 +346,7 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
   if (n_app == dv.C) {
     // room for the whole block (state creation included): no scores are needed
     HIP_TRY(kvm::launch_select(dv, (int)m, n_app, true, stream));
-    HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, 0, true, false, copy, false, so, sn, stream));
+    HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, 0, true, false, copy, false, so, sn, rec, stream));
   } else {
     if (scored)
       ;   // by the attention launch ahead of the fold
@@ -359,7 +359,7 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
     } else if (n_app > 0) {
       // new rows first, so that the remaining tokens can be scored against them too
       HIP_TRY(kvm::launch_select(dv, (int)m, n_app, false, stream));
-      HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, (int)m, true, false, false, false, so, sn, stream));
+      HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, (int)m, true, false, false, false, so, sn, kvm::Record{}, stream));
       if (st->mfma)
         HIP_TRY(kvm::launch_score_mfma(dv, sn, (int)m, (int)m_after, false, stream));
       else
@@ -368,24 +368,23 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
     const int mc = st->dbg[KVM_DEBUG_MERGE_COPY];  // 1 / 2 force it on / off: for comparisons
     const bool small = mc ? mc == 1 : (int64_t)dv.Ufull * m_after < 64 * 1024;
     if (in_place)
-      HIP_TRY(kvm::launch_merge_inplace(dv, src, n_app > 0, sn, stream));
+      HIP_TRY(kvm::launch_merge_inplace(dv, src, n_app > 0, sn, rec, stream));
     else if (small)
-      HIP_TRY(kvm::launch_merge_copy(dv, src, n_app > 0, so, sn, (int)m, stream));
+      HIP_TRY(kvm::launch_merge_copy(dv, src, n_app > 0, so, sn, (int)m, rec, stream));
     else
-      HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, 0, false, true, true, n_app > 0, so, sn, stream));
+      HIP_TRY(kvm::launch_accum(dv, src, (int)m, (int)m_after, 0, false, true, true, n_app > 0, so, sn, rec, stream));
   }
   return KVM_OK;
 }
 
-// The record of a fold (kvm_state_trace), for the units of `dv` (unit u0 on of the state): where the kernel-per-step path is
-// to leave its assignments and scores, the caller's buffers at fold number `fold` instead of the scratch.  (Copied there
-// behind every fold they were two more launches in the chain: 126 of 5.6 us, 0.7 ms, of a training step on 8 x 32768 tokens.)
-Dev recorded(const kvm_state *st, Dev dv, int64_t u0, int64_t fold) {
-  if (fold >= st->trace_max) return dv;
-  const int64_t at = (fold * st->dv.U + u0) * dv.C;
-  if (st->trace_assign) dv.pi = st->trace_assign + at;
-  if (st->trace_score) dv.score = (float2 *)(st->trace_score + 2 * at);
-  return dv;
+// The record of fold number `fold` (kvm_state_trace), from unit u0 of the state on.
+kvm::Record record_of(const kvm_state *st, int64_t u0, int64_t fold) {
+  kvm::Record rec;
+  if (fold >= st->trace_max) return rec;
+  const int64_t at = (fold * st->dv.U + u0) * st->dv.C;
+  if (st->trace_assign) rec.assign = st->trace_assign + at;
+  if (st->trace_score) rec.score = st->trace_score + 2 * at;
+  return rec;
 }
 
 // The one-launch fold path (a run of folds in one kernel; bf16, d = 128 states whose tables fit LDS)
@@ -635,7 +634,6 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
   const int so = slot_of(st, st->folds), sn = in_place ? so : slot_of(st, st->folds + 1);
   const size_t ntok = (size_t)dv.U * dv.C;
   const int split = fold_split_on(st, 1, stream);
-  Dev rdv = dv;
   if (split > 0) {
     kvm::FoldRunArgs run;
     int rc_run = fused_run(st, split, in_place, stream, &run);
@@ -649,14 +647,13 @@ int fold_block(kvm_state *st, const Src &src, int64_t e, int32_t *assign_out, fl
     rc_run = launch_run(st, src, run, st->dbg[KVM_DEBUG_FOLD_WAVES] != 16, nullptr, stream);
     if (rc_run != KVM_OK) return rc_run;
   } else {
-    rdv = recorded(st, dv, 0, st->folds);
-    int rc = fold_launches(st, rdv, src, m, m_after, so, sn, in_place, kbar_block, scored, stream);
+    int rc = fold_launches(st, dv, src, m, m_after, so, sn, in_place, kbar_block, scored, record_of(st, 0, st->folds), stream);
     if (rc != KVM_OK) return rc;
   }
   if (assign_out)
-    HIP_TRY(hipMemcpyAsync(assign_out, rdv.pi, ntok * 4, hipMemcpyDeviceToDevice, stream));
+    HIP_TRY(hipMemcpyAsync(assign_out, dv.pi, ntok * 4, hipMemcpyDeviceToDevice, stream));
   if (score_out)
-    HIP_TRY(hipMemcpyAsync(score_out, rdv.score, ntok * 8, hipMemcpyDeviceToDevice, stream));
+    HIP_TRY(hipMemcpyAsync(score_out, dv.score, ntok * 8, hipMemcpyDeviceToDevice, stream));
   st->m = m_after;
   st->folds += 1;
   if (in_place) st->inplace += 1;
@@ -1094,7 +1091,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         {
           ProfileSpan span(st, 0, stream);
           if (scored) {
-            Dev kdv = recorded(st, dv, 0, st->folds);
+            Dev kdv = dv;
             kdv.kbar = (char *)dv.kbar + (size_t)slab * dv.Ufull * C * d * es;
             HIP_TRY(kvm::launch_attn_score(kdv, a, slot_of(st, st->folds), (int)st->m, stream));
           } else if (kvm::attention_on_mfma(dv))
@@ -1273,11 +1270,11 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
         if (batched) HIP_TRY(kvm::launch_memkey(cdv[c2], advance(cin, lo0 - t0, es), run, fstream[c2]));
         for (int i = 0; i < run; ++i) {
           const int64_t lo = plan[next_fold + i].s + C - L;  // first token of the overflow block
-          const Dev rdv = recorded(st, cdv[c2], (int64_t)c2 * cb * dv.Hkv, st->folds + i);
-          const int rc = batched ? fold_launches(st, rdv, advance(cin, lo - t0, es), steps[i].m, steps[i].m_after, steps[i].so,
-                                                 steps[i].sn, false, i, false, fstream[c2])
-                                 : fold_launches(st, rdv, advance(cring, lo % L, es), steps[i].m, steps[i].m_after, steps[i].so,
-                                                 steps[i].sn, false, -1, false, fstream[c2]);
+          const kvm::Record rec = record_of(st, (int64_t)c2 * cb * dv.Hkv, st->folds + i);
+          const int rc = batched ? fold_launches(st, cdv[c2], advance(cin, lo - t0, es), steps[i].m, steps[i].m_after,
+                                                 steps[i].so, steps[i].sn, false, i, false, rec, fstream[c2])
+                                 : fold_launches(st, cdv[c2], advance(cring, lo % L, es), steps[i].m, steps[i].m_after,
+                                                 steps[i].so, steps[i].sn, false, -1, false, rec, fstream[c2]);
           if (rc != KVM_OK) return rc;
         }
       }

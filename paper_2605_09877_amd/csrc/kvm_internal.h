@@ -74,13 +74,20 @@ struct AttnArgs {
   int32_t slot[kMaxGroup];  // readout slot of that state version
 };
 
+// Where the record of a fold goes (kvm_state_trace), from the first unit of the launch on; nulls: nowhere.  Written, and never
+// read, by the fold's last launch: the fold works in its own scratch whatever becomes of the caller's memory.
+struct Record {
+  int32_t *assign = nullptr;   // [U, C]
+  float *score = nullptr;      // [U, C, 2]
+};
+
 // fold.hip
 hipError_t launch_memkey(const Dev &dv, const Src &src, int n_blocks, hipStream_t st);
 hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st);
 hipError_t launch_select(const Dev &dv, int m, int n_app, bool take_all, hipStream_t st);
 hipError_t launch_accum(const Dev &dv, const Src &src, int m_before, int m_after, int row_begin,
                         bool do_create, bool do_merge, bool do_copy, bool check_app, int slot_old,
-                        int slot_new, hipStream_t st);
+                        int slot_new, const Record &rec, hipStream_t st);
 // selection + creation + second scoring pass of a small append, one launch
 constexpr int kAppendMax = 16;
 __host__ __device__ inline bool append_fits(int C, int n_app) {
@@ -89,8 +96,8 @@ __host__ __device__ inline bool append_fits(int C, int n_app) {
 hipError_t launch_append(const Dev &dv, const Src &src, int m, int n_app, int slot_new, hipStream_t st);
 // the merge of a small fold in a prefill: token-centred merge into slot_new + copies of untouched rows
 hipError_t launch_merge_copy(const Dev &dv, const Src &src, bool check_app, int slot_old, int slot_new,
-                             int m_before, hipStream_t st);
-hipError_t launch_merge_inplace(const Dev &dv, const Src &src, bool check_app, int slot, hipStream_t st);
+                             int m_before, const Record &rec, hipStream_t st);
+hipError_t launch_merge_inplace(const Dev &dv, const Src &src, bool check_app, int slot, const Record &rec, hipStream_t st);
 hipError_t launch_refresh(const Dev &dv, int m, int slot, hipStream_t st);
 hipError_t launch_ring_copy(const Dev &dv, const Src &src, int64_t src_t0, int64_t p0, int64_t p1,
                             hipStream_t st);
