@@ -1104,23 +1104,22 @@ hipError_t launch_attn_score(const Dev &dv, const AttnArgs &a, int slot, int m, 
 }
 
 hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds, hipStream_t st) {
-  static const hipError_t attr = hipFuncSetAttribute((const void *)attn_mfma_kernel_q128,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBesideFoldLds);
-  static const hipError_t attr_quad = hipFuncSetAttribute((const void *)attn_quad_kernel_d128,
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kQuadLds);
-  if (attr != hipSuccess) return attr;
-  if (attr_quad != hipSuccess) return attr_quad;
+  static OncePerDevice<hipError_t> of_quad, of_beside;
   if (a.nq_total <= 0) return hipSuccess;
   unsigned of_32;
   const dim3 grid(tile_workgroups(dv, a, &of_32));
   if (dv.d == 128 && grid.x <= kQuadMost && !beside_folds) {
+    if (const hipError_t e = allow_lds(of_quad, (const void *)attn_quad_kernel_d128, kQuadLds); e != hipSuccess) return e;
     hipLaunchKernelGGL(attn_quad_kernel_d128, dim3(of_32), dim3(256), kQuadLds, st, dv, a);
   } else if (dv.d == 64 && grid.x <= kSplitMost) {
     hipLaunchKernelGGL(attn_split_kernel_d64, dim3(of_32), dim3(256), 0, st, dv, a);
-  } else if (dv.d == 64)
+  } else if (dv.d == 64) {
     hipLaunchKernelGGL(attn_mfma_kernel_d64, grid, dim3(256), 0, st, dv, a);
-  else
+  } else {
+    if (beside_folds)
+      if (const hipError_t e = allow_lds(of_beside, (const void *)attn_mfma_kernel_q128, kBesideFoldLds); e != hipSuccess) return e;
     hipLaunchKernelGGL(attn_mfma_kernel_q128, grid, dim3(256), beside_folds ? kBesideFoldLds : 0, st, dv, a);
+  }
   return hipGetLastError();
 }
 

@@ -866,18 +866,7 @@ hipError_t launch_delta_mfma(const Bwd &a, int64_t rows, hipStream_t st) {
 }
 
 namespace {
-hipError_t allow_lds() {   // more than 64 KiB of LDS per workgroup has to be asked for once
-  static const hipError_t rc = [] {
-    const void *kernels[3] = {(const void *)bwd_mfma_kernel<kRoleDQ>, (const void *)bwd_mfma_kernel<kRoleKV>,
-                              (const void *)bwd_mfma_both_kernel};
-    for (const void *k : kernels) {
-      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }();
-  return rc;
-}
+OncePerDevice<hipError_t> g_dq, g_kv, g_both;   // more than 64 KiB of LDS per workgroup has to be asked for
 MfmaChunk chunk_of(const Bwd &a, int64_t cs, int nq, int m, bool folded, int section) {
   const Dev &dv = a.dv;
   MfmaChunk c;
@@ -906,15 +895,16 @@ Grids grids_of(const Dev &dv, int nq, int m) {
 // The launches of one chunk: dq (and the temperature sums); dk and dv of its own tokens and of the state rows.
 hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool folded, int role, int section,
                                 hipStream_t st) {
-  if (const hipError_t e = allow_lds(); e != hipSuccess) return e;
   const MfmaChunk c = chunk_of(a, cs, nq, m, folded, section);
   const Grids g = grids_of(a.dv, nq, m);
   if (role == kRoleDQ) {
+    if (const hipError_t e = allow_lds(g_dq, (const void *)bwd_mfma_kernel<kRoleDQ>, kBwdLdsBytes); e != hipSuccess) return e;
     hipLaunchKernelGGL((bwd_mfma_kernel<kRoleDQ>), dim3(g.dq), dim3(256), kBwdLdsBytes, st, a, c);
     return hipGetLastError();
   }
   const unsigned n = section == kSecBoth ? g.state + g.window : section == kSecState ? g.state : g.window;
   if (n == 0) return hipSuccess;
+  if (const hipError_t e = allow_lds(g_kv, (const void *)bwd_mfma_kernel<kRoleKV>, kBwdLdsBytes); e != hipSuccess) return e;
   hipLaunchKernelGGL((bwd_mfma_kernel<kRoleKV>), dim3(n), dim3(256), kBwdLdsBytes, st, a, c);
   return hipGetLastError();
 }
@@ -925,7 +915,7 @@ bool backward_fits_one_launch(const Dev &dv, int m) {
   return g.dq + g.window + g.state <= (dv.Hq <= 2 * dv.Hkv ? kBwdOneLaunch : kBwdOneLaunchHeads);
 }
 hipError_t launch_backward_mfma_both(const Bwd &a, int64_t cs, int nq, int m, bool folded, hipStream_t st) {
-  if (const hipError_t e = allow_lds(); e != hipSuccess) return e;
+  if (const hipError_t e = allow_lds(g_both, (const void *)bwd_mfma_both_kernel, kBwdLdsBytes); e != hipSuccess) return e;
   const Grids g = grids_of(a.dv, nq, m);
   hipLaunchKernelGGL(bwd_mfma_both_kernel, dim3(g.dq + g.window + g.state), dim3(256), kBwdLdsBytes, st, a,
                      chunk_of(a, cs, nq, m, folded, kSecBoth), (int)g.dq);

@@ -1406,12 +1406,6 @@ hipError_t launch_refresh16(const Dev &dv, int m, int slot, hipStream_t st) {
 hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &run_, bool narrow, hipEvent_t done,
                              hipStream_t st) {
   if (run_.n <= 0) return hipSuccess;
-  static const hipError_t attr16 = hipFuncSetAttribute((const void *)fold_fused_kernel<16>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsWide);
-  static const hipError_t attr8 = hipFuncSetAttribute((const void *)fold_fused_kernel<8>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsNarrow);
-  if (attr16 != hipSuccess) return attr16;
-  if (attr8 != hipSuccess) return attr8;
   FoldRunArgs run = run_;
   const int split = run.split, NW = narrow ? 8 : 16;
   if (split < 1 || (split > 1 && !run.xtab)) return hipErrorInvalidValue;
@@ -1422,6 +1416,8 @@ hipError_t launch_fold_fused(const Dev &dv, const Src &src, const FoldRunArgs &r
   FoldKernelArgs args{dv, src, run};
   void *argv[] = {&args};
   const void *kernel = narrow ? (const void *)fold_fused_kernel<8> : (const void *)fold_fused_kernel<16>;
+  static OncePerDevice<hipError_t> of_narrow, of_wide;
+  if (const hipError_t e = allow_lds(narrow ? of_narrow : of_wide, kernel, narrow ? kLdsNarrow : kLdsWide); e != hipSuccess) return e;
   const dim3 grid((unsigned)(dv.U * split)), block(64 * NW);
   const size_t lds = lds_bytes(dv, NW, split, limit);
   const hipError_t e = done ? hipExtLaunchKernel(kernel, grid, block, argv, lds, st, nullptr, done, 0)

@@ -5,7 +5,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "per_device.h"
+
 namespace kvm {
+
+// A kernel's launches may have `bytes` of dynamic LDS on the calling thread's device.
+inline hipError_t allow_lds(OncePerDevice<hipError_t> &once, const void *kernel, size_t bytes) {
+  return once([](int *dev) { return hipGetDevice(dev); },
+              [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
 
 // A strided source of per-token keys, values and merge gates for all units.
 // Element strides; the head_dim axis is contiguous.  Token index 0 is `k`'s first token.
