@@ -141,7 +141,9 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 # all: the current stream's handle comes straight from torch's C layer (0.1 us; through torch.cuda.current_stream() 1.5), a
 # device context (3 us) is entered only when another device is current, shapes are compared as they are.
 # Eight tokens of one sequence, preparation and decode step, 333 us before, 248 now; a prompt of 50 tokens 20.5, now 16.3.
-_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+# (A torch without them, one for CPUs alone, has the host-side parts of this module: sizes, schedules, errors.)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _stream() -> int:
