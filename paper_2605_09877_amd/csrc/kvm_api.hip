@@ -181,11 +181,29 @@ bool may_share(const kvm_config &c) {
   const int64_t U = (int64_t)c.batch * c.n_kv_heads;
   return use_mfma(c) && U < kFusedMinUnits && c.chunk_len <= (U < kShareFewUnits ? kShareLongBlock : kShareMaxBlock);
 }
-// Folds of a run: a group's where they run beside attention (attention_beside), half of one elsewhere.  Blocks whose memory
-// keys the scratch holds: two runs' (of fewer than 8 units half as many in either case).
+// Floating-point operations of a chunk's attention into m state rows.
+double chunk_flops(const kvm_config &c, int64_t m) {
+  const double C = c.chunk_len, keys = (double)m + C * c.n_bswa_chunks - 0.5 * C;
+  return 4.0 * c.head_dim * c.batch * c.n_q_heads * C * keys;
+}
+constexpr double kBesideMostFlops = 18e9;   // up to which attention leaves room for shared folds (attention_beside, below)
+// Folds of a run: a group's where they run beside attention, half of one elsewhere.  Blocks whose memory keys the scratch
+// holds: two runs', of fewer than 8 units half as many.  Which states may run beside attention is asked with the rows of a
+// block, the fewest there are.
+// States without grouped launches have the keys of up to eight blocks from one launch where those are small (16 MiB of them
+// all: a launch over 2 MiB of keys and more fills the chip by itself); the scratch also takes the partial results of a
+// decode step whose keys are shared, up to 2 MiB.
 constexpr int kFoldRunApart = 4;
+constexpr int64_t kGenericKeyBytes = (int64_t)16 << 20;
 int key_blocks(const kvm_config &c) {
-  return may_share(c) && (int64_t)c.batch * c.n_kv_heads >= kShareFewUnits ? 2 * kvm::kFoldMaxSteps : 2 * kFoldRunApart;
+  const int64_t U = (int64_t)c.batch * c.n_kv_heads;
+  if (!use_mfma(c)) {
+    const int64_t n = kGenericKeyBytes / (U * c.chunk_len * c.head_dim * (int64_t)esize(c.io_dtype));
+    return n < 1 ? 1 : n < 2 * kFoldRunApart ? (int)n : 2 * kFoldRunApart;
+  }
+  const bool beside = may_share(c) && U >= kShareFewUnits && (c.chunk_len <= kShareLongBlock || c.n_q_heads <= 2 * c.n_kv_heads) &&
+                      chunk_flops(c, c.chunk_len) <= kBesideMostFlops;
+  return beside ? 2 * kvm::kFoldMaxSteps : 2 * kFoldRunApart;
 }
 
 Layout layout_of(const kvm_config &c, int64_t Mcap) {
@@ -482,11 +500,8 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
 // 4 heads each (21.5) 1270 / 1290, 64 units, 512 rows, 4 heads each (30) 1790 / 1805.
 // The runs of folds are a group's eight then.  Elsewhere the launch waits for attention to leave and attention for the launch, and
 // they are half as long: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight.
-constexpr double kBesideMostFlops = 18e9;
 bool attention_beside(const kvm_state *st, int split, int64_t m) {
-  const Dev &dv = st->dv;
-  const double keys = (double)m + (double)dv.L - 0.5 * (double)dv.C;
-  return may_share(st->cfg) && kvm::fold_fused_beside(dv, split) && 4.0 * dv.d * dv.B * dv.Hq * dv.C * keys <= kBesideMostFlops;
+  return may_share(st->cfg) && kvm::fold_fused_beside(st->dv, split) && chunk_flops(st->cfg, m) <= kBesideMostFlops;
 }
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,

@@ -86,6 +86,39 @@ def test_state_bytes_cover_the_layout():
         lib.kvm_state_bytes(C.byref(cfg(budget_kind=kb.KVM_BUDGET_SQRT, budget_scale=4.0)), 4096)
 
 
+@pytest.mark.parametrize("kw,rows,blocks", [
+    # states that fold by themselves chunk by chunk: as many blocks of keys as 16 MiB hold, one at least and eight at most
+    (dict(io_dtype=kb.KVM_F32, head_dim=64, batch=1, n_q_heads=2, n_kv_heads=2, chunk_len=64), 64, 8),
+    (dict(io_dtype=kb.KVM_F32, batch=64, n_q_heads=32, n_kv_heads=32, chunk_len=512), 512, 1),
+    (dict(head_dim=64, batch=48, n_q_heads=16, n_kv_heads=16, chunk_len=64), 64, 2),
+    (dict(head_dim=64, batch=8, n_q_heads=16, n_kv_heads=4, chunk_len=256), 256, 8),
+    (dict(chunk_len=40, batch=16, n_q_heads=32, n_kv_heads=32), 128, 3),
+    # bf16, head_dim 128: two runs of eight folds where they may run beside attention, two of four elsewhere
+    (dict(batch=2, n_q_heads=16, n_kv_heads=16), 512, 16),
+    (dict(batch=2, n_q_heads=3, n_kv_heads=3), 512, 8),                          # fewer than 8 units
+    (dict(batch=16, n_q_heads=16, n_kv_heads=16), 512, 8),                       # 256 units
+    (dict(batch=2, n_q_heads=16, n_kv_heads=16, chunk_len=512), 512, 16),
+    (dict(batch=8, n_q_heads=16, n_kv_heads=8, chunk_len=512), 512, 8),          # attention is the longer part
+    (dict(batch=1, n_q_heads=32, n_kv_heads=8, chunk_len=512), 512, 8),          # four heads on a long block's keys
+    (dict(batch=1, n_q_heads=16, n_kv_heads=16, chunk_len=1024), 1024, 8),
+])
+def test_scratch_holds_the_keys_that_a_run_can_use(kw, rows, blocks):
+    lib = kb.load_library()
+    c = cfg(budget_fixed=rows, **kw)
+    U, d, C_, m = c.batch * c.n_kv_heads, c.head_dim, c.chunk_len, -(-max(rows, c.chunk_len) // 64) * 64
+    es = 2 if c.io_dtype == kb.KVM_BF16 else 4
+    mfma = es == 2 and d == 128 and C_ % 64 == 0
+    L, slots = 2 * C_, 16 if mfma else 2
+    need = U * m * d * (8 + 4 + slots * 2 * es) + U * m * 12 + 2 * U * L * d * es + U * L * 4 + blocks * U * C_ * d * es + U * C_ * 20
+    split = 1
+    while mfma and 2 * split <= 16 and U * 2 * split <= 256 and m // 64 >= 2 * split:
+        split *= 2
+    if split > 1:
+        need += U * (8 + 2 * split * 2 * C_) * 8
+    got = lib.kvm_state_bytes(C.byref(c), 64 * C_)
+    assert need <= got <= need + 20 * 256, (got - need) / (U * C_ * d * es)
+
+
 def test_the_library_allocates_no_memory():
     """Buffers and workspaces are the caller's: no source of the library names an allocation, on the device or pinned on
     the host (kvm_decode_step_multi_static promises it for code that cannot have one)."""
