@@ -359,9 +359,15 @@ __global__ __launch_bounds__(256) void append_kernel(Dev dv, Src src, int m, int
   }
 }
 
-// A token's entry in the record of its fold (kvm_state_trace), by the fold's last launch.  (Two copies behind every fold were two
-// more launches in the chain, 126 of 5.6 us in a training step on 8 x 32768 tokens.)
-__device__ __forceinline__ void record_token(const Dev &dv, const Record &rec, int64_t tj) {
+// The record of a fold (kvm_state_trace), by further workgroups of its last launch: 256 tokens of unit u each.  (Two copies behind every
+// fold were two more launches in the chain, 126 of 5.6 us in a training step on 8 x 32768 tokens; by the waves that merge, it
+// slowed launches down that record nothing: 20480 tokens, 64 units, 1000 rows 3.60 -> 3.68 ms.)
+constexpr int kRecordTok = 256;
+inline int record_blocks(const Dev &dv, const Record &rec) { return rec.assign || rec.score ? (dv.C + kRecordTok - 1) / kRecordTok : 0; }
+__device__ __forceinline__ void record_tokens(const Dev &dv, const Record &rec, int blk, int u) {
+  const int j = blk * kRecordTok + threadIdx.x;
+  if (j >= dv.C) return;
+  const int64_t tj = (int64_t)u * dv.C + j;
   if (rec.assign) rec.assign[tj] = dv.pi[tj];
   if (rec.score) {
     const float2 s = dv.score[tj];
@@ -383,16 +389,18 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void accum_kernel(Dev dv, Src src, int m_before, int m_after,
                                                     int row_begin, int do_create, int do_merge,
                                                     int do_copy, int check_app, int slot_old,
-                                                    int slot_new, Record rec) {
+                                                    int slot_new, int n_row_blocks, Record rec) {
   constexpr int CPL = D / 64;
+  if ((int)blockIdx.x >= n_row_blocks) {
+    record_tokens(dv, rec, blockIdx.x - n_row_blocks, blockIdx.y);
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int u = blockIdx.y, b = u / dv.Hkv, h = u % dv.Hkv;
   const int row_first = row_begin + (blockIdx.x * 4 + wave) * kAccumRows;
+  if (row_first >= m_after) return;
   const int C = dv.C;
   const int64_t base = (int64_t)u * C;
-  if (rec.assign || rec.score)
-    for (int j = blockIdx.x * 256 + threadIdx.x; j < C; j += gridDim.x * 256) record_token(dv, rec, base + j);
-  if (row_first >= m_after) return;
   const T *vsrc = (const T *)src.v + b * src.v_b + h * src.v_h;
   const float *gsrc = src.g ? src.g + b * src.g_b + h * src.g_h : nullptr;
   const T *kbar = (const T *)dv.kbar + base * D;
@@ -520,8 +528,8 @@ __global__ __launch_bounds__(256) void accum_kernel(Dev dv, Src src, int m_befor
 // row: it adds every token with that target, in ascending position, and rewrites the row's
 // readout; the other waves leave at once.
 template <typename T, int D>
-__device__ __forceinline__ void merge_token_wave(const Dev &dv, const Src &src, int check_app, int slot, const Record &rec,
-                                                 int blk, int u) {
+__device__ __forceinline__ void merge_token_wave(const Dev &dv, const Src &src, int check_app, int slot, int blk,
+                                                 int u) {
   constexpr int CPL = D / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = u / dv.Hkv, h = u % dv.Hkv;
@@ -529,7 +537,6 @@ __device__ __forceinline__ void merge_token_wave(const Dev &dv, const Src &src, 
   const int j = blk * 4 + wave;
   if (j >= C) return;
   const int64_t base = (int64_t)u * C;
-  if (lane == 0) record_token(dv, rec, base + j);
   const int row = dv.pi[base + j];
   if (row < dv.S || row == 0x7fffffff) return;
   if (check_app && dv.app[base + j] >= 0) return;
@@ -609,8 +616,11 @@ __device__ __forceinline__ void merge_token_wave(const Dev &dv, const Src &src, 
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void merge_inplace_kernel(Dev dv, Src src, int check_app, int slot, Record rec) {
-  merge_token_wave<T, D>(dv, src, check_app, slot, rec, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(256) void merge_inplace_kernel(Dev dv, Src src, int check_app, int slot, int n_tok_blocks, Record rec) {
+  if ((int)blockIdx.x < n_tok_blocks)
+    merge_token_wave<T, D>(dv, src, check_app, slot, blockIdx.x, blockIdx.y);
+  else
+    record_tokens(dv, rec, blockIdx.x - n_tok_blocks, blockIdx.y);
 }
 
 // The same merge for a prefill's small folds, where the new state version lives in another slot:
@@ -663,9 +673,11 @@ __device__ __forceinline__ void copy_untouched_wave(const Dev &dv, int check_app
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void merge_copy_kernel(Dev dv, Src src, int check_app, int slot_old, int slot_new,
-                                                         int m_before, int n_tok_blocks, Record rec) {
+                                                         int m_before, int n_tok_blocks, int n_row_blocks, Record rec) {
   if ((int)blockIdx.x < n_tok_blocks)
-    merge_token_wave<T, D>(dv, src, check_app, slot_new, rec, blockIdx.x, blockIdx.y);
+    merge_token_wave<T, D>(dv, src, check_app, slot_new, blockIdx.x, blockIdx.y);
+  else if ((int)blockIdx.x >= n_tok_blocks + n_row_blocks)
+    record_tokens(dv, rec, blockIdx.x - n_tok_blocks - n_row_blocks, blockIdx.y);
   else
     copy_untouched_wave<T, D>(dv, check_app, slot_old, slot_new, m_before, blockIdx.x - n_tok_blocks, blockIdx.y);
 }
@@ -766,24 +778,27 @@ hipError_t launch_accum(const Dev &dv, const Src &src, int m_before, int m_after
                         bool do_create, bool do_merge, bool do_copy, bool check_app, int slot_old,
                         int slot_new, const Record &rec, hipStream_t st) {
   if (m_after <= row_begin) return hipSuccess;
-  dim3 grid((m_after - row_begin + 4 * kAccumRows - 1) / (4 * kAccumRows), dv.U);
+  const int n_row_blocks = (m_after - row_begin + 4 * kAccumRows - 1) / (4 * kAccumRows);
+  dim3 grid(n_row_blocks + record_blocks(dv, rec), dv.U);
   KVM_DISPATCH(dv, accum_kernel, grid, dim3(256), 0, st, dv, src, m_before, m_after, row_begin,
-               do_create ? 1 : 0, do_merge ? 1 : 0, do_copy ? 1 : 0, check_app ? 1 : 0, slot_old, slot_new, rec);
+               do_create ? 1 : 0, do_merge ? 1 : 0, do_copy ? 1 : 0, check_app ? 1 : 0, slot_old, slot_new, n_row_blocks,
+               rec);
   return hipGetLastError();
 }
 
 hipError_t launch_merge_inplace(const Dev &dv, const Src &src, bool check_app, int slot, const Record &rec, hipStream_t st) {
-  dim3 grid((dv.C + 3) / 4, dv.U);
-  KVM_DISPATCH(dv, merge_inplace_kernel, grid, dim3(256), 0, st, dv, src, check_app ? 1 : 0, slot, rec);
+  const int n_tok_blocks = (dv.C + 3) / 4;
+  dim3 grid(n_tok_blocks + record_blocks(dv, rec), dv.U);
+  KVM_DISPATCH(dv, merge_inplace_kernel, grid, dim3(256), 0, st, dv, src, check_app ? 1 : 0, slot, n_tok_blocks, rec);
   return hipGetLastError();
 }
 
 hipError_t launch_merge_copy(const Dev &dv, const Src &src, bool check_app, int slot_old, int slot_new,
                              int m_before, const Record &rec, hipStream_t st) {
   const int n_tok_blocks = (dv.C + 3) / 4, n_row_blocks = (m_before + 4 * kCopyRows - 1) / (4 * kCopyRows);
-  dim3 grid(n_tok_blocks + n_row_blocks, dv.U);
+  dim3 grid(n_tok_blocks + n_row_blocks + record_blocks(dv, rec), dv.U);
   KVM_DISPATCH(dv, merge_copy_kernel, grid, dim3(256), 0, st, dv, src, check_app ? 1 : 0, slot_old, slot_new,
-               m_before, n_tok_blocks, rec);
+               m_before, n_tok_blocks, n_row_blocks, rec);
   return hipGetLastError();
 }
 
