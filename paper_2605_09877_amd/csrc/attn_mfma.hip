@@ -1088,8 +1088,8 @@ static unsigned tile_workgroups(const Dev &dv, const AttnArgs &a, unsigned *of_3
   return (unsigned)(n_groups * per_group);
 }
 
-bool attention_takes_scores(const Dev &dv, const AttnArgs &a) {
-  if (!attention_on_mfma(dv)) return attn_rows_score_workgroups(dv, a) <= kMostWorkgroups;
+bool attention_takes_scores(const Dev &dv, const AttnArgs &a, int m) {
+  if (!attention_on_mfma(dv)) return attn_rows_take_scores(dv, a, m);
   unsigned of_32;
   return dv.d == 64 && tile_workgroups(dv, a, &of_32) <= kSplitMost;
 }

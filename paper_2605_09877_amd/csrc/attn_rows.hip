@@ -487,8 +487,27 @@ hipError_t launch_attn_rows(const Dev &dv, const AttnArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-int64_t attn_rows_score_workgroups(const Dev &dv, const AttnArgs &a) {
+static int64_t attn_rows_score_workgroups(const Dev &dv, const AttnArgs &a) {
   return (int64_t)a.nq_total * dv.Hq * dv.B + (int64_t)(dv.C + 3) / 4 * dv.U;
+}
+// In that launch attention has the scoring's registers, and as many of its workgroups on a compute unit as those leave: of fp32 heads of
+// 64 channels five where two rows of a lane are under way, two with one (eight by itself), of 128 seven (eight); bf16, 64: three,
+// two (six), 128: four, one (six).  So up to the number of workgroups that was still faster.  Us per call, apart / one launch (workgroups):
+//   fp32, 64:   4 x 4 heads, 256-token blocks, 1000 rows (5120) 2791 / 2629, 2 x 8 heads on 2, 512, 1000 (8704) 2778 / 2727; but 8 x 4, 256,
+//               1000 (10240) 4827 / 5040, 16 x 4, 128, 300 (10240) 2054 / 2173.  Up to 64 rows: 4 x 4, 64 (1280) 297 / 289, but 8 x 4
+//               (2560) 413 / 449, 8 x 16 on 4 (8704) 744 / 1137
+//   fp32, 128:  16 x 4, 512, 64 (40960) 21036 / 20793, 8 x 16 on 4, 512, 300 (69632) 30998 / 30963
+//   bf16, 64:   1 x 4, 480, 900 (2400) 870 / 860, but 8 x 4, 96, 128 (3840) 404 / 438, 8 x 16 on 4, 200, 128 (27200) 2515 / 2902.  Up to 64
+//               rows: 4 x 4, 48 (960) 188 / 181, but 8 x 4 (1920) 228 / 259
+//   bf16, 128:  8 x 4, 480, 128 (19200) 7254 / 7080, 8 x 16 on 4, 48, 128 (6528) 662 / 660, but 8 x 16 on 4, 96, 40 (13056) 1283 / 1353.
+//               Up to 64 rows: 1 x 4, 48 (240) 206 / 148, but 2 x 8 on 2 (792) 223 / 245, 8 x 16 on 4 (6528) 553 / 1138
+bool attn_rows_take_scores(const Dev &dv, const AttnArgs &a, int m) {
+  const bool two = m > 64;
+  int64_t most = kMostWorkgroups;
+  if (dv.d == 64) most = dv.io == 0 ? (two ? 9216 : 1280) : (two ? 2560 : 1024);
+  else if (dv.io != 0 && !two) most = 256;
+  else if (dv.io != 0 && dv.Hq > dv.Hkv) most = 6656;
+  return attn_rows_score_workgroups(dv, a) <= most;
 }
 hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st) {
   const dim3 grid((unsigned)attn_rows_score_workgroups(dv, a));

@@ -1064,7 +1064,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     AttnArgs one;
     one.n_chunks = 1;
     one.nq_total = (int32_t)C;
-    const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one) && (dv.U > 1 || similarity <= 240.0e6)));
+    const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one, (int)m_max) && (dv.U > 1 || similarity <= 240.0e6)));
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.
     const bool serial = (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || apart)) || captured(stream);
@@ -1102,7 +1102,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
           a.slot[i] = (int32_t)slot_of(st, st->folds);
         }
         const int64_t n_app = ch.folds ? rows_after(c, st->table, st->m, ce) - st->m : C;
-        const bool scored = !st->mfma && n_app < C && kvm::attention_takes_scores(dv, a);
+        const bool scored = !st->mfma && n_app < C && kvm::attention_takes_scores(dv, a, (int)st->m);
         {
           ProfileSpan span(st, 0, stream);
           if (scored) {

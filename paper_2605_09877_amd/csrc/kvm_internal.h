@@ -209,11 +209,11 @@ hipError_t launch_attn_mfma(const Dev &dv, const AttnArgs &a, bool beside_folds,
 
 // A chunk's attention with the first scoring pass of the fold after it (rows [0, m) of readout slot `slot`, memory keys at
 // dv.kbar), one launch: for states without the matrix-core folds, where its one dimension holds the workgroups (a dimension
-// takes fewer than 2^32 threads; the launches apart have three).
+// takes fewer than 2^32 threads; the launches apart have three) and it is the faster way.
 constexpr int64_t kMostWorkgroups = (1 << 24) - 1;   // of 256 threads
-bool attention_takes_scores(const Dev &dv, const AttnArgs &a);
+bool attention_takes_scores(const Dev &dv, const AttnArgs &a, int m);
 hipError_t launch_attn_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st);
-int64_t attn_rows_score_workgroups(const Dev &dv, const AttnArgs &a);
+bool attn_rows_take_scores(const Dev &dv, const AttnArgs &a, int m);
 hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, int m, hipStream_t st);
 
 // backward.hip: the backward pass of a whole-sequence prefill that started from an empty state.

@@ -35,7 +35,7 @@ def test_more_workgroups_than_a_dimension_holds(batch):
     import torch
     import paper_2605_09877_amd as pkg
     from paper_2605_09877_amd import synth as sy
-    w1 = sy.shrink(sy.WORKLOADS["tiny_f32"], batch=1, n_q_heads=64, n_kv_heads=1, seq=128, n_bswa_chunks=1)
+    w1 = sy.shrink(sy.WORKLOADS["tiny_f32"], batch=1, n_q_heads=64, n_kv_heads=1, head_dim=128, seq=128, n_bswa_chunks=1)
     qkv = sy.make_qkv(w1, "cuda:0")
     res = []
     for n in (1, batch):
@@ -46,3 +46,31 @@ def test_more_workgroups_than_a_dimension_holds(batch):
         res.append((out, *(state[key] for key in ("sK", "sV", "n", "khat", "vhat"))))
     for one, many in zip(*res):
         assert bool((many == one).all())
+
+
+@pytest.mark.parametrize("io,d,C,rows,heads,many", [
+    ("f32", 64, 40, 40, (2, 2), 20), ("f32", 64, 72, 100, (2, 2), 60),        # workgroups beyond the line for states of up to 64 rows, of more
+    ("bf16", 64, 40, 33, (2, 1), 16), ("bf16", 64, 72, 100, (2, 2), 16),
+    ("bf16", 128, 40, 64, (1, 1), 6), ("bf16", 128, 72, 100, (4, 2), 24),
+    ("f32", 128, 256, 256, (4, 4), 16),                                       # attention long enough to hide the folds
+])
+def test_a_sequence_among_many(io, d, C, rows, heads, many):
+    """Alone a sequence has a chunk's scores taken along by its attention launch, among many in a launch of their own or
+    beside attention: the same outputs, state and record to the bit."""
+    import torch
+    import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import synth as sy
+    w = sy.shrink(sy.WORKLOADS["tiny_f32"], io=io, batch=many, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, seq=C * 6 + 5, chunk_len=C,
+                  budget_kind="table", budget_table=(rows, rows, rows, rows + 20, rows + 20, rows + 21))
+    q, k, v = sy.make_qkv(w, "cuda:0")
+    res = []
+    for n in (1, many):
+        st = pkg.state_for(sy.shrink(w, batch=n), device="cuda:0")
+        assign, score = st.trace(6)
+        out, lse = st.prefill(*(x[:n].contiguous() for x in (q, k, v)), want_lse=True)
+        state = st.export()
+        nf = st.folds
+        res.append([x[0] for x in (out, lse)] + [x[:nf, 0] for x in (assign, score.view(torch.int32))] +
+                   [state[key][0] for key in ("sK", "sV", "n", "khat", "vhat")])
+    for i, (one, among) in enumerate(zip(*res)):
+        assert torch.equal(one, among), i
