@@ -743,13 +743,17 @@ hipError_t launch_memkey(const Dev &dv, const Src &src, int n_blocks, hipStream_
   return hipGetLastError();
 }
 
-// Workgroups up to which a lane of the scoring kernel has two rows under way (kvm_score.h).
-constexpr unsigned kScoreTwoMost = 1024;
-hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st) {
+// Workgroups up to which a lane of the scoring kernel has two rows under way (kvm_score.h).  Us per call, one / two: bf16 heads of 64
+// channels 8 on 4, 600 rows: 12 sequences, 64-token blocks (768) 1486 / 1448, 8, 128 (1024) 843 / 860; of 128 beside attention, 4 x 4
+// heads, 480-token blocks, 480 rows (960) 3711 / 3428.  fp32 heads of 64 beside attention: one, whose workgroups are two on a compute unit
+// and leave attention the rest (with two rows seven): 8 x 4 heads, 256-token blocks, 1000 rows 4748 / 5627, 4 x 4, 512, 1000 3772 / 4226.
+constexpr unsigned kScoreTwoMost = 960;
+hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, bool beside_attention, hipStream_t st) {
   dim3 grid((dv.C + 3) / 4, dv.U);
+  const bool two = grid.x * grid.y <= kScoreTwoMost && !(beside_attention && dv.io == 0 && dv.d == 64);
 #define KVM_SCORE(T, D)                                                                                                  \
   do {                                                                                                                   \
-    if (grid.x * grid.y <= kScoreTwoMost)                                                                                \
+    if (two)                                                                                                             \
       hipLaunchKernelGGL((score_kernel<T, D, true>), grid, dim3(256), 0, st, dv, slot, row0, row1, first_pass ? 1 : 0);  \
     else                                                                                                                 \
       hipLaunchKernelGGL((score_kernel<T, D, false>), grid, dim3(256), 0, st, dv, slot, row0, row1, first_pass ? 1 : 0); \

@@ -371,7 +371,7 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
     else if (st->mfma)
       HIP_TRY(kvm::launch_score_mfma(dv, so, 0, (int)m, true, stream));
     else
-      HIP_TRY(kvm::launch_score(dv, so, 0, (int)m, true, stream));
+      HIP_TRY(kvm::launch_score(dv, so, 0, (int)m, true, !in_place, stream));
     if (kvm::append_fits(dv.C, n_app)) {
       HIP_TRY(kvm::launch_append(dv, src, (int)m, n_app, sn, stream));
     } else if (n_app > 0) {
@@ -381,7 +381,7 @@ int fold_launches(const kvm_state *st, Dev dv, const Src &src, int64_t m, int64_
       if (st->mfma)
         HIP_TRY(kvm::launch_score_mfma(dv, sn, (int)m, (int)m_after, false, stream));
       else
-        HIP_TRY(kvm::launch_score(dv, sn, (int)m, (int)m_after, false, stream));
+        HIP_TRY(kvm::launch_score(dv, sn, (int)m, (int)m_after, false, !in_place, stream));
     }
     const int mc = st->dbg[KVM_DEBUG_MERGE_COPY];  // 1 / 2 force it on / off: for comparisons
     const bool small = mc ? mc == 1 : (int64_t)dv.Ufull * m_after < 64 * 1024;

@@ -91,7 +91,7 @@ struct Record {
 
 // fold.hip
 hipError_t launch_memkey(const Dev &dv, const Src &src, int n_blocks, hipStream_t st);
-hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, hipStream_t st);
+hipError_t launch_score(const Dev &dv, int slot, int row0, int row1, bool first_pass, bool beside_attention, hipStream_t st);
 hipError_t launch_select(const Dev &dv, int m, int n_app, bool take_all, hipStream_t st);
 hipError_t launch_accum(const Dev &dv, const Src &src, int m_before, int m_after, int row_begin,
                         bool do_create, bool do_merge, bool do_copy, bool check_app, int slot_old,
