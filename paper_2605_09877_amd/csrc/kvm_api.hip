@@ -1030,6 +1030,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     bool folds;
   };
   std::vector<Chunk> plan;
+  int n_folds = 0, n_scored = 0;   // scored: the block does not become rows as it is
   {
     int64_t m = st->m, ver = st->folds;
     for (int64_t cs = t0; cs < t_end; cs += C) {
@@ -1037,7 +1038,10 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
       Chunk ch{cs, (int32_t)(ce - cs), (int32_t)m, ver, false};
       if (ce - cs == C && ce >= L && c.budget_kind != KVM_BUDGET_NONE) {
         ch.folds = true;
-        m = rows_after(c, st->table, m, ce);
+        const int64_t m_after = rows_after(c, st->table, m, ce);
+        ++n_folds;
+        n_scored += m_after - m < C;
+        m = m_after;
         ver += 1;
       }
       plan.push_back(ch);
@@ -1056,15 +1060,29 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     // (and a call of a few chunks has nothing to pipeline: the events would cost more than they buy)
     // So do states without grouped launches (fp32, head_dim 64, odd blocks) whose attention takes the scores of a chunk's fold
     // along (launch_attn_score): the events would cost some 20 us a chunk.  Pipelined / serial, us per call (blocks, rows): bf16 d 64
-    // 8 units (256, 700) 238 / 143, 8 units (512, 1000) 567 / 558; fp32 d 64 4 units (512, 1000) 1312 / 938; fp32 d 128 8 units (128,
-    // 1000) 968 / 794, 8 units (512, 2000) 8900 / 7120, 1 unit (512, 900) 456 / 451.  A single unit whose block and state are larger
-    // still leaves room for both at once, 1 unit (1000, 1100) 1496 / 1555; and where attention goes by itself the small ones alone
-    // are serial, bf16 d 64 32 units, 4 heads each (320, 1100) 1846 / 2141.
+    // 8 units (256, 700) 238 / 143, 8 units (512, 1000) 567 / 558; fp32 d 64 4 units (512, 1000) 1296 / 1120; fp32 d 128 8 units (128,
+    // 1000) 968 / 794, 16 units (512, 1000) 7886 / 7527, 64 units (256, 1000) 21186 / 18576; and where attention goes by itself the
+    // small ones alone are serial, bf16 d 64 32 units, 4 heads each (320, 1100) 1846 / 2141.
+    // But attention of the row kernel on whole chunks that is long against the fold hides it: from 4.5 GFLOP a chunk on, in fp32 where
+    // scoring is at most a quarter of it (fp64 sums of a row per key, against two products per query: m / 2G : keys): fp32 d 128 16 units (512, 512) 5187 /
+    // 5264, 32 units (512, 512) 9983 / 10268, 64 units (256, 300) 9084 / 9255, (512, 512) 19971 / 20793, 32 units, 4 heads each (512, 1000)
+    // 41073 / 41676; bf16 d 128 16 units (480, 900) 4737 / 5037, 32 units, 4 heads each (200, 900) 7078 / 7547; but 3 units (1024, 1024: 4.0) 4296 /
+    // 3909; and from 1.5 GFLOP on while blocks become rows as they are, without scores: fp32 d 128 64 units (64, 830) 1473 / 1572.
+    // And one chain of few units with long blocks, one head each, leaves room for both at once: fp32 d 128 1 unit (1000, 1100) 1496 / 1555, 2 units
+    // (512, 512) 805 / 851, (768, 768) 1599 / 1787, 3 units (512, 512) 1169 / 1259; but 3 units (384, 384) 840 / 790, 2 units (256, 1000)
+    // 1232 / 1159, 1 unit (512, 512) 657 / 633, 2 units (1024, 1024) 3122 / 2741.
     const double similarity = (double)C * (double)m_max * (double)d * (double)es;
     AttnArgs one;
     one.n_chunks = 1;
     one.nq_total = (int32_t)C;
-    const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one, (int)m_max) && (dv.U > 1 || similarity <= 240.0e6)));
+    const bool few_scored = 4 * n_scored <= n_folds;
+    const double keys = (double)m_max + (double)L - 0.5 * (double)C, scoring = (double)m_max * dv.Hkv / (2.0 * dv.Hq * keys);
+    const bool long_attention = chunk_flops(c, m_max) >= (few_scored ? 1.5e9 : 4.5e9) &&
+                                (few_scored || c.io_dtype == KVM_BF16 || scoring <= 0.25);
+    const bool few_units = c.io_dtype == KVM_F32 && d == 128 && dv.B % 2 != 0 && dv.Hq == dv.Hkv && dv.U * C <= 1536 &&
+                           (dv.U == 1 ? similarity > 240.0e6 : C >= 512);
+    const bool hides = kvm::attention_on_mfma(dv) ? dv.U == 1 && similarity > 240.0e6 : long_attention || few_units;
+    const bool apart = st->group == 1 && (similarity <= 24.0e6 || (kvm::attention_takes_scores(dv, one, (int)m_max) && !hides));
     // A call that is captured into a graph keeps to the caller's stream: graphs of several streams that
     // wait for each other have crashed the runtime, at the end of the capture and at a replay.
     const bool serial = (forced ? forced == 1 : (copy_us > 45.0 || plan.size() <= 4 || apart)) || captured(stream);
