@@ -434,7 +434,9 @@ kvm::Record record_of(const kvm_state *st, int64_t u0, int64_t fold) {
 // step / shared: 32 blocks of 256, 200 rows: 2 units 556 / 556, 4 units 585 / 565, with 8 heads each 642 / 602; 20 of 256, 512 rows: 2 units 382 / 359,
 // 4 units 395 / 366; 20 of 64, 520 rows, 4 units 360 / 310; 20 of 128, 1000 rows, one unit 396 / 330.  Growing: 32 of 256, up to 362 rows, 2 units
 // 845 / 680; 20 of 256, up to 1150 rows, 2 units 835 / 555; 78 of 256, 4 units of two heads 4050 / 2127.  But 32 of 64, 128 rows: one
-// unit 450 / 481, 4 units 469 / 491.
+// unit 450 / 481, 4 units 469 / 491; and without appends, blocks of 256 and 320 rows, the fifth tile a workgroup's second: 32 blocks, one unit 579 /
+// 628, 2 units 604 / 634, 3 units 0.94 (4 units 1.00 to 1.02), 448 rows 0.95 to 0.98 (4 units 1.00 to 1.04), 256 rows, one unit 528 / 557 (2 units
+// 1.03), blocks of 128, one unit 494 / 506.
 // Longer blocks lost with fixed rows: 512 tokens, 512 rows, 24 blocks, 2 units 532 / 557, 4 units 552 / 560.
 // A fold by itself (decode, the fold entry point, chunk by chunk) is shared from units x block = 8192 or 1024 rows on.  Us
 // alone: 8 units of 128-token blocks on 256 rows 45 / 48, 16 of 256 on 256 47 / 49, 32 of 128 on 512 48 / 48; 32 of 256
@@ -467,7 +469,11 @@ int fold_split(const kvm_state *st, int64_t blocks) {
   if (path == 1 || U >= kFusedMinUnits) return whole;
   if (!may_share(st->cfg)) return 0;
   if (U < kShareFewUnits) {
-    if (st->dv.Mcap < 256 || blocks < (st->dv.Mcap >= 512 ? 20 : 32)) return 0;
+    const int M = st->dv.Mcap;
+    if (M < 256 || blocks < (M >= 512 ? 20 : 32)) return 0;
+    if (M < 512 && !(st->cfg.budget_kind != KVM_BUDGET_FIXED && M > C)) {   // no appends
+      if (C > 128 ? U < (M > C ? 4 : 2) : C > 64 && U == 1 && M <= 256) return 0;
+    }
   } else if (C > kShareLongBlock) {
     if (blocks < (U < 64 ? 12 : 8) || st->dv.Hq > 2 * st->dv.Hkv) return 0;
   } else if (st->m < kShareAnyRows && (blocks == 1 ? U * C < kShareAlone : blocks < (U < 64 ? 7 : 5))) {
@@ -490,18 +496,28 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
   return split > 1 && captured(stream) ? 0 : split;
 }
 
-// Whether the attention launches of a prefill leave room on every compute unit for the workgroup of a shared fold.
+// Whether the attention launches of a prefill that folds `blocks` blocks leave room on every compute unit for the workgroup of a shared fold.
 // Two attention workgroups fill a compute unit's LDS but for 32 KiB: a run of folds then waits, all of its workgroups for the
 // last, until one has left everywhere.  With one (kBesideFoldLds) attention has three quarters of its rate
-// and the chain starts at once: worth it while the chain is the longer of the two, some 22 us a fold against a chunk's
-// attention at 0.9 PFLOP/s.  Us per call of 8192 tokens, two / one per compute unit (GFLOP a chunk): 2 x 16 heads, growing,
-// 65536 tokens (5.8) 7570 / 6350; 64 units of 64-token blocks (0.8) 2300 / 1976; 32 units, 2 heads each, growing (2.9)
-// 1865 / 1610; 64 units, 512 rows, 2 heads each (15) 1280 / 1165; 16 units, 4 heads each (7.5) 672 / 639; but 32 units, 900 rows,
-// 4 heads each (21.5) 1270 / 1290, 64 units, 512 rows, 4 heads each (30) 1790 / 1805.
+// and the chain starts at once: worth it while the chain is the longer of the two.  A fold takes 15 us and more, attention, at
+// three quarters of 0.9 PFLOP/s, 26 us for the most that it may be.  Us per call, two / one per compute unit (GFLOP a chunk): 2 x 16 heads, growing,
+// 65536 tokens (5.8) 7570 / 6350; 64 units of 64-token blocks (0.8) 2300 / 1976, with 4 heads each, 700 rows (6.7) 1640 / 1371; 64 units of
+// 128-token blocks, 4 heads each (15) 2309 / 2250; 32 units, 2 heads each, growing (2.9) 1865 / 1610; 64 units, 512 rows, 2 heads each (15) 1280 / 1165;
+// 16 units of 512-token blocks, 2 heads each, 900 rows (14) 1264 / 1137; but 32 units, 900 rows, 4 heads each (21.5) 1270 / 1290, 64 units, 512 rows,
+// 4 heads each (30) 1790 / 1805.  (512-token blocks, whose folds are longer, gain at 21.5 still: 1625 / 1490.)
+// The shortest folds, of one tile a workgroup, and fewer workgroups than compute units: 256-token blocks, 256 rows, 24 units (8.1) 1.02, 32 units, 4
+// heads each (10.7) 1006 / 1056, 16 units, 8 heads each 0.97, 48 units (16) 0.95; 512 rows, 24 units (11.3) 1.05, 16 units, 8 heads each (15) 0.96.
+// And with three heads and more on a KV head, where attention is the more of the two, the end of a call, when nothing folds any more, weighs in short calls:
+// 9 blocks of 256, 24 to 48 units, 256 to 700 rows 0.93 to 0.99 (one 1.03), of 128, 24 and 48 units 0.93 to 1.01, 32 units 1.00 to 1.05; 14 blocks 1.00 to 1.06.
 // The runs of folds are a group's eight then.  Elsewhere the launch waits for attention to leave and attention for the launch, and
 // they are half as long: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight.
-bool attention_beside(const kvm_state *st, int split, int64_t m) {
-  return may_share(st->cfg) && kvm::fold_fused_beside(st->dv, split) && chunk_flops(st->cfg, m) <= kBesideMostFlops;
+constexpr double kBesideShortFlops = 9.5e9, kBesideMidFlops = 13e9;   // of one tile a workgroup: up to 256 rows, more
+bool attention_beside(const kvm_state *st, int split, int64_t m, int64_t blocks) {
+  const Dev &dv = st->dv;
+  if (!may_share(st->cfg) || !kvm::fold_fused_beside(dv, split)) return false;
+  if (dv.Hq > 2 * dv.Hkv && blocks < 12) return false;
+  const bool one_tile = dv.Mcap <= 64 * split && (int64_t)dv.U * split < kComputeUnits;
+  return chunk_flops(st->cfg, m) <= (!one_tile ? kBesideMostFlops : dv.Mcap <= 256 ? kBesideShortFlops : kBesideMidFlops);
 }
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
@@ -1170,7 +1186,7 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
   // With a unit's rows shared among workgroups the narrow one is the default: it is the shape that
   // fits beside an attention workgroup, and sharing is chosen where the folds are to run hidden.
   const bool narrow_folds = st->dbg[KVM_DEBUG_FOLD_WAVES] == 8 || (st->dbg[KVM_DEBUG_FOLD_WAVES] == 0 && split > 1);
-  const bool beside = narrow_folds && attention_beside(st, split, m_max);
+  const bool beside = narrow_folds && attention_beside(st, split, m_max, n_folds);
   hipStream_t fstream[kvm_state::kMaxChains];
   Dev cdv[kvm_state::kMaxChains];
   const int cb = dv.B / n_chains;  // sequences per chain
