@@ -507,17 +507,19 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
 // 4 heads each (30) 1790 / 1805.  (512-token blocks, whose folds are longer, gain at 21.5 still: 1625 / 1490.)
 // The shortest folds, of one tile a workgroup, and fewer workgroups than compute units: 256-token blocks, 256 rows, 24 units (8.1) 1.02, 32 units, 4
 // heads each (10.7) 1006 / 1056, 16 units, 8 heads each 0.97, 48 units (16) 0.95; 512 rows, 24 units (11.3) 1.05, 16 units, 8 heads each (15) 0.96.
+// Eight heads on a KV head: 32 units of 128-token blocks, 700 rows (15) 1236 / 1291, but 512 rows (11.8) 1.01 to 1.02.
 // And with three heads and more on a KV head, where attention is the more of the two, the end of a call, when nothing folds any more, weighs in short calls:
 // 9 blocks of 256, 24 to 48 units, 256 to 700 rows 0.93 to 0.99 (one 1.03), of 128, 24 and 48 units 0.93 to 1.01, 32 units 1.00 to 1.05; 14 blocks 1.00 to 1.06.
 // The runs of folds are a group's eight then.  Elsewhere the launch waits for attention to leave and attention for the launch, and
 // they are half as long: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight.
-constexpr double kBesideShortFlops = 9.5e9, kBesideMidFlops = 13e9;   // of one tile a workgroup: up to 256 rows, more
+constexpr double kBesideShortFlops = 9.5e9, kBesideMidFlops = 13e9;   // of one tile a workgroup: up to 256 rows, more (and of eight heads)
 bool attention_beside(const kvm_state *st, int split, int64_t m, int64_t blocks) {
   const Dev &dv = st->dv;
   if (!may_share(st->cfg) || !kvm::fold_fused_beside(dv, split)) return false;
   if (dv.Hq > 2 * dv.Hkv && blocks < 12) return false;
   const bool one_tile = dv.Mcap <= 64 * split && (int64_t)dv.U * split < kComputeUnits;
-  return chunk_flops(st->cfg, m) <= (!one_tile ? kBesideMostFlops : dv.Mcap <= 256 ? kBesideShortFlops : kBesideMidFlops);
+  const double most = one_tile && dv.Mcap <= 256 ? kBesideShortFlops : one_tile || dv.Hq >= 8 * dv.Hkv ? kBesideMidFlops : kBesideMostFlops;
+  return chunk_flops(st->cfg, m) <= most;
 }
 // done: an event that stands for the end of this launch afterwards, or null
 int launch_run(kvm_state *st, const Src &src, const kvm::FoldRunArgs &run, bool narrow, hipEvent_t done,
