@@ -424,14 +424,18 @@ int heads_together(const Dev &dv) {
 // Workgroups that share the keys of one sequence in a decode step.  n_groups workgroups, each
 // walking all the keys, leave the chip idle when there are few of them, and a workgroup's walk is
 // a chain of memory round trips; the shares are at least one round of the loop.  Their results must
-// fit the state's scratch (gq heads' d sums and two words each).
+// fit the state's scratch (gq heads' d sums and two words each).  And they are put together by one workgroup, share by share: up to
+// 32 of them.  Us per 64 steps, 64 / 32 shares: fp32, 128 channels, 2048 rows, 4 x 4 heads 1314 / 889, 8 x 8 on 2 1596 / 1119; bf16, 128,
+// 4000 rows, 4 x 4 1248 / 827; bf16, 64, 6000, 8 x 8 on 2 1605 / 1097; fp32, 64, 4000, 4 x 4 1339 / 932.  But fp32, 128, 4000 rows in
+// one or two pairs 744 / 776.
 int shares_for(const Dev &dv, int gq, int n_groups, int keys, int round) {
   if (n_groups > kShareGroups) return 1;
   const int64_t room = dv.kbar_bytes / (gq * (dv.d * 4 + 8));
   int s = (int)(room < kSplitWorkgroups ? room : kSplitWorkgroups) / n_groups;
   const int most = (keys + round - 1) / round;
   s = s < most ? s : most;
-  s = s < kMaxSplit ? s : kMaxSplit;
+  const int at_most = n_groups <= 2 && dv.io == 0 && dv.d == 128 ? kMaxSplit : kMaxSplit / 2;
+  s = s < at_most ? s : at_most;
   return s > 1 ? s : 1;
 }
 // Eight waves per workgroup where a decode launch, one workgroup per (sequence, head group), has no more of them than compute

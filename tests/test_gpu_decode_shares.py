@@ -28,11 +28,21 @@ def reference(st, w, q, k, v, pos):
 
 @pytest.mark.parametrize("io,d", [("bf16", 128), ("f32", 128), ("bf16", 64), ("f32", 64)])
 @pytest.mark.parametrize("group", [1, 2, 4])
-@pytest.mark.parametrize("rows", [64, 127, 129, 1000])
+@pytest.mark.parametrize("rows", [64, 127, 129, 1000, 2200])   # the last: as many shares as there may be, of several rounds
 def test_shared_keys_against_softmax_attention(io, d, group, rows):
+    run(io, d, 2, 2, group, rows)
+
+
+@pytest.mark.parametrize("batch,rows", [(1, 1900), (1, 4200), (2, 2200), (3, 2200)])
+def test_as_many_shares_as_lanes(batch, rows):
+    """fp32, 128 channels: 64 shares for one or two heads, 32 for three."""
+    run("f32", 128, batch, 1, 1, rows)
+
+
+def run(io, d, batch, heads, group, rows):
     import paper_2605_09877_amd as pkg
     from paper_2605_09877_amd import synth as sy
-    w = sy.shrink(sy.WORKLOADS["decode"], io=io, batch=2, n_q_heads=2 * group, n_kv_heads=2, head_dim=d, rope_dims=16,
+    w = sy.shrink(sy.WORKLOADS["decode"], io=io, batch=batch, n_q_heads=heads * group, n_kv_heads=heads, head_dim=d, rope_dims=16,
                   chunk_len=64, state_rows=rows, budget_fixed=rows)
     st = pkg.state_for(w, max_tokens=rows + 512, device=DEV)
     pre = sy.make_decode_state(w, DEV)
@@ -40,7 +50,7 @@ def test_shared_keys_against_softmax_attention(io, d, group, rows):
     gen = torch.Generator(device=DEV).manual_seed(rows + d)
     rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(st.dtype)
     for step in range(3):
-        q, k, v = rnd(2, w.n_q_heads, d), rnd(2, 2, d), rnd(2, 2, d)
+        q, k, v = rnd(batch, w.n_q_heads, d), rnd(batch, heads, d), rnd(batch, heads, d)
         want = reference(st, w, q, k, v, st.tokens)
         got = st.decode(q, k, v).double()
         tol = 1e-4 if io == "f32" else 1e-4 + 2.0 ** -8 * want.abs()
