@@ -51,3 +51,44 @@ def test_outputs_do_not_depend_on_the_batch(C, rows, T, heads, scale):
         st = pkg.state_for(wn, device="cuda:0", **sy.make_params(wn, "cuda:0", plain=True))
         res.append([x[0].clone() for x in st.prefill(q[:n].contiguous(), k[:n].contiguous(), v[:n].contiguous(), want_lse=True)])
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("where", ["v", "k"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("C,heads,back", [(64, (4, 1), 5), (128, (2, 2), 70), (256, (4, 2), 1)])
+@pytest.mark.parametrize("many", [False, True])
+def test_a_value_that_is_not_finite_stays_within_64_positions(C, heads, back, value, where, many):
+    """head_dim 128, either kernel: a token of the last block, `back` tokens from the prompt's end, holds a value that is not
+    finite.  Queries of earlier 64 positions, other channels of v, other heads and sequences have the bits that they have
+    without it.  With k the 32 queries of its piece share the reference point of their exponentials p, which then moves: p are
+    rounded to bf16 from another scale, 2^-9 of each at most, either time, so that their sum, in lse, is off by 2^-8
+    and the output, a mean of v weighted by them, by 2^-8 of the largest v, beside its own two roundings."""
+    import torch
+    import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import synth as sy
+    T, batch, G = C * 4 - 3, 1 + many * (8 * 128 // heads[0]), heads[0] // heads[1]
+    tiles = (batch * heads[1] + 7) // 8 * 8 * (C // 32 * (G // 4) if G % 4 == 0 else (C + 127) // 128 * G)
+    assert (tiles > 64) == many
+    w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], rope_dims=16, seq=T, chunk_len=C,
+                  budget_fixed=2 * C)
+    q, k, v = sy.make_qkv(w, "cuda:0")
+    params = sy.make_params(w, "cuda:0", plain=False)
+
+    def run(k, v):
+        st = pkg.state_for(w, device="cuda:0", **params)
+        return st.prefill(q, k, v, params["gate"], want_lse=True)
+
+    at = T - back
+    want, want_lse = run(k, v)
+    k2, v2 = k.clone(), v.clone()
+    (k2 if where == "k" else v2)[0, at, 0, 3] = value
+    out, lse = run(k2, v2)
+    assert torch.equal(out[:, :, G:], want[:, :, G:]) and torch.equal(out[1:], want[1:])
+    assert torch.equal(lse[:, :at // 32 * 32], want_lse[:, :at // 32 * 32]) and torch.equal(out[:, :at // 64 * 64], want[:, :at // 64 * 64])
+    if where == "v":
+        others = [c for c in range(128) if c != 3]
+        assert torch.equal(lse, want_lse) and torch.equal(out[..., others], want[..., others])
+        assert not out[0, at:, :G, 3].isfinite().any()
+    else:
+        torch.testing.assert_close(out[:, :at].float(), want[:, :at].float(), rtol=2 ** -8, atol=2 ** -8 * float(v.abs().max()))
+        torch.testing.assert_close(lse[:, :at], want_lse[:, :at], rtol=1e-5, atol=2 ** -8)

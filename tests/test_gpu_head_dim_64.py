@@ -37,13 +37,17 @@ def test_prefill_against_the_oracle(C, rows, T, heads, split, signs):
 @pytest.mark.parametrize("where", ["v", "k"])
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
 @pytest.mark.parametrize("C,heads,back,split", [(64, (4, 1), 5, None), (128, (8, 8), 70, None), (256, (4, 2), 1, 512)])
-def test_a_value_that_is_not_finite_reaches_only_the_queries_that_see_it(C, heads, back, split, value, where):
+@pytest.mark.parametrize("many", [False, True])   # up to 128 workgroups of the tile kernel: the one whose waves split the keys; more
+def test_a_value_that_is_not_finite_reaches_only_the_queries_that_see_it(C, heads, back, split, value, where, many):
     """One token of the last block, `back` tokens from the prompt's end, holds a value that is not finite (a padded tail).
     Queries before it, of the same 64-key tile too, are what they are without it, up to the two results' bf16
     rounding (2^-8 of the element each) and 1e-5 for sums in another order; queries from it on see it."""
     import paper_2605_09877_amd as pkg
     from paper_2605_09877_amd import synth as sy
-    T, batch = C * 4 - 3, 1024 // (C * heads[0]) + 1
+    T, batch = C * 4 - 3, 1024 // (C * heads[0]) + 1 + many * (8 * 128 // heads[0])
+    G = heads[0] // heads[1]
+    tiles = (batch * heads[1] + 7) // 8 * 8 * (C // 32 * (G // 4) if G % 4 == 0 else (C + 127) // 128 * G)
+    assert (tiles > 128) == many
     w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64, rope_dims=16,
                   seq=T, chunk_len=C, budget_fixed=2 * C)
     q, k, v = sy.make_qkv(w, "cuda:0")
@@ -61,7 +65,6 @@ def test_a_value_that_is_not_finite_reaches_only_the_queries_that_see_it(C, head
     k2, v2 = k.clone(), v.clone()
     (k2 if where == "k" else v2)[0, at, 0, 3] = value
     out, lse = run(k2, v2)
-    G = heads[0] // heads[1]
     torch.testing.assert_close(out[:, :at], want[:, :at], rtol=2 ** -7, atol=1e-5)
     torch.testing.assert_close(lse[:, :at], want_lse[:, :at], rtol=1e-5, atol=1e-5)
     assert torch.equal(out[:, :, G:], want[:, :, G:]) and torch.equal(out[1:], want[1:])   # other heads and sequences
