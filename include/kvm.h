@@ -287,10 +287,14 @@ int kvm_state_import(kvm_state *st, const double *sK, const float *sV, const flo
  *                               one-launch path (ignored where the shape does not allow it)
  *   KVM_DEBUG_FOLD_PATIENCE     n: the workgroups that share a unit wait (n - 1) * 10 ns for all of
  *                               them to have started before one takes the unit by itself
- *   KVM_DEBUG_COMPUTE_UNITS     n: folds are arranged as on a device with n compute units (n <= 256) */
+ *   KVM_DEBUG_COMPUTE_UNITS     n: folds are arranged as on a device with n compute units (n <= 256)
+ *   KVM_DEBUG_BACKWARD_LAUNCHES a chunk of the backward pass on the matrix cores (bf16, head_dim 128, C % 64 == 0)
+ *                               1: is one launch, 2: several, D = dout . out formed by the one of dq,
+ *                               3: several, D formed ahead of them (a captured call, which keeps to one
+ *                               stream, forms it as in 2) */
 enum { KVM_DEBUG_FOLD_PATH = 0, KVM_DEBUG_FOLD_WAVES = 1, KVM_DEBUG_PREFILL_SCHEDULE = 2, KVM_DEBUG_FOLD_CHAINS = 3,
        KVM_DEBUG_MERGE_COPY = 4, KVM_DEBUG_BACKWARD_PATH = 5, KVM_DEBUG_FOLD_SPLIT = 6, KVM_DEBUG_FOLD_PATIENCE = 7, KVM_DEBUG_COMPUTE_UNITS = 8,
-       KVM_DEBUG_KNOBS = 9 };
+       KVM_DEBUG_BACKWARD_LAUNCHES = 9, KVM_DEBUG_KNOBS = 10 };
 int kvm_debug_set(kvm_state *st, int knob, int value);
 
 /* Kernel timing for benchmarks (no passage of the paper: a measurement aid).  While enabled,

@@ -30,8 +30,9 @@ EXPORTS = [
     "kvm_backward_workspace_bytes", "kvm_prefill_backward", "kvm_debug_set",
 ]
 (KVM_DEBUG_FOLD_PATH, KVM_DEBUG_FOLD_WAVES, KVM_DEBUG_PREFILL_SCHEDULE, KVM_DEBUG_FOLD_CHAINS, KVM_DEBUG_MERGE_COPY,
- KVM_DEBUG_BACKWARD_PATH, KVM_DEBUG_FOLD_SPLIT, KVM_DEBUG_FOLD_PATIENCE, KVM_DEBUG_COMPUTE_UNITS) = range(9)
-KVM_DEBUG_KNOBS = 9  # number of knobs the library knows of; kvm_debug_set refuses any index from here on
+ KVM_DEBUG_BACKWARD_PATH, KVM_DEBUG_FOLD_SPLIT, KVM_DEBUG_FOLD_PATIENCE, KVM_DEBUG_COMPUTE_UNITS,
+ KVM_DEBUG_BACKWARD_LAUNCHES) = range(10)
+KVM_DEBUG_KNOBS = 10  # number of knobs the library knows of; kvm_debug_set refuses any index from here on
 
 
 class kvm_config(C.Structure):

@@ -646,12 +646,12 @@ hipError_t run_backward(const Bwd &a_in, const BwdChunk *chunks, int n_chunks, h
   // of its own: the events between three streams cost 8 to 16 us a chunk, twice.
   int m_max = 0;
   for (int i = 0; i < n_chunks; ++i) m_max = chunks[i].m > m_max ? chunks[i].m : m_max;
-  const bool one_launch = on_mfma && backward_fits_one_launch(dv, m_max);
+  const bool one_launch = on_mfma && (a.launches ? a.launches == 1 : backward_fits_one_launch(dv, m_max));
   const bool use_side = on_mfma && !one_launch && x.side && x.side2 && x.fork && x.dq_done && x.join_state && x.join_window[0] &&
                         x.join_window[1];
   // D = dout . out per query.  The matrix-core dq kernel forms it for its own queries, which saves a pass over
   // out and dout but puts dq ahead of the state rows in the chain.
-  const bool delta_first = !on_mfma || one_launch || (use_side && delta_ahead(dv, chunks, n_chunks));
+  const bool delta_first = !on_mfma || one_launch || (use_side && (a.launches ? a.launches == 3 : delta_ahead(dv, chunks, n_chunks)));
   if (delta_first && on_mfma)
     BWD_TRY(launch_delta_mfma(a, q_rows, st));   // (the order of dq's own sum: D is the same whoever forms it)
   else if (delta_first)

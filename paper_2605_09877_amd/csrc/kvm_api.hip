@@ -1698,6 +1698,7 @@ int kvm_prefill_backward(kvm_state *st, const void *q, const void *k, const void
   kvm::Bwd a;
   a.dv = st->dv;
   a.on_mfma = on_mfma;
+  a.launches = st->dbg[KVM_DEBUG_BACKWARD_LAUNCHES];
   a.T = T;
   a.q = q; a.k = k; a.v = v; a.out = out; a.dout = dout;
   a.gate = gate; a.lse = lse; a.assign = assign; a.score = score;

@@ -223,6 +223,7 @@ hipError_t launch_attn_rows_score(const Dev &dv, const AttnArgs &a, int slot, in
 struct Bwd {
   Dev dv;  // dimensions, parameters and the final sums (sK, sV, rho) of the state after the forward
   bool on_mfma;  // attention adjoints on the matrix cores (decides the workspace layout and the launches)
+  int32_t launches;  // KVM_DEBUG_BACKWARD_LAUNCHES
   int64_t T;
   const void *q, *k, *v, *out, *dout;
   const float *gate, *lse;

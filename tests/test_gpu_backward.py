@@ -84,9 +84,10 @@ def check(w, name, got, ref, f32_bar=1e-4):
     assert worst <= 1.0, f"{name}: bf16 error is {worst:.3f} x the 2e-2 bound"
 
 
-def run_backward_case(w, plain, units=None, split=None):
+def run_backward_case(w, plain, units=None, split=None, knobs=None):
     """Forward with the fold record on, backward, and the oracle on every unit (or on the sampled
-    `units`: then the gradients summed over all units -- LN_s, temperatures -- are not checked)."""
+    `units`: then the gradients summed over all units -- LN_s, temperatures -- are not checked).
+    knobs: {kvm_debug_set knob: value}."""
     pkg, sy = kvm(), synth()
     q, k, v = sy.make_qkv(w, DEV)
     params = sy.make_params(w, DEV, plain=plain)
@@ -95,6 +96,8 @@ def run_backward_case(w, plain, units=None, split=None):
     gen.manual_seed(w.seed + 31337)
     dout = torch.randn(q.shape, generator=gen, device=DEV, dtype=torch.float32).to(q.dtype)
     st = pkg.state_for(w, device=DEV, **params)
+    for knob, value in (knobs or {}).items():
+        st.debug_set(knob, value)
     assign, score = st.trace(w.seq // w.chunk_len + 1)
     if split is None:
         out, lse = st.prefill(q, k, v, gate, want_lse=True)

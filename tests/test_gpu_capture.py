@@ -39,9 +39,11 @@ def test_captured_prefill(batch, heads, chunk, schedule):
             assert torch.equal(e[key], ref[key]), key
 
 
-def test_captured_backward():
-    """The gradients of a captured backward pass are those of one on the library's streams."""
+@pytest.mark.parametrize("launches", [0, 2, 3])   # by the library's choice one a chunk; several, on its streams when not captured
+def test_captured_backward(launches):
+    """The gradients of a captured backward pass, which keeps to the caller's stream, are those of one that does not."""
     import paper_2605_09877_amd as pkg
+    from paper_2605_09877_amd import binding as b
     from paper_2605_09877_amd import synth as sy
     w = sy.shrink(sy.WORKLOADS["prefill_fixed"], batch=2, n_q_heads=4, n_kv_heads=2, chunk_len=256, seq=256 * 4 + 77,
                   budget_fixed=300)
@@ -49,6 +51,7 @@ def test_captured_backward():
     params = sy.make_params(w, DEV, plain=False)
     dout = torch.randn(q.shape, generator=torch.Generator(DEV).manual_seed(1), device=DEV).to(q.dtype)
     st = pkg.state_for(w, device=DEV, **params)
+    st.debug_set(b.KVM_DEBUG_BACKWARD_LAUNCHES, launches)
     assign, score = st.trace(w.seq // w.chunk_len + 1)
     out, lse = st.prefill(q, k, v, params["gate"], want_lse=True)
     args = (q, k, v, params["gate"], out, lse, dout, assign, score)
