@@ -1073,8 +1073,9 @@ __global__ __launch_bounds__(256, 2) void attn_split_score_kernel_d64(Dev dv, At
 // Launches of up to so many workgroups of the tile kernels go to the others: as many of theirs, four times the number, as find a
 // place at once.  head_dim 128 (one per compute unit), us per call, tiles / four at a time: 64 workgroups: 3 x 8 heads on 2,
 // 904 tokens 105 / 90; 4 heads, 4000 tokens 297 / 290; but 128: 2 x 16 heads, 612 tokens 41.7 / 44.4, 256: 8 x 8 heads on 2, 587 tokens
-// 40 / 57.  head_dim 64 (two and more per compute unit): 128 workgroups: 2 x 16 heads on 4, 4173 tokens 655 / 522; but 256: 8 x 16
-// heads, 2000 tokens 470 / 483.
+// 40 / 57.  head_dim 64 (two and more per compute unit; with the scores of the fold in the same launch), 4173 tokens: 64 workgroups: 2 x 16 heads on
+// 4 655 / 338, 96: the same in 384-token blocks 519 / 387, 128: in 512-token blocks 495 / 375, 4 x 16 heads on 4 714 / 530, with 1000
+// rows 1312 / 1059, 4 x 16 heads 1446 / 1270; but 256: 8 x 16 heads, 2000 tokens 470 / 483.
 constexpr unsigned kQuadMost = 64, kSplitMost = 128;
 
 // Workgroups of the tile kernels (four heads x 32 positions, or 128 positions of one head, each) and of the others.

@@ -177,7 +177,8 @@ struct SeqDesc {
 };
 // The same of up to kPackStates states as a kernel argument: no table to write ahead of the launch (copied from the host it was a
 // launch of its own of 4.8 us and as much of host time; 3 x 4 heads on 2, 353 rows: 12.4 us a step before,
-// 10.2 now).
+// 10.2 now).  64 of them, 2.3 KiB, of the 4 KiB that a launch's arguments may have (16 steps, 8 heads on 2, 300 rows, table / arguments: 64 states
+// 504 / 477 us; 96, 3.4 KiB: 605 / 575).
 constexpr int kPackStates = 64;
 struct SeqPack {
   const void *khat[kPackStates];   // current readout version, first unit; v-hat is decode_value_offset() bytes further on
@@ -278,7 +279,9 @@ hipError_t launch_backward_mfma(const Bwd &a, int64_t cs, int nq, int m, bool fo
                                 hipStream_t st);
 // both roles in one launch, where a whole chunk's workgroups into m state rows are few enough; needs D.  Whole calls of training,
 // launches of their own on three streams / one, us (workgroups): 224 of 32 units 1050 / 801, 8 units, growing, 8465 tokens (up to 128)
-// 3990 / 2960, 12 units of 64-token chunks, 20764 tokens (120) 27300 / 17500, 512 of 96 units 2118 / 1972, 704 of 128 units 2550 / 2474;
+// 3990 / 2960, 12 units of 64-token chunks, 20764 tokens (120) 27300 / 17500, 512 of 96 units 2118 / 1972, 704 of 128 units 2550 / 2474,
+// 768 of 128 units 3517 / 3317, 960 of 96 4514 / 4028, 1024 of 64, 1536 rows 9511 / 7917, of 64 with two heads each 2876 / 2799.  (Beyond, as far as
+// measured, one launch is still ahead: 1280 of 160 units 5770 / 5416, 1536 of 128 3879 / 3660, 2048 of 256 8061 / 7728.)  But
 // with four heads per KV head: 96 of 8 units 4110 / 2750, 224 of 16 1632 / 1619, but 336 of 24 1737 / 1776, 448 of 32 1910 / 2050 (their
 // loops are long, and the kernel of both roles spills more in them).
 constexpr unsigned kBwdOneLaunch = 1024, kBwdOneLaunchHeads = 256;   // (up to two query heads per KV head; more)
