@@ -508,15 +508,17 @@ int fold_split_on(const kvm_state *st, int64_t blocks, hipStream_t stream) {
 // The shortest folds, of one tile a workgroup, and fewer workgroups than compute units: 256-token blocks, 256 rows, 24 units (8.1) 1.02, 32 units, 4
 // heads each (10.7) 1006 / 1056, 16 units, 8 heads each 0.97, 48 units (16) 0.95; 512 rows, 24 units (11.3) 1.05, 16 units, 8 heads each (15) 0.96.
 // Eight heads on a KV head: 32 units of 128-token blocks, 700 rows (15) 1236 / 1291, but 512 rows (11.8) 1.01 to 1.02.
-// And with three heads and more on a KV head, where attention is the more of the two, the end of a call, when nothing folds any more, weighs in short calls:
-// 9 blocks of 256, 24 to 48 units, 256 to 700 rows 0.93 to 0.99 (one 1.03), of 128, 24 and 48 units 0.93 to 1.01, 32 units 1.00 to 1.05; 14 blocks 1.00 to 1.06.
+// And three heads and more on a KV head, where attention is the more of the two, with blocks longer than 128 tokens in short calls: 7 to 11 blocks of 256,
+// 24 units 0.93 to 0.98, 16 units 0.94 to 1.04; of 64, 16 units 1.05 to 1.10, of 128, 32 units 1.01 to 1.08 (24 units 0.96); 14 blocks of 256 1.00 to 1.06.
+// The call's last launch leaves none where nothing folds behind it: 7.4 blocks of 256, 32 units, 2 heads each, 212 us for 222, 1918 tokens of
+// 64 units, 2 heads each, 1.07, of 128 units 1.05.
 // The runs of folds are a group's eight then.  Elsewhere the launch waits for attention to leave and attention for the launch, and
 // they are half as long: 64 units, 1024 rows in 128-token blocks, 2 heads each, 2090 us in runs of four, 2230 in runs of eight.
 constexpr double kBesideShortFlops = 9.5e9, kBesideMidFlops = 13e9;   // of one tile a workgroup: up to 256 rows, more (and of eight heads)
 bool attention_beside(const kvm_state *st, int split, int64_t m, int64_t blocks) {
   const Dev &dv = st->dv;
   if (!may_share(st->cfg) || !kvm::fold_fused_beside(dv, split)) return false;
-  if (dv.Hq > 2 * dv.Hkv && blocks < 12) return false;
+  if (dv.Hq > 2 * dv.Hkv && dv.C > 128 && blocks < 12) return false;
   const bool one_tile = dv.Mcap <= 64 * split && (int64_t)dv.U * split < kComputeUnits;
   const double most = one_tile && dv.Mcap <= 256 ? kBesideShortFlops : one_tile || dv.Hq >= 8 * dv.Hkv ? kBesideMidFlops : kBesideMostFlops;
   return chunk_flops(st->cfg, m) <= most;
@@ -1374,8 +1376,9 @@ int kvm_prefill_chunked(kvm_state *st, const void *q, const void *k, const void 
     }
     {
       ProfileSpan span(st, 0, stream);
+      // (no room beside the last launch where nothing folds any more)
       if (kvm::attention_on_mfma(dv))
-        HIP_TRY(kvm::launch_attn_mfma(dv, a, beside, stream));
+        HIP_TRY(kvm::launch_attn_mfma(dv, a, beside && (g1 < n_chunks || plan[n_chunks - 1].folds), stream));
       else
         HIP_TRY(kvm::launch_attn_rows(dv, a, stream));
     }

@@ -317,3 +317,41 @@ def test_selection_forms_agree_with_a_kernel_per_step(chunk, steps):
         torch.cuda.synchronize()
         res.append((st, assign[:st.folds].clone(), st.export()))
     same(*res)
+
+
+@pytest.mark.parametrize("chunk,heads,tail,blocks,rows", [
+    (256, (16, 16), 0, 8, 512), (256, (16, 16), 97, 8, 512),     # room beside every launch; not beside the last, behind which nothing folds
+    (256, (48, 16), 1, 11, 300), (256, (48, 16), 1, 13, 300),    # three heads on a KV head: none in short calls
+    (128, (48, 16), 1, 8, 300), (256, (128, 16), 5, 13, 512),    # blocks of 128; eight heads, one tile a workgroup: none
+])
+def test_outputs_do_not_depend_on_the_room_beside_attention(chunk, heads, tail, blocks, rows):
+    """Outputs and state of a prompt whose folds are shared beside attention, against a kernel per step, chunk by chunk."""
+    pkg, b, sy = kit()
+    w = make(sy, chunk, heads[1], chunk * blocks + tail, rows)
+    w = sy.shrink(w, n_q_heads=heads[0])
+    q, k, v = sy.make_qkv(w, DEV)
+    p = sy.make_params(w, DEV, plain=False)
+    res = []
+    for knobs in ({}, {b.KVM_DEBUG_FOLD_PATH: 2, b.KVM_DEBUG_PREFILL_SCHEDULE: 1}):
+        st = pkg.state_for(w, device=DEV, **p)
+        for knob, value in knobs.items():
+            st.debug_set(knob, value)
+        assign, _ = st.trace(blocks + 1)
+        out, lse = st.prefill(q, k, v, p["gate"], want_lse=True)
+        torch.cuda.synchronize()
+        res.append((st, assign[:st.folds].clone(), st.export(), out, lse))
+    assert res[0][0].fold_path == 1 and torch.equal(res[0][3], res[1][3]) and torch.equal(res[0][4], res[1][4])
+    same(*[r[:3] for r in res])
+
+
+@pytest.mark.parametrize("chunk,units,budget,path", [
+    (256, 1, 256, 2), (256, 2, 256, 1), (256, 3, 320, 2), (256, 4, 320, 1), (128, 1, 256, 2), (128, 1, 257, 1), (128, 2, 256, 1), (64, 1, 256, 1),
+    (256, 1, 512, 1), (256, 1, (256, 256, 257, 300), 1),
+])
+def test_few_units_that_do_not_grow(chunk, units, budget, path):
+    """Prompts of 32 blocks on either side of the rule for states of fewer than 512 rows without appends."""
+    _, b, sy = kit()
+    w = make(sy, chunk, units, chunk * 32, budget)
+    got = run(w, {})
+    assert got[0].fold_path == path
+    same(got, run(w, {b.KVM_DEBUG_FOLD_PATH: 2}))
