@@ -1320,7 +1320,9 @@ __global__ __launch_bounds__(64 * NW, 4) void fold_fused_kernel(FoldKernelArgs) 
       }
     }
     // The next fold of the run reads what this one wrote, this workgroup's own stores: with resident tiles behind
-    // barriers of its own that wait for them, so that this one is for LDS alone.
+    // barriers of its own that wait for them, so that this one is for LDS alone.  (With full barriers here and ahead of the
+    // exchange 8192 tokens, 2 units, 128-token blocks, 600 rows 976 -> 998 us, 64 units of 64-token blocks 1947 -> 1977, 65536 tokens,
+    // growing, 32 units 5.95 -> 5.99 ms; either one alone costs nothing.)
     if (cx.resident) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
